@@ -37,6 +37,21 @@ __device__ __forceinline__ void st_nt(float2* p, float2 v) {
 __device__ __forceinline__ float2 ld_nt(const float2* p) {
     return make_float2(__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y));
 }
+// The same for a pair of floats of any 4-byte alignment (a caller's array).
+__device__ __forceinline__ float2 ld_nt_pair(const float* p) {
+    return make_float2(__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1));
+}
+__device__ __forceinline__ void st_nt_pair(float* p, float2 v) {
+    __builtin_nontemporal_store(v.x, p);
+    __builtin_nontemporal_store(v.y, p + 1);
+}
+
+// Plain row number i0 n + i1 of storage row r (layout.h).
+__device__ __forceinline__ long plain_row(long r, int n) {
+    int i0, i1;
+    mesh_row_inv(r, n, i0, i1);
+    return (long)i0 * n + i1;
+}
 
 // Lanes-per-transform and values-per-lane choices per transform length.
 template <int H>
@@ -61,10 +76,16 @@ struct Cfg {
 
 // ---------------------------------------------------------- last axis
 
-template <int N>
+// DENSE: the real rows are read from a caller's [N][N][N] array in plain row
+// order (any 4-byte alignment) instead of from the buffer itself, so a
+// caller's mesh needs no copy into the workspace layout first.  That copy moved
+// as many bytes as the pass and took longer (512^3: 411 us for the copy, 218 us
+// for the pass).  With all four layout copies folded into the first and last
+// passes, a 512^3 R2C plus C2R takes 1.76 ms instead of 2.75 ms.
+template <int N, bool DENSE>
 __global__ void __launch_bounds__(Cfg<N / 2>::T * Cfg<N / 2>::ROWS)
-k_fft_x_r2c(float2* __restrict__ buf, int cs, long nrows, long bufStride,
-            const float2* __restrict__ tw, int ntw,
+k_fft_x_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, long nrows,
+            long bufStride, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int H = N / 2, E = Cfg<H>::E, T = Cfg<H>::T, ROWS = Cfg<H>::ROWS;
     constexpr int LS = lds_slots(H);
@@ -77,9 +98,11 @@ k_fft_x_r2c(float2* __restrict__ buf, int cs, long nrows, long bufStride,
     // rowp points at row 0 for rows past the end, so every load is in bounds
     // and none sits in a branch (which would make each wait for its data)
     float2 v[E];
+    const float* src = reinterpret_cast<const float*>(rowp);
+    if constexpr (DENSE) src = real + plain_row(valid ? row : 0, N) * N;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        v[e] = ld_nt(&rowp[j + e * T]);
+        v[e] = ld_nt_pair(src + 2 * (j + e * T));
         if (!valid) v[e] = make_float2(0.f, 0.f);
     }
     float2* L = lds + r * LS;
@@ -104,10 +127,11 @@ k_fft_x_r2c(float2* __restrict__ buf, int cs, long nrows, long bufStride,
 
 // kmul_buf >= 0: the spectrum of buffer kmul_buf is first multiplied by i k2
 // (zero on the Nyquist column), i.e. this pass also takes the spectral
-// derivative along the last axis.
-template <int N>
+// derivative along the last axis.  DENSE: the real rows go to a caller's
+// [N][N][N] array in plain row order (as in k_fft_x_r2c).
+template <int N, bool DENSE>
 __global__ void __launch_bounds__(Cfg<N / 2>::T * Cfg<N / 2>::ROWS)
-k_fft_x_c2r(float2* __restrict__ buf, int cs, long nrows, long bufStride, int kmul_buf,
+k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, int cs, long nrows, long bufStride, int kmul_buf,
             const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int H = N / 2, E = Cfg<H>::E, T = Cfg<H>::T, ROWS = Cfg<H>::ROWS;
@@ -152,8 +176,10 @@ k_fft_x_c2r(float2* __restrict__ buf, int cs, long nrows, long bufStride, int km
     fft_lds<H, E, 1>(v, L, 1, 0, j, st);
     __syncthreads();
     if (!valid) return;
+    float* dst = reinterpret_cast<float*>(rowp);
+    if constexpr (DENSE) dst = real + plain_row(row, N) * N;
 #pragma unroll
-    for (int e = 0; e < E; ++e) st_nt(&rowp[j + e * T], L[lpad(j + e * T)]);
+    for (int e = 0; e < E; ++e) st_nt_pair(dst + 2 * (j + e * T), L[lpad(j + e * T)]);
 }
 
 // ---------------------------------------------------------- strided axes
@@ -161,11 +187,14 @@ k_fft_x_c2r(float2* __restrict__ buf, int cs, long nrows, long bufStride, int km
 // Tile t -> (a, cb): columns cb*W .. cb*W+W-1 of the rows with the other slow
 // index fixed to a; element p of the transform sits in mesh row (a, p) for
 // AXIS = 1 and (p, a) for AXIS = 0 (storage order: layout.h).
-template <int H, int DIR, int AXIS>
+// `spec`, with SPEC: a caller's dense half spectrum [H][H][H/2+1] (AXIS = 0),
+// which the forward pass writes and the inverse pass reads in place of the
+// buffer, so that no separate pass changes the layout (512^3: 251 us each way).
+template <int H, int DIR, int AXIS, bool SPEC>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W, Cfg<H>::MINW)
-k_fft_strided(float2* __restrict__ buf, int cs, int ncb, long bufStride,
-              const float2* __restrict__ tw, int ntw,
-            const float2* __restrict__ st) {
+k_fft_strided(float2* __restrict__ buf, typename std::conditional<DIR < 0, float2*, const float2*>::type
+              __restrict__ spec, int cs, int ncb, long bufStride, const float2* __restrict__ st) {
+    static_assert(!SPEC || AXIS == 0, "dense spectra are the first or last pass, along axis 0");
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W;
     __shared__ float2 lds[lds_slots(H) * W];
     const int c = threadIdx.x % W, j = threadIdx.x / W;
@@ -175,13 +204,33 @@ k_fft_strided(float2* __restrict__ buf, int cs, int ncb, long bufStride,
     auto at = [&](int p) -> float2& {
         return base[(AXIS == 1 ? mesh_row(a, p, H) : mesh_row(p, a, H)) * cs];
     };
+    // dense element p of the column: row (p, a), column k2 (one past the half
+    // spectrum is padding, loaded from column H/2 and replaced by zero)
+    const int k2 = cb * W + c;
+    const bool stored = k2 <= H / 2;
+    auto dense = [&](int p) -> long {
+        return ((long)p * H + a) * (H / 2 + 1) + (stored ? k2 : H / 2);
+    };
     float2 v[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = at(j + e * T);
+    for (int e = 0; e < E; ++e) {
+        if constexpr (SPEC && DIR > 0) {
+            v[e] = spec[dense(j + e * T)];
+            if (!stored) v[e] = make_float2(0.f, 0.f);
+        } else {
+            v[e] = at(j + e * T);
+        }
+    }
     fft_lds<H, E, DIR>(v, lds, W, c, j, st);
     __syncthreads();
+    if constexpr (SPEC && DIR < 0) {
+        if (!stored) return;
 #pragma unroll
-    for (int e = 0; e < E; ++e) at(j + e * T) = lds[lpad(j + e * T) * W + c];
+        for (int e = 0; e < E; ++e) spec[dense(j + e * T)] = lds[lpad(j + e * T) * W + c];
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) at(j + e * T) = lds[lpad(j + e * T) * W + c];
+    }
 }
 
 __device__ __forceinline__ int signed_freq(int p, int n) { return p < n / 2 ? p : p - n; }
@@ -696,54 +745,72 @@ void size_switch(int n, F&& f) {
     }
 }
 
+// real == nullptr: in place
 template <int N>
-void x_r2c(float2* buf, int cs, int nbuf, long bufStride, const Twiddles& tw,
+void x_r2c(const float* real, float2* buf, int cs, int nbuf, long bufStride, const Twiddles& tw,
            hipStream_t s) {
     constexpr int ROWS = Cfg<N / 2>::ROWS, T = Cfg<N / 2>::T;
     long nrows = (long)N * N;
     dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS), nbuf);
-    hipLaunchKernelGGL(k_fft_x_r2c<N>, grid, dim3(T * ROWS), 0, s, buf, cs, nrows, bufStride, tw.w, tw.n, tw.stages);
+    if (real)
+        hipLaunchKernelGGL((k_fft_x_r2c<N, true>), grid, dim3(T * ROWS), 0, s, real, buf, cs, nrows,
+                           bufStride, tw.w, tw.n, tw.stages);
+    else
+        hipLaunchKernelGGL((k_fft_x_r2c<N, false>), grid, dim3(T * ROWS), 0, s, nullptr, buf, cs,
+                           nrows, bufStride, tw.w, tw.n, tw.stages);
 }
 
 template <int N>
-void x_c2r(float2* buf, int cs, int nbuf, long bufStride, int kmul_buf, const Twiddles& tw,
-           hipStream_t s) {
+void x_c2r(float2* buf, float* real, int cs, int nbuf, long bufStride, int kmul_buf,
+           const Twiddles& tw, hipStream_t s) {
     constexpr int ROWS = Cfg<N / 2>::ROWS, T = Cfg<N / 2>::T;
     long nrows = (long)N * N;
     dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS), nbuf);
-    hipLaunchKernelGGL(k_fft_x_c2r<N>, grid, dim3(T * ROWS), 0, s, buf, cs, nrows, bufStride,
-                       kmul_buf, tw.w, tw.n, tw.stages);
+    if (real)
+        hipLaunchKernelGGL((k_fft_x_c2r<N, true>), grid, dim3(T * ROWS), 0, s, buf, real, cs, nrows,
+                           bufStride, kmul_buf, tw.w, tw.n, tw.stages);
+    else
+        hipLaunchKernelGGL((k_fft_x_c2r<N, false>), grid, dim3(T * ROWS), 0, s, buf, nullptr, cs,
+                           nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
 }
 
-template <int N>
-void strided(float2* buf, int cs, int axis, int dir, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
+template <int N, int DIR, int AXIS, bool SPEC, class Spec>
+void strided(float2* buf, Spec spec, int cs, int nbuf, long bufStride, const Twiddles& tw,
+             hipStream_t s) {
     constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
     int ncb = cs / W;
-    dim3 grid(N * ncb, nbuf), block(T * W);
-    if (axis == 1 && dir < 0)
-        hipLaunchKernelGGL((k_fft_strided<N, -1, 1>), grid, block, 0, s, buf, cs, ncb, bufStride, tw.w, tw.n, tw.stages);
-    else if (axis == 1)
-        hipLaunchKernelGGL((k_fft_strided<N, 1, 1>), grid, block, 0, s, buf, cs, ncb, bufStride, tw.w, tw.n, tw.stages);
-    else if (dir < 0)
-        hipLaunchKernelGGL((k_fft_strided<N, -1, 0>), grid, block, 0, s, buf, cs, ncb, bufStride, tw.w, tw.n, tw.stages);
-    else
-        hipLaunchKernelGGL((k_fft_strided<N, 1, 0>), grid, block, 0, s, buf, cs, ncb, bufStride, tw.w, tw.n, tw.stages);
+    hipLaunchKernelGGL((k_fft_strided<N, DIR, AXIS, SPEC>), dim3(N * ncb, nbuf), dim3(T * W), 0, s,
+                       buf, spec, cs, ncb, bufStride, tw.stages);
 }
 
 }  // namespace
 
 void launch_fft_x_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) { x_r2c<decltype(nn)::value>(buf, cs, nbuf, bufStride, tw, s); });
+    size_switch(n, [&](auto nn) {
+        x_r2c<decltype(nn)::value>(nullptr, buf, cs, nbuf, bufStride, tw, s);
+    });
+}
+
+void launch_fft_x_r2c_from(const float* real, float2* buf, int n, int cs, const Twiddles& tw,
+                           hipStream_t s) {
+    size_switch(n, [&](auto nn) { x_r2c<decltype(nn)::value>(real, buf, cs, 1, 0, tw, s); });
 }
 
 void launch_fft_x_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) { x_c2r<decltype(nn)::value>(buf, cs, nbuf, bufStride, -1, tw, s); });
+    size_switch(n, [&](auto nn) {
+        x_c2r<decltype(nn)::value>(buf, nullptr, cs, nbuf, bufStride, -1, tw, s);
+    });
+}
+
+void launch_fft_x_c2r_to(float2* buf, float* real, int n, int cs, const Twiddles& tw,
+                         hipStream_t s) {
+    size_switch(n, [&](auto nn) { x_c2r<decltype(nn)::value>(buf, real, cs, 1, 0, -1, tw, s); });
 }
 
 void launch_fft_x_c2r_dk2(float2* buf, int n, int cs, int nbuf, long bufStride, int kmul_buf,
                           const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
-        x_c2r<decltype(nn)::value>(buf, cs, nbuf, bufStride, kmul_buf, tw, s);
+        x_c2r<decltype(nn)::value>(buf, nullptr, cs, nbuf, bufStride, kmul_buf, tw, s);
     });
 }
 
@@ -772,7 +839,11 @@ void launch_fft_y_merge(float2* g1, const float2* g2, int n, int cs, const Twidd
 void launch_fft_axis(float2* buf, int n, int cs, int axis, int dir, int nbuf, long bufStride,
                      const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
-        strided<decltype(nn)::value>(buf, cs, axis, dir, nbuf, bufStride, tw, s);
+        constexpr int N = decltype(nn)::value;
+        if (axis == 1 && dir < 0) strided<N, -1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        else if (axis == 1) strided<N, 1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        else if (dir < 0) strided<N, -1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        else strided<N, 1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
     });
 }
 
@@ -856,6 +927,28 @@ void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const
     launch_fft_axis(buf, n, cs, 0, 1, nbuf, bufStride, tw, s);
     launch_fft_axis(buf, n, cs, 1, 1, nbuf, bufStride, tw, s);
     launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
+}
+
+void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
+                           const Twiddles& tw, hipStream_t s) {
+    launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
+    launch_fft_axis(buf, n, cs, 1, -1, 1, 0, tw, s);
+    size_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        if (spec) strided<N, -1, 0, true>(buf, spec, cs, 1, 0, tw, s);
+        else strided<N, -1, 0, false>(buf, nullptr, cs, 1, 0, tw, s);
+    });
+}
+
+void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, int cs,
+                           const Twiddles& tw, hipStream_t s) {
+    size_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        if (spec) strided<N, 1, 0, true>(buf, spec, cs, 1, 0, tw, s);
+        else strided<N, 1, 0, false>(buf, nullptr, cs, 1, 0, tw, s);
+    });
+    launch_fft_axis(buf, n, cs, 1, 1, 1, 0, tw, s);
+    launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
 }
 
 }  // namespace pmx

@@ -30,8 +30,15 @@ int device_cus();
 // Real rows -> half spectra along the last axis, in place, for `nbuf` buffers
 // `bufStride` float2 apart.  Unnormalised exp(-i k x).
 void launch_fft_x_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
+// The same with the real rows read from a dense [n]^3 array in plain row order
+// (4-byte aligned) and the half spectra written to `buf`.
+void launch_fft_x_r2c_from(const float* real, float2* buf, int n, int cs, const Twiddles& tw,
+                           hipStream_t s);
 // Inverse of the above without the 1/n factor (Hermitian rows assumed).
 void launch_fft_x_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
+// The same with the real rows written to a dense [n]^3 array in plain row order.
+void launch_fft_x_c2r_to(float2* buf, float* real, int n, int cs, const Twiddles& tw,
+                         hipStream_t s);
 // as launch_fft_x_c2r, with buffer kmul_buf multiplied by i k2 first
 void launch_fft_x_c2r_dk2(float2* buf, int n, int cs, int nbuf, long bufStride, int kmul_buf,
                           const Twiddles& tw, hipStream_t s);
@@ -66,6 +73,13 @@ void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const flo
 // Full 3-D transforms built from the passes above.
 void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
 void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
+// The same between a dense real mesh [n]^3 and a dense half spectrum
+// [n][n][n/2+1] (nullptr: the spectrum stays in, or comes from, `buf`), through
+// `buf`; the first and last pass read and write the caller's layout.
+void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
+                           const Twiddles& tw, hipStream_t s);
+void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, int cs,
+                           const Twiddles& tw, hipStream_t s);
 
 // ---------------------------------------------------------------- particles
 // Particle state is fixed point so that kick and drift are exactly invertible:
@@ -234,12 +248,8 @@ void launch_add_from_pitched(const float* src, float* dst, int n, long rp, float
                              hipStream_t s);
 void launch_dot_pitched(const float* src, const float* b, int n, long rp, double* partials,
                         int nblocks, hipStream_t s);
-// Compact [n]^3 <-> pitched rows.
-void launch_to_pitched(const float* src, float* dst, int n, long rp, float scale,
-                       hipStream_t s);
+// Pitched rows -> compact [n]^3.
 void launch_from_pitched(const float* src, float* dst, int n, long rp, hipStream_t s);
-// dense half spectrum [n][n][n/2+1] -> workspace layout (to_ws) or back
-void launch_spec_copy(const float2* src, float2* dst, int n, int cs, bool to_ws, hipStream_t s);
 // AoS [P][3] component j -> pitched mesh j (three meshes).
 void launch_deinterleave(const float* v, float* dst, long dstStride, int np, long rp,
                          hipStream_t s);

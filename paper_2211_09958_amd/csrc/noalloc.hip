@@ -110,9 +110,7 @@ extern "C" int pm_power_spectrum_noalloc(const float* dens, int32_t mesh, double
     const Twiddles twd{reinterpret_cast<const float2*>(base + kTwOff), kMaxMesh,
                        reinterpret_cast<const float2*>(base + kStageOff)};
     const int cs = complex_row_stride(mesh);
-    const long cst = (long)mesh * mesh * cs;
-    launch_to_pitched(dens, reinterpret_cast<float*>(spec), mesh, 2L * cs, 1.f, s);
-    launch_fft3_r2c(spec, mesh, cs, 1, cst, twd, s);
+    launch_fft3_r2c_dense(dens, spec, nullptr, mesh, cs, twd, s);
     launch_zero(bins, 3 * (size_t)n_bins * sizeof(double), s);
     launch_pk_bin(spec, mesh, cs, n_bins, bins, s);
     if (hipGetLastError() != hipSuccess) {

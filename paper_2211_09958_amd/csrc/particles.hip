@@ -1189,34 +1189,11 @@ k_dot_pitched(const float* __restrict__ src, const float* __restrict__ b, int n,
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_to_pitched(const float* __restrict__ src, float* __restrict__ dst, int n, long rp, float scale) {
-    const long N = (long)n * n * n;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const long row = i / n;
-        dst[mesh_row((int)(row / n), (int)(row % n), n) * rp + (i % n)] = scale * src[i];
-    }
-}
-
-__global__ void __launch_bounds__(kBlock)
 k_from_pitched(const float* __restrict__ src, float* __restrict__ dst, int n, long rp) {
     const long N = (long)n * n * n;
     for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
         const long row = i / n;
         dst[i] = src[mesh_row((int)(row / n), (int)(row % n), n) * rp + (i % n)];
-    }
-}
-
-// Half spectrum [n][n][n/2+1] (dense, plain row order) <-> the workspace layout
-// (rows of cs values in the blocked order of layout.h).
-__global__ void __launch_bounds__(kBlock)
-k_spec_copy(const float2* __restrict__ src, float2* __restrict__ dst, int n, int cs, int to_ws) {
-    const int h = n / 2 + 1;
-    const long N = (long)n * n * h;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const long row = i / h;
-        const long w = mesh_row((int)(row / n), (int)(row % n), n) * cs + (i % h);
-        if (to_ws) dst[w] = src[i];
-        else dst[i] = src[w];
     }
 }
 
@@ -1606,21 +1583,9 @@ void launch_dot_pitched(const float* src, const float* b, int n, long rp, double
     hipLaunchKernelGGL(k_dot_pitched, dim3(nblocks), dim3(kBlock), 0, s, src, b, n, rp, partials);
 }
 
-void launch_to_pitched(const float* src, float* dst, int n, long rp, float scale,
-                       hipStream_t s) {
-    const long N = (long)n * n * n;
-    hipLaunchKernelGGL(k_to_pitched, dim3(grid_for(N)), dim3(kBlock), 0, s, src, dst, n, rp, scale);
-}
-
 void launch_from_pitched(const float* src, float* dst, int n, long rp, hipStream_t s) {
     const long N = (long)n * n * n;
     hipLaunchKernelGGL(k_from_pitched, dim3(grid_for(N)), dim3(kBlock), 0, s, src, dst, n, rp);
-}
-
-void launch_spec_copy(const float2* src, float2* dst, int n, int cs, bool to_ws, hipStream_t s) {
-    const long N = (long)n * n * (n / 2 + 1);
-    hipLaunchKernelGGL(k_spec_copy, dim3(grid_for(N)), dim3(kBlock), 0, s, src, dst, n, cs,
-                       to_ws ? 1 : 0);
 }
 
 void launch_deinterleave(const float* v, float* dst, long dstStride, int np, long rp,

@@ -492,14 +492,16 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
     { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_c2r(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
 }
 
-// Gradient synthesis on the particle lattice: the real mesh in C0 becomes
-// s_j = IDFT(i n_j radial(|n|^2) DFT(C0)) in C1..C3 (the force chain; radial
-// carries the 1/k^2, the k units and the 1/Np^3 of the inverse).
-void grad_synthesis(pm_ctx* ctx, const float* radial) {
+// Gradient synthesis on the particle lattice: the real mesh in C0 (or `field`,
+// a dense [Np]^3 array, when given) becomes s_j = IDFT(i n_j radial(|n|^2) DFT(C0))
+// in C1..C3 (the force chain; radial carries the 1/k^2, the k units and the
+// 1/Np^3 of the inverse).
+void grad_synthesis(pm_ctx* ctx, const float* radial, const float* field = nullptr) {
     hipStream_t s = ctx->stream;
     const int np = ctx->np, cs = ctx->cs_p;
     const long cst = ctx->plan.cplx_elems;
-    launch_fft_x_r2c(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    if (field) launch_fft_x_r2c_from(field, ctx->C[0], np, cs, ctx->twd, s);
+    else launch_fft_x_r2c(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
     launch_fft_axis(ctx->C[0], np, cs, 1, -1, 1, cst, ctx->twd, s);
     launch_grad_z(ctx->C[0], ctx->C[1], cst, np, cs, radial, ctx->twd, s);
     launch_fft_axis(ctx->C[1], np, cs, 1, 1, 1, cst, ctx->twd, s);
@@ -508,8 +510,8 @@ void grad_synthesis(pm_ctx* ctx, const float* radial) {
 }
 
 // Transpose of grad_synthesis: the real mesh Sum_j IDFT(conj(i n_j radial)
-// DFT(v_j)) of v [P][3] (lattice order) in C0.
-void grad_transpose(pm_ctx* ctx, const float* v, const float* radial) {
+// DFT(v_j)) of v [P][3] (lattice order) in C0, or in the dense array `out`.
+void grad_transpose(pm_ctx* ctx, const float* v, const float* radial, float* out = nullptr) {
     hipStream_t s = ctx->stream;
     const int np = ctx->np, cs = ctx->cs_p;
     const long cst = ctx->plan.cplx_elems;
@@ -521,7 +523,8 @@ void grad_transpose(pm_ctx* ctx, const float* v, const float* radial) {
     launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], np, cs, radial, nullptr, 0.f,
                       ctx->twd, s);
     launch_fft_axis(ctx->C[0], np, cs, 1, 1, 1, cst, ctx->twd, s);
-    launch_fft_x_c2r(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    if (out) launch_fft_x_c2r_to(ctx->C[0], out, np, cs, ctx->twd, s);
+    else launch_fft_x_c2r(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
 }
 
 // Zel'dovich displacement (a = 1) of white noise `noise` [Np^3] with the radial
@@ -533,8 +536,7 @@ void ic_synthesis(pm_ctx* ctx, const float* noise, const float* radial, float* s
     hipStream_t s = ctx->stream;
     const long rp = 2L * ctx->cs_p;
     KTimer t(ctx, PM_K_OTHER, 0);
-    launch_to_pitched(noise, ctx->creal(0), ctx->np, rp, 1.f, s);
-    grad_synthesis(ctx, radial);
+    grad_synthesis(ctx, radial, noise);
     launch_ic_state(ctx->creal(1), ctx->creal_stride(), rp, (float)ctx->sched.D0,
                     (float)ctx->sched.G0, ctx->lat, xq, pq, id, s_out, s, s2v,
                     (float)ctx->sched.D20, (float)ctx->sched.G20);
@@ -543,8 +545,7 @@ void ic_synthesis(pm_ctx* ctx, const float* noise, const float* radial, float* s
 // dL/dnoise = transpose of the Zel'dovich synthesis applied to s_bar [P][3].
 void ic_transpose(pm_ctx* ctx, const float* s_bar, float* g_noise) {
     KTimer t(ctx, PM_K_OTHER, 0);
-    grad_transpose(ctx, s_bar, ctx->radial_ic);
-    launch_from_pitched(ctx->creal(0), g_noise, ctx->np, 2L * ctx->cs_p, ctx->stream);
+    grad_transpose(ctx, s_bar, ctx->radial_ic, g_noise);
 }
 
 // The six Hessian entries (a, b), a <= b, of the potential of the linear density.
@@ -564,8 +565,7 @@ void lpt_second_order(pm_ctx* ctx, const float* noise, float* s2_out) {
     const float kf = (float)(2.0 * kPi / ctx->cfg.box);
     float *r0 = ctx->creal(0), *r1 = ctx->creal(1), *r2 = ctx->creal(2), *r3 = ctx->creal(3);
     KTimer t(ctx, PM_K_OTHER, 0);
-    launch_to_pitched(noise, r0, np, rp, 1.f, s);
-    launch_fft3_r2c(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    launch_fft3_r2c_dense(noise, ctx->C[0], nullptr, np, cs, ctx->twd, s);
     for (int a = 0; a < 3; ++a)
         launch_lpt_mul(ctx->C[0], ctx->C[1 + a], np, cs, a, a, 0, ctx->radial_ic, kf, false, s);
     launch_fft3_c2r(ctx->C[1], np, cs, 3, cst, ctx->twd, s);
@@ -600,8 +600,7 @@ int lpt_second_order_transpose(pm_ctx* ctx, const float* noise, const float* s2_
     if (hipMemcpyAsync(r3, r0, (size_t)np * np * rp * sizeof(float), hipMemcpyDeviceToDevice, s) !=
         hipSuccess)
         return ctx->fail(PM_EHIP, "device copy failed");
-    launch_to_pitched(noise, r0, np, rp, 1.f, s);
-    launch_fft3_r2c(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    launch_fft3_r2c_dense(noise, ctx->C[0], nullptr, np, cs, ctx->twd, s);
     // C1 = Sum_ab (n_a n_b / |n|^2) DFT(phi_ab_bar)
     for (int k = 0; k < 6; ++k) {
         const int a = kPairs[k][0], b = kPairs[k][1];
@@ -1195,8 +1194,7 @@ int pm_loss_pk(pm_ctx* ctx, const float* dens, int32_t n_bins, const double* pk_
     if (!std::isfinite(weight)) return ctx->fail(PM_EINVAL, "weight must be finite");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_to_pitched(dens, ctx->creal(0), ng, ctx->lat.rp, 1.f, s);
-    launch_fft3_r2c(ctx->C[0], ng, ctx->cs, 1, ctx->plan.cplx_elems, ctx->twd, s);
+    launch_fft3_r2c_dense(dens, ctx->C[0], nullptr, ng, ctx->cs, ctx->twd, s);
     launch_zero(ctx->pkbins, 3 * (size_t)n_bins * sizeof(double), s);
     launch_pk_bin(ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, s);
     PM_TRY(ctx->hip_check("pm_loss_pk"));
@@ -1236,8 +1234,7 @@ int pm_loss_pk(pm_ctx* ctx, const float* dens, int32_t n_bins, const double* pk_
                        hipMemcpyHostToDevice, s) != hipSuccess)
         return ctx->fail(PM_EHIP, "upload of the loss table failed");
     launch_radial_scale(ctx->C[0], ng, ctx->cs, ctx->losstab, s);
-    launch_fft3_c2r(ctx->C[0], ng, ctx->cs, 1, ctx->plan.cplx_elems, ctx->twd, s);
-    launch_from_pitched(ctx->creal(0), g_dens, ng, ctx->lat.rp, s);
+    launch_fft3_c2r_dense(nullptr, ctx->C[0], g_dens, ng, ctx->cs, ctx->twd, s);
     return ctx->hip_check("pm_loss_pk");
 }
 
@@ -1271,8 +1268,7 @@ int pm_power_spectrum(pm_ctx* ctx, const float* dens, int32_t n_bins, double* k_
     if (n_bins < 1 || n_bins > ctx->ng) return ctx->fail(PM_EINVAL, "n_bins must be in [1, mesh]");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_to_pitched(dens, ctx->creal(0), ng, ctx->lat.rp, 1.f, s);
-    launch_fft3_r2c(ctx->C[0], ng, ctx->cs, 1, ctx->plan.cplx_elems, ctx->twd, s);
+    launch_fft3_r2c_dense(dens, ctx->C[0], nullptr, ng, ctx->cs, ctx->twd, s);
     launch_zero(ctx->pkbins, 3 * (size_t)n_bins * sizeof(double), s);
     launch_pk_bin(ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, s);
     PM_TRY(ctx->hip_check("pm_power_spectrum"));
@@ -1339,9 +1335,7 @@ int pm_fft_r2c(pm_ctx* ctx, const float* real, float* spec) {
     if (!real || !spec) return ctx->fail(PM_EINVAL, "real and spec are required");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_to_pitched(real, ctx->creal(0), ng, ctx->lat.rp, 1.f, s);
-    launch_fft3_r2c(ctx->C[0], ng, ctx->cs, 1, ctx->plan.cplx_elems, ctx->twd, s);
-    launch_spec_copy(ctx->C[0], reinterpret_cast<float2*>(spec), ng, ctx->cs, false, s);
+    launch_fft3_r2c_dense(real, ctx->C[0], reinterpret_cast<float2*>(spec), ng, ctx->cs, ctx->twd, s);
     return ctx->hip_check("pm_fft_r2c");
 }
 
@@ -1350,9 +1344,8 @@ int pm_fft_c2r(pm_ctx* ctx, const float* spec, float* real) {
     if (!real || !spec) return ctx->fail(PM_EINVAL, "real and spec are required");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_spec_copy(reinterpret_cast<const float2*>(spec), ctx->C[0], ng, ctx->cs, true, s);
-    launch_fft3_c2r(ctx->C[0], ng, ctx->cs, 1, ctx->plan.cplx_elems, ctx->twd, s);
-    launch_from_pitched(ctx->creal(0), real, ng, ctx->lat.rp, s);
+    launch_fft3_c2r_dense(reinterpret_cast<const float2*>(spec), ctx->C[0], real, ng, ctx->cs,
+                          ctx->twd, s);
     return ctx->hip_check("pm_fft_c2r");
 }
 
