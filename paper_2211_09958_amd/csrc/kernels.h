@@ -149,9 +149,10 @@ void launch_bin_zero(Bins& b, hipStream_t s);
 // for any other layout.
 bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
 // Density delta = rho - 1 (particle mass (ng/np)^3) into a real mesh with pitch
-// L.rp; every cell written once (no pre-zeroing), deterministic.
+// L.rp (nullable) and/or a caller's dense [ng]^3 array in plain order (nullable,
+// any 4-byte alignment); every cell written once (no pre-zeroing), deterministic.
 void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
-                            hipStream_t s);
+                            float* dense, hipStream_t s);
 // out_j = Sum_p coeff v_{p,j} w(x_p, node) for j = 0..2 into meshes out + j*outStride
 // (64-bit fixed point, bitwise reproducible); vmax_scratch is one device word.
 void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, unsigned* vmax_scratch,
@@ -174,14 +175,15 @@ void launch_gather_kick_drift(uint32_t* xq, int32_t* pq, const uint32_t* id, con
                               long fStride, const Lattice& L, const Bins& b, float kick,
                               float drift, int do_drift, uint32_t* ck_x, int32_t* ck_p,
                               unsigned* ovf, bool count_bins, hipStream_t s);
-// out[id[p]][j] = Sum w F_j (lattice order).
-void launch_gather_force(const uint32_t* xq, const uint32_t* id, const float* fmesh, long fStride,
-                         const Lattice& L, const Bins& b, float* out, hipStream_t s);
+// out[p][j] = Sum w F_j for the particle in storage slot p.
+void launch_gather_force(const uint32_t* xq, const float* fmesh, long fStride, const Lattice& L,
+                         const Bins& b, float* out, hipStream_t s);
 // Reverse step at x: F = gather; p -= coeff F (exact inverse of the forward
-// kick; pq nullable); xi += coeff Sum_j pi_j grad w . F~_j; partials Sum pi . F.
+// kick; pq nullable); xi (taken as zero with xi_zero) += coeff Sum_j pi_j grad w .
+// F~_j; partials Sum pi . F.
 void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long fStride,
                        const Lattice& L, const Bins& b, float coeff, const float* pi, float* xi,
-                       double* partials, hipStream_t s);
+                       bool xi_zero, double* partials, hipStream_t s);
 // xi += g_scale Sum grad w . mesh (mesh row pitch given; rows in the workspace
 // order of layout.h, or in plain order when dense).  mode 1 also does the rest
 // of a reverse step: partials Sum xi . p, pi += drift xi, x -= drift p (exact
@@ -191,16 +193,17 @@ void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long
 void launch_wgrad(const float* mesh, long pitch, float g_scale, uint32_t* xq, const int32_t* pq,
                   float* xi, float* pi, const Lattice& L, const Bins& b, float drift, int mode,
                   double* partials, hipStream_t s, bool dense = false, bool count_bins = false);
-// Displacements (float, Mpc/h, lattice order) -> fixed-point positions q + s
-// in lattice order, id = identity.
-void launch_to_fixed(const float* disp, uint32_t* xq, uint32_t* id, const Lattice& L,
-                     hipStream_t s);
+// Displacements (float, Mpc/h, lattice order) -> fixed-point positions q + s in
+// lattice order, counted into b's counts, keys and ranks for a following
+// launch_bin(counted = true).
+void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bins& b,
+                           hipStream_t s);
 // Fixed-point state (any order) -> displacement (minimum image of x - q) and
 // momentum in lattice order (disp, mom, pq nullable).
 void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
                        const Lattice& L, float* disp, float* mom, hipStream_t s);
-// [P][3] float records: mode 0 out[k] = in[id[k]], mode 1 out[id[k]] = in[k].
-void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P, int mode,
+// [P][3] float records to lattice order: out[id[k]] = in[k].
+void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P,
                           hipStream_t s);
 // Fixed-point state (any order) scattered to lattice order by id.
 void launch_state_to_lattice(const uint32_t* xq, const int32_t* pq, const uint32_t* id, long P,
@@ -248,8 +251,6 @@ void launch_add_from_pitched(const float* src, float* dst, int n, long rp, float
                              hipStream_t s);
 void launch_dot_pitched(const float* src, const float* b, int n, long rp, double* partials,
                         int nblocks, hipStream_t s);
-// Pitched rows -> compact [n]^3.
-void launch_from_pitched(const float* src, float* dst, int n, long rp, hipStream_t s);
 // AoS [P][3] component j -> pitched mesh j (three meshes).
 void launch_deinterleave(const float* v, float* dst, long dstStride, int np, long rp,
                          hipStream_t s);

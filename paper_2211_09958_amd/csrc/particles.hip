@@ -44,11 +44,13 @@ namespace {
 constexpr int kBlock = 256;
 constexpr double kFix = 4294967296.0;  // 2^32
 
+// Lattice coordinates of particle p (np a power of two: shifts and masks, since
+// a 64-bit division takes some hundred instructions).
 __device__ __forceinline__ void lattice_index(long p, int np, int jj[3]) {
-    jj[2] = (int)(p % np);
-    long q = p / np;
-    jj[1] = (int)(q % np);
-    jj[0] = (int)(q / np);
+    const int lg = __ffs(np) - 1, m = np - 1;
+    jj[2] = (int)p & m;
+    jj[1] = (int)(p >> lg) & m;
+    jj[0] = (int)(p >> (2 * lg));
 }
 
 // Tiles are numbered in Morton (Z) order so that consecutive bins, and hence
@@ -151,14 +153,16 @@ __device__ __forceinline__ uint32_t bin_key(const uint32_t x[3], const Lattice& 
 // one's rank among the particles of its key.  One atomic per distinct key in
 // the wave, all issued together: the lanes are grouped by key first (no memory
 // traffic), then every group's first lane adds the group size, and rank = that
-// slot + the lane's place in its group.  Every active lane must call it.
+// slot + the lane's place in its group.  Every active lane must call it.  The
+// group's key is read with v_readlane (the leader is the same for all lanes):
+// through the LDS crossbar, the loop waited for each of its up to 20 groups.
 __device__ __forceinline__ uint32_t bin_rank(uint32_t key, uint32_t* __restrict__ counts) {
     const int lane = __lane_id();
     unsigned long long pending = __ballot(1);
     unsigned long long mine = 0ull;   // lanes sharing this lane's key
     while (pending) {
         const int leader = __ffsll((long long)pending) - 1;
-        const uint32_t lk = (uint32_t)__shfl((int)key, leader);
+        const uint32_t lk = (uint32_t)__builtin_amdgcn_readlane((int)key, leader);
         const unsigned long long same = __ballot(key == lk) & pending;
         if ((same >> lane) & 1ull) mine = same;
         pending &= ~same;
@@ -181,6 +185,32 @@ k_bin_count(const uint32_t* __restrict__ xq, Lattice L, int tile, long P,
         keys[i] = key;
         ranks[i] = rank;
     }
+}
+
+// Displacements in lattice order -> fixed-point positions q + s, counted into
+// the bins in the same pass (reading the positions back for the count would
+// move as many bytes again).
+__global__ void __launch_bounds__(kBlock)
+k_to_fixed_count(const float* __restrict__ disp, uint32_t* __restrict__ xq, Lattice L, int tile,
+                 long P, uint32_t* __restrict__ counts, uint32_t* __restrict__ keys,
+                 uint32_t* __restrict__ ranks) {
+    const long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if (p >= P) return;
+    int jj[3];
+    lattice_index(p, L.np, jj);
+    float d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) d[a] = disp[3 * p + a];
+    uint32_t x[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        x[a] = (uint32_t)jj[a] * L.qstep + (uint32_t)__float2ll_rn(__fmul_rn(d[a], L.len_to_pos));
+#pragma unroll
+    for (int a = 0; a < 3; ++a) xq[3 * p + a] = x[a];
+    const uint32_t key = bin_key(x, L, tile);
+    const uint32_t rank = bin_rank(key, counts);
+    keys[p] = key;
+    ranks[p] = rank;
 }
 
 // Exclusive block scan of 1024 threads x 4 values.
@@ -458,7 +488,9 @@ __device__ __forceinline__ void deposit_kept(unsigned long long* acc, const floa
 // faster on gfx950 than floating-point LDS atomics.  The kernel is bound by its
 // vector-ALU instruction count (a wave64 instruction takes four cycles), so the
 // per-corner work is kept to an index add, two products and the fixed-point
-// conversion, and the write-out handles four cells per thread.
+// conversion, and the write-out handles four cells per thread.  The density can
+// also go to a caller's plain [ng]^3 array (dense), in the same write-out or
+// instead of the workspace mesh (out null).
 // Threads per scatter work-group; the 32 KB accumulator tile leaves room for
 // four work-groups per CU, so larger ones keep more waves in flight.
 constexpr int scatter_threads() { return 2 * kBlock; }
@@ -468,7 +500,7 @@ __global__ void __launch_bounds__(scatter_threads())
 k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, float coeff,
                const unsigned* __restrict__ vmax_bits, Lattice L, int nt,
                const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ord,
-               float* __restrict__ out, long outStride) {
+               float* __restrict__ out, long outStride, float* __restrict__ dense) {
     constexpr int T3 = T * T * T, NTH = scatter_threads();
     static_assert(T % 4 == 0, "the write-out handles four cells of a row at a time");
     __shared__ __align__(16) unsigned long long acc[T3];
@@ -590,7 +622,17 @@ k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, 
                 const unsigned lo = (unsigned)v4[i];
                 r4[i] = (float)fma((double)lo, inv_scale, (double)hi * hi_scale);
             }
-            *reinterpret_cast<float4*>(o + g) = make_float4(r4[0], r4[1], r4[2], r4[3]);
+            if (VEC || out)
+                *reinterpret_cast<float4*>(o + g) = make_float4(r4[0], r4[1], r4[2], r4[3]);
+            if (!VEC && dense) {   // a caller's mesh: plain row order, any alignment
+                float* d = dense + ((long)(lo[0] + l0) * L.ng + lo[1] + l1) * L.ng + lo[2] + l2;
+                if ((reinterpret_cast<uintptr_t>(dense) & 15) == 0) {
+                    *reinterpret_cast<float4*>(d) = make_float4(r4[0], r4[1], r4[2], r4[3]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d[i] = r4[i];
+                }
+            }
         }
         __syncthreads();
     }
@@ -629,17 +671,18 @@ enum GatherMode { kKickDrift = 0, kForce = 1, kUnkickVjp = 2, kWgrad = 3 };
 struct GatherArgs {
     uint32_t* xq;
     int32_t* pq;
-    const uint32_t* id;
+    const uint32_t* id;   // kKickDrift checkpoints
     const float* mesh;    // 3 meshes mStride apart (1 for kWgrad)
     long mStride;
     long pitch;           // real-row pitch of the meshes
     int dense;            // 1: meshes in plain row order (a caller's [Ng]^3 array)
     float coeff;          // kick coefficient, or the mesh scale for kWgrad
     float drift;
-    int flag;             // kKickDrift: drift?; kWgrad: 1 full reverse step, 2 xi only
+    int flag;             // kKickDrift: drift?; kWgrad: 1 full reverse step, 2 xi only;
+                          // kUnkickVjp: 1 xi starts at zero (not read)
     uint32_t* ck_x;       // kKickDrift checkpoint, lattice order (nullable)
     int32_t* ck_p;
-    float* out;           // kForce output, lattice order
+    float* out;           // kForce output, by storage slot
     const float* pi_in;   // kUnkickVjp
     float* xi;            // kUnkickVjp, kWgrad
     float* pi;            // kWgrad
@@ -686,7 +729,11 @@ __device__ __forceinline__ void gather_load(const GatherArgs& A, uint32_t p, Gat
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             r.pin[a] = A.pi_in[3 * (size_t)p + a];
-            r.xin[a] = A.xi[3 * (size_t)p + a];
+            r.xin[a] = 0.f;
+        }
+        if (!A.flag) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) r.xin[a] = A.xi[3 * (size_t)p + a];
         }
     } else if constexpr (MODE == kWgrad) {
 #pragma unroll
@@ -783,9 +830,8 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
             A.branks[p] = rank;
         }
     } else if constexpr (MODE == kForce) {
-        const long q = A.id[p];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) A.out[3 * q + a] = F[a];
+        for (int a = 0; a < 3; ++a) A.out[3 * (size_t)p + a] = F[a];
     } else if constexpr (MODE == kUnkickVjp) {
         if (A.pq) {
 #pragma unroll
@@ -880,21 +926,6 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_to_fixed(const float* __restrict__ disp, uint32_t* __restrict__ xq, uint32_t* __restrict__ id,
-           Lattice L, long P) {
-    for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
-         p += (long)gridDim.x * kBlock) {
-        int jj[3];
-        lattice_index(p, L.np, jj);
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            xq[3 * p + a] = (uint32_t)jj[a] * L.qstep +
-                            (uint32_t)__float2ll_rn(__fmul_rn(disp[3 * p + a], L.len_to_pos));
-        id[p] = (uint32_t)p;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock)
 k_from_fixed(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
              const uint32_t* __restrict__ id, Lattice L, long P, float* __restrict__ disp,
              float* __restrict__ mom) {
@@ -914,14 +945,15 @@ k_from_fixed(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
 
 __global__ void __launch_bounds__(kBlock)
 k_permute_by_id(const float* __restrict__ in, const uint32_t* __restrict__ id,
-                float* __restrict__ out, long P, int mode) {
+                float* __restrict__ out, long P) {
     for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
          p += (long)gridDim.x * kBlock) {
         const long q = id[p];
-        const long src = mode == 0 ? q : p, dst = mode == 0 ? p : q;
-        out[3 * dst] = in[3 * src];
-        out[3 * dst + 1] = in[3 * src + 1];
-        out[3 * dst + 2] = in[3 * src + 2];
+        float v[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) v[a] = in[3 * p + a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) out[3 * q + a] = v[a];
     }
 }
 
@@ -1189,15 +1221,6 @@ k_dot_pitched(const float* __restrict__ src, const float* __restrict__ b, int n,
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_from_pitched(const float* __restrict__ src, float* __restrict__ dst, int n, long rp) {
-    const long N = (long)n * n * n;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const long row = i / n;
-        dst[i] = src[mesh_row((int)(row / n), (int)(row % n), n) * rp + (i % n)];
-    }
-}
-
-__global__ void __launch_bounds__(kBlock)
 k_deinterleave(const float* __restrict__ v, float* __restrict__ dst, long dstStride, int np, long rp) {
     const long P = (long)np * np * np;
     for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
@@ -1366,27 +1389,27 @@ bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
 template <bool VEC>
 static void scatter_dispatch(const uint32_t* xq, const float* v, float coeff, const unsigned* vmax,
                              const Lattice& L, const Bins& b, float* out, long outStride,
-                             hipStream_t s) {
+                             float* dense, hipStream_t s) {
     const unsigned ntiles = (unsigned)b.nt * b.nt * b.nt;
     switch (b.tile) {
         case 4:
             hipLaunchKernelGGL((k_scatter_tile<4, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
-                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride);
+                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
         case 8:
             hipLaunchKernelGGL((k_scatter_tile<8, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
-                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride);
+                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
         default:
             hipLaunchKernelGGL((k_scatter_tile<16, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
-                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride);
+                               coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
     }
 }
 
 void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
-                            hipStream_t s) {
-    scatter_dispatch<false>(xq, nullptr, 0.f, nullptr, L, b, mesh, 0, s);
+                            float* dense, hipStream_t s) {
+    scatter_dispatch<false>(xq, nullptr, 0.f, nullptr, L, b, mesh, 0, dense, s);
 }
 
 void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, unsigned* vmax_scratch,
@@ -1396,7 +1419,7 @@ void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, unsigne
     launch_zero(vmax_scratch, sizeof(unsigned), s);
     const long nb = std::min<long>(grid_for(3 * P), 4096);
     hipLaunchKernelGGL(k_absmax, dim3((unsigned)nb), dim3(kBlock), 0, s, v, 3 * P, vmax_scratch);
-    scatter_dispatch<true>(xq, v, coeff, vmax_scratch, L, b, out, outStride, s);
+    scatter_dispatch<true>(xq, v, coeff, vmax_scratch, L, b, out, outStride, nullptr, s);
 }
 
 template <int MODE>
@@ -1449,11 +1472,10 @@ void launch_gather_kick_drift(uint32_t* xq, int32_t* pq, const uint32_t* id, con
     gather_dispatch<kKickDrift>(A, L, b, s);
 }
 
-void launch_gather_force(const uint32_t* xq, const uint32_t* id, const float* fmesh, long fStride,
-                         const Lattice& L, const Bins& b, float* out, hipStream_t s) {
+void launch_gather_force(const uint32_t* xq, const float* fmesh, long fStride, const Lattice& L,
+                         const Bins& b, float* out, hipStream_t s) {
     GatherArgs A{};
     A.xq = const_cast<uint32_t*>(xq);
-    A.id = id;
     A.mesh = fmesh;
     A.mStride = fStride;
     A.pitch = L.rp;
@@ -1463,8 +1485,9 @@ void launch_gather_force(const uint32_t* xq, const uint32_t* id, const float* fm
 
 void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long fStride,
                        const Lattice& L, const Bins& b, float coeff, const float* pi, float* xi,
-                       double* partials, hipStream_t s) {
+                       bool xi_zero, double* partials, hipStream_t s) {
     GatherArgs A{};
+    A.flag = xi_zero ? 1 : 0;
     A.xq = const_cast<uint32_t*>(xq);
     A.pq = pq;
     A.mesh = fmesh;
@@ -1496,10 +1519,12 @@ void launch_wgrad(const float* mesh, long pitch, float g_scale, uint32_t* xq, co
     gather_dispatch<kWgrad>(A, L, b, s);
 }
 
-void launch_to_fixed(const float* disp, uint32_t* xq, uint32_t* id, const Lattice& L,
-                     hipStream_t s) {
+void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bins& b,
+                           hipStream_t s) {
     const long P = (long)L.np * L.np * L.np;
-    hipLaunchKernelGGL(k_to_fixed, dim3(grid_for(P)), dim3(kBlock), 0, s, disp, xq, id, L, P);
+    launch_bin_zero(b, s);
+    hipLaunchKernelGGL(k_to_fixed_count, dim3(grid_for(P)), dim3(kBlock), 0, s, disp, xq, L, b.tile,
+                       P, b.counts, b.keys, b.ranks);
 }
 
 void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
@@ -1509,9 +1534,9 @@ void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id
                        mom);
 }
 
-void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P, int mode,
+void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P,
                           hipStream_t s) {
-    hipLaunchKernelGGL(k_permute_by_id, dim3(grid_for(P)), dim3(kBlock), 0, s, in, id, out, P, mode);
+    hipLaunchKernelGGL(k_permute_by_id, dim3(grid_for(P)), dim3(kBlock), 0, s, in, id, out, P);
 }
 
 void launch_state_to_lattice(const uint32_t* xq, const int32_t* pq, const uint32_t* id, long P,
@@ -1581,11 +1606,6 @@ void launch_add_from_pitched(const float* src, float* dst, int n, long rp, float
 void launch_dot_pitched(const float* src, const float* b, int n, long rp, double* partials,
                         int nblocks, hipStream_t s) {
     hipLaunchKernelGGL(k_dot_pitched, dim3(nblocks), dim3(kBlock), 0, s, src, b, n, rp, partials);
-}
-
-void launch_from_pitched(const float* src, float* dst, int n, long rp, hipStream_t s) {
-    const long N = (long)n * n * n;
-    hipLaunchKernelGGL(k_from_pitched, dim3(grid_for(N)), dim3(kBlock), 0, s, src, dst, n, rp);
 }
 
 void launch_deinterleave(const float* v, float* dst, long dstStride, int np, long rp,

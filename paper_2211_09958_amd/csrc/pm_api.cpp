@@ -421,6 +421,20 @@ double sort_particles(pm_ctx* ctx, bool cotangents) {
     return bytes + (cotangents ? 112.0 : 64.0) * P;
 }
 
+// Fixed-point positions of a caller's displacements in the working positions,
+// in lattice order and counted into the bins; the running state is gone.
+void load_once(pm_ctx* ctx, const float* disp) {
+    launch_to_fixed_count(disp, ctx->xq, ctx->lat, ctx->bins, ctx->stream);
+    ctx->sorts_since_compact = kLatticeOrder;
+    ctx->counts_ready = false;
+}
+
+// Bins the positions of load_once; the records stay in lattice order.
+double order_once(pm_ctx* ctx) {
+    launch_bin(ctx->xq, ctx->lat, ctx->bins, true, ctx->stream);
+    return 12.0 * ctx->P;
+}
+
 // The working records were just written in lattice order.
 void records_in_lattice_order(pm_ctx* ctx) {
     ctx->sorts_since_compact = kLatticeOrder;
@@ -431,16 +445,28 @@ void records_in_lattice_order(pm_ctx* ctx) {
 // the next sort's bins.
 void count_next_bins(pm_ctx* ctx) { launch_bin_zero(ctx->bins, ctx->stream); }
 
+// What compute_force and the building blocks bin: the running state (with or
+// without its cotangents), whose records compact every few sorts, or one set of
+// positions used once (counted by launch_to_fixed_count), which stays in
+// lattice order: compacting its records costs more than the one or two kernels
+// that read them through the order save (512^3 particles: 2.24 ms for the
+// compaction alone; force on a 512^3 mesh 9.88 -> 7.52 ms without it, with the
+// count in the pass that loads the positions and with slot-ordered
+// output; density and P(k) at 256^3 0.948 -> 0.607 ms; sparse sets, 128^3 on
+// 512^3, gain nothing and lose nothing).
+enum Particles { kState, kStateCotangents, kOnce };
+
 // PM force meshes of the working particles: sort into bins, delta -> C0
 // (x,y-transformed spectrum left in C0), F~_j real meshes in C1..C3.
-void compute_force(pm_ctx* ctx, double a, bool cotangents) {
+void compute_force(pm_ctx* ctx, double a, Particles which) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
     const double r = mesh_r(ng), c = mesh_c(ng), P = (double)ctx->P;
-    { KTimer t(ctx, PM_K_BIN, 0); t.bytes = sort_particles(ctx, cotangents); }
+    { KTimer t(ctx, PM_K_BIN, 0);
+      t.bytes = which == kOnce ? order_once(ctx) : sort_particles(ctx, which == kStateCotangents); }
     { KTimer t(ctx, PM_K_SCATTER, 12 * P + r);
-      launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), s); }
+      launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), nullptr, s); }
     { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_r2c(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
       launch_fft_axis(ctx->C[0], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
@@ -918,7 +944,7 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
                  ctx->lpt2() ? ctx->tmpv : nullptr);
     records_in_lattice_order(ctx);
     for (int n = 0; n <= N; ++n) {
-        compute_force(ctx, sc.a[n], false);
+        compute_force(ctx, sc.a[n], kState);
         const double kick = (n > 0 ? sc.kick_b[n - 1] : 0.0) + (n < N ? sc.kick_a[n] : 0.0);
         uint32_t* ckx = nullptr;
         int32_t* ckp = nullptr;
@@ -944,8 +970,7 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
         launch_from_fixed(ctx->xq, ctx->pq, ctx->id, ctx->lat, disp_out, mom_out, s);
         if (dens) {
             sort_particles(ctx, false);
-            launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), s);
-            launch_from_pitched(ctx->creal(0), dens, ctx->ng, ctx->lat.rp, s);
+            launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, nullptr, dens, s);
         }
     }
     (void)hipEventRecord(ctx->ev[1], s);
@@ -992,7 +1017,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     // force evaluation, then + m grad w . dL/ddelta
     if (g_disp) PM_TRY(copy_d2d(ctx, ctx->xi, g_disp, vec));
     else launch_zero(ctx->xi, vec, s);
-    compute_force(ctx, sc.a[N], true);
+    compute_force(ctx, sc.a[N], kStateCotangents);
     const int nbu = (int)unkick_vjp_partials(ctx->bins), nbw = (int)wgrad_partials(ctx->bins);
     if (g_dens) {
         KTimer t(ctx, PM_K_WGRAD, 24.0 * P + mesh_r(ctx->ng));
@@ -1002,7 +1027,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     {
         KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
         launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
-                          ctx->bins, (float)sc.kick_b[N - 1], ctx->pi, ctx->xi, ctx->partials, s);
+                          ctx->bins, (float)sc.kick_b[N - 1], ctx->pi, ctx->xi, false, ctx->partials, s);
     }
     launch_reduce(ctx->partials, nbu, ctx->sums, slotS + N, s);
 
@@ -1030,8 +1055,8 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
             // reset to the stored (lattice-order) state; cotangents to lattice order
             PM_TRY(copy_d2d(ctx, ctx->xq, ckx, vec));
             PM_TRY(copy_d2d(ctx, ctx->pq, ckx + 3 * P, vec));
-            launch_permute_by_id(ctx->xi, ctx->id, ctx->xi_alt, P, 1, s);
-            launch_permute_by_id(ctx->pi, ctx->id, ctx->pi_alt, P, 1, s);
+            launch_permute_by_id(ctx->xi, ctx->id, ctx->xi_alt, P, s);
+            launch_permute_by_id(ctx->pi, ctx->id, ctx->pi_alt, P, s);
             std::swap(ctx->xi, ctx->xi_alt);
             std::swap(ctx->pi, ctx->pi_alt);
             launch_iota(ctx->id, P, s);
@@ -1039,12 +1064,12 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
             ++nck;
         }
         // recompute F(x_n); un-kick and (i) at x_n
-        compute_force(ctx, sc.a[n], true);
+        compute_force(ctx, sc.a[n], kStateCotangents);
         const double c0 = (n > 0 ? sc.kick_b[n - 1] : 0.0) + sc.kick_a[n];
         {
             KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
             launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
-                              ctx->bins, (float)c0, ctx->pi, ctx->xi, ctx->partials, s);
+                              ctx->bins, (float)c0, ctx->pi, ctx->xi, false, ctx->partials, s);
         }
         launch_reduce(ctx->partials, nbu, ctx->sums, slotS + n, s);
     }
@@ -1289,11 +1314,9 @@ int pm_power_spectrum(pm_ctx* ctx, const float* dens, int32_t n_bins, double* k_
 int pm_density(pm_ctx* ctx, const float* disp, float* dens) {
     PM_TRY(ctx_check(ctx));
     if (!disp || !dens) return ctx->fail(PM_EINVAL, "disp and dens are required");
-    launch_to_fixed(disp, ctx->xq, ctx->id, ctx->lat, ctx->stream);
-    records_in_lattice_order(ctx);
-    sort_particles(ctx, false);
-    launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), ctx->stream);
-    launch_from_pitched(ctx->creal(0), dens, ctx->ng, ctx->lat.rp, ctx->stream);
+    load_once(ctx, disp);
+    order_once(ctx);
+    launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, nullptr, dens, ctx->stream);
     return ctx->hip_check("pm_density");
 }
 
@@ -1301,11 +1324,10 @@ int pm_force(pm_ctx* ctx, const float* disp, double a, float* force) {
     PM_TRY(ctx_check(ctx));
     if (!disp || !force) return ctx->fail(PM_EINVAL, "disp and force are required");
     if (ctx->cfg.filter && !ctx->have_filter) return ctx->fail(PM_ESTATE, "pm_set_filter not called");
-    launch_to_fixed(disp, ctx->xq, ctx->id, ctx->lat, ctx->stream);
-    records_in_lattice_order(ctx);
-    compute_force(ctx, a, false);
-    launch_gather_force(ctx->xq, ctx->id, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins,
-                        force, ctx->stream);
+    load_once(ctx, disp);
+    compute_force(ctx, a, kOnce);
+    launch_gather_force(ctx->xq, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins, force,
+                        ctx->stream);
     return ctx->hip_check("pm_force");
 }
 
@@ -1314,19 +1336,14 @@ int pm_force_vjp(pm_ctx* ctx, const float* disp, double a, const float* v, float
     if (!disp || !v || !xi) return ctx->fail(PM_EINVAL, "disp, v and xi are required");
     if (ctx->cfg.filter && !ctx->have_filter) return ctx->fail(PM_ESTATE, "pm_set_filter not called");
     hipStream_t s = ctx->stream;
-    launch_to_fixed(disp, ctx->xq, ctx->id, ctx->lat, s);
-    records_in_lattice_order(ctx);
-    compute_force(ctx, a, false);
-    // v and xi in the records' (sorted) order
-    launch_permute_by_id(v, ctx->id, ctx->pi, ctx->P, 0, s);
-    launch_zero(ctx->xi, (size_t)ctx->P * 3 * sizeof(float), s);
+    load_once(ctx, disp);
+    compute_force(ctx, a, kOnce);
     launch_unkick_vjp(ctx->xq, nullptr, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins,
-                      1.f, ctx->pi, ctx->xi, nullptr, s);
+                      1.f, v, xi, true, nullptr, s);
     if (ctx->cfg.filter) launch_zero(ctx->gtheta, kNParam * sizeof(float), s);
-    vjp_mesh(ctx, ctx->xq, ctx->pi, 1.f, a);
-    launch_wgrad(ctx->creal(0), ctx->lat.rp, ctx->mass(), ctx->xq, nullptr, ctx->xi, nullptr,
-                 ctx->lat, ctx->bins, 0.f, 2, nullptr, s);
-    launch_permute_by_id(ctx->xi, ctx->id, xi, ctx->P, 1, s);
+    vjp_mesh(ctx, ctx->xq, v, 1.f, a);
+    launch_wgrad(ctx->creal(0), ctx->lat.rp, ctx->mass(), ctx->xq, nullptr, xi, nullptr, ctx->lat,
+                 ctx->bins, 0.f, 2, nullptr, s);
     return ctx->hip_check("pm_force_vjp");
 }
 

@@ -1,0 +1,61 @@
+"""Density, force and force VJP of a caller's displacements: binned once, records in lattice order,
+outputs by storage slot."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import context, dev, host
+from oracle import mesh as M
+from oracle import pm as opm
+from synthetic import normal
+
+pytestmark = pytest.mark.gpu
+
+
+def disps(np_, box):
+    """All particles of a wave in few bins, in many bins, and a pile in one cell."""
+    n = np_ ** 3
+    q = opm.lattice(np_, box)
+    smooth = 0.3 * box / np_ * normal((n, 3), 1)
+    spread = box * normal((n, 3), 2)
+    pile = box * 0.37 - q + 1e-3 * box / np_ * normal((n, 3), 3)
+    return {"smooth": smooth, "spread": spread, "pile": pile}
+
+
+@pytest.mark.parametrize("np_,ng", [(8, 8), (8, 16), (16, 32), (16, 64), (32, 32)])
+@pytest.mark.parametrize("kind", ["smooth", "spread", "pile"])
+def test_density_into_any_alignment(np_, ng, kind):
+    box = 50.0
+    pm = context(np_, ng, box, 1)
+    d = dev(disps(np_, box)[kind])
+    out = torch.full((ng ** 3 + 8,), np.nan, dtype=torch.float32, device="cuda")
+    got = []
+    for words in (0, 1):
+        view = out[words:words + ng ** 3]
+        rc = pm.lib.pm_density(pm.ctx, ctypes.c_void_p(d.data_ptr()),
+                               ctypes.c_void_p(view.data_ptr()))
+        assert rc == 0
+        got.append(view.clone())
+    assert torch.equal(got[0], got[1])
+    # CIC weights of 32-bit positions: 2^-32 box against cells of box / ng, 8 corners of 2^-24
+    units = np.rint(host(d).astype(np.float32) * np.float32(2.0 ** 32 / box)).astype(np.float64)
+    x = opm.lattice(np_, box) + units * (box / 2.0 ** 32)
+    want = M.density(x, ng, box, np_ ** 3)
+    assert np.abs(host(got[0]).reshape(want.shape) - want).max() < 1e-6 * max(1.0, want.max())
+
+
+def test_building_blocks_leave_the_stored_run():
+    """Force, VJP and density between pm_forward and pm_adjoint change nothing in the adjoint,
+    and a second call gives the same bits as the first."""
+    pm = context(16, 32, 40.0, 3)
+    noise, g = dev(normal((16, 16, 16), 5)), dev(normal((32, 32, 32), 6))
+    pm.forward(noise)
+    want = pm.adjoint(g_dens=g)[0].clone()
+    d, v = dev(normal((16 ** 3, 3), 7)), dev(normal((16 ** 3, 3), 8))
+    first = [t.clone() for t in (pm.force(d, 0.5), pm.force_vjp(d, 0.5, v), pm.density(d))]
+    pm.forward(noise)
+    again = [pm.force(d, 0.5), pm.force_vjp(d, 0.5, v), pm.density(d)]
+    assert all(torch.equal(a, b) for a, b in zip(first, again))
+    assert torch.equal(pm.adjoint(g_dens=g)[0], want)
