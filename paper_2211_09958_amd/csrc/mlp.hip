@@ -30,179 +30,230 @@ __device__ __forceinline__ float feature0(long n2, int n) {
     return 2.f * sqrtf((float)n2) / (float)n;
 }
 
-// One lane per |n|^2 entry.  The hidden layers are streamed: each first-layer
-// unit is computed once and immediately added into the 64 second-layer sums
-// (W2 kept transposed in LDS so that the 64 weights of one input are
-// contiguous), so only the 64 sums stay in registers.  Every sum still runs
-// over its inputs in index order.
+// A work-group of four waves per 64 |n|^2 entries, one lane per entry in each:
+// wave w computes first-layer units 16w .. 16w+15 (passed to the others through
+// LDS) and then second-layer units 16w .. 16w+15; wave 0 adds the output layer.
+// The weights are the same for all lanes and come through scalar loads, so the
+// inner product is one vector instruction per weight with nothing read from LDS.
+// Bound by the vector ALUs (4160 FMAs and 128 SiLUs per entry; an FMA costs a
+// SiLU's thirtieth).  One lane per entry with the weights read from LDS took
+// 47 us for the 12289 entries of a 128^3 mesh (192 waves on 1024 SIMDs) and
+// 100 us for the 196609 of 512^3 (LDS reads); this takes 16.5 and 54 us.  Every
+// sum runs over its inputs in index order.
 __global__ void __launch_bounds__(256)
 k_mlp_table(const float* __restrict__ theta, int n, float a, float fscale, long ntab,
             float* __restrict__ radial, float* __restrict__ table) {
-    __shared__ float w2t[HID * HID];                 // w2t[i][o] = W2[o][i]
-    __shared__ float th[OW2];                        // W1 | b1
-    __shared__ float tail[NPAR - OB2];               // b2 | W3 | b3
-    for (int k = threadIdx.x; k < HID * HID; k += 256)
-        w2t[(k % HID) * HID + k / HID] = theta[OW2 + k];
-    for (int k = threadIdx.x; k < OW2; k += 256) th[k] = theta[k];
-    for (int k = threadIdx.x; k < NPAR - OB2; k += 256) tail[k] = theta[OB2 + k];
-    __syncthreads();
-    const float* b2 = tail;
-    const float* w3 = tail + (OW3 - OB2);
-    const float b3 = tail[OB3 - OB2];
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < ntab; e += (long)gridDim.x * 256) {
-        const float x0 = feature0(e, n), x1 = a;
-        float z[HID];
+    __shared__ float hs[HID][64];   // first-layer units, then second-layer terms, by entry
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (long e0 = (long)blockIdx.x * 64; e0 < ntab; e0 += (long)gridDim.x * 64) {
+        const long e = e0 + lane;
+        const float x0 = feature0(e < ntab ? e : 0, n), x1 = a;
 #pragma unroll
-        for (int o = 0; o < HID; ++o) z[o] = b2[o];
-#pragma unroll 1
-        for (int i = 0; i < HID; ++i) {
-            const float z1 = th[OW1 + 2 * i] * x0 + th[OW1 + 2 * i + 1] * x1 + th[OB1 + i];
-            const float h1 = z1 * sigmoid(z1);
-            const float* wr = w2t + i * HID;
-#pragma unroll
-            for (int o = 0; o < HID; ++o) z[o] += wr[o] * h1;
+        for (int k = 0; k < 16; ++k) {
+            const int i = 16 * w + k;
+            const float z1 = theta[OW1 + 2 * i] * x0 + theta[OW1 + 2 * i + 1] * x1 + theta[OB1 + i];
+            hs[i][lane] = z1 * sigmoid(z1);
         }
-        float g = b3;
+        __syncthreads();
+        float h1[HID];
 #pragma unroll
-        for (int o = 0; o < HID; ++o) g += w3[o] * (z[o] * sigmoid(z[o]));
-        const float f = 1.f + g;
-        if (table) table[e] = f;
-        if (radial) radial[e] = e == 0 ? 0.f : f * fscale / (float)e;
+        for (int i = 0; i < HID; ++i) h1[i] = hs[i][lane];
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+            const int o = 16 * w + k;
+            const float* wr = theta + OW2 + o * HID;
+            float z = theta[OB2 + o];
+#pragma unroll
+            for (int i = 0; i < HID; ++i) z += wr[i] * h1[i];
+            hs[o][lane] = z * sigmoid(z);
+        }
+        __syncthreads();
+        if (w == 0) {
+            float g = theta[OB3];
+#pragma unroll
+            for (int o = 0; o < HID; ++o) g += theta[OW3 + o] * hs[o][lane];
+            const float f = 1.f + g;
+            if (e < ntab) {
+                if (table) table[e] = f;
+                if (radial) radial[e] = e == 0 ? 0.f : f * fscale / (float)e;
+            }
+        }
+        __syncthreads();   // hs is rewritten by the next entries
     }
 }
 
 constexpr int kChunk = 64;   // table entries per tile
 constexpr int kBwdBlocks = 256;
 
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// D += A B on the FP32 matrix cores, A 32 x 64, B 64 x 32, D 32 x 32, with
+// a(k) and b(k) this lane's A[lane % 32][k] and B[k][lane % 32] for k = 2 step +
+// lane / 32.  Element r of D sits in row mfma_row(r, lane), column lane % 32.
+template <class FA, class FB>
+__device__ __forceinline__ v16f mfma64(v16f d, FA a, FB b) {
+#pragma unroll
+    for (int s = 0; s < 32; ++s) d = __builtin_amdgcn_mfma_f32_32x32x2f32(a(s), b(s), d, 0, 0, 0);
+    return d;
+}
+__device__ __forceinline__ int mfma_row(int r, int lane) {
+    return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+}
+
 // Block-partial dL/dtheta for dL/df = fbar over the table; partials to scratch.
-// Sums that many lanes add to one parameter are reduced across the wave (output
-// layer) or kept in per-thread registers over the chunks (first layer) and
-// combined once at the end, instead of contended LDS float atomics.
+// Per chunk of 64 entries the second layer is three 64 x 64 x 64 products, on
+// the FP32 matrix cores, each of the four waves taking a 32 x 32 quadrant:
+//   Z2 = W2 H1,   dW2 += dZ2 H1^T,   dH1 = W2^T dZ2
+// (H1, dZ2 and dH1 are [unit][entry], in LDS rows of 65 so that rows and columns
+// are both free of bank conflicts; W2 stays in registers in both layouts).  The
+// first layer is one lane per entry, wave w holding units 16w .. 16w+15.  On the
+// vector units the products read up to two LDS words per FMA: 352 us for the
+// 196609 entries of a 512^3 mesh and 36 us for the 12289 of 128^3; now 110 and
+// 21 us.  Sums over entries stay in registers until the last chunk, in a fixed
+// order.
 __global__ void __launch_bounds__(256)
 k_mlp_bwd(const float* __restrict__ theta, int n, float a, long ntab,
           const float* __restrict__ fbar, float* __restrict__ scratch) {
-    __shared__ float th[NPAR];
-    __shared__ float h1s[kChunk][HID + 1];
-    __shared__ float dz2s[kChunk][HID + 1];
-    __shared__ float g1[192];        // dW1 (128) | db1 (64)
-    __shared__ float g3[HID + 1];    // dW3 (64) | db3
-    const int tid = threadIdx.x;
-    for (int i = tid; i < NPAR; i += 256) th[i] = theta[i];
-    for (int i = tid; i < 192; i += 256) g1[i] = 0.f;
-    for (int i = tid; i < HID + 1; i += 256) g3[i] = 0.f;
-    // per-thread accumulators: dW2[o][ib*16 .. +16) with o = tid/4, ib = tid%4,
-    // and the first-layer terms of hidden units ib .. ib+15 over this thread's entries
-    const int o2 = tid >> 2, ib = (tid & 3) * 16;
-    float acc2[16], acc1[16][3];
+    constexpr int PL = kChunk + 1;
+    static_assert(kChunk == 64 && HID == 64, "one entry per lane, four 32 x 32 quadrants");
+    __shared__ float h1s[HID * PL];    // H1, then dH1
+    __shared__ float dz2s[HID * PL];
+    __shared__ float red[2][2][HID];   // db2 and dW3 by column half
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mh = 32 * (w >> 1), nh = 32 * (w & 1);   // the wave's quadrant
+    const int c = lane & 31, kh = lane >> 5;
+    float w2[32], w2t[32];   // W2[mh + c][.] and W2[.][mh + c] at k = 2 s + kh
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        acc2[k] = 0.f;
-        acc1[k][0] = acc1[k][1] = acc1[k][2] = 0.f;
+    for (int s = 0; s < 32; ++s) {
+        w2[s] = theta[OW2 + (mh + c) * HID + 2 * s + kh];
+        w2t[s] = theta[OW2 + (2 * s + kh) * HID + mh + c];
     }
-    float accb2 = 0.f;
-    __syncthreads();
+    v16f dw2 = {0.f};
+    float db2[16], dw3[16], dw1[16][3], db3 = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) db2[k] = dw3[k] = dw1[k][0] = dw1[k][1] = dw1[k][2] = 0.f;
     for (long c0 = (long)blockIdx.x * kChunk; c0 < ntab; c0 += (long)gridDim.x * kChunk) {
-        // phase A: one lane per entry (every wave holds the same 64 entries),
-        // forward + output-layer backward; wave w takes second-layer units
-        // 16w .. 16w+15, so the four waves split the 64 x 64 second layer
-        {
-            const int lane = tid & 63, w = tid >> 6;
-            const long e = c0 + lane;
-            const bool valid = e < ntab;
-            const float x0 = feature0(valid ? e : 0, n), x1 = a;
-            const float dg = valid ? fbar[e] : 0.f;
-            float h1[HID];
-#pragma unroll
-            for (int i = 0; i < HID; ++i) {
-                const float z = th[OW1 + 2 * i] * x0 + th[OW1 + 2 * i + 1] * x1 + th[OB1 + i];
-                h1[i] = z * sigmoid(z);
-            }
-            if (w == 0) {
-#pragma unroll
-                for (int i = 0; i < HID; ++i) h1s[lane][i] = h1[i];
-            }
-            for (int o = 16 * w; o < 16 * w + 16; ++o) {
-                float z = th[OB2 + o];
-#pragma unroll
-                for (int i = 0; i < HID; ++i) z += th[OW2 + o * HID + i] * h1[i];
-                const float sg = sigmoid(z);
-                const float h2 = z * sg;
-                const float s3 = wave_sum(dg * h2);
-                if (lane == 0) g3[o] += s3;
-                dz2s[lane][o] = dg * th[OW3 + o] * (sg * (1.f + z * (1.f - sg)));
-            }
-            if (w == 0) {
-                const float sb3 = wave_sum(dg);
-                if (lane == 0) g3[HID] += sb3;
-            }
-        }
-        __syncthreads();
-        // phase B: dW2 += dz2^T h1, db2 += sum dz2
-#pragma unroll 4
-        for (int e = 0; e < kChunk; ++e) {
-            const float d = dz2s[e][o2];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) acc2[k] += d * h1s[e][ib + k];
-            if ((tid & 3) == 0) accb2 += d;
-        }
-        // phase C: dh1 = dz2 W2 -> dz1 -> dW1, db1 (entry e = tid/4, 16 hidden units)
-        {
-            const int e = tid >> 2;
-            const long ge = c0 + e;
-            const float x0 = feature0(ge < ntab ? ge : 0, n), x1 = a;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int i = ib + k;
-                float dh = 0.f;
-                for (int o = 0; o < HID; ++o) dh += dz2s[e][o] * th[OW2 + o * HID + i];
-                const float z = th[OW1 + 2 * i] * x0 + th[OW1 + 2 * i + 1] * x1 + th[OB1 + i];
-                const float sg = sigmoid(z);
-                const float dz = dh * (sg * (1.f + z * (1.f - sg)));
-                acc1[k][0] += dz * x0;
-                acc1[k][1] += dz * x1;
-                acc1[k][2] += dz;
-            }
-        }
-        __syncthreads();
-    }
-    // first layer: sum over the 16 lanes of each wave that share ib (lane bits
-    // 2..5), then one LDS add per (wave, ib) group
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            float v = acc1[k][q];
-#pragma unroll
-            for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
-            acc1[k][q] = v;
-        }
-    if ((tid & 63) < 4) {
+        // first layer at entry c0 + lane
+        const long e = c0 + lane;
+        const float x0 = feature0(e < ntab ? e : 0, n), x1 = a;
+        float ds1[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const int i = ib + k;
-            atomicAdd(&g1[2 * i], acc1[k][0]);
-            atomicAdd(&g1[2 * i + 1], acc1[k][1]);
-            atomicAdd(&g1[128 + i], acc1[k][2]);
+            const int i = 16 * w + k;
+            const float z = theta[OW1 + 2 * i] * x0 + theta[OW1 + 2 * i + 1] * x1 + theta[OB1 + i];
+            const float sg = sigmoid(z);
+            h1s[i * PL + lane] = z * sg;
+            ds1[k] = sg * (1.f + z * (1.f - sg));
+        }
+        // dL/df at this lane's column of the second layer's quadrant
+        const long ec = c0 + nh + c;
+        const float dg = ec < ntab ? fbar[ec] : 0.f;
+        if (mh == 0 && kh == 0) db3 += dg;
+        __syncthreads();
+        v16f z2 = {0.f};
+        z2 = mfma64(z2, [&](int s) { return w2[s]; },
+                    [&](int s) { return h1s[(2 * s + kh) * PL + nh + c]; });
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int o = mh + mfma_row(r, lane);
+            const float z = z2[r] + theta[OB2 + o];
+            const float sg = sigmoid(z);
+            const float dz = dg * theta[OW3 + o] * (sg * (1.f + z * (1.f - sg)));
+            dw3[r] += dg * (z * sg);
+            db2[r] += dz;
+            dz2s[o * PL + nh + c] = dz;
+        }
+        __syncthreads();
+        dw2 = mfma64(dw2, [&](int s) { return dz2s[(mh + c) * PL + 2 * s + kh]; },
+                     [&](int s) { return h1s[(nh + c) * PL + 2 * s + kh]; });
+        v16f dh = {0.f};
+        dh = mfma64(dh, [&](int s) { return w2t[s]; },
+                    [&](int s) { return dz2s[(2 * s + kh) * PL + nh + c]; });
+        __syncthreads();   // H1 has been read
+#pragma unroll
+        for (int r = 0; r < 16; ++r) h1s[(mh + mfma_row(r, lane)) * PL + nh + c] = dh[r];
+        __syncthreads();
+        // a thread's own slots: the next chunk's first layer may overwrite them
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float dz = h1s[(16 * w + k) * PL + lane] * ds1[k];
+            dw1[k][0] += dz * x0;
+            dw1[k][1] += dz * x1;
+            dw1[k][2] += dz;
         }
     }
-    __syncthreads();
     float* out = scratch + (long)blockIdx.x * NPAR;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) out[OW2 + o2 * HID + ib + k] = acc2[k];
-    if ((tid & 3) == 0) out[OB2 + o2] = accb2;
-    for (int i = tid; i < 128; i += 256) out[OW1 + i] = g1[i];
-    for (int i = tid; i < 64; i += 256) out[OB1 + i] = g1[128 + i];
-    for (int i = tid; i < HID; i += 256) out[OW3 + i] = g3[i];
-    if (tid == 0) out[OB3] = g3[HID];
+    for (int r = 0; r < 16; ++r)
+        out[OW2 + (mh + mfma_row(r, lane)) * HID + nh + c] = dw2[r];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int i = 16 * w + k;
+        const float s0 = wave_sum(dw1[k][0]), s1 = wave_sum(dw1[k][1]), s2 = wave_sum(dw1[k][2]);
+        if (lane == 0) {
+            out[OW1 + 2 * i] = s0;
+            out[OW1 + 2 * i + 1] = s1;
+            out[OB1 + i] = s2;
+        }
+    }
+    // second-layer biases and output weights: over the 32 columns, then the halves
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float sb = db2[r], sw = dw3[r];
+#pragma unroll
+        for (int o = 1; o < 32; o <<= 1) {
+            sb += __shfl_xor(sb, o);
+            sw += __shfl_xor(sw, o);
+        }
+        if (c == 0) {
+            red[w & 1][0][mh + mfma_row(r, lane)] = sb;
+            red[w & 1][1][mh + mfma_row(r, lane)] = sw;
+        }
+    }
+    db3 = wave_sum(db3);
+    __syncthreads();
+    if (threadIdx.x < HID) {
+        out[OB2 + threadIdx.x] = red[0][0][threadIdx.x] + red[1][0][threadIdx.x];
+        out[OW3 + threadIdx.x] = red[0][1][threadIdx.x] + red[1][1][threadIdx.x];
+    }
+    __syncthreads();
+    if (w < 2 && lane == 0) red[w][0][0] = db3;   // waves 0 and 1 hold the two halves
+    __syncthreads();
+    if (threadIdx.x == 0) out[OB3] = red[0][0][0] + red[1][0][0];
 }
 
-__global__ void __launch_bounds__(256)
+// gtheta += the block partials, 64 parameters per work-group: each of the 16
+// waves adds every 16th block's partials (eight loads in flight), then the
+// waves' sums are added in order.  (One thread per parameter added all the
+// blocks one load after the other: 47 us for 193 blocks, 62 us for 256; now
+// under 5 us.)
+__global__ void __launch_bounds__(1024)
 k_mlp_reduce(const float* __restrict__ scratch, int nblocks, float* __restrict__ gtheta) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= NPAR) return;
+    __shared__ float part[16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane;
+    const int pc = p < NPAR ? p : NPAR - 1;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += scratch[(long)b * NPAR + p];
-    gtheta[p] += s;
+    int b = w;
+    for (; b + 7 * 16 < nblocks; b += 8 * 16) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = scratch[(long)(b + 16 * u) * NPAR + pc];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; b < nblocks; b += 16) s += scratch[(long)b * NPAR + pc];
+    part[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && p < NPAR) {
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += part[k][lane];
+        gtheta[p] += t;
+    }
 }
 
 __global__ void __launch_bounds__(256)
@@ -228,8 +279,8 @@ long mlp_backward_scratch(int) { return (long)kBwdBlocks * NPAR; }
 void launch_mlp_table(const float* theta, int n, float, float a, float fscale, float* radial,
                       float* table, hipStream_t s) {
     const long ntab = 3L * (n / 2) * (n / 2) + 1;
-    long nb = (ntab + 255) / 256;
-    if (nb > 2048) nb = 2048;
+    long nb = (ntab + 63) / 64;
+    if (nb > 4096) nb = 4096;
     hipLaunchKernelGGL(k_mlp_table, dim3((unsigned)nb), dim3(256), 0, s, theta, n, a, fscale, ntab,
                        radial, table);
 }
@@ -241,7 +292,7 @@ void launch_mlp_backward(const float* theta, int n, float, float a, const float*
     if (nb > kBwdBlocks) nb = kBwdBlocks;
     hipLaunchKernelGGL(k_mlp_bwd, dim3((unsigned)nb), dim3(256), 0, s, theta, n, a, ntab, fbar,
                        scratch);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + 255) / 256), dim3(256), 0, s, scratch, (int)nb,
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + 63) / 64), dim3(1024), 0, s, scratch, (int)nb,
                        gtheta);
 }
 
