@@ -729,6 +729,180 @@ k_grad_adj_z_pipe(const float2* __restrict__ src, long srcStride, float2* dst, i
     }
 }
 
+// Shell b = round(|n|) of integer |n|^2 = q: sqrt(q) + 1/2 >= b exactly when
+// q >= b^2 - b + 1, so the single-precision guess is put right in integers.
+__device__ __forceinline__ int shell_of(int q) {
+    int b = (int)(sqrtf((float)q) + 0.5f);
+    if (q < b * b - b + 1) --b;
+    else if (q >= b * b + b + 1) ++b;
+    return b;
+}
+
+// Slot of value i of work-group b's partial sums: the memory of the tile it
+// starts with, in a buffer of the spectrum's layout (3 nbins <= 3 H values in
+// a tile of H W >= 8 H slots of 8 bytes).
+template <int H>
+__device__ __forceinline__ long shell_slot(int b, int i, int cs, int ncb) {
+    constexpr int W = Cfg<H>::W;
+    return mesh_row(i / W, b / ncb, H) * cs + (b % ncb) * W + i % W;
+}
+
+// Last (axis-0) pass of a forward transform that only feeds shell sums: per
+// shell b = 1..nbins {Sum w |d_k|^2, Sum w |n|, Sum w} in FP64, w the multiplicity
+// of a half-spectrum mode.  The spectrum is neither written nor read back (a
+// transform pass that stores it and a binning pass that reads it moved 3c more
+// bytes than this one's c).
+//
+// FP64 LDS atomics run at about one lane per cycle and were what bounded the
+// binning, so a lane first adds what shares a shell: modes n0 and -n0, and then a
+// run of E/2 consecutive |n0|, along which the shell number never falls, in
+// registers; one atomic per sum and shell change.  Work-groups take several
+// tiles (two work-groups per CU) and leave their sums to k_shell_reduce, in the
+// slots of their first tile (in `part`, which may be the buffer itself: nobody
+// else reads that tile): FP64 atomics on one HBM word take turns of some 50 ns.
+// 256^3: 56 us for the binning pass, after 34 us for the transform pass; now
+// 47 us for both with the reduction (51 us with atomics on the totals).
+template <int H>
+__global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
+k_fft_shells(const float2* buf, float2* part, int cs, int ncb, int ntiles, int nbins,
+             const float2* __restrict__ st) {
+    constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, L = (H / 2) / T;
+    static_assert(L * T == H / 2 && L >= 1, "each lane bins a run of L values of |n0|");
+    __shared__ float2 lds[lds_slots(H) * W + H];
+    extern __shared__ double sums[];   // [2 nbins] power and |n|, then [nbins] counts
+    uint32_t* count = reinterpret_cast<uint32_t*>(sums + 2 * nbins);
+    float2* tab = lds + lds_slots(H) * W;
+    for (int i = threadIdx.x; i < H - 1; i += T * W) tab[i] = st[H + i];
+    for (int i = threadIdx.x; i < nbins; i += T * W) {
+        sums[2 * i] = sums[2 * i + 1] = 0.0;
+        count[i] = 0u;
+    }
+    __syncthreads();
+    const int c = threadIdx.x % W, j = threadIdx.x / W;
+    for (int tile = (int)xcd_block(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
+        const int i1 = tile / ncb, k2 = (tile % ncb) * W + c;
+        const int n1 = signed_freq(i1, H);
+        float2 v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = buf[mesh_row(j + e * T, i1, H) * cs + k2];
+        fft_lds_tab<H, E, -1>(v, lds, W, c, j, tab);
+        __syncthreads();
+        if (k2 <= H / 2) {
+            const uint32_t w = (k2 == 0 || k2 == H / 2) ? 1u : 2u;
+            const int r2 = n1 * n1 + k2 * k2;
+            int shell = 0;
+            uint32_t n = 0;
+            double power = 0.0, radius = 0.0;
+            auto flush = [&]() {
+                if (n == 0 || shell < 1 || shell > nbins) return;
+                atomicAdd(&sums[2 * (shell - 1)], power);
+                atomicAdd(&sums[2 * (shell - 1) + 1], radius);
+                atomicAdd(&count[shell - 1], n);
+            };
+            const int last = j == T - 1 ? H / 2 : j * L + L - 1;   // n0 = H/2 has no lane of its own
+            for (int p = j * L; p <= last; ++p) {
+                const int q = p * p + r2, b = shell_of(q);
+                if (b != shell) {
+                    flush();
+                    shell = b;
+                    n = 0;
+                    power = radius = 0.0;
+                }
+                const float2 d = lds[lpad(p) * W + c];
+                double s = (double)d.x * d.x + (double)d.y * d.y;
+                uint32_t m = w;
+                if (p != 0 && p != H / 2) {
+                    const float2 g = lds[lpad(H - p) * W + c];
+                    s += (double)g.x * g.x + (double)g.y * g.y;
+                    m += w;
+                }
+                power += w * s;
+                radius += m * sqrt((double)q);
+                n += m;
+            }
+            flush();
+        }
+        __syncthreads();   // the next tile's transform reuses lds
+    }
+    const int b = (int)xcd_block(blockIdx.x, gridDim.x);
+    for (int i = threadIdx.x; i < 3 * nbins; i += T * W) {
+        const int k = i / 3, q = i - 3 * k;
+        const double x = q == 2 ? (double)count[k] : sums[2 * k + q];
+        *reinterpret_cast<double*>(part + shell_slot<H>(b, i, cs, ncb)) = x;
+    }
+}
+
+// bins[i] = the sum of the nparts work-groups' values i, 64 values per
+// work-group: each of its 16 waves adds every 16th part, then wave 0 adds the
+// waves' sums (a fixed order: the sums repeat bit for bit).
+template <int H>
+__global__ void __launch_bounds__(1024)
+k_shell_reduce(const float2* __restrict__ part, int cs, int ncb, int nparts, int nvals,
+               double* __restrict__ bins) {
+    __shared__ double red[16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane, ic = i < nvals ? i : nvals - 1;
+    auto at = [&](int b) {
+        return *reinterpret_cast<const double*>(part + shell_slot<H>(b, ic, cs, ncb));
+    };
+    double s = 0.0;
+    int b = w;
+    for (; b + 7 * 16 < nparts; b += 8 * 16) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = at(b + 16 * u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; b < nparts; b += 16) s += at(b);
+    red[w][lane] = s;
+    __syncthreads();
+    if (w == 0 && i < nvals) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += red[k][lane];
+        bins[i] = t;
+    }
+}
+
+// Axis-0 pass of a radial cotangent, in place: forward transform of a spectrum
+// already transformed along axes 2 and 1, times table[b - 1] for the modes of
+// shell b = 1..nbins (0 elsewhere), inverse transform.
+template <int H>
+__global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W, Cfg<H>::MINW)
+k_fft_shell_scale(float2* __restrict__ buf, int cs, int ncb, int nbins,
+                  const float* __restrict__ table, const float2* __restrict__ st) {
+    constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W;
+    __shared__ float2 lds[lds_slots(H) * W + H];
+    float2* tab = lds + lds_slots(H) * W;
+    // read first in the second stage, after the first stage's barrier
+    for (int i = threadIdx.x; i < H - 1; i += T * W) tab[i] = st[H + i];
+    const int c = threadIdx.x % W, j = threadIdx.x / W;
+    const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
+    const int i1 = tile / ncb, k2 = (tile % ncb) * W + c;
+    const int n1 = signed_freq(i1, H), r2 = n1 * n1 + k2 * k2;
+    auto off = [&](int p) -> long { return mesh_row(p, i1, H) * cs + k2; };
+    float2 v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = buf[off(j + e * T)];
+    fft_lds_tab<H, E, -1>(v, lds, W, c, j, tab);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int p = j + e * T, n0 = signed_freq(p, H);
+        const int b = shell_of(n0 * n0 + r2);
+        const bool in = b >= 1 && b <= nbins && k2 <= H / 2;
+        const float t = in ? table[in ? b - 1 : 0] : 0.f;
+        const float2 d = lds[lpad(p) * W + c];
+        v[e] = make_float2(t * d.x, t * d.y);
+    }
+    __syncthreads();
+    fft_lds_tab<H, E, 1>(v, lds, W, c, j, tab);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) buf[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
+}
+
 // Calls f(std::integral_constant<int, n>) for the supported power-of-two sizes.
 template <class F>
 void size_switch(int n, F&& f) {
@@ -929,6 +1103,37 @@ void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const
     launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
 }
 
+void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int cs, int nbins,
+                       double* bins, const Twiddles& tw, hipStream_t s) {
+    launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
+    launch_fft_axis(buf, n, cs, 1, -1, 1, 0, tw, s);
+    size_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
+        const int ncb = (N / 2 + W) / W;   // column blocks that hold stored modes
+        const int ntiles = N * ncb;
+        const int nwg = std::min(ntiles, 2 * device_cus());
+        hipLaunchKernelGGL(k_fft_shells<N>, dim3(nwg), dim3(T * W),
+                           (2 * sizeof(double) + sizeof(uint32_t)) * nbins, s, buf, part, cs, ncb,
+                           ntiles, nbins, tw.stages);
+        hipLaunchKernelGGL(k_shell_reduce<N>, dim3((3 * nbins + 63) / 64), dim3(1024), 0, s, part,
+                           cs, ncb, nwg, 3 * nbins, bins);
+    });
+}
+
+void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, const float* table,
+                            const Twiddles& tw, hipStream_t s) {
+    size_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
+        const int ncb = cs / W;
+        hipLaunchKernelGGL(k_fft_shell_scale<N>, dim3(N * ncb), dim3(T * W), 0, s, buf, cs, ncb,
+                           nbins, table, tw.stages);
+    });
+    launch_fft_axis(buf, n, cs, 1, 1, 1, 0, tw, s);
+    launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
+}
+
 void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
                            const Twiddles& tw, hipStream_t s) {
     launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
@@ -944,8 +1149,7 @@ void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, 
                            const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
-        if (spec) strided<N, 1, 0, true>(buf, spec, cs, 1, 0, tw, s);
-        else strided<N, 1, 0, false>(buf, nullptr, cs, 1, 0, tw, s);
+        strided<N, 1, 0, true>(buf, spec, cs, 1, 0, tw, s);
     });
     launch_fft_axis(buf, n, cs, 1, 1, 1, 0, tw, s);
     launch_fft_x_c2r_to(buf, real, n, cs, tw, s);

@@ -74,12 +74,23 @@ void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const flo
 void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
 void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
 // The same between a dense real mesh [n]^3 and a dense half spectrum
-// [n][n][n/2+1] (nullptr: the spectrum stays in, or comes from, `buf`), through
-// `buf`; the first and last pass read and write the caller's layout.
+// [n][n][n/2+1], through `buf`; the first and last pass read and write the
+// caller's layout.  R2C with spec == nullptr leaves the spectrum in `buf`.
 void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
                            const Twiddles& tw, hipStream_t s);
 void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, int cs,
                            const Twiddles& tw, hipStream_t s);
+
+// Shell sums of the transform of a dense real mesh: bins[3(b-1) + {0,1,2}] =
+// {Sum w |d_k|^2, Sum w |n|, Sum w} for b = round(|n|) in [1, nbins], nbins <= n.
+// `part`, of the buffer's size, holds partial sums: a buffer of its own leaves
+// the spectrum transformed along axes 2 and 1 in `buf`; it may be `buf` itself.
+void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int cs, int nbins,
+                       double* bins, const Twiddles& tw, hipStream_t s);
+// real = unnormalised inverse DFT of table[b - 1] d_k (0 off the shells) for the
+// spectrum that launch_fft_shells left in `buf`; table has nbins values.
+void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, const float* table,
+                            const Twiddles& tw, hipStream_t s);
 
 // ---------------------------------------------------------------- particles
 // Particle state is fixed point so that kick and drift are exactly invertible:
@@ -269,11 +280,12 @@ void launch_axpby_scatter(float* out, const float* x, float a, const float* y, f
 // Loss L = n^-3 Sum (d - t)^2 partials, g = 2 (d - t) / n^3 (nullable).
 void launch_mse(const float* d, const float* t, float* g, long n3, double* partials,
                 int nblocks, hipStream_t s);
-// P(k) shells from a full half spectrum [n][n][cs]: bins[3*b + {0,1,2}] +=
-// {w |d_k|^2, w |n|, w} for b = round(|n|) in [1, nbins].
-void launch_pk_bin(const float2* spec, int n, int cs, int nbins, double* bins, hipStream_t s);
-// spec[k] *= table[|n|^2] over the half spectrum
-void launch_radial_scale(float2* spec, int n, int cs, const float* table, hipStream_t s);
+// P(k) loss from launch_fft_shells' bins: with P_b = norm bins[3b]/bins[3b+2] and
+// the shells that hold modes and a nonzero finite target,
+// out[0] = weight mean_b (P_b / target_b - 1)^2, and table[b] = 2 norm /
+// bins[3b+2] dL/dP_b (0 on the other shells).
+void launch_pk_loss(const double* bins, const double* target, int nbins, double norm, double weight,
+                    double* out, float* table, hipStream_t s);
 // block partials of Sum (minimum-image a - b)^2; g = gscale * (a - b) wrapped (nullable)
 void launch_mse_periodic(const float* a, const float* b, float* g, long n, float box, float gscale,
                          double* partials, int nblocks, hipStream_t s);

@@ -110,9 +110,7 @@ extern "C" int pm_power_spectrum_noalloc(const float* dens, int32_t mesh, double
     const Twiddles twd{reinterpret_cast<const float2*>(base + kTwOff), kMaxMesh,
                        reinterpret_cast<const float2*>(base + kStageOff)};
     const int cs = complex_row_stride(mesh);
-    launch_fft3_r2c_dense(dens, spec, nullptr, mesh, cs, twd, s);
-    launch_zero(bins, 3 * (size_t)n_bins * sizeof(double), s);
-    launch_pk_bin(spec, mesh, cs, n_bins, bins, s);
+    launch_fft_shells(dens, spec, spec, mesh, cs, n_bins, bins, twd, s);
     if (hipGetLastError() != hipSuccess) {
         set_context_free_error("pm_power_spectrum_noalloc: kernel launch failed");
         return PM_EHIP;

@@ -1309,49 +1309,36 @@ k_mse(const float* __restrict__ d, const float* __restrict__ t, float* __restric
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
+// One work-group (see launch_pk_loss).
 __global__ void __launch_bounds__(kBlock)
-k_pk_bin(const float2* __restrict__ spec, int n, int cs, int nbins, double* __restrict__ bins) {
-    extern __shared__ double sb[];
-    for (int i = threadIdx.x; i < 3 * nbins; i += kBlock) sb[i] = 0.0;
-    __syncthreads();
-    const int h = n / 2 + 1;
-    const long N = (long)n * n * h;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const int k2 = (int)(i % h);
-        const long row = i / h;
-        const int i1 = (int)(row % n), i0 = (int)(row / n);
-        const int n0 = i0 < n / 2 ? i0 : i0 - n, n1 = i1 < n / 2 ? i1 : i1 - n;
-        const long nsq = (long)n0 * n0 + (long)n1 * n1 + (long)k2 * k2;
-        const double kn = sqrt((double)nsq);
-        const int b = (int)floor(kn + 0.5);
-        if (b < 1 || b > nbins) continue;
-        const float2 d = spec[mesh_row(i0, i1, n) * cs + k2];
-        const double w = (k2 == 0 || k2 == n / 2) ? 1.0 : 2.0;
-        atomicAdd(&sb[3 * (b - 1)], w * ((double)d.x * d.x + (double)d.y * d.y));
-        atomicAdd(&sb[3 * (b - 1) + 1], w * kn);
-        atomicAdd(&sb[3 * (b - 1) + 2], w);
+k_pk_loss(const double* __restrict__ bins, const double* __restrict__ target, int nbins,
+          double norm, double weight, double* __restrict__ out, float* __restrict__ table) {
+    __shared__ double tot[2];
+    double acc = 0.0, used = 0.0;
+    auto usable = [&](int b) {
+        return bins[3 * b + 2] > 0.0 && target[b] != 0.0 && isfinite(target[b]);
+    };
+    for (int b = threadIdx.x; b < nbins; b += kBlock)
+        if (usable(b)) {
+            const double r = bins[3 * b] / bins[3 * b + 2] * norm / target[b] - 1.0;
+            acc += r * r;
+            used += 1.0;
+        }
+    acc = block_sum(acc);
+    used = block_sum(used);
+    if (threadIdx.x == 0) {
+        tot[0] = acc;
+        tot[1] = used;
+        out[0] = weight * acc / used;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < 3 * nbins; i += kBlock)
-        if (sb[i] != 0.0) atomicAdd(&bins[i], sb[i]);
-}
-
-// Multiplies every half-spectrum mode by table[|n|^2] (a radial cotangent).
-__global__ void __launch_bounds__(kBlock)
-k_radial_scale(float2* __restrict__ spec, int n, int cs, const float* __restrict__ table) {
-    const int h = n / 2 + 1;
-    const long N = (long)n * n * h;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const int k2 = (int)(i % h);
-        const long row = i / h;
-        const int i1 = (int)(row % n), i0 = (int)(row / n);
-        const int n0 = i0 < n / 2 ? i0 : i0 - n, n1 = i1 < n / 2 ? i1 : i1 - n;
-        const float t = table[n0 * n0 + n1 * n1 + k2 * k2];
-        const long o = mesh_row(i0, i1, n) * cs + k2;
-        float2 d = spec[o];
-        d.x *= t;
-        d.y *= t;
-        spec[o] = d;
+    for (int b = threadIdx.x; b < nbins; b += kBlock) {
+        double t = 0.0;
+        if (usable(b)) {
+            const double r = bins[3 * b] / bins[3 * b + 2] * norm / target[b] - 1.0;
+            t = 2.0 * (weight * 2.0 * r / (target[b] * tot[1])) * norm / bins[3 * b + 2];
+        }
+        table[b] = (float)t;
     }
 }
 
@@ -1685,21 +1672,16 @@ void launch_mse(const float* d, const float* t, float* g, long n3, double* parti
                        partials);
 }
 
-void launch_radial_scale(float2* spec, int n, int cs, const float* table, hipStream_t s) {
-    const long N = (long)n * n * (n / 2 + 1);
-    hipLaunchKernelGGL(k_radial_scale, dim3(grid_for(N)), dim3(kBlock), 0, s, spec, n, cs, table);
+void launch_pk_loss(const double* bins, const double* target, int nbins, double norm, double weight,
+                    double* out, float* table, hipStream_t s) {
+    hipLaunchKernelGGL(k_pk_loss, dim3(1), dim3(kBlock), 0, s, bins, target, nbins, norm, weight,
+                       out, table);
 }
 
 void launch_mse_periodic(const float* a, const float* b, float* g, long n, float box, float gscale,
                          double* partials, int nblocks, hipStream_t s) {
     hipLaunchKernelGGL(k_mse_periodic, dim3(nblocks), dim3(kBlock), 0, s, a, b, g, n, box,
                        1.f / box, gscale, partials);
-}
-
-void launch_pk_bin(const float2* spec, int n, int cs, int nbins, double* bins, hipStream_t s) {
-    const long N = (long)n * n * (n / 2 + 1);
-    hipLaunchKernelGGL(k_pk_bin, dim3(grid_for(N) < 2048 ? grid_for(N) : 2048), dim3(kBlock),
-                       3 * nbins * sizeof(double), s, spec, n, cs, nbins, bins);
 }
 
 }  // namespace pmx

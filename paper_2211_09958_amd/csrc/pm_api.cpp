@@ -204,8 +204,8 @@ struct pm_ctx {
     int32_t* fin_p;
     float *s_ic, *tmpv, *noise;
     float *radial_f, *radial_ic, *radial_ic_dom, *radial_lpt, *theta, *gtheta, *fbar, *mlp_scratch;
-    float* losstab;                    // radial cotangent table of pm_loss_pk
-    std::vector<float> losstab_host;   // its host copy (kept alive across the async upload)
+    float* losstab;                    // targets, loss and shell factors of pm_loss_pk
+    std::vector<double> loss_target;   // the targets, kept alive across their async upload
     float2* tw;
     float2* tw_stages;
     Twiddles twd;
@@ -1225,50 +1225,37 @@ int pm_loss_pk(pm_ctx* ctx, const float* dens, int32_t n_bins, const double* pk_
     if (!dens || !pk_target) return ctx->fail(PM_EINVAL, "dens and pk_target are required");
     if (n_bins < 1 || n_bins > ctx->ng) return ctx->fail(PM_EINVAL, "n_bins must be in [1, mesh]");
     if (!std::isfinite(weight)) return ctx->fail(PM_EINVAL, "weight must be finite");
+    // shells b <= round(sqrt(3) ng / 2) hold modes; further ones are empty
+    const int b_max = (int)std::floor(std::sqrt(0.75) * ctx->ng + 0.5);
+    bool usable = false;
+    for (int b = 1; b <= n_bins && b <= b_max; ++b)
+        usable = usable || (pk_target[b - 1] != 0.0 && std::isfinite(pk_target[b - 1]));
+    if (!usable) return ctx->fail(PM_EINVAL, "no shell has both modes and a nonzero target");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_fft3_r2c_dense(dens, ctx->C[0], nullptr, ng, ctx->cs, ctx->twd, s);
-    launch_zero(ctx->pkbins, 3 * (size_t)n_bins * sizeof(double), s);
-    launch_pk_bin(ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, s);
-    PM_TRY(ctx->hip_check("pm_loss_pk"));
-    std::vector<double> h(3 * (size_t)n_bins);
-    if (hipMemcpyAsync(h.data(), ctx->pkbins, h.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return ctx->fail(PM_EHIP, "reading P(k) failed");
-    // P_b = L^3 / Ng^6 * <|delta_k|^2>_b; L = w * mean_b (P_b / T_b - 1)^2 over the
-    // shells holding modes and a nonzero target
-    const double L = ctx->cfg.box, n6 = std::pow((double)ng, 6.0), L3 = L * L * L;
-    std::vector<double> gP(n_bins, 0.0);
-    int used = 0;
-    for (int b = 0; b < n_bins; ++b)
-        if (h[3 * b + 2] > 0 && pk_target[b] != 0.0 && std::isfinite(pk_target[b])) ++used;
-    if (used == 0) return ctx->fail(PM_EINVAL, "no shell has both modes and a nonzero target");
-    double acc = 0.0;
-    for (int b = 0; b < n_bins; ++b) {
-        const double cnt = h[3 * b + 2];
-        if (!(cnt > 0 && pk_target[b] != 0.0 && std::isfinite(pk_target[b]))) continue;
-        const double r = h[3 * b] / cnt * L3 / n6 / pk_target[b] - 1.0;
-        acc += r * r;
-        gP[b] = weight * 2.0 * r / (pk_target[b] * used);
-    }
-    if (loss) *loss = weight * acc / used;
-    if (!std::isfinite(acc)) return ctx->fail(PM_ENUMERIC, "non-finite P(k) loss");
-    if (!g_dens) return PM_OK;
-    // d L / d delta(x) = 2 Sum_k t_k delta_k e^{ik.x} (unnormalised inverse DFT of the
-    // half spectrum) with t_k = dL/dP_b L^3 / (Ng^6 N_b): a radial table in |n|^2
-    const long ntab = ctx->plan.ntab_f;
-    ctx->losstab_host.assign(ntab, 0.f);
-    for (long q = 1; q < ntab; ++q) {
-        const int b = (int)std::floor(std::sqrt((double)q) + 0.5);
-        if (b < 1 || b > n_bins || gP[b - 1] == 0.0) continue;
-        ctx->losstab_host[q] = (float)(2.0 * gP[b - 1] * L3 / (n6 * h[3 * (b - 1) + 2]));
-    }
-    if (hipMemcpyAsync(ctx->losstab, ctx->losstab_host.data(), ntab * sizeof(float),
+    // P_b = L^3 / Ng^6 <|delta_k|^2>_b; dL/d delta(x) = 2 Sum_k t_k delta_k e^{ik.x}
+    // (unnormalised inverse DFT) with t_k = dL/dP_b L^3 / (Ng^6 N_b), one value per
+    // shell.  Targets, loss and shell factors live in losstab: [n_bins] | [2] | [n_bins]
+    const double L = ctx->cfg.box, norm = L * L * L / std::pow((double)ng, 6.0);
+    double* target_dev = reinterpret_cast<double*>(ctx->losstab);
+    double* loss_dev = target_dev + n_bins;
+    float* table_dev = reinterpret_cast<float*>(loss_dev + 2);
+    ctx->loss_target.assign(pk_target, pk_target + n_bins);
+    if (hipMemcpyAsync(target_dev, ctx->loss_target.data(), n_bins * sizeof(double),
                        hipMemcpyHostToDevice, s) != hipSuccess)
-        return ctx->fail(PM_EHIP, "upload of the loss table failed");
-    launch_radial_scale(ctx->C[0], ng, ctx->cs, ctx->losstab, s);
-    launch_fft3_c2r_dense(nullptr, ctx->C[0], g_dens, ng, ctx->cs, ctx->twd, s);
-    return ctx->hip_check("pm_loss_pk");
+        return ctx->fail(PM_EHIP, "upload of the loss targets failed");
+    launch_fft_shells(dens, ctx->C[0], ctx->C[1], ng, ctx->cs, n_bins, ctx->pkbins, ctx->twd, s);
+    launch_pk_loss(ctx->pkbins, target_dev, n_bins, norm, weight, loss_dev, table_dev, s);
+    if (g_dens)
+        launch_fft_shell_scale(ctx->C[0], g_dens, ng, ctx->cs, n_bins, table_dev, ctx->twd, s);
+    PM_TRY(ctx->hip_check("pm_loss_pk"));
+    double v = 0.0;
+    if (hipMemcpyAsync(&v, loss_dev, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return ctx->fail(PM_EHIP, "reading the P(k) loss failed");
+    if (loss) *loss = v;
+    if (!std::isfinite(v)) return ctx->fail(PM_ENUMERIC, "non-finite P(k) loss");
+    return PM_OK;
 }
 
 int pm_loss_disp(pm_ctx* ctx, const float* disp, const float* disp_target, double weight,
@@ -1301,9 +1288,7 @@ int pm_power_spectrum(pm_ctx* ctx, const float* dens, int32_t n_bins, double* k_
     if (n_bins < 1 || n_bins > ctx->ng) return ctx->fail(PM_EINVAL, "n_bins must be in [1, mesh]");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_fft3_r2c_dense(dens, ctx->C[0], nullptr, ng, ctx->cs, ctx->twd, s);
-    launch_zero(ctx->pkbins, 3 * (size_t)n_bins * sizeof(double), s);
-    launch_pk_bin(ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, s);
+    launch_fft_shells(dens, ctx->C[0], ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, ctx->twd, s);
     PM_TRY(ctx->hip_check("pm_power_spectrum"));
     std::vector<double> h(3 * (size_t)n_bins);
     if (hipMemcpyAsync(h.data(), ctx->pkbins, h.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
