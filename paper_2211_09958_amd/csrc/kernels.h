@@ -123,6 +123,7 @@ struct Bins {
     uint32_t* ranks;    // [P]
     uint32_t* ord;      // [P] storage slot of the k-th particle in bin order
     uint32_t* scan_tmp; // scan block sums
+    bool zeroed = false; // the counts are zero once the stream's work is done
     long nkeys() const { return (long)nt * nt * nt * 8; }
 };
 
@@ -151,7 +152,8 @@ struct Records {
 // gather that moved the particles (see count_bins below) and only the scan and
 // the order remain.
 void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, bool counted, hipStream_t s);
-// Zeroes the bin counts ahead of a gather that counts the particles it moves.
+// Zeroes the bin counts (unless the last sort left them so) ahead of a kernel that
+// counts particles.
 void launch_bin_zero(Bins& b, hipStream_t s);
 // Moves every record array from src to dst in the order b.ord and resets b.ord
 // to the identity (each bin then a contiguous range of the records).  The

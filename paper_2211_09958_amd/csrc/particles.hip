@@ -243,6 +243,24 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
     return r;
 }
 
+// Sum over the work-group, valid in every thread.
+__device__ __forceinline__ uint32_t block_total(uint32_t v) {
+    __shared__ uint32_t wsum[kScanThreads / 64];
+    for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    uint32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) t += wsum[w];
+    __syncthreads();
+    return t;
+}
+
+// Exclusive scan of one chunk of kScanChunk values per work-group.  ONE: the
+// whole scan in this launch, each work-group first adding up all the chunks
+// before its own (for few chunks that costs less than two more launches);
+// otherwise the chunk's total goes to bsum and k_scan_add finishes.
+template <bool ONE>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_local(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, long n,
              uint32_t* __restrict__ bsum) {
@@ -254,44 +272,45 @@ k_scan_local(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, long n
         v[k] = base + k < n ? in[base + k] : 0u;
         s += v[k];
     }
-    uint32_t ex = block_exclusive_scan(s, &tot);
+    uint32_t before = 0;
+    if constexpr (ONE) {
+        const uint4* q = reinterpret_cast<const uint4*>(in);
+        for (long i = threadIdx.x; i < (long)blockIdx.x * (kScanChunk / 4); i += kScanThreads) {
+            const uint4 x = q[i];
+            before += x.x + x.y + x.z + x.w;
+        }
+        before = block_total(before);
+    }
+    uint32_t ex = before + block_exclusive_scan(s, &tot);
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
         if (base + k < n) out[base + k] = ex;
         ex += v[k];
     }
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    if (!ONE && threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(kScanThreads)
-k_scan_bsum(uint32_t* __restrict__ bsum, long nb) {
-    __shared__ uint32_t tot;
-    uint32_t carry = 0;
-    for (long c = 0; c < nb; c += kScanThreads) {
-        const long i = c + threadIdx.x;
-        uint32_t v = i < nb ? bsum[i] : 0u;
-        uint32_t ex = block_exclusive_scan(v, &tot);
-        if (i < nb) bsum[i] = carry + ex;
-        carry += tot;
-        __syncthreads();
-    }
-}
-
+// Adds the totals of the chunks before its own to every value of a chunk.
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_add(uint32_t* __restrict__ out, long n, const uint32_t* __restrict__ bsum) {
+    uint32_t add = 0;
+    for (unsigned i = threadIdx.x; i < blockIdx.x; i += kScanThreads) add += bsum[i];
+    add = block_total(add);
     const long base = (long)blockIdx.x * kScanChunk;
-    const uint32_t add = bsum[blockIdx.x];
     for (int k = threadIdx.x; k < kScanChunk; k += kScanThreads)
         if (base + k < n) out[base + k] += add;
 }
 
 // Sorted order: the particle in storage slot i goes to bin position
-// offsets[key] + rank.
+// offsets[key] + rank.  The bins' nk counts, read by the scan, are cleared for
+// the next count.
 __global__ void __launch_bounds__(kBlock)
 k_index(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ ranks,
-        const uint32_t* __restrict__ offsets, long P, uint32_t* __restrict__ ord) {
+        const uint32_t* __restrict__ offsets, long P, uint32_t* __restrict__ ord,
+        uint32_t* __restrict__ counts, long nk) {
     const long i = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (i < P) ord[offsets[keys[i]] + ranks[i]] = (uint32_t)i;
+    if (i < nk) counts[i] = 0u;
 }
 
 // Words per particle of the record sets the sorts move: positions, momenta,
@@ -328,6 +347,22 @@ k_compact_sorted(uint32_t* __restrict__ ord, long P, Records rec) {
 
 // ------------------------------------------------------------- scatter
 
+struct RangePairs {
+    unsigned long long S = 0, cls = 0;
+};
+constexpr RangePairs range_pairs() {
+    RangePairs p;
+    int r = 0;
+    for (unsigned long long S = 1; S < 8; ++S)
+        for (unsigned long long cls = 0; cls < 8; ++cls)
+            if ((cls & S) == S) {
+                p.S |= S << (3 * r);
+                p.cls |= cls << (3 * r);
+                ++r;
+            }
+    return p;
+}
+
 // The 20 particle ranges a tile work-group visits: its own 8 classes, then for
 // every non-empty axis subset S the classes of neighbour (tile - S) whose spill
 // bits contain S.
@@ -340,21 +375,15 @@ __device__ __forceinline__ void tile_range(int r, int tx, int ty, int tz, int nt
         *re = offsets[k0 + 8];
         return;
     }
-    int idx = r - 1;
-    for (int S = 1; S < 8; ++S)
-        for (int cls = 0; cls < 8; ++cls)
-            if ((cls & S) == S) {
-                if (idx == 0) {
-                    const int nx = (tx - ((S >> 2) & 1) + nt) % nt;
-                    const int ny = (ty - ((S >> 1) & 1) + nt) % nt;
-                    const int nz = (tz - (S & 1) + nt) % nt;
-                    const uint32_t k = morton3(nx, ny, nz) * 8 + cls;
-                    *rs = offsets[k];
-                    *re = offsets[k + 1];
-                    return;
-                }
-                --idx;
-            }
+    // the (S, class) pairs with class containing S, three bits each
+    constexpr RangePairs pairs = range_pairs();
+    const int sh = 3 * (r - 1);
+    const int S = (int)(pairs.S >> sh) & 7, cls = (int)(pairs.cls >> sh) & 7;
+    const int m = nt - 1;   // nt is a power of two
+    const uint32_t k = morton3((tx - ((S >> 2) & 1)) & m, (ty - ((S >> 1) & 1)) & m,
+                               (tz - (S & 1)) & m) * 8 + cls;
+    *rs = offsets[k];
+    *re = offsets[k + 1];
 }
 
 constexpr int kRanges = 20;
@@ -491,19 +520,22 @@ __device__ __forceinline__ void deposit_kept(unsigned long long* acc, const floa
 // conversion, and the write-out handles four cells per thread.  The density can
 // also go to a caller's plain [ng]^3 array (dense), in the same write-out or
 // instead of the workspace mesh (out null).
-// Threads per scatter work-group; the 32 KB accumulator tile leaves room for
-// four work-groups per CU, so larger ones keep more waves in flight.
-constexpr int scatter_threads() { return 2 * kBlock; }
+// Threads per scatter work-group; the 32 KB accumulator tile of T = 16 leaves
+// room for four work-groups per CU, so larger ones keep more waves in flight.
+// Smaller tiles hold an eighth of the particles, and the vector scatter
+// accumulates its three components side by side instead of in three passes.
+constexpr int scatter_threads(int T) { return T < 16 ? kBlock : 2 * kBlock; }
 
 template <int T, bool VEC>
-__global__ void __launch_bounds__(scatter_threads())
+__global__ void __launch_bounds__(scatter_threads(T))
 k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, float coeff,
                const unsigned* __restrict__ vmax_bits, Lattice L, int nt,
                const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ord,
                float* __restrict__ out, long outStride, float* __restrict__ dense) {
-    constexpr int T3 = T * T * T, NTH = scatter_threads();
+    constexpr int T3 = T * T * T, NTH = scatter_threads(T);
+    constexpr bool SIDE = VEC && T < 16;   // three accumulator tiles, one pass
     static_assert(T % 4 == 0, "the write-out handles four cells of a row at a time");
-    __shared__ __align__(16) unsigned long long acc[T3];
+    __shared__ __align__(16) unsigned long long acc[SIDE ? 3 * T3 : T3];
     __shared__ uint32_t rs[kRanges], pre[kRanges + 1];
     const uint32_t tile = xcd_block(blockIdx.x, gridDim.x);
     const int tx = compact3(tile >> 2), ty = compact3(tile >> 1), tz = compact3(tile);
@@ -546,7 +578,8 @@ k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, 
     uint32_t kcell[4];
     // the accumulator starts at zero; each component's write-out clears the
     // slots it reads for the next one
-    for (int c = threadIdx.x; c < T3 / 2; c += NTH) acc2[c] = make_ulonglong2(0ull, 0ull);
+    for (int c = threadIdx.x; c < (SIDE ? 3 : 1) * T3 / 2; c += NTH)
+        acc2[c] = make_ulonglong2(0ull, 0ull);
     __syncthreads();
     // cell value v * 2^-e (minus the mean density 1 for the density), formed
     // from v's 32-bit halves with one rounding: hi 2^(32-e) + lo 2^-e exactly,
@@ -575,7 +608,23 @@ k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, 
         };
         uint32_t ns = 0;   // slot of the particle after the next
         uint32_t k = threadIdx.x;
-        if constexpr (VEC) {
+        if constexpr (SIDE) {
+            if (comp == 0) {
+                uint32_t p = k < total ? slot(k) : 0u;
+                for (; k < total; k += NTH) {
+                    uint32_t x[3];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) x[a] = xq[3 * (long)p + a];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) kv[a] = vals[3 * (long)p + a];
+                    if (k + NTH < total) p = slot(k + NTH);
+                    corners<T>(x, L, lo, kw, kcell);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) deposit_kept(acc + a * T3, kw, kcell, amp * kv[a], e);
+                }
+            }
+            k = total;   // nothing left for the passes below
+        } else if constexpr (VEC) {
             // the thread's first particle: corners and values computed in the
             // first component's pass and kept for the other two
             if (comp == 0) {
@@ -607,9 +656,9 @@ k_scatter_tile(const uint32_t* __restrict__ xq, const float* __restrict__ vals, 
             const int c = 4 * q;
             const int l2 = c % T, l1 = (c / T) % T, l0 = c / (T * T);
             const long g = mesh_row(lo[0] + l0, lo[1] + l1, L.ng) * L.rp + lo[2] + l2;
-            const int sl = tile_slot<T>(l0, l1, l2);   // four consecutive slots
+            const int sl = tile_slot<T>(l0, l1, l2) + (SIDE ? comp * T3 : 0);   // four in a row
             const ulonglong2 a = acc2[sl / 2], b = acc2[sl / 2 + 1];
-            if (comp + 1 < NC) {
+            if (!SIDE && comp + 1 < NC) {
                 acc2[sl / 2] = make_ulonglong2(0ull, 0ull);
                 acc2[sl / 2 + 1] = make_ulonglong2(0ull, 0ull);
             }
@@ -709,7 +758,9 @@ struct GatherArgs {
 // Threads per gather work-group: the three-mesh tile takes 59 KB of LDS (two
 // work-groups per CU), so those modes use larger work-groups to keep more waves
 // in flight.
-constexpr int gather_threads(int mode) { return mode == kWgrad ? kBlock : 4 * kBlock; }
+constexpr int gather_threads(int mode, int T) {
+    return mode == kWgrad || T < 16 ? kBlock : 4 * kBlock;
+}
 
 // A particle's inputs, loaded before any of its outputs is stored (a load after
 // a store to an array that may alias it would wait a full memory round trip).
@@ -877,9 +928,9 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
 }
 
 template <int T, int MODE>
-__global__ void __launch_bounds__(gather_threads(MODE), MODE == kWgrad ? 1 : 8)
+__global__ void __launch_bounds__(gather_threads(MODE, T), MODE == kWgrad ? 1 : (T < 16 ? 4 : 8))
 k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offsets) {
-    constexpr int NTH = gather_threads(MODE);
+    constexpr int NTH = gather_threads(MODE, T);
     constexpr int NM = MODE == kWgrad ? 1 : 3;
     constexpr int TH = T + 1, TH3 = TH * TH * TH;
     __shared__ float mf[NM * TH3];
@@ -1371,7 +1422,15 @@ int grid_for(long n) {
 
 }  // namespace
 
-int choose_tile(int ng) { return ng >= 32 ? 16 : ng / 2; }
+// Tile side in cells.  Meshes up to 128^3 have at most 512 tiles of 16^3, too few
+// for 256 CUs.  With 8^3 tiles the density scatter, the vector scatter and the
+// kick, un-kick and mesh-gradient gathers of 32^3 particles on 64^3 take 5.7,
+// 8.2, 6.0, 5.8 and 5.4 us instead of 6.8, 14.7, 8.7, 8.3 and 8.0; of 128^3
+// particles on 128^3 19.4, 36, 34, 37 and 31 us instead of 19.4, 52, 28, 32 and
+// 36 (the three-mesh gathers pay for the larger share of halo cells, about
+// half of what the other two gain).  From 256^3 on, 16^3 tiles fill the chip, and
+// their halos and key count are smaller.
+int choose_tile(int ng) { return ng >= 256 ? 16 : (ng >= 16 ? 8 : 4); }
 
 long scan_tmp_elems(long nkeys) { return (nkeys + 1 + kScanChunk - 1) / kScanChunk + 1; }
 
@@ -1386,26 +1445,33 @@ void launch_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 void launch_bin_zero(Bins& b, hipStream_t s) {
-    launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
+    if (!b.zeroed) launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
+    b.zeroed = false;
 }
 
 void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, bool counted, hipStream_t s) {
     const long P = (long)L.np * L.np * L.np;
-    const long nk = b.nkeys();
     if (!counted) {
         launch_bin_zero(b, s);
         hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((P + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, xq, L, b.tile, P, b.counts, b.keys, b.ranks);
     }
-    const long n = nk + 1;
+    const long n = b.nkeys() + 1;
     const long nb = (n + kScanChunk - 1) / kScanChunk;
-    hipLaunchKernelGGL(k_scan_local, dim3((unsigned)nb), dim3(kScanThreads), 0, s, b.counts,
-                       b.offsets, n, b.scan_tmp);
-    hipLaunchKernelGGL(k_scan_bsum, dim3(1), dim3(kScanThreads), 0, s, b.scan_tmp, nb);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, s, b.offsets, n,
-                       b.scan_tmp);
-    hipLaunchKernelGGL(k_index, dim3((unsigned)((P + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       b.keys, b.ranks, b.offsets, P, b.ord);
+    // up to 16 chunks (meshes to 256^3) in one launch, about 3 us; the last of 16
+    // work-groups then reads 240 KB more than its own chunk
+    if (nb <= 16) {
+        hipLaunchKernelGGL(k_scan_local<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s,
+                           b.counts, b.offsets, n, b.scan_tmp);
+    } else {
+        hipLaunchKernelGGL(k_scan_local<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s,
+                           b.counts, b.offsets, n, b.scan_tmp);
+        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, s, b.offsets, n,
+                           b.scan_tmp);
+    }
+    hipLaunchKernelGGL(k_index, dim3(grid_for(std::max(P, n))), dim3(kBlock), 0, s, b.keys, b.ranks,
+                       b.offsets, P, b.ord, b.counts, n);
+    b.zeroed = true;
 }
 
 bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
@@ -1427,15 +1493,15 @@ static void scatter_dispatch(const uint32_t* xq, const float* v, float coeff, co
     const unsigned ntiles = (unsigned)b.nt * b.nt * b.nt;
     switch (b.tile) {
         case 4:
-            hipLaunchKernelGGL((k_scatter_tile<4, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
+            hipLaunchKernelGGL((k_scatter_tile<4, VEC>), dim3(ntiles), dim3(scatter_threads(4)), 0, s, xq, v,
                                coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
         case 8:
-            hipLaunchKernelGGL((k_scatter_tile<8, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
+            hipLaunchKernelGGL((k_scatter_tile<8, VEC>), dim3(ntiles), dim3(scatter_threads(8)), 0, s, xq, v,
                                coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
         default:
-            hipLaunchKernelGGL((k_scatter_tile<16, VEC>), dim3(ntiles), dim3(scatter_threads()), 0, s, xq, v,
+            hipLaunchKernelGGL((k_scatter_tile<16, VEC>), dim3(ntiles), dim3(scatter_threads(16)), 0, s, xq, v,
                                coeff, vmax, L, b.nt, b.offsets, b.ord, out, outStride, dense);
             break;
     }
@@ -1468,15 +1534,15 @@ static void gather_dispatch(GatherArgs A, const Lattice& L, const Bins& b, hipSt
     }
     switch (b.tile) {
         case 4:
-            hipLaunchKernelGGL((k_gather_tile<4, MODE>), dim3(ntiles), dim3(gather_threads(MODE)), 0, s, A, L, b.nt,
+            hipLaunchKernelGGL((k_gather_tile<4, MODE>), dim3(ntiles), dim3(gather_threads(MODE, 4)), 0, s, A, L, b.nt,
                                b.offsets);
             break;
         case 8:
-            hipLaunchKernelGGL((k_gather_tile<8, MODE>), dim3(ntiles), dim3(gather_threads(MODE)), 0, s, A, L, b.nt,
+            hipLaunchKernelGGL((k_gather_tile<8, MODE>), dim3(ntiles), dim3(gather_threads(MODE, 8)), 0, s, A, L, b.nt,
                                b.offsets);
             break;
         default:
-            hipLaunchKernelGGL((k_gather_tile<16, MODE>), dim3(ntiles), dim3(gather_threads(MODE)), 0, s, A, L,
+            hipLaunchKernelGGL((k_gather_tile<16, MODE>), dim3(ntiles), dim3(gather_threads(MODE, 16)), 0, s, A, L,
                                b.nt, b.offsets);
             break;
     }

@@ -24,7 +24,8 @@ def disps(np_, box):
     return {"smooth": smooth, "spread": spread, "pile": pile}
 
 
-@pytest.mark.parametrize("np_,ng", [(8, 8), (8, 16), (16, 32), (16, 64), (32, 32)])
+@pytest.mark.parametrize("np_,ng", [(8, 8), (8, 16), (16, 32), (16, 64), (32, 32), (16, 128),
+                                    (32, 256)])
 @pytest.mark.parametrize("kind", ["smooth", "spread", "pile"])
 def test_density_into_any_alignment(np_, ng, kind):
     box = 50.0
