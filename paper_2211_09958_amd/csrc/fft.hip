@@ -331,6 +331,219 @@ k_fft_y_merge(float2* __restrict__ g1, const float2* __restrict__ g2, int cs, in
     }
 }
 
+// ---------------------------------------------------------- planes
+
+// Both transforms of a plane i0 = const (axes 2 and 1) by one work-group, the
+// plane's half spectrum staying in LDS between them, for meshes up to
+// kMaxPlane.  These are bound by launches and by the latency of each pass (a
+// launch costs the host 3-4 us; a pass over the 2 MB of a 64^3 mesh runs 3.5-5
+// us), so one launch in place of two or three is what counts: 7.2 us for the
+// force meshes' inverse of 64^3 instead of 3.4 + 4.6 + 5.2, 9.8 us for the
+// cotangents' merged forward instead of 4.6 + 3.6 + 4.5.  At 128^3 a plane takes
+// 72 KB of LDS, there are 128 of them for 256 CUs, and the fused forms take
+// 28-34 us where the separate passes take 26-27: no gain; at 256^3 a plane does
+// not fit in LDS.
+template <int N>
+struct Plane {
+    static constexpr int H = N / 2, PW = H + 1;          // complex row length, columns
+    static constexpr int EX = fft_values_per_lane(H), TX = H / EX;
+    static constexpr int EY = fft_values_per_lane(N), TY = N / EY;
+    // every row, and every column, has its lanes
+    static constexpr int NT = ((PW * TY > N * TX ? PW * TY : N * TX) + 63) / 64 * 64;
+    static constexpr int LS = lds_slots(H);
+    static constexpr int SLOTS = N * LS > lds_slots(N) * PW ? N * LS : lds_slots(N) * PW;
+    // M[lpad(i1) PW + k2]: the plane's half spectrum
+    static __device__ __forceinline__ int at(int i1, int k2) { return lpad(i1) * PW + k2; }
+};
+
+// Forward axis-2 transforms of the plane's rows, the row's pairs given in v and
+// the post-twiddles of the lane's outputs in w, to M.
+template <int N>
+__device__ __forceinline__ void plane_rows_r2c(float2 (&v)[Plane<N>::EX],
+                                               const float2 (&w)[Plane<N>::EX], float2* lds,
+                                               const float2* __restrict__ st) {
+    using P = Plane<N>;
+    constexpr int H = P::H;
+    const int r = threadIdx.x / P::TX, j = threadIdx.x % P::TX;
+    const bool act = r < N;
+    float2* L = lds + (act ? r : 0) * P::LS;
+    fft_lds<H, P::EX, -1>(v, L, 1, 0, j, st, act);
+    __syncthreads();
+    float2 nyq = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int e = 0; e < P::EX; ++e) {
+        const int k = j + e * P::TX;
+        const float2 zk = L[lpad(k)], zc = cconj(L[lpad((H - k) & (H - 1))]);
+        const float2 A = cadd(zk, zc), B = csub(zk, zc);
+        const float2 iwB = cmul_i<1>(cmul(w[e], B));
+        v[e] = make_float2(0.5f * (A.x - iwB.x), 0.5f * (A.y - iwB.y));
+        if (k == 0) {
+            v[e] = make_float2(zk.x + zk.y, 0.f);
+            nyq = make_float2(zk.x - zk.y, 0.f);
+        }
+    }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+        for (int e = 0; e < P::EX; ++e) lds[P::at(r, j + e * P::TX)] = v[e];
+        if (j == 0) lds[P::at(r, H)] = nyq;
+    }
+    __syncthreads();
+}
+
+// Axis-1 transforms of the plane's columns to M, in place for FROM_M, otherwise
+// of value(i1, k2), all of whose loads are issued before the first transform.
+template <int N, int DIR, bool FROM_M, class Value>
+__device__ __forceinline__ void plane_columns(float2* lds, const float2* __restrict__ st,
+                                              Value&& value) {
+    using P = Plane<N>;
+    const int j = threadIdx.x / P::PW, c = threadIdx.x % P::PW;
+    const bool act = j < P::TY;
+    float2 v[P::EY];
+#pragma unroll
+    for (int e = 0; e < P::EY; ++e) v[e] = value(act ? j + e * P::TY : 0, act ? c : 0);
+    if constexpr (FROM_M) __syncthreads();   // M's columns are in registers
+    fft_lds<N, P::EY, DIR>(v, lds, P::PW, c, act ? j : 0, st, act);
+    __syncthreads();
+}
+
+// The plane's values i = p PW + k2 of M, NT at a time: f(round, p, k2, M value).
+template <int N, class F>
+__device__ __forceinline__ void plane_each(const float2* lds, F&& f) {
+    using P = Plane<N>;
+    constexpr int ALL = N * P::PW;
+#pragma unroll
+    for (int u = 0; u < (ALL + P::NT - 1) / P::NT; ++u) {
+        const int i = u * P::NT + threadIdx.x;
+        const int p = i / P::PW, k2 = i - p * P::PW;
+        if (i < ALL) f(u, p, k2, lds[P::at(p, k2)]);
+    }
+}
+
+// Inverse axis-2 transforms of M's rows; the real rows' pairs end in lds, row r's
+// pair k at lds[r LS + lpad(k)].  KMUL: times i k2 first (zero on the Nyquist
+// column).
+template <int N>
+__device__ __forceinline__ void plane_rows_c2r(float2* lds, bool kmul,
+                                               const float2 (&w)[Plane<N>::EX],
+                                               const float2* __restrict__ st) {
+    using P = Plane<N>;
+    constexpr int H = P::H;
+    const int r = threadIdx.x / P::TX, j = threadIdx.x % P::TX;
+    const bool act = r < N;
+    auto value = [&](int k) {
+        const float2 y = lds[P::at(act ? r : 0, k)];
+        if (!kmul) return y;
+        if (k == H) return make_float2(0.f, 0.f);
+        return make_float2(-(float)k * y.y, (float)k * y.x);
+    };
+    float2 v[P::EX];
+#pragma unroll
+    for (int e = 0; e < P::EX; ++e) {
+        const int k = j + e * P::TX;
+        const float2 xk = value(k), xc = cconj(value(H - k));
+        v[e] = cadd(cadd(xk, xc), cmul_i<1>(cmulc(csub(xk, xc), w[e])));
+    }
+    __syncthreads();
+    fft_lds<H, P::EX, 1>(v, lds + (act ? r : 0) * P::LS, 1, 0, j, st, act);
+    __syncthreads();
+}
+
+// Forward: real rows of plane blockIdx.x (in buffer blockIdx.y, or in the dense
+// array `real` when given) -> half spectrum along axes 2 and 1 in the buffer.
+// MERGE: buffer 0 like that; grid row 1 takes buffers 1 and 2 together and leaves
+// n1 S_1 + k2 S_2 of their spectra in buffer 1 (as k_fft_y_merge).
+template <int N, bool MERGE>
+__global__ void __launch_bounds__(Plane<N>::NT)
+k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, long bufStride,
+            const float2* __restrict__ tw, int ntw, const float2* __restrict__ st) {
+    using P = Plane<N>;
+    __shared__ float2 lds[P::SLOTS];
+    const int i0 = (int)xcd_block(blockIdx.x, N), twN = ntw / N;
+    const int r = threadIdx.x / P::TX, j = threadIdx.x % P::TX;
+    const bool two = MERGE && blockIdx.y == 1;
+    float2* b = buf + blockIdx.y * bufStride;
+    auto load = [&](const float2* from, float2 (&v)[P::EX]) {
+        const int i1 = r < N ? r : 0;
+        const float* row = real ? real + ((long)i0 * N + i1) * N
+                                : reinterpret_cast<const float*>(from + mesh_row(i0, i1, N) * cs);
+#pragma unroll
+        for (int e = 0; e < P::EX; ++e) {
+            const int k = 2 * (j + e * P::TX);
+            v[e] = make_float2(row[k], row[k + 1]);
+        }
+    };
+    float2 v[P::EX], v2[P::EX], w[P::EX];
+    load(b, v);
+    if (two) load(b + bufStride, v2);
+#pragma unroll
+    for (int e = 0; e < P::EX; ++e) w[e] = tw[(j + e * P::TX) * twN];
+    auto column = [&](int i1, int k2) { return lds[P::at(i1, k2)]; };
+    plane_rows_r2c<N>(v, w, lds, st);
+    plane_columns<N, -1, true>(lds, st, column);
+    if (!two) {
+        plane_each<N>(lds, [&](int, int p, int k2, float2 y) {
+            b[mesh_row(i0, p, N) * cs + k2] = y;
+        });
+        return;
+    }
+    if constexpr (MERGE) {
+        // n1 S_1, held by the thread that adds k2 S_2 to it
+        float2 h[(N * P::PW + P::NT - 1) / P::NT];
+        plane_each<N>(lds, [&](int u, int p, int, float2 y) {
+            const float f1 = p == N / 2 ? 0.f : (float)signed_freq(p, N);
+            h[u] = make_float2(f1 * y.x, f1 * y.y);
+        });
+        __syncthreads();   // the first spectrum has been read
+        plane_rows_r2c<N>(v2, w, lds, st);
+        plane_columns<N, -1, true>(lds, st, column);
+        plane_each<N>(lds, [&](int u, int p, int k2, float2 y) {
+            const float f2 = k2 == P::H ? 0.f : (float)k2;
+            b[mesh_row(i0, p, N) * cs + k2] = make_float2(h[u].x + f2 * y.x, h[u].y + f2 * y.y);
+        });
+    }
+}
+
+// Inverse: spectrum of plane blockIdx.x -> real rows, in place in buffer
+// blockIdx.y or to the dense array `real` when given.  FORCE: grid row 0 takes
+// buffer 0 in place; rows 1 and 2 both read `g` and leave the axis-1 derivative
+// (times i n1 before the axis-1 transform) in buffer 1 and the axis-2 derivative
+// (times i k2 before the axis-2 transform) in buffer 2.
+template <int N, bool FORCE>
+__global__ void __launch_bounds__(Plane<N>::NT)
+k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real, int cs,
+            long bufStride, const float2* __restrict__ tw, int ntw,
+            const float2* __restrict__ st) {
+    using P = Plane<N>;
+    __shared__ float2 lds[P::SLOTS];
+    const int i0 = (int)xcd_block(blockIdx.x, N), comp = blockIdx.y;
+    float2* b = buf + comp * bufStride;
+    const float2* src = FORCE && comp > 0 ? g : b;
+    const bool d1 = FORCE && comp == 1;
+    float2 w[P::EX];
+#pragma unroll
+    for (int e = 0; e < P::EX; ++e)
+        w[e] = tw[(threadIdx.x % P::TX + e * P::TX) * (ntw / N)];
+    plane_columns<N, 1, false>(lds, st, [&](int p, int k2) {
+        const float2 y = src[mesh_row(i0, p, N) * cs + k2];
+        if (!d1) return y;
+        const float f1 = p == N / 2 ? 0.f : (float)signed_freq(p, N);
+        return make_float2(-f1 * y.y, f1 * y.x);
+    });
+    plane_rows_c2r<N>(lds, FORCE && comp == 2, w, st);
+#pragma unroll
+    for (int u = 0; u < (N * P::H + P::NT - 1) / P::NT; ++u) {
+        const int i = u * P::NT + threadIdx.x;
+        if (i >= N * P::H) break;
+        const int p = i / P::H, k = i % P::H;
+        float* row = real ? real + ((long)i0 * N + p) * N
+                          : reinterpret_cast<float*>(b + mesh_row(i0, p, N) * cs);
+        const float2 y = lds[p * P::LS + lpad(k)];
+        row[2 * k] = y.x;
+        row[2 * k + 1] = y.y;
+    }
+}
+
 // Axis-0 pass with the fused gradient multiply (see launch_grad_z).  Writes
 // F~_0 = IFFT_0(i n0 radial delta) and G = IFFT_0(radial delta); F~_1 and F~_2
 // are i n1 G and i n2 G, and since n1 and n2 are constant along axis 0 those
@@ -339,8 +552,8 @@ k_fft_y_merge(float2* __restrict__ g1, const float2* __restrict__ g2, int cs, in
 // two spectra instead of three.
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
-k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, long dstStride, int cs,
-         int ncb, const float* __restrict__ radial, const float2* __restrict__ tw, int ntw,
+k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __restrict__ dst_g,
+         int cs, int ncb, const float* __restrict__ radial, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     // exchange buffer | the H-point part of the stage-twiddle table (read from
@@ -376,11 +589,8 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, long dstStrid
     __syncthreads();
     fft_lds_tab<H, E, 1>(v, lds, W, c, j, tab);
     __syncthreads();
-    {
-        float2* og = dst + dstStride;
 #pragma unroll
-        for (int e = 0; e < E; ++e) og[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
-    }
+    for (int e = 0; e < E; ++e) dst_g[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int n0 = signed_freq(j + e * T, n);
@@ -419,8 +629,8 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, long dstStrid
 // from evicting the table from L2.
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
-k_grad_z_pipe(const float2* __restrict__ src, float2* __restrict__ dst, long dstStride, int cs,
-              int ncb, int ntiles, const float* __restrict__ radial, const float2* __restrict__ tw,
+k_grad_z_pipe(const float2* __restrict__ src, float2* __restrict__ dst,
+              float2* __restrict__ dst_g, int cs, int ncb, int ntiles, const float* __restrict__ radial, const float2* __restrict__ tw,
               int ntw, const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     constexpr int LS = lds_slots(H) * W;
@@ -506,7 +716,7 @@ k_grad_z_pipe(const float2* __restrict__ src, float2* __restrict__ dst, long dst
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < E; ++e)
-            st_nt(const_cast<float2*>(at(dst + dstStride, e * estride, lo)), lds[lpad(j + e * T) * W + c]);
+            st_nt(const_cast<float2*>(at(dst_g, e * estride, lo)), lds[lpad(j + e * T) * W + c]);
         // F~_0 multiplier i n0 (zero on the Nyquist plane) on the kept column;
         // each lane reads back only the slots it wrote itself
 #pragma unroll
@@ -903,20 +1113,32 @@ k_fft_shell_scale(float2* __restrict__ buf, int cs, int ncb, int nbins,
     for (int e = 0; e < E; ++e) buf[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
 }
 
-// Calls f(std::integral_constant<int, n>) for the supported power-of-two sizes.
+// Calls f(std::integral_constant<int, n>) for the supported power-of-two sizes:
+// plane_switch up to kMaxPlane, pass_switch above, size_switch all.
 template <class F>
-void size_switch(int n, F&& f) {
+void plane_switch(int n, F&& f) {
     switch (n) {
         case 8: f(std::integral_constant<int, 8>{}); break;
         case 16: f(std::integral_constant<int, 16>{}); break;
         case 32: f(std::integral_constant<int, 32>{}); break;
         case 64: f(std::integral_constant<int, 64>{}); break;
+        default: break;
+    }
+}
+template <class F>
+void pass_switch(int n, F&& f) {
+    switch (n) {
         case 128: f(std::integral_constant<int, 128>{}); break;
         case 256: f(std::integral_constant<int, 256>{}); break;
         case 512: f(std::integral_constant<int, 512>{}); break;
         case 1024: f(std::integral_constant<int, 1024>{}); break;
         default: break;
     }
+}
+template <class F>
+void size_switch(int n, F&& f) {
+    if (n <= kMaxPlane) plane_switch(n, f);
+    else pass_switch(n, f);
 }
 
 // real == nullptr: in place
@@ -960,37 +1182,37 @@ void strided(float2* buf, Spec spec, int cs, int nbuf, long bufStride, const Twi
 }  // namespace
 
 void launch_fft_x_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) {
+    pass_switch(n, [&](auto nn) {
         x_r2c<decltype(nn)::value>(nullptr, buf, cs, nbuf, bufStride, tw, s);
     });
 }
 
 void launch_fft_x_r2c_from(const float* real, float2* buf, int n, int cs, const Twiddles& tw,
                            hipStream_t s) {
-    size_switch(n, [&](auto nn) { x_r2c<decltype(nn)::value>(real, buf, cs, 1, 0, tw, s); });
+    pass_switch(n, [&](auto nn) { x_r2c<decltype(nn)::value>(real, buf, cs, 1, 0, tw, s); });
 }
 
 void launch_fft_x_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) {
+    pass_switch(n, [&](auto nn) {
         x_c2r<decltype(nn)::value>(buf, nullptr, cs, nbuf, bufStride, -1, tw, s);
     });
 }
 
 void launch_fft_x_c2r_to(float2* buf, float* real, int n, int cs, const Twiddles& tw,
                          hipStream_t s) {
-    size_switch(n, [&](auto nn) { x_c2r<decltype(nn)::value>(buf, real, cs, 1, 0, -1, tw, s); });
+    pass_switch(n, [&](auto nn) { x_c2r<decltype(nn)::value>(buf, real, cs, 1, 0, -1, tw, s); });
 }
 
 void launch_fft_x_c2r_dk2(float2* buf, int n, int cs, int nbuf, long bufStride, int kmul_buf,
                           const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) {
+    pass_switch(n, [&](auto nn) {
         x_c2r<decltype(nn)::value>(buf, nullptr, cs, nbuf, bufStride, kmul_buf, tw, s);
     });
 }
 
 void launch_fft_y_split(float2* g, float2* out_g, int n, int cs, const Twiddles& tw,
                         hipStream_t s) {
-    size_switch(n, [&](auto nn) {
+    pass_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         constexpr int W = Cfg<N>::WY, T = Cfg<N>::T;
         const int ncb = cs / W;
@@ -1001,7 +1223,7 @@ void launch_fft_y_split(float2* g, float2* out_g, int n, int cs, const Twiddles&
 
 void launch_fft_y_merge(float2* g1, const float2* g2, int n, int cs, const Twiddles& tw,
                         hipStream_t s) {
-    size_switch(n, [&](auto nn) {
+    pass_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         constexpr int W = Cfg<N>::WY, T = Cfg<N>::T;
         const int ncb = cs / W;
@@ -1012,16 +1234,21 @@ void launch_fft_y_merge(float2* g1, const float2* g2, int n, int cs, const Twidd
 
 void launch_fft_axis(float2* buf, int n, int cs, int axis, int dir, int nbuf, long bufStride,
                      const Twiddles& tw, hipStream_t s) {
-    size_switch(n, [&](auto nn) {
-        constexpr int N = decltype(nn)::value;
-        if (axis == 1 && dir < 0) strided<N, -1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-        else if (axis == 1) strided<N, 1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-        else if (dir < 0) strided<N, -1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-        else strided<N, 1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-    });
+    if (axis == 1)
+        pass_switch(n, [&](auto nn) {
+            constexpr int N = decltype(nn)::value;
+            if (dir < 0) strided<N, -1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+            else strided<N, 1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        });
+    else
+        size_switch(n, [&](auto nn) {
+            constexpr int N = decltype(nn)::value;
+            if (dir < 0) strided<N, -1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+            else strided<N, 1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        });
 }
 
-void launch_grad_z(const float2* src, float2* dst, long dstStride, int n, int cs,
+void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
                    const float* radial, const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
         constexpr int NN = decltype(nn)::value;
@@ -1031,10 +1258,10 @@ void launch_grad_z(const float2* src, float2* dst, long dstStride, int n, int cs
             const int ntiles = NN * ncb;
             const int nwg = std::min(ntiles, device_cus());
             hipLaunchKernelGGL(k_grad_z_pipe<NN>, dim3(nwg), dim3(T * W), 0, s, src, dst,
-                               dstStride, cs, ncb, ntiles, radial, tw.w, tw.n, tw.stages);
+                               dst_g, cs, ncb, ntiles, radial, tw.w, tw.n, tw.stages);
         } else {
             hipLaunchKernelGGL(k_grad_z<NN>, dim3(NN * ncb), dim3(T * W), 0, s, src, dst,
-                               dstStride, cs, ncb, radial, tw.w, tw.n, tw.stages);
+                               dst_g, cs, ncb, radial, tw.w, tw.n, tw.stages);
         }
     });
 }
@@ -1091,22 +1318,67 @@ void fill_stage_twiddles(float2* table) {
     }
 }
 
-void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    launch_fft_x_r2c(buf, n, cs, nbuf, bufStride, tw, s);
+void launch_fft_xy_r2c(const float* real, float2* buf, int n, int cs, int nbuf, long bufStride,
+                       const Twiddles& tw, hipStream_t s) {
+    if (n <= kMaxPlane) {
+        plane_switch(n, [&](auto nn) {
+            constexpr int N = decltype(nn)::value;
+            hipLaunchKernelGGL((k_plane_r2c<N, false>), dim3(N, nbuf), dim3(Plane<N>::NT), 0, s,
+                               real, buf, cs, bufStride, tw.w, tw.n, tw.stages);
+        });
+        return;
+    }
+    if (real) launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
+    else launch_fft_x_r2c(buf, n, cs, nbuf, bufStride, tw, s);
     launch_fft_axis(buf, n, cs, 1, -1, nbuf, bufStride, tw, s);
+}
+
+void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long bufStride,
+                       const Twiddles& tw, hipStream_t s) {
+    if (n <= kMaxPlane) {
+        plane_switch(n, [&](auto nn) {
+            constexpr int N = decltype(nn)::value;
+            hipLaunchKernelGGL((k_plane_c2r<N, false>), dim3(N, nbuf), dim3(Plane<N>::NT), 0, s,
+                               buf, nullptr, real, cs, bufStride, tw.w, tw.n, tw.stages);
+        });
+        return;
+    }
+    launch_fft_axis(buf, n, cs, 1, 1, nbuf, bufStride, tw, s);
+    if (real) launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
+    else launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
+}
+
+void launch_plane_r2c_merge(float2* buf, int n, int cs, long bufStride, const Twiddles& tw,
+                            hipStream_t s) {
+    plane_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        hipLaunchKernelGGL((k_plane_r2c<N, true>), dim3(N, 2), dim3(Plane<N>::NT), 0, s, nullptr,
+                           buf, cs, bufStride, tw.w, tw.n, tw.stages);
+    });
+}
+
+void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bufStride,
+                            const Twiddles& tw, hipStream_t s) {
+    plane_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        hipLaunchKernelGGL((k_plane_c2r<N, true>), dim3(N, 3), dim3(Plane<N>::NT), 0, s, buf, g,
+                           nullptr, cs, bufStride, tw.w, tw.n, tw.stages);
+    });
+}
+
+void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
+    launch_fft_xy_r2c(nullptr, buf, n, cs, nbuf, bufStride, tw, s);
     launch_fft_axis(buf, n, cs, 0, -1, nbuf, bufStride, tw, s);
 }
 
 void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
     launch_fft_axis(buf, n, cs, 0, 1, nbuf, bufStride, tw, s);
-    launch_fft_axis(buf, n, cs, 1, 1, nbuf, bufStride, tw, s);
-    launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
+    launch_fft_yx_c2r(buf, nullptr, n, cs, nbuf, bufStride, tw, s);
 }
 
 void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int cs, int nbins,
                        double* bins, const Twiddles& tw, hipStream_t s) {
-    launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
-    launch_fft_axis(buf, n, cs, 1, -1, 1, 0, tw, s);
+    launch_fft_xy_r2c(real, buf, n, cs, 1, 0, tw, s);
     size_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
@@ -1130,14 +1402,12 @@ void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, 
         hipLaunchKernelGGL(k_fft_shell_scale<N>, dim3(N * ncb), dim3(T * W), 0, s, buf, cs, ncb,
                            nbins, table, tw.stages);
     });
-    launch_fft_axis(buf, n, cs, 1, 1, 1, 0, tw, s);
-    launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
+    launch_fft_yx_c2r(buf, real, n, cs, 1, 0, tw, s);
 }
 
 void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
                            const Twiddles& tw, hipStream_t s) {
-    launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
-    launch_fft_axis(buf, n, cs, 1, -1, 1, 0, tw, s);
+    launch_fft_xy_r2c(real, buf, n, cs, 1, 0, tw, s);
     size_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         if (spec) strided<N, -1, 0, true>(buf, spec, cs, 1, 0, tw, s);
@@ -1151,8 +1421,7 @@ void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, 
         constexpr int N = decltype(nn)::value;
         strided<N, 1, 0, true>(buf, spec, cs, 1, 0, tw, s);
     });
-    launch_fft_axis(buf, n, cs, 1, 1, 1, 0, tw, s);
-    launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
+    launch_fft_yx_c2r(buf, real, n, cs, 1, 0, tw, s);
 }
 
 }  // namespace pmx

@@ -27,6 +27,26 @@ void fill_stage_twiddles(float2* table);
 int device_cus();
 
 // ---------------------------------------------------------------- FFT
+// Meshes up to kMaxPlane per side take their axis-2 and axis-1 transforms in one
+// launch (a plane per work-group); larger ones in a pass per axis.
+constexpr int kMaxPlane = 64;
+// Axes 2 and 1 of `nbuf` buffers `bufStride` float2 apart, in place: real rows ->
+// half spectra transformed along both (r2c), and back (c2r).  With `real` (one
+// buffer) the real rows are read from, or written to, a dense [n]^3 array in
+// plain row order.
+void launch_fft_xy_r2c(const float* real, float2* buf, int n, int cs, int nbuf, long bufStride,
+                       const Twiddles& tw, hipStream_t s);
+void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long bufStride,
+                       const Twiddles& tw, hipStream_t s);
+// n <= kMaxPlane: three real buffers -> S_0 in the first and n1 S_1 + k2 S_2 in
+// the second (the inputs of launch_grad_adj_z)
+void launch_plane_r2c_merge(float2* buf, int n, int cs, long bufStride, const Twiddles& tw,
+                            hipStream_t s);
+// n <= kMaxPlane: the outputs of launch_grad_z, F~_0 in the first of three buffers
+// and G in `g` (a buffer of its own), -> the three real force meshes
+void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bufStride,
+                            const Twiddles& tw, hipStream_t s);
+// The passes of one axis below, but for axis 0, take n > kMaxPlane only.
 // Real rows -> half spectra along the last axis, in place, for `nbuf` buffers
 // `bufStride` float2 apart.  Unnormalised exp(-i k x).
 void launch_fft_x_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
@@ -55,10 +75,10 @@ void launch_fft_axis(float2* buf, int n, int cs, int axis, int dir, int nbuf, lo
                      const Twiddles& tw, hipStream_t s);
 // Fused axis-0 pass of the force: forward axis-0 FFT of src (already
 // transformed along axes 2 and 1), then dst = IFFT_0(i n0 radial delta) (zero
-// on the Nyquist plane of axis 0) and dst + dstStride = G = IFFT_0(radial
-// delta); launch_fft_y_split and launch_fft_x_c2r_dk2 turn G into the axis-1
-// and axis-2 components.
-void launch_grad_z(const float2* src, float2* dst, long dstStride, int n, int cs,
+// on the Nyquist plane of axis 0) and dst_g = G = IFFT_0(radial delta);
+// launch_fft_y_split and launch_fft_x_c2r_dk2, or launch_plane_c2r_force, turn G
+// into the axis-1 and axis-2 components.
+void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
                    const float* radial, const Twiddles& tw, hipStream_t s);
 // Fused axis-0 pass of the transpose: dst = inverse-axis-0 of
 // Sum_j conj(M_j) forward-axis-0(G_j), with M_j = i n_j radial, given G_0 at src

@@ -129,7 +129,9 @@ struct Plan {
         ntab_p = 3L * (np / 2) * (np / 2) + 1;
         nckpt = n_checkpoints(c);
         const size_t vec = (size_t)P * 3 * sizeof(float);
-        cplx = take(4 * (size_t)cplx_elems * sizeof(float2));
+        // a fifth buffer where the plane kernels read G while they write the
+        // second and third force mesh
+        cplx = take((ng <= kMaxPlane ? 5 : 4) * (size_t)cplx_elems * sizeof(float2));
         disp = take(vec);
         mom = take(vec);
         xi = take(vec);
@@ -193,7 +195,7 @@ struct pm_ctx {
     Bins bins;
     int np, ng, cs, cs_p;
     long P;
-    float2* C[4];
+    float2* C[5];   // C[4] on meshes up to kMaxPlane only
     // Working particle records, kept in bin order and double-buffered: each
     // sort moves them from the current arrays to the *_alt arrays, which then
     // become current.  id is the lattice index of each record.
@@ -467,15 +469,25 @@ void compute_force(pm_ctx* ctx, double a, Particles which) {
       t.bytes = which == kOnce ? order_once(ctx) : sort_particles(ctx, which == kStateCotangents); }
     { KTimer t(ctx, PM_K_SCATTER, 12 * P + r);
       launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), nullptr, s); }
+    const float* radial;
+    if (ng <= kMaxPlane) {   // planes: one launch for axes 2 and 1, timed with the last axis
+        { KTimer t(ctx, PM_K_FFT_X, r + c);
+          launch_fft_xy_r2c(nullptr, ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
+        { KTimer t(ctx, PM_K_MLP, 0); radial = force_radial(ctx, a); }
+        { KTimer t(ctx, PM_K_GRAD_Z, 3 * c);
+          launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[4], ng, cs, radial, ctx->twd, s); }
+        { KTimer t(ctx, PM_K_FFT_X, 3 * r + 2 * c);
+          launch_plane_c2r_force(ctx->C[1], ctx->C[4], ng, cs, cst, ctx->twd, s); }
+        return;
+    }
     { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_r2c(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
       launch_fft_axis(ctx->C[0], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
-    const float* radial;
     { KTimer t(ctx, PM_K_MLP, 0); radial = force_radial(ctx, a); }
     // F~_0 -> C1 and G -> C2; axis 1: F~_0 in place, G -> F~_1 (C2) and IFFT_1(G)
     // (C3); last axis: C2R of the three, C3 times i k2 first (= F~_2)
     { KTimer t(ctx, PM_K_GRAD_Z, 3 * c);
-      launch_grad_z(ctx->C[0], ctx->C[1], cst, ng, cs, radial, ctx->twd, s); }
+      launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[2], ng, cs, radial, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 5 * c);
       launch_fft_axis(ctx->C[1], ng, cs, 1, 1, 1, cst, ctx->twd, s);
       launch_fft_y_split(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
@@ -493,12 +505,19 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
     { KTimer t(ctx, PM_K_SCATTER_VEC, 24 * P + 3 * r);
       launch_scatter_vec(xq, v, coeff, ctx->maxbits + kExtraSlots - 1, ctx->lat, ctx->bins,
                          ctx->creal(1), ctx->creal_stride(), s); }
-    { KTimer t(ctx, PM_K_FFT_X, 3 * (r + c)); launch_fft_x_r2c(ctx->C[1], ng, cs, 3, cst, ctx->twd, s); }
-    { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
-      launch_fft_axis(ctx->C[1], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
-    // n1 G_1 + n2 G_2 into C2, the transposed axis-0 pass's second spectrum
-    { KTimer t(ctx, PM_K_FFT_STRIDED, 3 * c);
-      launch_fft_y_merge(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
+    // G_0 into C1 and n1 G_1 + n2 G_2 into C2, the transposed axis-0 pass's inputs
+    const bool planes = ng <= kMaxPlane;
+    if (planes) {
+        KTimer t(ctx, PM_K_FFT_X, 3 * r + 2 * c);
+        launch_plane_r2c_merge(ctx->C[1], ng, cs, cst, ctx->twd, s);
+    } else {
+        { KTimer t(ctx, PM_K_FFT_X, 3 * (r + c));
+          launch_fft_x_r2c(ctx->C[1], ng, cs, 3, cst, ctx->twd, s); }
+        { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
+          launch_fft_axis(ctx->C[1], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
+        { KTimer t(ctx, PM_K_FFT_STRIDED, 3 * c);
+          launch_fft_y_merge(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
+    }
     float* fbar = nullptr;
     const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ng, 3.0));
     if (ctx->cfg.filter) {
@@ -513,9 +532,15 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
         launch_mlp_backward(ctx->theta, ng, (float)ctx->cfg.box, (float)a, fbar, ctx->gtheta,
                             ctx->mlp_scratch, mlp_backward_scratch(ng), s);
     }
-    { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
-      launch_fft_axis(ctx->C[0], ng, cs, 1, 1, 1, cst, ctx->twd, s); }
-    { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_c2r(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
+    if (planes) {
+        KTimer t(ctx, PM_K_FFT_X, r + c);
+        launch_fft_yx_c2r(ctx->C[0], nullptr, ng, cs, 1, cst, ctx->twd, s);
+    } else {
+        { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
+          launch_fft_axis(ctx->C[0], ng, cs, 1, 1, 1, cst, ctx->twd, s); }
+        { KTimer t(ctx, PM_K_FFT_X, r + c);
+          launch_fft_x_c2r(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
+    }
 }
 
 // Gradient synthesis on the particle lattice: the real mesh in C0 (or `field`,
@@ -526,10 +551,16 @@ void grad_synthesis(pm_ctx* ctx, const float* radial, const float* field = nullp
     hipStream_t s = ctx->stream;
     const int np = ctx->np, cs = ctx->cs_p;
     const long cst = ctx->plan.cplx_elems;
-    if (field) launch_fft_x_r2c_from(field, ctx->C[0], np, cs, ctx->twd, s);
-    else launch_fft_x_r2c(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
-    launch_fft_axis(ctx->C[0], np, cs, 1, -1, 1, cst, ctx->twd, s);
-    launch_grad_z(ctx->C[0], ctx->C[1], cst, np, cs, radial, ctx->twd, s);
+    launch_fft_xy_r2c(field, ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    if (np <= kMaxPlane) {
+        // G needs a buffer of its own: on a finer mesh the second half of C0, whose
+        // size is 4 or more of the particle grid's, is free
+        float2* g = np < ctx->ng ? ctx->C[0] + ctx->plan.cplx_elems / 2 : ctx->C[4];
+        launch_grad_z(ctx->C[0], ctx->C[1], g, np, cs, radial, ctx->twd, s);
+        launch_plane_c2r_force(ctx->C[1], g, np, cs, cst, ctx->twd, s);
+        return;
+    }
+    launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[2], np, cs, radial, ctx->twd, s);
     launch_fft_axis(ctx->C[1], np, cs, 1, 1, 1, cst, ctx->twd, s);
     launch_fft_y_split(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
     launch_fft_x_c2r_dk2(ctx->C[1], np, cs, 3, cst, 2, ctx->twd, s);
@@ -543,14 +574,16 @@ void grad_transpose(pm_ctx* ctx, const float* v, const float* radial, float* out
     const long cst = ctx->plan.cplx_elems;
     const long rp = 2L * cs;
     launch_deinterleave(v, ctx->creal(1), ctx->creal_stride(), np, rp, s);
-    launch_fft_x_r2c(ctx->C[1], np, cs, 3, cst, ctx->twd, s);
-    launch_fft_axis(ctx->C[1], np, cs, 1, -1, 1, cst, ctx->twd, s);
-    launch_fft_y_merge(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
+    if (np <= kMaxPlane) {
+        launch_plane_r2c_merge(ctx->C[1], np, cs, cst, ctx->twd, s);
+    } else {
+        launch_fft_x_r2c(ctx->C[1], np, cs, 3, cst, ctx->twd, s);
+        launch_fft_axis(ctx->C[1], np, cs, 1, -1, 1, cst, ctx->twd, s);
+        launch_fft_y_merge(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
+    }
     launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], np, cs, radial, nullptr, 0.f,
                       ctx->twd, s);
-    launch_fft_axis(ctx->C[0], np, cs, 1, 1, 1, cst, ctx->twd, s);
-    if (out) launch_fft_x_c2r_to(ctx->C[0], out, np, cs, ctx->twd, s);
-    else launch_fft_x_c2r(ctx->C[0], np, cs, 1, cst, ctx->twd, s);
+    launch_fft_yx_c2r(ctx->C[0], out, np, cs, 1, cst, ctx->twd, s);
 }
 
 // Zel'dovich displacement (a = 1) of white noise `noise` [Np^3] with the radial
@@ -786,6 +819,7 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
     ctx->cs_p = p.cs_p;
     ctx->P = p.P;
     for (int k = 0; k < 4; ++k) ctx->C[k] = ctx->at<float2>(p.cplx) + k * p.cplx_elems;
+    ctx->C[4] = ctx->ng <= kMaxPlane ? ctx->C[3] + p.cplx_elems : nullptr;
     ctx->xq = ctx->at<uint32_t>(p.disp);
     ctx->pq = ctx->at<int32_t>(p.mom);
     ctx->xi = ctx->at<float>(p.xi);
