@@ -352,35 +352,40 @@ struct Plane {
     static constexpr int NT = ((PW * TY > N * TX ? PW * TY : N * TX) + 63) / 64 * 64;
     static constexpr int LS = lds_slots(H);
     static constexpr int SLOTS = N * LS > lds_slots(N) * PW ? N * LS : lds_slots(N) * PW;
+    // lanes without a row or column transform one of this region's, which nobody
+    // reads (a branch around their stores changes which products the compiler
+    // contracts, and with it the last bits of every transform)
+    static constexpr int ALL = NT > N * TX || NT > PW * TY ? 2 * SLOTS : SLOTS;
     // M[lpad(i1) PW + k2]: the plane's half spectrum
     static __device__ __forceinline__ int at(int i1, int k2) { return lpad(i1) * PW + k2; }
 };
 
-// Forward axis-2 transforms of the plane's rows, the row's pairs given in v and
-// the post-twiddles of the lane's outputs in w, to M.
+// Forward axis-2 transforms of the plane's rows, the row's pairs given in v, to M.
 template <int N>
-__device__ __forceinline__ void plane_rows_r2c(float2 (&v)[Plane<N>::EX],
-                                               const float2 (&w)[Plane<N>::EX], float2* lds,
+__device__ __forceinline__ void plane_rows_r2c(float2 (&v)[Plane<N>::EX], float2* lds,
+                                               const float2* __restrict__ tw, int twN,
                                                const float2* __restrict__ st) {
     using P = Plane<N>;
     constexpr int H = P::H;
     const int r = threadIdx.x / P::TX, j = threadIdx.x % P::TX;
     const bool act = r < N;
-    float2* L = lds + (act ? r : 0) * P::LS;
-    fft_lds<H, P::EX, -1>(v, L, 1, 0, j, st, act);
+    float2* L = act ? lds + r * P::LS : lds + P::SLOTS + (r - N) % N * P::LS;
+    fft_lds<H, P::EX, -1>(v, L, 1, 0, j, st);
     __syncthreads();
     float2 nyq = make_float2(0.f, 0.f);
 #pragma unroll
     for (int e = 0; e < P::EX; ++e) {
         const int k = j + e * P::TX;
-        const float2 zk = L[lpad(k)], zc = cconj(L[lpad((H - k) & (H - 1))]);
-        const float2 A = cadd(zk, zc), B = csub(zk, zc);
-        const float2 iwB = cmul_i<1>(cmul(w[e], B));
-        v[e] = make_float2(0.5f * (A.x - iwB.x), 0.5f * (A.y - iwB.y));
+        float2 zk = L[lpad(k)], zc = cconj(L[lpad((H - k) & (H - 1))]);
+        float2 A = cadd(zk, zc), B = csub(zk, zc);
+        float2 w = tw[k * twN];
+        float2 iwB = cmul_i<1>(cmul(w, B));
+        float2 X = make_float2(0.5f * (A.x - iwB.x), 0.5f * (A.y - iwB.y));
         if (k == 0) {
-            v[e] = make_float2(zk.x + zk.y, 0.f);
+            X = make_float2(zk.x + zk.y, 0.f);
             nyq = make_float2(zk.x - zk.y, 0.f);
         }
+        v[e] = X;
     }
     __syncthreads();
     if (act) {
@@ -403,7 +408,7 @@ __device__ __forceinline__ void plane_columns(float2* lds, const float2* __restr
 #pragma unroll
     for (int e = 0; e < P::EY; ++e) v[e] = value(act ? j + e * P::TY : 0, act ? c : 0);
     if constexpr (FROM_M) __syncthreads();   // M's columns are in registers
-    fft_lds<N, P::EY, DIR>(v, lds, P::PW, c, act ? j : 0, st, act);
+    fft_lds<N, P::EY, DIR>(v, act ? lds : lds + P::SLOTS, P::PW, c, act ? j : 0, st);
     __syncthreads();
 }
 
@@ -418,6 +423,13 @@ __device__ __forceinline__ void plane_each(const float2* lds, F&& f) {
         const int p = i / P::PW, k2 = i - p * P::PW;
         if (i < ALL) f(u, p, k2, lds[P::at(p, k2)]);
     }
+}
+
+// i k y with both products rounded (not contracted into the sums they enter), as
+// in k_fft_x_c2r, which passes them through LDS.
+__device__ __forceinline__ float2 times_ik(float k, float2 y) {
+#pragma clang fp contract(off)
+    return make_float2(-(k * y.y), k * y.x);
 }
 
 // Inverse axis-2 transforms of M's rows; the real rows' pairs end in lds, row r's
@@ -435,7 +447,7 @@ __device__ __forceinline__ void plane_rows_c2r(float2* lds, bool kmul,
         const float2 y = lds[P::at(act ? r : 0, k)];
         if (!kmul) return y;
         if (k == H) return make_float2(0.f, 0.f);
-        return make_float2(-(float)k * y.y, (float)k * y.x);
+        return times_ik((float)k, y);
     };
     float2 v[P::EX];
 #pragma unroll
@@ -445,7 +457,8 @@ __device__ __forceinline__ void plane_rows_c2r(float2* lds, bool kmul,
         v[e] = cadd(cadd(xk, xc), cmul_i<1>(cmulc(csub(xk, xc), w[e])));
     }
     __syncthreads();
-    fft_lds<H, P::EX, 1>(v, lds + (act ? r : 0) * P::LS, 1, 0, j, st, act);
+    float2* L = act ? lds + r * P::LS : lds + P::SLOTS + (r - N) % N * P::LS;
+    fft_lds<H, P::EX, 1>(v, L, 1, 0, j, st);
     __syncthreads();
 }
 
@@ -458,7 +471,7 @@ __global__ void __launch_bounds__(Plane<N>::NT)
 k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, long bufStride,
             const float2* __restrict__ tw, int ntw, const float2* __restrict__ st) {
     using P = Plane<N>;
-    __shared__ float2 lds[P::SLOTS];
+    __shared__ float2 lds[P::ALL];
     const int i0 = (int)xcd_block(blockIdx.x, N), twN = ntw / N;
     const int r = threadIdx.x / P::TX, j = threadIdx.x % P::TX;
     const bool two = MERGE && blockIdx.y == 1;
@@ -473,13 +486,11 @@ k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
             v[e] = make_float2(row[k], row[k + 1]);
         }
     };
-    float2 v[P::EX], v2[P::EX], w[P::EX];
+    float2 v[P::EX], v2[P::EX];
     load(b, v);
     if (two) load(b + bufStride, v2);
-#pragma unroll
-    for (int e = 0; e < P::EX; ++e) w[e] = tw[(j + e * P::TX) * twN];
     auto column = [&](int i1, int k2) { return lds[P::at(i1, k2)]; };
-    plane_rows_r2c<N>(v, w, lds, st);
+    plane_rows_r2c<N>(v, lds, tw, twN, st);
     plane_columns<N, -1, true>(lds, st, column);
     if (!two) {
         plane_each<N>(lds, [&](int, int p, int k2, float2 y) {
@@ -495,7 +506,7 @@ k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
             h[u] = make_float2(f1 * y.x, f1 * y.y);
         });
         __syncthreads();   // the first spectrum has been read
-        plane_rows_r2c<N>(v2, w, lds, st);
+        plane_rows_r2c<N>(v2, lds, tw, twN, st);
         plane_columns<N, -1, true>(lds, st, column);
         plane_each<N>(lds, [&](int u, int p, int k2, float2 y) {
             const float f2 = k2 == P::H ? 0.f : (float)k2;
@@ -515,21 +526,24 @@ k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
             long bufStride, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     using P = Plane<N>;
-    __shared__ float2 lds[P::SLOTS];
+    __shared__ float2 lds[P::ALL];
     const int i0 = (int)xcd_block(blockIdx.x, N), comp = blockIdx.y;
     float2* b = buf + comp * bufStride;
     const float2* src = FORCE && comp > 0 ? g : b;
-    const bool d1 = FORCE && comp == 1;
     float2 w[P::EX];
 #pragma unroll
     for (int e = 0; e < P::EX; ++e)
         w[e] = tw[(threadIdx.x % P::TX + e * P::TX) * (ntw / N)];
-    plane_columns<N, 1, false>(lds, st, [&](int p, int k2) {
-        const float2 y = src[mesh_row(i0, p, N) * cs + k2];
-        if (!d1) return y;
-        const float f1 = p == N / 2 ? 0.f : (float)signed_freq(p, N);
-        return make_float2(-f1 * y.y, f1 * y.x);
-    });
+    auto spectrum = [&](int p, int k2) { return src[mesh_row(i0, p, N) * cs + k2]; };
+    if (FORCE && comp == 1) {
+        plane_columns<N, 1, false>(lds, st, [&](int p, int k2) {
+            const float2 y = spectrum(p, k2);
+            const float f1 = p == N / 2 ? 0.f : (float)signed_freq(p, N);
+            return make_float2(-f1 * y.y, f1 * y.x);
+        });
+    } else {
+        plane_columns<N, 1, false>(lds, st, spectrum);
+    }
     plane_rows_c2r<N>(lds, FORCE && comp == 2, w, st);
 #pragma unroll
     for (int u = 0; u < (N * P::H + P::NT - 1) / P::NT; ++u) {

@@ -143,11 +143,9 @@ constexpr int lds_slots(int H) { return H + H / 16 + 1; }
 // One Stockham stage of span Ns, then the rest recursively.  `st` is the
 // stage twiddle table of this transform length (see fft_plan.h): lanes with
 // consecutive k read consecutive entries.
-// `act`: lanes without a transform of their own (false) take part in the
-// barriers only.
 template <int H, int E, int DIR, int Ns>
 __device__ __forceinline__ void fft_stage(float2 (&v)[E], float2* lds, int PS, int off, int j,
-                                          const float2* __restrict__ st, bool act = true) {
+                                          const float2* __restrict__ st) {
     constexpr int REM = H / Ns;
     constexpr int R = E < REM ? E : REM;
     constexpr int T = H / E;
@@ -168,19 +166,15 @@ __device__ __forceinline__ void fft_stage(float2 (&v)[E], float2* lds, int PS, i
         }
         dft<R, DIR>(u);
         const int base = (b - k) * R + k;
-        if (act) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) lds[lpad(base + r * Ns) * PS + off] = u[r];
-        }
+        for (int r = 0; r < R; ++r) lds[lpad(base + r * Ns) * PS + off] = u[r];
     }
     if constexpr (Ns * R < H) {
         __syncthreads();
-        if (act) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = lds[lpad(j + e * T) * PS + off];
-        }
+        for (int e = 0; e < E; ++e) v[e] = lds[lpad(j + e * T) * PS + off];
         __syncthreads();
-        fft_stage<H, E, DIR, Ns * R>(v, lds, PS, off, j, st, act);
+        fft_stage<H, E, DIR, Ns * R>(v, lds, PS, off, j, st);
     }
 }
 
@@ -189,10 +183,10 @@ __device__ __forceinline__ void fft_stage(float2 (&v)[E], float2* lds, int PS, i
 // is the combined stage-twiddle table (fft_plan.h).
 template <int H, int E, int DIR>
 __device__ __forceinline__ void fft_lds(float2 (&v)[E], float2* lds, int PS, int off, int j,
-                                        const float2* __restrict__ stages, bool act = true) {
+                                        const float2* __restrict__ stages) {
     static_assert((H & (H - 1)) == 0 && (E & (E - 1)) == 0 && E <= H, "power-of-two sizes");
     static_assert(E == fft_values_per_lane(H), "lane shape must match the twiddle tables");
-    fft_stage<H, E, DIR, 1>(v, lds, PS, off, j, stages + H, act);
+    fft_stage<H, E, DIR, 1>(v, lds, PS, off, j, stages + H);
 }
 
 // As fft_lds, with `tab` the H-point transform's own part of the stage table
