@@ -756,11 +756,16 @@ k_grad_z_pipe(const float2* __restrict__ src, float2* __restrict__ dst,
 // along the column, so n1 G_1 + n2 G_2 comes combined from the axis-1 pass
 // (k_fft_y_merge) as the second input spectrum: three column FFTs per tile
 // (four with the filter cotangent).
+// FILT: the mode's term of dL/df(|n|^2), summed over +-n0, goes to
+// modes[(|n0| n + i1) cs + k2], which k_filter_shells adds up by |n|^2.  Added to
+// the table with global atomics instead (34 M of them on 197k words at 512^3,
+// each served at the memory side), they were two thirds of this pass: 1.49 ms
+// with them, 0.77 ms now and 0.13 ms for the sums (128^3: 40 us, now 15 + 16).
 template <int H, bool FILT>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_adj_z(const float2* __restrict__ src, long srcStride, float2* dst,
              const float2* dens, int cs, int ncb, const float* __restrict__ radial,
-             float* __restrict__ fbar, float fscale, const float2* __restrict__ tw, int ntw,
+             float* __restrict__ modes, float fscale, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     // exchange buffer | the H-point part of the stage-twiddle table (read from
@@ -814,7 +819,7 @@ k_grad_adj_z(const float2* __restrict__ src, long srcStride, float2* dst,
         __syncthreads();
         // each lane turns its own elements' dens_k into their contribution (in
         // the same LDS slot), then the modes n0 and -n0, which share |n|^2, are
-        // added before one atomic per pair
+        // added
         const float mult = (k2 == 0 || k2 == n / 2) ? 1.f : 2.f;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -829,18 +834,13 @@ k_grad_adj_z(const float2* __restrict__ src, long srcStride, float2* dst,
             lds[lpad(p) * W + c] = make_float2(fs, 0.f);
         }
         __syncthreads();
-        if (in_half) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int p = j + e * T;
-                if (p > n / 2) continue;
-                const int n0 = signed_freq(p, n);
-                const int nsq = n0 * n0 + n1 * n1 + k2 * k2;
-                if (nsq == 0) continue;
-                float fs = lds[lpad(p) * W + c].x;
-                if (p != 0 && p != n / 2) fs += lds[lpad(n - p) * W + c].x;
-                atomicAdd(&fbar[nsq], fs);
-            }
+        for (int e = 0; e < E; ++e) {
+            const int p = j + e * T;
+            if (p > n / 2) continue;
+            float fs = lds[lpad(p) * W + c].x;
+            if (p != 0 && p != n / 2) fs += lds[lpad(n - p) * W + c].x;
+            modes[((long)p * n + i1) * cs + k2] = fs;
         }
     }
     // delta_bar_k = -i R (n0 G_0 + n1 G_1 + n2 G_2)
@@ -855,6 +855,66 @@ k_grad_adj_z(const float2* __restrict__ src, long srcStride, float2* dst,
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) dst[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
+}
+
+// Work-group (s, t): the sums over the modes of |n0| = t, t + kFilterSplits, ... of
+// k_grad_adj_z's terms, by |n|^2 = q in the shell s width <= q < (s + 1) width, to
+// part[t][q].  A column (|n0|, +-n1) meets a shell in one run of k2, found from two
+// square roots, so every term is read once and added in LDS (FP64).  16 lanes
+// share a column: at width 8 n a run is some 16 values, one or two 64-byte
+// reads (one lane per column and shells of a 256th of the table, about one
+// value per run, took 548 us at 512^3; this takes 125 us, 11 us at 128^3).
+// Every entry is written: no clearing pass.
+constexpr int kFilterSplits = 16, kFilterThreads = 512;
+__global__ void __launch_bounds__(kFilterThreads)
+k_filter_shells(const float* __restrict__ modes, int n, int cs, int width, int ntab,
+                float* __restrict__ part) {
+    extern __shared__ double acc[];   // [width]
+    const int q0 = (int)blockIdx.x * width, q1 = q0 + width;
+    for (int i = threadIdx.x; i < width; i += kFilterThreads) acc[i] = 0.0;
+    __syncthreads();
+    const int m = n / 2;
+    // smallest k >= 0 with k^2 >= x
+    auto root = [](int x) {
+        if (x <= 0) return 0;
+        int k = (int)sqrtf((float)x);
+        while (k * k >= x) --k;
+        while (k * k < x) ++k;
+        return k;
+    };
+    const int lane = threadIdx.x & 15, group = threadIdx.x >> 4;
+    for (int p = blockIdx.y; p <= m; p += kFilterSplits) {
+        // the columns that meet the shell at some 0 <= k2 <= m
+        const int i_end = min(root(q1 - p * p), m + 1);
+        for (int i1 = root(q0 - m * m - p * p) + group; i1 < i_end; i1 += kFilterThreads / 16) {
+            const int r2 = p * p + i1 * i1;
+            const int k1 = min(root(q1 - r2), m + 1);
+            const float* row = modes + ((long)p * n + i1) * cs;
+            // -n1 sits in row n - i1; n1 = 0 and the Nyquist plane have no partner
+            const bool paired = i1 > 0 && i1 < m;
+            const float* other = paired ? modes + ((long)p * n + n - i1) * cs : row;
+            for (int k = root(q0 - r2) + lane; k < k1; k += 16) {
+                const float a = row[k], b = other[k];
+                atomicAdd(&acc[r2 + k * k - q0], (double)(paired ? a + b : a));
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < width; i += kFilterThreads)
+        if (q0 + i < ntab) part[(long)blockIdx.y * ntab + q0 + i] = (float)acc[i];
+}
+
+__global__ void __launch_bounds__(256)
+k_filter_sum(const float* __restrict__ part, int ntab, float* __restrict__ fbar) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= ntab) return;
+    float v[kFilterSplits];
+#pragma unroll
+    for (int t = 0; t < kFilterSplits; ++t) v[t] = part[(long)t * ntab + q];
+    double s = 0.0;
+#pragma unroll
+    for (int t = 0; t < kFilterSplits; ++t) s += v[t];
+    fbar[q] = (float)s;
 }
 
 // k_grad_adj_z (without the filter cotangent) for the largest transforms, as a
@@ -1281,16 +1341,23 @@ void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
 }
 
 void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const float2* dens,
-                       int n, int cs, const float* radial, float* fbar, float fscale,
-                       const Twiddles& tw, hipStream_t s) {
+                       int n, int cs, const float* radial, float* fbar, float* modes,
+                       float fscale, const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
         constexpr int NN = decltype(nn)::value;
         constexpr int W = Cfg<NN>::W, T = Cfg<NN>::T;
         int ncb = cs / W;
         if (fbar) {
             hipLaunchKernelGGL((k_grad_adj_z<NN, true>), dim3(NN * ncb), dim3(T * W), 0, s, src,
-                               srcStride, dst, dens, cs, ncb, radial, fbar, fscale, tw.w, tw.n,
+                               srcStride, dst, dens, cs, ncb, radial, modes, fscale, tw.w, tw.n,
                                tw.stages);
+            constexpr int ntab = 3 * (NN / 2) * (NN / 2) + 1, width = 8 * NN;
+            float* part = modes + (long)(NN / 2 + 1) * NN * cs;
+            hipLaunchKernelGGL(k_filter_shells, dim3((ntab + width - 1) / width, kFilterSplits),
+                               dim3(kFilterThreads), width * sizeof(double), s, modes, NN, cs,
+                               width, ntab, part);
+            hipLaunchKernelGGL(k_filter_sum, dim3((ntab + 255) / 256), dim3(256), 0, s, part, ntab,
+                               fbar);
         } else if constexpr (NN == 1024) {
             const int ntiles = NN * ncb;
             const int nwg = std::min(ntiles, device_cus());
@@ -1298,7 +1365,7 @@ void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const flo
                                srcStride, dst, cs, ncb, ntiles, radial, tw.w, tw.n, tw.stages);
         } else {
             hipLaunchKernelGGL((k_grad_adj_z<NN, false>), dim3(NN * ncb), dim3(T * W), 0, s, src,
-                               srcStride, dst, dens, cs, ncb, radial, fbar, fscale, tw.w, tw.n,
+                               srcStride, dst, dens, cs, ncb, radial, nullptr, 0.f, tw.w, tw.n,
                                tw.stages);
         }
     });

@@ -84,12 +84,14 @@ void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
 // Sum_j conj(M_j) forward-axis-0(G_j), with M_j = i n_j radial, given G_0 at src
 // and n1 G_1 + n2 G_2 (from launch_fft_y_merge) at src + srcStride, both
 // already transformed along axes 2 and 1.  dst may equal the `dens` buffer.
-// When fbar != nullptr also accumulates
-// fbar[|n|^2] += mult * Sum_j Re(conj(G_j) i n_j fscale/|n|^2 dens_k)
-// (mult = 1 on the k2 = 0, n/2 planes, else 2) using forward-axis-0(dens).
+// When fbar != nullptr also forms
+// fbar[|n|^2] = Sum mult * Sum_j Re(conj(G_j) i n_j fscale/|n|^2 dens_k)
+// (mult = 1 on the k2 = 0, n/2 planes, else 2) using forward-axis-0(dens), with
+// `modes` (a complex buffer's size, overlapping none of the others) for the terms
+// and their partial sums.
 void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const float2* dens,
-                       int n, int cs, const float* radial, float* fbar, float fscale,
-                       const Twiddles& tw, hipStream_t s);
+                       int n, int cs, const float* radial, float* fbar, float* modes,
+                       float fscale, const Twiddles& tw, hipStream_t s);
 // Full 3-D transforms built from the passes above.
 void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
 void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);

@@ -520,13 +520,11 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
     }
     float* fbar = nullptr;
     const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ng, 3.0));
-    if (ctx->cfg.filter) {
-        fbar = ctx->fbar;
-        launch_zero(fbar, ctx->plan.ntab_f * sizeof(float), s);
-    }
+    if (ctx->cfg.filter) fbar = ctx->fbar;
+    // (C3 is free: its spectrum went into C2's)
     { KTimer t(ctx, PM_K_GRAD_ADJ_Z, (fbar ? 4 : 3) * c);
-      launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], ng, cs, ctx->radial_f, fbar, fscale,
-                        ctx->twd, s); }
+      launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], ng, cs, ctx->radial_f, fbar,
+                        ctx->creal(3), fscale, ctx->twd, s); }
     if (ctx->cfg.filter) {
         KTimer t(ctx, PM_K_MLP, 0);
         launch_mlp_backward(ctx->theta, ng, (float)ctx->cfg.box, (float)a, fbar, ctx->gtheta,
@@ -581,7 +579,7 @@ void grad_transpose(pm_ctx* ctx, const float* v, const float* radial, float* out
         launch_fft_axis(ctx->C[1], np, cs, 1, -1, 1, cst, ctx->twd, s);
         launch_fft_y_merge(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
     }
-    launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], np, cs, radial, nullptr, 0.f,
+    launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], np, cs, radial, nullptr, nullptr, 0.f,
                       ctx->twd, s);
     launch_fft_yx_c2r(ctx->C[0], out, np, cs, 1, cst, ctx->twd, s);
 }
