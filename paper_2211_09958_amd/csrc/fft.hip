@@ -182,6 +182,8 @@ k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, int cs, long nro
     for (int e = 0; e < E; ++e) st_nt_pair(dst + 2 * (j + e * T), L[lpad(j + e * T)]);
 }
 
+__device__ __forceinline__ int signed_freq(int p, int n) { return p < n / 2 ? p : p - n; }
+
 // ---------------------------------------------------------- strided axes
 
 // Tile t -> (a, cb): columns cb*W .. cb*W+W-1 of the rows with the other slow
@@ -232,8 +234,6 @@ k_fft_strided(float2* __restrict__ buf, typename std::conditional<DIR < 0, float
         for (int e = 0; e < E; ++e) at(j + e * T) = lds[lpad(j + e * T) * W + c];
     }
 }
-
-__device__ __forceinline__ int signed_freq(int p, int n) { return p < n / 2 ? p : p - n; }
 
 // Inverse axis-1 pass that splits G into the two spectra it feeds: out_g =
 // IFFT_1(G) (F~_2 = i k2 times it, applied by the last-axis C2R) and, in place,
@@ -328,6 +328,74 @@ k_fft_y_merge(float2* __restrict__ g1, const float2* __restrict__ g2, int cs, in
         const int p = j + e * T;
         const float2 y = lds[lpad(p) * W + c];
         g1[off(p)] = make_float2(h[e].x + f2 * y.x, h[e].y + f2 * y.y);
+    }
+}
+
+// Axis-0 pass with a 2LPT multiplier (launch_fft_z_mul).  A multiplier pass of
+// its own read and wrote the spectrum once more: 50 us per use at 256^3, for 24 us
+// of transform.
+struct LptMul {
+    int a, b, mode, accumulate;
+    const float* table;
+    float scale;
+};
+
+// The factor of mode (i0, i1, k2).
+template <int H>
+__device__ __forceinline__ float lpt_factor(const LptMul& M, int i0, int i1, int k2) {
+    const int nv[3] = {signed_freq(i0, H), signed_freq(i1, H), k2};
+    const bool nyq[3] = {i0 == H / 2, i1 == H / 2, k2 == H / 2};
+    const int m2 = nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2];
+    if (m2 == 0 || k2 > H / 2) return 0.f;
+    const int na = M.a == 0 ? nv[0] : (M.a == 1 ? nv[1] : nv[2]);
+    const int nb = M.b == 0 ? nv[0] : (M.b == 1 ? nv[1] : nv[2]);
+    const bool za = M.a == 0 ? nyq[0] : (M.a == 1 ? nyq[1] : nyq[2]);
+    const bool zb = M.b == 0 ? nyq[0] : (M.b == 1 ? nyq[1] : nyq[2]);
+    const float r = M.table ? M.table[m2] : 1.f / (float)m2;
+    float w;
+    if (M.mode == 0) w = M.a != M.b && (za || zb) ? 0.f : (float)(na * nb) * r;
+    else if (M.mode == 1) w = (float)(m2 - na * na) * r;
+    else w = (float)m2 * r;
+    return w * M.scale;
+}
+
+template <int H, int DIR>
+__global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W, Cfg<H>::MINW)
+k_fft_z_mul(const float2* __restrict__ src, float2* __restrict__ dst, int cs, int ncb, LptMul M,
+            const float2* __restrict__ st) {
+    constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W;
+    __shared__ float2 lds[lds_slots(H) * W];
+    const int c = threadIdx.x % W, j = threadIdx.x / W;
+    const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
+    const int i1 = tile / ncb, k2 = (tile % ncb) * W + c;
+    auto off = [&](int p) -> long { return mesh_row(p, i1, H) * cs + k2; };
+    float2 v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = src[off(j + e * T)];
+    if constexpr (DIR > 0) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const float w = lpt_factor<H>(M, j + e * T, i1, k2);
+            v[e] = make_float2(w * v[e].x, w * v[e].y);
+        }
+    }
+    fft_lds<H, E, DIR>(v, lds, W, c, j, st);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int q = j + e * T;
+        float2 y = lds[lpad(q) * W + c];
+        if constexpr (DIR < 0) {
+            const float w = lpt_factor<H>(M, q, i1, k2);
+            y.x *= w;
+            y.y *= w;
+            if (M.accumulate) {
+                const float2 d = dst[off(q)];
+                y.x += d.x;
+                y.y += d.y;
+            }
+        }
+        dst[off(q)] = y;
     }
 }
 
@@ -1306,20 +1374,13 @@ void launch_fft_y_merge(float2* g1, const float2* g2, int n, int cs, const Twidd
     });
 }
 
-void launch_fft_axis(float2* buf, int n, int cs, int axis, int dir, int nbuf, long bufStride,
-                     const Twiddles& tw, hipStream_t s) {
-    if (axis == 1)
-        pass_switch(n, [&](auto nn) {
-            constexpr int N = decltype(nn)::value;
-            if (dir < 0) strided<N, -1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-            else strided<N, 1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-        });
-    else
-        size_switch(n, [&](auto nn) {
-            constexpr int N = decltype(nn)::value;
-            if (dir < 0) strided<N, -1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-            else strided<N, 1, 0, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
-        });
+void launch_fft_y(float2* buf, int n, int cs, int dir, int nbuf, long bufStride,
+                  const Twiddles& tw, hipStream_t s) {
+    pass_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        if (dir < 0) strided<N, -1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+        else strided<N, 1, 1, false>(buf, nullptr, cs, nbuf, bufStride, tw, s);
+    });
 }
 
 void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
@@ -1411,7 +1472,7 @@ void launch_fft_xy_r2c(const float* real, float2* buf, int n, int cs, int nbuf, 
     }
     if (real) launch_fft_x_r2c_from(real, buf, n, cs, tw, s);
     else launch_fft_x_r2c(buf, n, cs, nbuf, bufStride, tw, s);
-    launch_fft_axis(buf, n, cs, 1, -1, nbuf, bufStride, tw, s);
+    launch_fft_y(buf, n, cs, -1, nbuf, bufStride, tw, s);
 }
 
 void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long bufStride,
@@ -1424,7 +1485,7 @@ void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long b
         });
         return;
     }
-    launch_fft_axis(buf, n, cs, 1, 1, nbuf, bufStride, tw, s);
+    launch_fft_y(buf, n, cs, 1, nbuf, bufStride, tw, s);
     if (real) launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
     else launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
 }
@@ -1447,14 +1508,21 @@ void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bu
     });
 }
 
-void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    launch_fft_xy_r2c(nullptr, buf, n, cs, nbuf, bufStride, tw, s);
-    launch_fft_axis(buf, n, cs, 0, -1, nbuf, bufStride, tw, s);
-}
-
-void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s) {
-    launch_fft_axis(buf, n, cs, 0, 1, nbuf, bufStride, tw, s);
-    launch_fft_yx_c2r(buf, nullptr, n, cs, nbuf, bufStride, tw, s);
+void launch_fft_z_mul(const float2* src, float2* dst, int n, int cs, int dir, int ax_a, int ax_b,
+                      int mode, const float* table, float scale, bool accumulate,
+                      const Twiddles& tw, hipStream_t s) {
+    const LptMul M{ax_a, ax_b, mode, accumulate ? 1 : 0, table, scale};
+    size_switch(n, [&](auto nn) {
+        constexpr int N = decltype(nn)::value;
+        constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
+        const int ncb = cs / W;
+        if (dir > 0)
+            hipLaunchKernelGGL((k_fft_z_mul<N, 1>), dim3(N * ncb), dim3(T * W), 0, s, src, dst, cs,
+                               ncb, M, tw.stages);
+        else
+            hipLaunchKernelGGL((k_fft_z_mul<N, -1>), dim3(N * ncb), dim3(T * W), 0, s, src, dst, cs,
+                               ncb, M, tw.stages);
+    });
 }
 
 void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int cs, int nbins,

@@ -46,7 +46,7 @@ void launch_plane_r2c_merge(float2* buf, int n, int cs, long bufStride, const Tw
 // and G in `g` (a buffer of its own), -> the three real force meshes
 void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bufStride,
                             const Twiddles& tw, hipStream_t s);
-// The passes of one axis below, but for axis 0, take n > kMaxPlane only.
+// The passes of axis 2 or axis 1 alone take n > kMaxPlane only.
 // Real rows -> half spectra along the last axis, in place, for `nbuf` buffers
 // `bufStride` float2 apart.  Unnormalised exp(-i k x).
 void launch_fft_x_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
@@ -70,9 +70,9 @@ void launch_fft_y_split(float2* g, float2* out_g, int n, int cs, const Twiddles&
 // column): the input of launch_grad_adj_z's second spectrum
 void launch_fft_y_merge(float2* g1, const float2* g2, int n, int cs, const Twiddles& tw,
                         hipStream_t s);
-// Complex transform along axis 0 or 1, in place; dir = -1 forward, +1 inverse.
-void launch_fft_axis(float2* buf, int n, int cs, int axis, int dir, int nbuf, long bufStride,
-                     const Twiddles& tw, hipStream_t s);
+// Complex transform along axis 1, in place; dir = -1 forward, +1 inverse.
+void launch_fft_y(float2* buf, int n, int cs, int dir, int nbuf, long bufStride,
+                  const Twiddles& tw, hipStream_t s);
 // Fused axis-0 pass of the force: forward axis-0 FFT of src (already
 // transformed along axes 2 and 1), then dst = IFFT_0(i n0 radial delta) (zero
 // on the Nyquist plane of axis 0) and dst_g = G = IFFT_0(radial delta);
@@ -92,10 +92,7 @@ void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
 void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const float2* dens,
                        int n, int cs, const float* radial, float* fbar, float* modes,
                        float fscale, const Twiddles& tw, hipStream_t s);
-// Full 3-D transforms built from the passes above.
-void launch_fft3_r2c(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
-void launch_fft3_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
-// The same between a dense real mesh [n]^3 and a dense half spectrum
+// Full 3-D transforms between a dense real mesh [n]^3 and a dense half spectrum
 // [n][n][n/2+1], through `buf`; the first and last pass read and write the
 // caller's layout.  R2C with spec == nullptr leaves the spectrum in `buf`.
 void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,
@@ -238,50 +235,63 @@ void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi,
 // launch_bin(counted = true).
 void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bins& b,
                            hipStream_t s);
-// Fixed-point state (any order) -> displacement (minimum image of x - q) and
-// momentum in lattice order (disp, mom, pq nullable).
-void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
-                       const Lattice& L, float* disp, float* mom, hipStream_t s);
+// Fixed-point state (any order) -> lattice order: displacement (minimum image of
+// x - q) and momentum, and the fixed-point state itself.
+void launch_final_state(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
+                        const Lattice& L, uint32_t* xo, int32_t* po, float* disp, float* mom,
+                        hipStream_t s);
 // [P][3] float records to lattice order: out[id[k]] = in[k].
 void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P,
                           hipStream_t s);
-// Fixed-point state (any order) scattered to lattice order by id.
-void launch_state_to_lattice(const uint32_t* xq, const int32_t* pq, const uint32_t* id, long P,
-                             uint32_t* xq_out, int32_t* pq_out, hipStream_t s);
 void launch_iota(uint32_t* id, long P, hipStream_t s);
 int particle_blocks(long P);
 
-// Dot products over [P][3] arrays into FP64 block partials (b indexed through
-// id when given: Sum_k a[k] . b[id[k]]).
-void launch_dot3(const float* a, const float* b, long P, double* partials, int nblocks,
-                 hipStream_t s, const uint32_t* id = nullptr);
 // sums[slot] = Sum of partials[0..nblocks)
 void launch_reduce(const double* partials, int nblocks, double* sums, int slot, hipStream_t s);
+// sums[slots.slot[k]] = Sum of partials[k nblocks .. (k + 1) nblocks) for k < nsets
+struct Slots {
+    int slot[9];
+};
+void launch_reduce_sets(const double* partials, int nblocks, int nsets, double* sums,
+                        const Slots& slots, hipStream_t s);
 // Reconstruction error of fixed-point positions in cells: partials of
 // Sum_k |a[k] - b[id[k]]|^2 (minimum image), *maxbits (as float bits) = max.
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,
                       double* partials, int nblocks, unsigned* maxbits, hipStream_t s);
 
 // Zel'dovich state from three real meshes s_j (pitch rp, on the particle
-// lattice): x = q + D0 s, p = G0 s in fixed point (xq, pq nullable), s_out
-// (nullable) = s; with s2v ([P][3] lattice order, 2LPT) the state adds D2 s2
-// and G2 s2.  launch_ic_check instead compares that state with the given
-// xq/pq: block partials of Sum|dx|^2 (cells^2), Sum|dp|^2 and Sum|p|^2 at
-// partials[0, nblocks, 2 nblocks) and max |dx| (cells) into *maxbits.
+// lattice): x = q + D0 s, p = G0 s in fixed point; with s2v ([P][3] lattice order,
+// 2LPT) the state adds D2 s2 and G2 s2.  launch_ic_float writes the same state
+// as displacement x - q and momentum, launch_ic_field s itself ([P][3]).
 void launch_ic_state(const float* smesh, long sStride, long rp, float D0, float G0,
-                     const Lattice& L, uint32_t* xq, int32_t* pq, uint32_t* id, float* s_out,
-                     hipStream_t s, const float* s2v = nullptr, float D2 = 0.f, float G2 = 0.f);
-void launch_ic_check(const float* smesh, long sStride, long rp, float D0, float G0,
-                     const Lattice& L, const uint32_t* xq, const int32_t* pq, const uint32_t* id,
-                     double* partials, int nblocks, unsigned* maxbits, hipStream_t s,
+                     const Lattice& L, uint32_t* xq, int32_t* pq, uint32_t* id, hipStream_t s,
                      const float* s2v = nullptr, float D2 = 0.f, float G2 = 0.f);
-// 2LPT spectral multiplier on a half spectrum (integer wave numbers nv, m2 =
-// |n|^2, R = table[m2] or 1/m2 when table is null): mode 0 nv[a] nv[b] R (0 on
-// the Nyquist plane of a or b when a != b), mode 1 (m2 - nv[a]^2) R, mode 2
-// m2 table[m2]; times scale, 0 at m2 = 0.  dst = w src, or += when accumulate
-// (dst and src distinct).
-void launch_lpt_mul(const float2* src, float2* dst, int n, int cs, int ax_a, int ax_b, int mode,
-                    const float* table, float scale, bool accumulate, hipStream_t s);
+void launch_ic_float(const float* smesh, long sStride, long rp, float D0, float G0,
+                     const Lattice& L, float* disp, float* mom, hipStream_t s,
+                     const float* s2v = nullptr, float D2 = 0.f, float G2 = 0.f);
+void launch_ic_field(const float* smesh, long sStride, long rp, const Lattice& L, float* out,
+                     hipStream_t s);
+// The state and cotangents at x_0 (sorted order) against the ICs: block partials,
+// set k at k nblocks, of
+//   0 Sum|dx|^2 (cells^2)  1 Sum|dp|^2  2 Sum|p|^2 (fixed-point units)
+//   3 Sum xi.s  4 Sum pi.s  5 Sum s_bar.s, s_bar = D0 xi + G0 pi
+//   6 Sum xi.s2  7 Sum pi.s2  8 Sum s2_bar.s2, s2_bar = D2 xi + G2 pi (2LPT, s2v given)
+// and max |dx| (cells) into *maxbits.  s_bar replaces s in the meshes, s2_bar goes
+// to [P][3] in lattice order.
+void launch_ic_adjoint(float* smesh, long sStride, long rp, float D0, float G0, const Lattice& L,
+                       const uint32_t* xq, const int32_t* pq, const uint32_t* id, const float* xi,
+                       const float* pi, double* partials, int nblocks, unsigned* maxbits,
+                       hipStream_t s, const float* s2v = nullptr, float* s2_bar = nullptr,
+                       float D2 = 0.f, float G2 = 0.f);
+// Axis-0 pass with a 2LPT multiplier w of integer wave numbers nv, m2 = |n|^2, R =
+// table[m2] (or 1/m2 when table is null): mode 0 nv[a] nv[b] R (0 on the Nyquist
+// plane of a or b when a != b), mode 1 (m2 - nv[a]^2) R, mode 2 m2 table[m2]; times
+// scale, 0 at m2 = 0.  dir = +1: dst = inverse transform of w src; dir = -1: dst =
+// w times the forward transform of src, or += when accumulate (dst and src
+// distinct).
+void launch_fft_z_mul(const float2* src, float2* dst, int n, int cs, int dir, int ax_a, int ax_b,
+                      int mode, const float* table, float scale, bool accumulate,
+                      const Twiddles& tw, hipStream_t s);
 // Real meshes of one layout: op 0 out = ab + ac + bc; op 1 out = a - b^2 (- c^2
 // if c); op 2 out = scale a b.  out may alias a.
 void launch_lpt_pointwise(const float* a, const float* b, const float* c, float* out, int n,
@@ -294,13 +304,6 @@ void launch_dot_pitched(const float* src, const float* b, int n, long rp, double
 // AoS [P][3] component j -> pitched mesh j (three meshes).
 void launch_deinterleave(const float* v, float* dst, long dstStride, int np, long rp,
                          hipStream_t s);
-// out = a * x + b * y over n floats (y nullable -> out = a x)
-void launch_axpby(float* out, const float* x, float a, const float* y, float b, long n,
-                  hipStream_t s);
-// out[id[k]] = a x[k] + b y[k] over [P][3] records (lattice-order output).
-void launch_axpby_scatter(float* out, const float* x, float a, const float* y, float b,
-                          const uint32_t* id, long P, hipStream_t s);
-
 // Loss L = n^-3 Sum (d - t)^2 partials, g = 2 (d - t) / n^3 (nullable).
 void launch_mse(const float* d, const float* t, float* g, long n3, double* partials,
                 int nblocks, hipStream_t s);

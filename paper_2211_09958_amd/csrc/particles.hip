@@ -1023,22 +1023,32 @@ k_undrift(uint32_t* __restrict__ xq, const int32_t* __restrict__ pq, const float
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
+// Final state of a forward run, to lattice order: displacement (minimum image of
+// x - q) and momentum for the caller, and the fixed-point state for the adjoint.
 __global__ void __launch_bounds__(kBlock)
-k_from_fixed(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
-             const uint32_t* __restrict__ id, Lattice L, long P, float* __restrict__ disp,
-             float* __restrict__ mom) {
-    for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
-         p += (long)gridDim.x * kBlock) {
-        const long q = id[p];
-        int jj[3];
-        lattice_index(q, L.np, jj);
+k_final_state(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
+              const uint32_t* __restrict__ id, Lattice L, long P, uint32_t* __restrict__ xo,
+              int32_t* __restrict__ po, float* __restrict__ disp, float* __restrict__ mom) {
+    const long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if (p >= P) return;
+    const long q = id[p];
+    uint32_t x[3];
+    int32_t m[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int32_t d = (int32_t)(xq[3 * p + a] - (uint32_t)jj[a] * L.qstep);
-            if (disp) disp[3 * q + a] = (float)d * L.pos_to_len;
-            if (mom) mom[3 * q + a] = (float)pq[3 * p + a] * L.mom_unit;
-        }
-    }
+    for (int a = 0; a < 3; ++a) x[a] = xq[3 * p + a];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) m[a] = pq[3 * p + a];
+    int jj[3];
+    lattice_index(q, L.np, jj);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) xo[3 * q + a] = x[a];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) po[3 * q + a] = m[a];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        disp[3 * q + a] = (float)(int32_t)(x[a] - (uint32_t)jj[a] * L.qstep) * L.pos_to_len;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) mom[3 * q + a] = (float)m[a] * L.mom_unit;
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -1055,21 +1065,6 @@ k_permute_by_id(const float* __restrict__ in, const uint32_t* __restrict__ id,
     }
 }
 
-__global__ void __launch_bounds__(kBlock)
-k_state_to_lattice(const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
-                   const uint32_t* __restrict__ id, long P, uint32_t* __restrict__ xo,
-                   int32_t* __restrict__ po) {
-    for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
-         p += (long)gridDim.x * kBlock) {
-        const long q = id[p];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            xo[3 * q + a] = xq[3 * p + a];
-            po[3 * q + a] = pq[3 * p + a];
-        }
-    }
-}
-
 __global__ void __launch_bounds__(kBlock) k_iota(uint32_t* __restrict__ id, long P) {
     for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
          p += (long)gridDim.x * kBlock)
@@ -1078,22 +1073,10 @@ __global__ void __launch_bounds__(kBlock) k_iota(uint32_t* __restrict__ id, long
 
 // ------------------------------------------------------------- small kernels
 
-__global__ void __launch_bounds__(kBlock)
-k_dot3(const float* __restrict__ a, const float* __restrict__ b, long P, double* partials,
-       const uint32_t* __restrict__ id) {
-    double acc = 0.0;
-    for (long p = (long)blockIdx.x * kBlock + threadIdx.x; p < P; p += (long)gridDim.x * kBlock) {
-        const long q = id ? (long)id[p] : p;
-        acc += (double)a[3 * p] * b[3 * q] + (double)a[3 * p + 1] * b[3 * q + 1] +
-               (double)a[3 * p + 2] * b[3 * q + 2];
-    }
-    double s = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
 __global__ void __launch_bounds__(1024)
-k_reduce(const double* __restrict__ partials, int n, double* __restrict__ sums, int slot) {
+k_reduce(const double* __restrict__ partials, int n, double* __restrict__ sums, Slots slots) {
     __shared__ double red[16];
+    partials += (long)blockIdx.x * n;   // one work-group per set of n partials
     // four independent running sums per thread (a fixed order, so the result
     // repeats bit for bit), so that four loads are in flight instead of one
     double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
@@ -1112,7 +1095,7 @@ k_reduce(const double* __restrict__ partials, int n, double* __restrict__ sums, 
     if (threadIdx.x == 0) {
         double s = 0.0;
         for (int w = 0; w < 16; ++w) s += red[w];
-        sums[slot] = s;
+        sums[slots.slot[blockIdx.x]] = s;
     }
 }
 
@@ -1156,117 +1139,136 @@ __device__ __forceinline__ void ic_fixed(const float s[3], const float* s2, cons
     }
 }
 
+// s at the lattice site jj from three real meshes.
+__device__ __forceinline__ void ic_field(const float* sm, long sStride, long o, float s[3]) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) s[a] = sm[a * sStride + o];
+}
+
+// What k_ic_state writes (lattice order): the fixed-point state and ids, that
+// state as displacement and momentum, or s itself.
+enum IcOutput { kIcFixed = 0, kIcFloat = 1, kIcField = 2 };
+
+template <int OUT>
 __global__ void __launch_bounds__(kBlock)
 k_ic_state(const float* __restrict__ sm, long sStride, long rp, float D0, float G0, Lattice L,
            long P, uint32_t* __restrict__ xq, int32_t* __restrict__ pq, uint32_t* __restrict__ id,
-           float* __restrict__ s_out, const float* __restrict__ s2v, float D2, float G2) {
-    for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
-         p += (long)gridDim.x * kBlock) {
-        int jj[3];
-        lattice_index(p, L.np, jj);
-        const long o = mesh_row(jj[0], jj[1], L.np) * rp + jj[2];
-        float s[3];
+           float* __restrict__ disp, float* __restrict__ mom, const float* __restrict__ s2v,
+           float D2, float G2) {
+    const long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if (p >= P) return;
+    int jj[3];
+    lattice_index(p, L.np, jj);
+    float s[3], s2[3] = {0.f, 0.f, 0.f};
+    ic_field(sm, sStride, mesh_row(jj[0], jj[1], L.np) * rp + jj[2], s);
+    if constexpr (OUT == kIcField) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) s[a] = sm[a * sStride + o];
-        uint32_t x[3];
-        int32_t m[3];
-        ic_fixed(s, s2v ? s2v + 3 * p : nullptr, jj, D0, G0, D2, G2, L, x, m);
+        for (int a = 0; a < 3; ++a) disp[3 * p + a] = s[a];
+        return;
+    }
+    if (s2v) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (xq) xq[3 * p + a] = x[a];
-            if (pq) pq[3 * p + a] = m[a];
-            if (s_out) s_out[3 * p + a] = s[a];
-        }
-        if (id) id[p] = (uint32_t)p;
+        for (int a = 0; a < 3; ++a) s2[a] = s2v[3 * p + a];
+    }
+    uint32_t x[3];
+    int32_t m[3];
+    ic_fixed(s, s2v ? s2 : nullptr, jj, D0, G0, D2, G2, L, x, m);
+    if constexpr (OUT == kIcFixed) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) xq[3 * p + a] = x[a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) pq[3 * p + a] = m[a];
+        id[p] = (uint32_t)p;
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            disp[3 * p + a] = (float)(int32_t)(x[a] - (uint32_t)jj[a] * L.qstep) * L.pos_to_len;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) mom[3 * p + a] = (float)m[a] * L.mom_unit;
     }
 }
 
+// End of the adjoint, one pass over the particles (sorted order) where the
+// check, six dot products and two weighted sums took one each: the
+// reconstructed state against the ICs of lattice particle id[p], the cotangents
+// against s and s2, and their combinations s_bar = D0 xi + G0 pi (over s in the
+// meshes: a site is read and written by its own particle only) and s2_bar = D2 xi
+// + G2 pi ([P][3], lattice order).  Block partials of kIcSums sums (see
+// launch_ic_adjoint), the last three with LPT2 only.
+template <bool LPT2>
 __global__ void __launch_bounds__(kBlock)
-k_ic_check(const float* __restrict__ sm, long sStride, long rp, float D0, float G0, Lattice L,
-           long P, const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
-           const uint32_t* __restrict__ id, double* partials, unsigned* maxbits,
-           const float* __restrict__ s2v, float D2, float G2) {
-    double ax = 0.0, ap = 0.0, aref = 0.0;
+k_ic_adjoint(float* sm, long sStride, long rp, float D0, float G0, Lattice L, long P,
+             const uint32_t* __restrict__ xq, const int32_t* __restrict__ pq,
+             const uint32_t* __restrict__ id, const float* __restrict__ xi,
+             const float* __restrict__ pi, double* __restrict__ partials,
+             unsigned* __restrict__ maxbits, const float* __restrict__ s2v,
+             float* __restrict__ s2_bar, float D2, float G2) {
+    constexpr int NS = LPT2 ? 9 : 6;
+    double sum[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) sum[k] = 0.0;
     float mx = 0.f;
     for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
          p += (long)gridDim.x * kBlock) {
-        // the state is in sorted order: compare with the ICs of lattice particle id[p]
-        int jj[3];
         const long lp = id[p];
+        uint32_t xr[3];
+        int32_t pr[3];
+        float vx[3], vp[3], s[3], s2[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) xr[a] = xq[3 * p + a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) pr[a] = pq[3 * p + a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) vx[a] = xi[3 * p + a];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) vp[a] = pi[3 * p + a];
+        int jj[3];
         lattice_index(lp, L.np, jj);
         const long o = mesh_row(jj[0], jj[1], L.np) * rp + jj[2];
-        float s[3];
+        ic_field(sm, sStride, o, s);
+        if constexpr (LPT2) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) s[a] = sm[a * sStride + o];
+            for (int a = 0; a < 3; ++a) s2[a] = s2v[3 * lp + a];
+        }
         uint32_t x[3];
         int32_t m[3];
-        ic_fixed(s, s2v ? s2v + 3 * lp : nullptr, jj, D0, G0, D2, G2, L, x, m);
-        float d2 = 0.f;
+        ic_fixed(s, LPT2 ? s2 : nullptr, jj, D0, G0, D2, G2, L, x, m);
+        float d2 = 0.f, b[3], b2[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const float d = (float)(int32_t)(xq[3 * p + a] - x[a]) * L.frac;
+            const float d = (float)(int32_t)(xr[a] - x[a]) * L.frac;
             d2 += d * d;
-            const double dp = (double)pq[3 * p + a] - m[a];
-            ap += dp * dp;
-            aref += (double)m[a] * m[a];
+            const double dp = (double)pr[a] - m[a];
+            sum[1] += dp * dp;
+            sum[2] += (double)m[a] * m[a];
+            b[a] = D0 * vx[a] + G0 * vp[a];
+            sum[3] += (double)vx[a] * s[a];
+            sum[4] += (double)vp[a] * s[a];
+            sum[5] += (double)b[a] * s[a];
+            sm[a * sStride + o] = b[a];
+            if constexpr (LPT2) {
+                b2[a] = D2 * vx[a] + G2 * vp[a];
+                sum[6] += (double)vx[a] * s2[a];
+                sum[7] += (double)vp[a] * s2[a];
+                sum[8] += (double)b2[a] * s2[a];
+            }
         }
-        ax += d2;
+        if constexpr (LPT2) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) s2_bar[3 * lp + a] = b2[a];
+        }
+        sum[0] += d2;
         mx = fmaxf(mx, sqrtf(d2));
     }
-    double s0 = block_sum(ax), s1 = block_sum(ap), s2 = block_sum(aref);
-    if (threadIdx.x == 0) {
-        partials[blockIdx.x] = s0;
-        partials[gridDim.x + blockIdx.x] = s1;
-        partials[2 * gridDim.x + blockIdx.x] = s2;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const double t = block_sum(sum[k]);
+        if (threadIdx.x == 0) partials[(long)k * gridDim.x + blockIdx.x] = t;
     }
     block_max_to(mx, maxbits);
 }
 
 // ------------------------------------------------ 2LPT initial conditions
-
-// Spectral multiplier on a half spectrum [n][n][cs] (workspace row order) with
-// integer wave numbers nv = (n0, n1, n2) and m2 = |n|^2, R = table[m2] (or
-// 1/m2 without a table):
-//   mode 0  nv[a] nv[b] R          (a != b: 0 on the Nyquist plane of a or b)
-//   mode 1  (m2 - nv[a]^2) R       (sum of the two other diagonal entries)
-//   mode 2  m2 table[m2]
-// times scale, 0 at m2 = 0.  dst = w src, or dst += w src when accumulate.
-__global__ void __launch_bounds__(kBlock)
-k_lpt_mul(const float2* __restrict__ src, float2* __restrict__ dst, int n, int cs, int ax_a,
-          int ax_b, int mode, const float* __restrict__ table, float scale, int accumulate) {
-    const int h = n / 2 + 1;
-    const long N = (long)n * n * h;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < N; i += (long)gridDim.x * kBlock) {
-        const int k2 = (int)(i % h);
-        const long row = i / h;
-        const int i1 = (int)(row % n), i0 = (int)(row / n);
-        const int nv[3] = {i0 < n / 2 ? i0 : i0 - n, i1 < n / 2 ? i1 : i1 - n, k2};
-        const bool nyq[3] = {i0 == n / 2, i1 == n / 2, k2 == n / 2};
-        const int m2 = nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2];
-        float w = 0.f;
-        if (m2 > 0) {
-            const float r = table ? table[m2] : 1.f / (float)m2;
-            if (mode == 0)
-                w = (ax_a != ax_b && (nyq[ax_a] || nyq[ax_b])) ? 0.f
-                                                               : (float)(nv[ax_a] * nv[ax_b]) * r;
-            else if (mode == 1)
-                w = (float)(m2 - nv[ax_a] * nv[ax_a]) * r;
-            else
-                w = (float)m2 * r;
-            w *= scale;
-        }
-        const long o = mesh_row(i0, i1, n) * cs + k2;
-        float2 v = src[o];
-        v.x *= w;
-        v.y *= w;
-        if (accumulate) {
-            const float2 d = dst[o];
-            v.x += d.x;
-            v.y += d.y;
-        }
-        dst[o] = v;
-    }
-}
 
 // Pointwise ops on real meshes of one layout (n^2 rows of pitch rp):
 //   op 0  out = a b + a c + b c
@@ -1327,23 +1329,6 @@ k_deinterleave(const float* __restrict__ v, float* __restrict__ dst, long dstStr
         const long o = mesh_row((int)(row / np), (int)(row % np), np) * rp + (p % np);
 #pragma unroll
         for (int a = 0; a < 3; ++a) dst[a * dstStride + o] = v[3 * p + a];
-    }
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_axpby(float* __restrict__ out, const float* __restrict__ x, float a, const float* __restrict__ y,
-        float b, long n) {
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long)gridDim.x * kBlock)
-        out[i] = y ? a * x[i] + b * y[i] : a * x[i];
-}
-
-__global__ void __launch_bounds__(kBlock)
-k_axpby_scatter(float* __restrict__ out, const float* __restrict__ x, float a,
-                const float* __restrict__ y, float b, const uint32_t* __restrict__ id, long P) {
-    for (long p = (long)blockIdx.x * kBlock + threadIdx.x; p < P; p += (long)gridDim.x * kBlock) {
-        const long q = id[p];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) out[3 * q + k] = a * x[3 * p + k] + b * y[3 * p + k];
     }
 }
 
@@ -1634,11 +1619,12 @@ void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi,
                        b.tile, b.counts, b.keys, b.ranks, partials);
 }
 
-void launch_from_fixed(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
-                       const Lattice& L, float* disp, float* mom, hipStream_t s) {
+void launch_final_state(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
+                        const Lattice& L, uint32_t* xo, int32_t* po, float* disp, float* mom,
+                        hipStream_t s) {
     const long P = (long)L.np * L.np * L.np;
-    hipLaunchKernelGGL(k_from_fixed, dim3(grid_for(P)), dim3(kBlock), 0, s, xq, pq, id, L, P, disp,
-                       mom);
+    hipLaunchKernelGGL(k_final_state, dim3(grid_for(P)), dim3(kBlock), 0, s, xq, pq, id, L, P, xo,
+                       po, disp, mom);
 }
 
 void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long P,
@@ -1646,23 +1632,19 @@ void launch_permute_by_id(const float* in, const uint32_t* id, float* out, long 
     hipLaunchKernelGGL(k_permute_by_id, dim3(grid_for(P)), dim3(kBlock), 0, s, in, id, out, P);
 }
 
-void launch_state_to_lattice(const uint32_t* xq, const int32_t* pq, const uint32_t* id, long P,
-                             uint32_t* xq_out, int32_t* pq_out, hipStream_t s) {
-    hipLaunchKernelGGL(k_state_to_lattice, dim3(grid_for(P)), dim3(kBlock), 0, s, xq, pq, id, P,
-                       xq_out, pq_out);
-}
-
 void launch_iota(uint32_t* id, long P, hipStream_t s) {
     hipLaunchKernelGGL(k_iota, dim3(grid_for(P)), dim3(kBlock), 0, s, id, P);
 }
 
-void launch_dot3(const float* a, const float* b, long P, double* partials, int nblocks,
-                 hipStream_t s, const uint32_t* id) {
-    hipLaunchKernelGGL(k_dot3, dim3(nblocks), dim3(kBlock), 0, s, a, b, P, partials, id);
+void launch_reduce(const double* partials, int nblocks, double* sums, int slot, hipStream_t s) {
+    Slots one{};
+    one.slot[0] = slot;
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, nblocks, sums, one);
 }
 
-void launch_reduce(const double* partials, int nblocks, double* sums, int slot, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, nblocks, sums, slot);
+void launch_reduce_sets(const double* partials, int nblocks, int nsets, double* sums,
+                        const Slots& slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce, dim3(nsets), dim3(1024), 0, s, partials, nblocks, sums, slots);
 }
 
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,
@@ -1673,27 +1655,37 @@ void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, 
 }
 
 void launch_ic_state(const float* smesh, long sStride, long rp, float D0, float G0,
-                     const Lattice& L, uint32_t* xq, int32_t* pq, uint32_t* id, float* s_out,
-                     hipStream_t s, const float* s2v, float D2, float G2) {
-    const long P = (long)L.np * L.np * L.np;
-    hipLaunchKernelGGL(k_ic_state, dim3(grid_for(P)), dim3(kBlock), 0, s, smesh, sStride, rp, D0,
-                       G0, L, P, xq, pq, id, s_out, s2v, D2, G2);
-}
-
-void launch_ic_check(const float* smesh, long sStride, long rp, float D0, float G0,
-                     const Lattice& L, const uint32_t* xq, const int32_t* pq, const uint32_t* id,
-                     double* partials, int nblocks, unsigned* maxbits, hipStream_t s,
+                     const Lattice& L, uint32_t* xq, int32_t* pq, uint32_t* id, hipStream_t s,
                      const float* s2v, float D2, float G2) {
     const long P = (long)L.np * L.np * L.np;
-    hipLaunchKernelGGL(k_ic_check, dim3(nblocks), dim3(kBlock), 0, s, smesh, sStride, rp, D0, G0,
-                       L, P, xq, pq, id, partials, maxbits, s2v, D2, G2);
+    hipLaunchKernelGGL(k_ic_state<kIcFixed>, dim3(grid_for(P)), dim3(kBlock), 0, s, smesh, sStride,
+                       rp, D0, G0, L, P, xq, pq, id, nullptr, nullptr, s2v, D2, G2);
 }
 
-void launch_lpt_mul(const float2* src, float2* dst, int n, int cs, int ax_a, int ax_b, int mode,
-                    const float* table, float scale, bool accumulate, hipStream_t s) {
-    const long N = (long)n * n * (n / 2 + 1);
-    hipLaunchKernelGGL(k_lpt_mul, dim3(grid_for(N)), dim3(kBlock), 0, s, src, dst, n, cs, ax_a,
-                       ax_b, mode, table, scale, accumulate ? 1 : 0);
+void launch_ic_float(const float* smesh, long sStride, long rp, float D0, float G0,
+                     const Lattice& L, float* disp, float* mom, hipStream_t s, const float* s2v,
+                     float D2, float G2) {
+    const long P = (long)L.np * L.np * L.np;
+    hipLaunchKernelGGL(k_ic_state<kIcFloat>, dim3(grid_for(P)), dim3(kBlock), 0, s, smesh, sStride,
+                       rp, D0, G0, L, P, nullptr, nullptr, nullptr, disp, mom, s2v, D2, G2);
+}
+
+void launch_ic_field(const float* smesh, long sStride, long rp, const Lattice& L, float* out,
+                     hipStream_t s) {
+    const long P = (long)L.np * L.np * L.np;
+    hipLaunchKernelGGL(k_ic_state<kIcField>, dim3(grid_for(P)), dim3(kBlock), 0, s, smesh, sStride,
+                       rp, 0.f, 0.f, L, P, nullptr, nullptr, nullptr, out, nullptr, nullptr, 0.f,
+                       0.f);
+}
+
+void launch_ic_adjoint(float* smesh, long sStride, long rp, float D0, float G0, const Lattice& L,
+                       const uint32_t* xq, const int32_t* pq, const uint32_t* id, const float* xi,
+                       const float* pi, double* partials, int nblocks, unsigned* maxbits,
+                       hipStream_t s, const float* s2v, float* s2_bar, float D2, float G2) {
+    const long P = (long)L.np * L.np * L.np;
+    auto k = s2v ? k_ic_adjoint<true> : k_ic_adjoint<false>;
+    hipLaunchKernelGGL(k, dim3(nblocks), dim3(kBlock), 0, s, smesh, sStride, rp, D0, G0, L, P, xq,
+                       pq, id, xi, pi, partials, maxbits, s2v, s2_bar, D2, G2);
 }
 
 void launch_lpt_pointwise(const float* a, const float* b, const float* c, float* out, int n,
@@ -1720,16 +1712,6 @@ void launch_deinterleave(const float* v, float* dst, long dstStride, int np, lon
     const long P = (long)np * np * np;
     hipLaunchKernelGGL(k_deinterleave, dim3(grid_for(P)), dim3(kBlock), 0, s, v, dst, dstStride, np,
                        rp);
-}
-
-void launch_axpby(float* out, const float* x, float a, const float* y, float b, long n,
-                  hipStream_t s) {
-    hipLaunchKernelGGL(k_axpby, dim3(grid_for(n)), dim3(kBlock), 0, s, out, x, a, y, b, n);
-}
-
-void launch_axpby_scatter(float* out, const float* x, float a, const float* y, float b,
-                          const uint32_t* id, long P, hipStream_t s) {
-    hipLaunchKernelGGL(k_axpby_scatter, dim3(grid_for(P)), dim3(kBlock), 0, s, out, x, a, y, b, id, P);
 }
 
 void launch_mse(const float* d, const float* t, float* g, long n3, double* partials,

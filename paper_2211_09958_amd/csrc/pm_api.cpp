@@ -102,7 +102,7 @@ int n_checkpoints(const pm_config& c) {
 // Workspace plan: byte offsets of every buffer, 256-byte aligned.
 struct Plan {
     size_t total = 0;
-    size_t cplx, disp, mom, xi, pi, disp2, mom2, xi2, pi2, id, id2, fin_disp, fin_mom, s_ic, tmpv,
+    size_t cplx, disp, mom, xi, pi, disp2, mom2, xi2, pi2, id, id2, fin_disp, fin_mom, tmpv,
         noise, ckpt;
     size_t counts, offsets, keys, ranks, ord, scan_tmp;
     size_t radial_f, radial_ic, radial_ic_dom, radial_lpt, losstab, tw, tw_stages, partials, sums, maxbits,
@@ -144,7 +144,6 @@ struct Plan {
         id2 = take((size_t)P * sizeof(uint32_t));
         fin_disp = take(vec);
         fin_mom = take(vec);
-        s_ic = take(vec);
         tmpv = take(vec);
         noise = take((size_t)P * sizeof(float));
         ckpt = take((size_t)nckpt * 2 * vec);
@@ -204,7 +203,7 @@ struct pm_ctx {
     float *xi, *xi_alt, *pi, *pi_alt;
     uint32_t *fin_x, *ckpt;        // final state and checkpoints, lattice order
     int32_t* fin_p;
-    float *s_ic, *tmpv, *noise;
+    float *tmpv, *noise;
     float *radial_f, *radial_ic, *radial_ic_dom, *radial_lpt, *theta, *gtheta, *fbar, *mlp_scratch;
     float* losstab;                    // targets, loss and shell factors of pm_loss_pk
     std::vector<double> loss_target;   // the targets, kept alive across their async upload
@@ -482,14 +481,14 @@ void compute_force(pm_ctx* ctx, double a, Particles which) {
     }
     { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_r2c(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
-      launch_fft_axis(ctx->C[0], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
+      launch_fft_y(ctx->C[0], ng, cs, -1, 1, cst, ctx->twd, s); }
     { KTimer t(ctx, PM_K_MLP, 0); radial = force_radial(ctx, a); }
     // F~_0 -> C1 and G -> C2; axis 1: F~_0 in place, G -> F~_1 (C2) and IFFT_1(G)
     // (C3); last axis: C2R of the three, C3 times i k2 first (= F~_2)
     { KTimer t(ctx, PM_K_GRAD_Z, 3 * c);
       launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[2], ng, cs, radial, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 5 * c);
-      launch_fft_axis(ctx->C[1], ng, cs, 1, 1, 1, cst, ctx->twd, s);
+      launch_fft_y(ctx->C[1], ng, cs, 1, 1, cst, ctx->twd, s);
       launch_fft_y_split(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_X, 3 * (r + c));
       launch_fft_x_c2r_dk2(ctx->C[1], ng, cs, 3, cst, 2, ctx->twd, s); }
@@ -514,7 +513,7 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
         { KTimer t(ctx, PM_K_FFT_X, 3 * (r + c));
           launch_fft_x_r2c(ctx->C[1], ng, cs, 3, cst, ctx->twd, s); }
         { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
-          launch_fft_axis(ctx->C[1], ng, cs, 1, -1, 1, cst, ctx->twd, s); }
+          launch_fft_y(ctx->C[1], ng, cs, -1, 1, cst, ctx->twd, s); }
         { KTimer t(ctx, PM_K_FFT_STRIDED, 3 * c);
           launch_fft_y_merge(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
     }
@@ -535,7 +534,7 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
         launch_fft_yx_c2r(ctx->C[0], nullptr, ng, cs, 1, cst, ctx->twd, s);
     } else {
         { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
-          launch_fft_axis(ctx->C[0], ng, cs, 1, 1, 1, cst, ctx->twd, s); }
+          launch_fft_y(ctx->C[0], ng, cs, 1, 1, cst, ctx->twd, s); }
         { KTimer t(ctx, PM_K_FFT_X, r + c);
           launch_fft_x_c2r(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
     }
@@ -559,50 +558,42 @@ void grad_synthesis(pm_ctx* ctx, const float* radial, const float* field = nullp
         return;
     }
     launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[2], np, cs, radial, ctx->twd, s);
-    launch_fft_axis(ctx->C[1], np, cs, 1, 1, 1, cst, ctx->twd, s);
+    launch_fft_y(ctx->C[1], np, cs, 1, 1, cst, ctx->twd, s);
     launch_fft_y_split(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
     launch_fft_x_c2r_dk2(ctx->C[1], np, cs, 3, cst, 2, ctx->twd, s);
 }
 
 // Transpose of grad_synthesis: the real mesh Sum_j IDFT(conj(i n_j radial)
-// DFT(v_j)) of v [P][3] (lattice order) in C0, or in the dense array `out`.
-void grad_transpose(pm_ctx* ctx, const float* v, const float* radial, float* out = nullptr) {
+// DFT(v_j)) of v [P][3] (lattice order; nullptr: of the real meshes in C1..C3) in
+// C0, or in the dense array `out`.  With radial2 the same transpose with that
+// table, from the same forward transforms, in C3.
+void grad_transpose(pm_ctx* ctx, const float* v, const float* radial, float* out = nullptr,
+                    const float* radial2 = nullptr) {
     hipStream_t s = ctx->stream;
     const int np = ctx->np, cs = ctx->cs_p;
     const long cst = ctx->plan.cplx_elems;
     const long rp = 2L * cs;
-    launch_deinterleave(v, ctx->creal(1), ctx->creal_stride(), np, rp, s);
+    if (v) launch_deinterleave(v, ctx->creal(1), ctx->creal_stride(), np, rp, s);
     if (np <= kMaxPlane) {
         launch_plane_r2c_merge(ctx->C[1], np, cs, cst, ctx->twd, s);
     } else {
         launch_fft_x_r2c(ctx->C[1], np, cs, 3, cst, ctx->twd, s);
-        launch_fft_axis(ctx->C[1], np, cs, 1, -1, 1, cst, ctx->twd, s);
+        launch_fft_y(ctx->C[1], np, cs, -1, 1, cst, ctx->twd, s);
         launch_fft_y_merge(ctx->C[2], ctx->C[3], np, cs, ctx->twd, s);
     }
-    launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], np, cs, radial, nullptr, nullptr, 0.f,
-                      ctx->twd, s);
-    launch_fft_yx_c2r(ctx->C[0], out, np, cs, 1, cst, ctx->twd, s);
+    for (const float* r : {radial, radial2}) {
+        if (!r) continue;
+        float2* dst = r == radial ? ctx->C[0] : ctx->C[3];
+        launch_grad_adj_z(ctx->C[1], cst, dst, dst, np, cs, r, nullptr, nullptr, 0.f, ctx->twd, s);
+        launch_fft_yx_c2r(dst, r == radial ? out : nullptr, np, cs, 1, cst, ctx->twd, s);
+    }
 }
 
 // Zel'dovich displacement (a = 1) of white noise `noise` [Np^3] with the radial
-// table; leaves s_j as real meshes in C1..C3 (particle-grid geometry) and writes
-// s_out [P][3] and the fixed-point state x = q + D0 s, p = G0 s (each nullable).
-// With s2v ([P][3] lattice order, 2LPT) the state adds D2 s2 and G2 s2.
-void ic_synthesis(pm_ctx* ctx, const float* noise, const float* radial, float* s_out,
-                  uint32_t* xq, int32_t* pq, uint32_t* id, const float* s2v = nullptr) {
-    hipStream_t s = ctx->stream;
-    const long rp = 2L * ctx->cs_p;
+// table: s_j as real meshes in C1..C3 (particle-grid geometry).
+void ic_synthesis(pm_ctx* ctx, const float* noise) {
     KTimer t(ctx, PM_K_OTHER, 0);
-    grad_synthesis(ctx, radial, noise);
-    launch_ic_state(ctx->creal(1), ctx->creal_stride(), rp, (float)ctx->sched.D0,
-                    (float)ctx->sched.G0, ctx->lat, xq, pq, id, s_out, s, s2v,
-                    (float)ctx->sched.D20, (float)ctx->sched.G20);
-}
-
-// dL/dnoise = transpose of the Zel'dovich synthesis applied to s_bar [P][3].
-void ic_transpose(pm_ctx* ctx, const float* s_bar, float* g_noise) {
-    KTimer t(ctx, PM_K_OTHER, 0);
-    grad_transpose(ctx, s_bar, ctx->radial_ic, g_noise);
+    grad_synthesis(ctx, ctx->radial_ic, noise);
 }
 
 // The six Hessian entries (a, b), a <= b, of the potential of the linear density.
@@ -623,20 +614,23 @@ void lpt_second_order(pm_ctx* ctx, const float* noise, float* s2_out) {
     float *r0 = ctx->creal(0), *r1 = ctx->creal(1), *r2 = ctx->creal(2), *r3 = ctx->creal(3);
     KTimer t(ctx, PM_K_OTHER, 0);
     launch_fft3_r2c_dense(noise, ctx->C[0], nullptr, np, cs, ctx->twd, s);
-    for (int a = 0; a < 3; ++a)
-        launch_lpt_mul(ctx->C[0], ctx->C[1 + a], np, cs, a, a, 0, ctx->radial_ic, kf, false, s);
-    launch_fft3_c2r(ctx->C[1], np, cs, 3, cst, ctx->twd, s);
+    // phi_ab's spectrum transformed back along axis 0, to buffer k
+    auto hessian = [&](int k, int a, int b) {
+        launch_fft_z_mul(ctx->C[0], ctx->C[k], np, cs, 1, a, b, 0, ctx->radial_ic, kf, false,
+                         ctx->twd, s);
+    };
+    for (int a = 0; a < 3; ++a) hessian(1 + a, a, a);
+    launch_fft_yx_c2r(ctx->C[1], nullptr, np, cs, 3, cst, ctx->twd, s);
     launch_lpt_pointwise(r1, r2, r3, r1, np, rp, 0, 1.f, s);
-    launch_lpt_mul(ctx->C[0], ctx->C[2], np, cs, 0, 1, 0, ctx->radial_ic, kf, false, s);
-    launch_lpt_mul(ctx->C[0], ctx->C[3], np, cs, 0, 2, 0, ctx->radial_ic, kf, false, s);
-    launch_fft3_c2r(ctx->C[2], np, cs, 2, cst, ctx->twd, s);
+    hessian(2, 0, 1);
+    hessian(3, 0, 2);
+    launch_fft_yx_c2r(ctx->C[2], nullptr, np, cs, 2, cst, ctx->twd, s);
     launch_lpt_pointwise(r1, r2, r3, r1, np, rp, 1, 1.f, s);
-    launch_lpt_mul(ctx->C[0], ctx->C[2], np, cs, 1, 2, 0, ctx->radial_ic, kf, false, s);
-    launch_fft3_c2r(ctx->C[2], np, cs, 1, cst, ctx->twd, s);
+    hessian(2, 1, 2);
+    launch_fft_yx_c2r(ctx->C[2], nullptr, np, cs, 1, cst, ctx->twd, s);
     launch_lpt_pointwise(r1, r2, nullptr, r0, np, rp, 1, 1.f, s);   // S in C0
     grad_synthesis(ctx, ctx->radial_lpt);
-    launch_ic_state(r1, ctx->creal_stride(), rp, 0.f, 0.f, ctx->lat, nullptr, nullptr, nullptr,
-                    s2_out, s);
+    launch_ic_field(r1, ctx->creal_stride(), rp, ctx->lat, s2_out, s);
 }
 
 // Transpose of lpt_second_order at `noise`: g_noise [Np^3] += its transpose
@@ -661,21 +655,24 @@ int lpt_second_order_transpose(pm_ctx* ctx, const float* noise, const float* s2_
     // C1 = Sum_ab (n_a n_b / |n|^2) DFT(phi_ab_bar)
     for (int k = 0; k < 6; ++k) {
         const int a = kPairs[k][0], b = kPairs[k][1];
-        launch_lpt_mul(ctx->C[0], ctx->C[2], np, cs, a, b, a == b ? 1 : 0, ctx->radial_ic, kf,
-                       false, s);
-        launch_fft3_c2r(ctx->C[2], np, cs, 1, cst, ctx->twd, s);
+        launch_fft_z_mul(ctx->C[0], ctx->C[2], np, cs, 1, a, b, a == b ? 1 : 0, ctx->radial_ic, kf,
+                         false, ctx->twd, s);
+        launch_fft_yx_c2r(ctx->C[2], nullptr, np, cs, 1, cst, ctx->twd, s);
         launch_lpt_pointwise(r2, r3, nullptr, r2, np, rp, 2, a == b ? 1.f : -2.f, s);
-        launch_fft3_r2c(ctx->C[2], np, cs, 1, cst, ctx->twd, s);
-        launch_lpt_mul(ctx->C[2], ctx->C[1], np, cs, a, b, 0, nullptr, 1.f, k > 0, s);
+        launch_fft_xy_r2c(nullptr, ctx->C[2], np, cs, 1, cst, ctx->twd, s);
+        launch_fft_z_mul(ctx->C[2], ctx->C[1], np, cs, -1, a, b, 0, nullptr, 1.f, k > 0, ctx->twd,
+                         s);
     }
     // Omega_m: < IDFT(d sqrt(P/V_c)/dOmega_m C1), noise >
-    launch_lpt_mul(ctx->C[1], ctx->C[2], np, cs, 0, 0, 2, ctx->radial_ic_dom, kf, false, s);
-    launch_fft3_c2r(ctx->C[2], np, cs, 1, cst, ctx->twd, s);
+    launch_fft_z_mul(ctx->C[1], ctx->C[2], np, cs, 1, 0, 0, 2, ctx->radial_ic_dom, kf, false,
+                     ctx->twd, s);
+    launch_fft_yx_c2r(ctx->C[2], nullptr, np, cs, 1, cst, ctx->twd, s);
     launch_dot_pitched(r2, noise, np, rp, ctx->partials, nb, s);
     launch_reduce(ctx->partials, nb, ctx->sums, slot, s);
     // noise: IDFT(sqrt(P/V_c) C1)
-    launch_lpt_mul(ctx->C[1], ctx->C[2], np, cs, 0, 0, 2, ctx->radial_ic, kf, false, s);
-    launch_fft3_c2r(ctx->C[2], np, cs, 1, cst, ctx->twd, s);
+    launch_fft_z_mul(ctx->C[1], ctx->C[2], np, cs, 1, 0, 0, 2, ctx->radial_ic, kf, false, ctx->twd,
+                     s);
+    launch_fft_yx_c2r(ctx->C[2], nullptr, np, cs, 1, cst, ctx->twd, s);
     launch_add_from_pitched(r2, g_noise, np, rp, 1.f, s);
     return PM_OK;
 }
@@ -830,7 +827,6 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
     ctx->id_alt = ctx->at<uint32_t>(p.id2);
     ctx->fin_x = ctx->at<uint32_t>(p.fin_disp);
     ctx->fin_p = ctx->at<int32_t>(p.fin_mom);
-    ctx->s_ic = ctx->at<float>(p.s_ic);
     ctx->tmpv = ctx->at<float>(p.tmpv);
     ctx->noise = ctx->at<float>(p.noise);
     ctx->ckpt = ctx->at<uint32_t>(p.ckpt);
@@ -972,8 +968,13 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
     PM_TRY(copy_d2d(ctx, ctx->noise, noise, (size_t)ctx->P * sizeof(float)));
     launch_zero(ctx->ovf, sizeof(unsigned), s);
     if (ctx->lpt2()) lpt_second_order(ctx, ctx->noise, ctx->tmpv);
-    ic_synthesis(ctx, ctx->noise, ctx->radial_ic, ctx->s_ic, ctx->xq, ctx->pq, ctx->id,
-                 ctx->lpt2() ? ctx->tmpv : nullptr);
+    ic_synthesis(ctx, ctx->noise);
+    {
+        KTimer t(ctx, PM_K_OTHER, 0);
+        launch_ic_state(ctx->creal(1), ctx->creal_stride(), 2L * ctx->cs_p, (float)sc.D0,
+                        (float)sc.G0, ctx->lat, ctx->xq, ctx->pq, ctx->id, s,
+                        ctx->lpt2() ? ctx->tmpv : nullptr, (float)sc.D20, (float)sc.G20);
+    }
     records_in_lattice_order(ctx);
     for (int n = 0; n <= N; ++n) {
         compute_force(ctx, sc.a[n], kState);
@@ -998,8 +999,8 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
     {
         KTimer t(ctx, PM_K_OTHER, 0);
         // final state in lattice order (private copy for the adjoint) and outputs
-        launch_state_to_lattice(ctx->xq, ctx->pq, ctx->id, ctx->P, ctx->fin_x, ctx->fin_p, s);
-        launch_from_fixed(ctx->xq, ctx->pq, ctx->id, ctx->lat, disp_out, mom_out, s);
+        launch_final_state(ctx->xq, ctx->pq, ctx->id, ctx->lat, ctx->fin_x, ctx->fin_p, disp_out,
+                           mom_out, s);
         if (dens) {
             sort_particles(ctx, false);
             launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, nullptr, dens, s);
@@ -1025,6 +1026,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     const size_t vec = (size_t)P * 3 * sizeof(float);
     // grid-stride reductions over the particles: block partials + one max per block
     const int nb = std::min(particle_blocks(P), 4096);
+    const int nb_ic = std::min(nb, 1024);   // nine sets of partials
     const int slotS = 0, slotD = N + 1, slotX = 2 * N + 1;   // S_m, D_n, extras
     const int xD0 = slotX, xG0 = slotX + 1, xSig = slotX + 2, xOm = slotX + 3,
               xIc = slotX + 4, xIcMom = slotX + 5, xIcMomRef = slotX + 6, xCk = slotX + 8,
@@ -1124,45 +1126,26 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     // ICs: x_0 = q + D0 s (+ D20 s2), p_0 = G0 s (+ G20 s2).  Reconstruction
     // check against the ICs.  2LPT: s2 in pi_alt (lattice order; free here).
     if (lpt2) lpt_second_order(ctx, ctx->noise, ctx->pi_alt);
-    ic_synthesis(ctx, ctx->noise, ctx->radial_ic, ctx->s_ic, nullptr, nullptr, nullptr);
+    ic_synthesis(ctx, ctx->noise);
     {
         KTimer t(ctx, PM_K_OTHER, 0);
-        launch_ic_check(ctx->creal(1), ctx->creal_stride(), 2L * ctx->cs_p, (float)sc.D0,
-                        (float)sc.G0, ctx->lat, ctx->xq, ctx->pq, ctx->id, ctx->partials, nb,
-                        ctx->maxbits, s, lpt2 ? ctx->pi_alt : nullptr, (float)sc.D20,
-                        (float)sc.G20);
-        launch_reduce(ctx->partials, nb, ctx->sums, xIc, s);
-        launch_reduce(ctx->partials + nb, nb, ctx->sums, xIcMom, s);
-        launch_reduce(ctx->partials + 2 * nb, nb, ctx->sums, xIcMomRef, s);
-        launch_dot3(ctx->xi, ctx->s_ic, P, ctx->partials, nb, s, ctx->id);
-        launch_reduce(ctx->partials, nb, ctx->sums, xD0, s);
-        launch_dot3(ctx->pi, ctx->s_ic, P, ctx->partials, nb, s, ctx->id);
-        launch_reduce(ctx->partials, nb, ctx->sums, xG0, s);
-        // s_bar = D0 xi + G0 pi, in lattice order
-        launch_axpby_scatter(ctx->tmpv, ctx->xi, (float)sc.D0, ctx->pi, (float)sc.G0, ctx->id, P, s);
-        launch_dot3(ctx->tmpv, ctx->s_ic, P, ctx->partials, nb, s);
-        launch_reduce(ctx->partials, nb, ctx->sums, xSig, s);
-        if (lpt2) {
-            launch_dot3(ctx->xi, ctx->pi_alt, P, ctx->partials, nb, s, ctx->id);
-            launch_reduce(ctx->partials, nb, ctx->sums, xD20, s);
-            launch_dot3(ctx->pi, ctx->pi_alt, P, ctx->partials, nb, s, ctx->id);
-            launch_reduce(ctx->partials, nb, ctx->sums, xG20, s);
-            // s2_bar = D20 xi + G20 pi, in lattice order
-            launch_axpby_scatter(ctx->xi_alt, ctx->xi, (float)sc.D20, ctx->pi, (float)sc.G20,
-                                 ctx->id, P, s);
-            launch_dot3(ctx->xi_alt, ctx->pi_alt, P, ctx->partials, nb, s);
-            launch_reduce(ctx->partials, nb, ctx->sums, xSig2, s);
-        }
-    }
-    ic_transpose(ctx, ctx->tmpv, g_noise);
-    if (lpt2) PM_TRY(lpt_second_order_transpose(ctx, ctx->noise, ctx->xi_alt, g_noise, xOm2, nb));
-    // Omega_m dependence of P(k): s' = synthesis with d radial / d Omega_m
-    ic_synthesis(ctx, ctx->noise, ctx->radial_ic_dom, ctx->xi_alt, nullptr, nullptr, nullptr);
-    {
-        KTimer t(ctx, PM_K_OTHER, 0);
-        launch_dot3(ctx->tmpv, ctx->xi_alt, P, ctx->partials, nb, s);
+        // checks and scalar sums; s_bar = D0 xi + G0 pi over s in C1..C3, and s2_bar =
+        // D20 xi + G20 pi in xi_alt (lattice order)
+        const int nsets = lpt2 ? 9 : 6;
+        const Slots slots{{xIc, xIcMom, xIcMomRef, xD0, xG0, xSig, xD20, xG20, xSig2}};
+        launch_ic_adjoint(ctx->creal(1), ctx->creal_stride(), 2L * ctx->cs_p, (float)sc.D0,
+                          (float)sc.G0, ctx->lat, ctx->xq, ctx->pq, ctx->id, ctx->xi, ctx->pi,
+                          ctx->partials, nb_ic, ctx->maxbits, s, lpt2 ? ctx->pi_alt : nullptr,
+                          lpt2 ? ctx->xi_alt : nullptr, (float)sc.D20, (float)sc.G20);
+        launch_reduce_sets(ctx->partials, nb_ic, nsets, ctx->sums, slots, s);
+        // dL/dnoise = transpose of the synthesis applied to s_bar; and, with the
+        // Omega_m derivative of its table, the field whose product with the noise is
+        // <s_bar, ds/dOmega_m> (the synthesis is linear in the noise)
+        grad_transpose(ctx, nullptr, ctx->radial_ic, g_noise, ctx->radial_ic_dom);
+        launch_dot_pitched(ctx->creal(3), ctx->noise, ctx->np, 2L * ctx->cs_p, ctx->partials, nb, s);
         launch_reduce(ctx->partials, nb, ctx->sums, xOm, s);
     }
+    if (lpt2) PM_TRY(lpt_second_order_transpose(ctx, ctx->noise, ctx->xi_alt, g_noise, xOm2, nb));
     if (g_filter) PM_TRY(copy_d2d(ctx, g_filter, ctx->gtheta, kNParam * sizeof(float)));
     (void)hipEventRecord(ctx->ev[3], s);
     PM_TRY(ctx->hip_check("pm_adjoint"));
@@ -1222,12 +1205,13 @@ int pm_initial_conditions(pm_ctx* ctx, const float* noise, float* disp_out, floa
     PM_TRY(ctx_check(ctx));
     if (!noise || !disp_out || !mom_out) return ctx->fail(PM_EINVAL, "noise, disp and mom are required");
     if (ctx->lpt2()) lpt_second_order(ctx, noise, ctx->tmpv);
-    ic_synthesis(ctx, noise, ctx->radial_ic, ctx->s_ic, ctx->xq, ctx->pq, ctx->id,
-                 ctx->lpt2() ? ctx->tmpv : nullptr);
-    records_in_lattice_order(ctx);
+    ic_synthesis(ctx, noise);
     {
         KTimer t(ctx, PM_K_OTHER, 0);
-        launch_from_fixed(ctx->xq, ctx->pq, ctx->id, ctx->lat, disp_out, mom_out, ctx->stream);
+        const Schedule& sc = ctx->sched;
+        launch_ic_float(ctx->creal(1), ctx->creal_stride(), 2L * ctx->cs_p, (float)sc.D0,
+                        (float)sc.G0, ctx->lat, disp_out, mom_out, ctx->stream,
+                        ctx->lpt2() ? ctx->tmpv : nullptr, (float)sc.D20, (float)sc.G20);
     }
     return ctx->hip_check("pm_initial_conditions");
 }
