@@ -458,16 +458,17 @@ void count_next_bins(pm_ctx* ctx) { launch_bin_zero(ctx->bins, ctx->stream); }
 enum Particles { kState, kStateCotangents, kOnce };
 
 // PM force meshes of the working particles: sort into bins, delta -> C0
-// (x,y-transformed spectrum left in C0), F~_j real meshes in C1..C3.
-void compute_force(pm_ctx* ctx, double a, Particles which) {
+// (x,y-transformed spectrum left in C0) and, when given, to the caller's plain
+// array `dens` in the same write-out, F~_j real meshes in C1..C3.
+void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
     const double r = mesh_r(ng), c = mesh_c(ng), P = (double)ctx->P;
     { KTimer t(ctx, PM_K_BIN, 0);
       t.bytes = which == kOnce ? order_once(ctx) : sort_particles(ctx, which == kStateCotangents); }
-    { KTimer t(ctx, PM_K_SCATTER, 12 * P + r);
-      launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), nullptr, s); }
+    { KTimer t(ctx, PM_K_SCATTER, 12 * P + (dens ? 2 : 1) * r);
+      launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), dens, s); }
     const float* radial;
     if (ng <= kMaxPlane) {   // planes: one launch for axes 2 and 1, timed with the last axis
         { KTimer t(ctx, PM_K_FFT_X, r + c);
@@ -977,7 +978,9 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
     }
     records_in_lattice_order(ctx);
     for (int n = 0; n <= N; ++n) {
-        compute_force(ctx, sc.a[n], kState);
+        // the last force is taken at the final positions: its density is the run's
+        // (a sort and a scatter of their own took 3.6 ms at 512^3/1024^3)
+        compute_force(ctx, sc.a[n], kState, n == N ? dens : nullptr);
         const double kick = (n > 0 ? sc.kick_b[n - 1] : 0.0) + (n < N ? sc.kick_a[n] : 0.0);
         uint32_t* ckx = nullptr;
         int32_t* ckp = nullptr;
@@ -1001,10 +1004,6 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
         // final state in lattice order (private copy for the adjoint) and outputs
         launch_final_state(ctx->xq, ctx->pq, ctx->id, ctx->lat, ctx->fin_x, ctx->fin_p, disp_out,
                            mom_out, s);
-        if (dens) {
-            sort_particles(ctx, false);
-            launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, nullptr, dens, s);
-        }
     }
     (void)hipEventRecord(ctx->ev[1], s);
     PM_TRY(ctx->hip_check("pm_forward"));
