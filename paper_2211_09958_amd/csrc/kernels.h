@@ -186,10 +186,14 @@ bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
 void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
                             float* dense, hipStream_t s);
 // out_j = Sum_p coeff v_{p,j} w(x_p, node) for j = 0..2 into meshes out + j*outStride
-// (64-bit fixed point, bitwise reproducible); vmax_scratch is one device word.
-void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, unsigned* vmax_scratch,
+// (64-bit fixed point, bitwise reproducible); *vmax holds max |v| as float bits
+// (launch_absmax, or the maxima of the kernel that wrote v).
+void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, const unsigned* vmax,
                         const Lattice& L, const Bins& b, float* out, long outStride,
                         hipStream_t s);
+
+// *out = max(*out, max |v| over n floats), as float bits.
+void launch_absmax(const float* v, long n, unsigned* out, hipStream_t s);
 
 // Gathers: one work-group per tile of the current bins (the particles' state
 // is read and written in their storage slots, through b.ord); partials
@@ -221,15 +225,19 @@ void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long
 // of a reverse step: partials Sum xi . p, pi += drift xi, x -= drift p (exact
 // inverse of the forward drift); mode 2 only updates xi.
 // count_bins (mode 1): the un-drifted particles are counted as in
-// launch_gather_kick_drift.
+// launch_gather_kick_drift.  pmax (mode 1, nullable): max |pi| of the new pi, one
+// value per partial.
 void launch_wgrad(const float* mesh, long pitch, float g_scale, uint32_t* xq, const int32_t* pq,
                   float* xi, float* pi, const Lattice& L, const Bins& b, float drift, int mode,
-                  double* partials, hipStream_t s, bool dense = false, bool count_bins = false);
+                  double* partials, hipStream_t s, bool dense = false, bool count_bins = false,
+                  float* pmax = nullptr);
 // The rest of a reverse step where pi was zero and the force transpose adds
 // nothing to xi: pi = drift xi, x -= drift p, block partials of Sum xi . p, the
-// un-drifted particles counted into b (as launch_wgrad with count_bins).
+// un-drifted particles counted into b and max |pi| per block in pmax (as
+// launch_wgrad with count_bins and pmax).
 void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi, const Lattice& L,
-                    const Bins& b, float drift, double* partials, int nblocks, hipStream_t s);
+                    const Bins& b, float drift, double* partials, float* pmax, int nblocks,
+                    hipStream_t s);
 // Displacements (float, Mpc/h, lattice order) -> fixed-point positions q + s in
 // lattice order, counted into b's counts, keys and ranks for a following
 // launch_bin(counted = true).
@@ -248,12 +256,22 @@ int particle_blocks(long P);
 
 // sums[slot] = Sum of partials[0..nblocks)
 void launch_reduce(const double* partials, int nblocks, double* sums, int slot, hipStream_t s);
-// sums[slots.slot[k]] = Sum of partials[k nblocks .. (k + 1) nblocks) for k < nsets
-struct Slots {
-    int slot[9];
+// The same for several sets of partials in one launch, and with maxs also *vmax =
+// max of nmax non-negative floats, as float bits.
+struct ReduceSets {
+    int nsets = 0;
+    const double* src[9];
+    int n[9], slot[9];
+    const float* maxs = nullptr;
+    int nmax = 0;
+    unsigned* vmax = nullptr;
+    void add(const double* partials, int count, int to) {
+        src[nsets] = partials;
+        n[nsets] = count;
+        slot[nsets++] = to;
+    }
 };
-void launch_reduce_sets(const double* partials, int nblocks, int nsets, double* sums,
-                        const Slots& slots, hipStream_t s);
+void launch_reduce_sets(const ReduceSets& r, double* sums, hipStream_t s);
 // Reconstruction error of fixed-point positions in cells: partials of
 // Sum_k |a[k] - b[id[k]]|^2 (minimum image), *maxbits (as float bits) = max.
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,

@@ -117,19 +117,24 @@ __device__ __forceinline__ double block_sum(double v) {
     return s;
 }
 
+// Max over a work-group of NTH threads; valid in thread 0.
+template <int NTH = kBlock>
+__device__ __forceinline__ float block_max(float m) {
+    __shared__ float red[NTH / 64];
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_down(m, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < NTH / 64; ++w) m = fmaxf(m, red[w]);
+    __syncthreads();
+    return m;
+}
+
 // Max of a non-negative float over the block, as float bits atomically folded
 // into *out by one lane per block (non-negative floats order like their bits).
 __device__ __forceinline__ void block_max_to(float m, unsigned* out) {
-    __shared__ float red[kBlock / 64];
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_down(m, o));
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) red[wid] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) m = fmaxf(m, red[w]);
-        atomicMax(out, __float_as_uint(m));
-    }
-    __syncthreads();
+    m = block_max(m);
+    if (threadIdx.x == 0) atomicMax(out, __float_as_uint(m));
 }
 
 // ------------------------------------------------------------- binning
@@ -753,6 +758,7 @@ struct GatherArgs {
     uint32_t* branks;
     int btile;
     unsigned* ovf;        // kKickDrift: set to 1 when a momentum leaves the int32 range
+    float* pmax;          // kWgrad flag 1: max |pi| written, one per tile (nullable)
 };
 
 // Threads per gather work-group: the three-mesh tile takes 59 KB of LDS (two
@@ -812,7 +818,7 @@ __device__ __forceinline__ void gather_load(const GatherArgs& A, uint32_t p, Gat
 template <int T, int MODE>
 __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattice& L,
                                                const float* mf, const int lo[3], uint32_t p,
-                                               const GatherRec& r) {
+                                               const GatherRec& r, float& pmax) {
     constexpr int NM = MODE == kWgrad ? 1 : 3;
     constexpr int TH = T + 1, TH3 = TH * TH * TH;
     const int mask = L.ng - 1;
@@ -912,7 +918,9 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
             for (int a = 0; a < 3; ++a) {
                 const int32_t m = r.pm[a];
                 acc += (double)xv[a] * ((double)m * L.mom_unit);
-                A.pi[3 * (size_t)p + a] = r.pin[a] + A.drift * xv[a];
+                const float pn = r.pin[a] + A.drift * xv[a];
+                A.pi[3 * (size_t)p + a] = pn;
+                pmax = fmaxf(pmax, fabsf(pn));
                 xn[a] = r.x[a] - drift_units(A.drift, m, L);
                 A.xq[3 * (size_t)p + a] = xn[a];
             }
@@ -940,6 +948,7 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
     const uint32_t pbeg = offsets[tile * 8], pend = offsets[tile * 8 + 8];
     const int mask = L.ng - 1;
     double acc = 0.0;
+    float pmax = 0.f;
     if (pbeg < pend) {   // uniform across the work-group
         // this thread's first particle: its slot and inputs are loaded ahead of
         // the mesh tile, so their latency overlaps the tile's
@@ -970,17 +979,21 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
             dst[T * TH * TH] = src[rowh * A.pitch];
         }
         __syncthreads();
-        if (k0 < pend) acc += gather_apply<T, MODE>(A, L, mf, lo, p0, r0);
+        if (k0 < pend) acc += gather_apply<T, MODE>(A, L, mf, lo, p0, r0, pmax);
         for (uint32_t k = k0 + NTH; k < pend; k += NTH) {   // bins larger than the work-group
             const uint32_t p = A.ord[k];
             GatherRec r;
             gather_load<MODE>(A, p, r);
-            acc += gather_apply<T, MODE>(A, L, mf, lo, p, r);
+            acc += gather_apply<T, MODE>(A, L, mf, lo, p, r, pmax);
         }
     }
     if (A.partials) {
         const double s = block_sum<NTH>(acc);
         if (threadIdx.x == 0) A.partials[tile] = s;
+    }
+    if (MODE == kWgrad && A.pmax) {
+        pmax = block_max<NTH>(pmax);
+        if (threadIdx.x == 0) A.pmax[tile] = pmax;
     }
 }
 
@@ -992,8 +1005,9 @@ __global__ void __launch_bounds__(kBlock)
 k_undrift(uint32_t* __restrict__ xq, const int32_t* __restrict__ pq, const float* __restrict__ xi,
           float* __restrict__ pi, Lattice L, long P, float drift, int tile,
           uint32_t* __restrict__ counts, uint32_t* __restrict__ keys, uint32_t* __restrict__ ranks,
-          double* __restrict__ partials) {
+          double* __restrict__ partials, float* __restrict__ pmax) {
     double acc = 0.0;
+    float mx = 0.f;
     for (long p = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x; p < P;
          p += (long)gridDim.x * kBlock) {
         uint32_t x[3];
@@ -1013,14 +1027,22 @@ k_undrift(uint32_t* __restrict__ xq, const int32_t* __restrict__ pq, const float
 #pragma unroll
         for (int a = 0; a < 3; ++a) xq[3 * p + a] = x[a];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) pi[3 * p + a] = drift * v[a];
+        for (int a = 0; a < 3; ++a) {
+            const float pn = drift * v[a];
+            pi[3 * p + a] = pn;
+            mx = fmaxf(mx, fabsf(pn));
+        }
         const uint32_t key = bin_key(x, L, tile);
         const uint32_t rank = bin_rank(key, counts);
         keys[p] = key;
         ranks[p] = rank;
     }
     const double s = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+    mx = block_max(mx);
+    if (threadIdx.x == 0) {
+        partials[blockIdx.x] = s;
+        pmax[blockIdx.x] = mx;
+    }
 }
 
 // Final state of a forward run, to lattice order: displacement (minimum image of
@@ -1073,10 +1095,20 @@ __global__ void __launch_bounds__(kBlock) k_iota(uint32_t* __restrict__ id, long
 
 // ------------------------------------------------------------- small kernels
 
+// Work-group k: sums[slot[k]] = the sum of n[k] partials at src[k]; with maxs, one
+// more work-group takes the maximum of nmax floats, as float bits, to *vmax.
 __global__ void __launch_bounds__(1024)
-k_reduce(const double* __restrict__ partials, int n, double* __restrict__ sums, Slots slots) {
+k_reduce(ReduceSets R, double* __restrict__ sums) {
     __shared__ double red[16];
-    partials += (long)blockIdx.x * n;   // one work-group per set of n partials
+    if ((int)blockIdx.x == R.nsets) {
+        float m = 0.f;
+        for (int i = threadIdx.x; i < R.nmax; i += 1024) m = fmaxf(m, R.maxs[i]);
+        m = block_max<1024>(m);
+        if (threadIdx.x == 0) *R.vmax = __float_as_uint(m);
+        return;
+    }
+    const double* partials = R.src[blockIdx.x];
+    const int n = R.n[blockIdx.x];
     // four independent running sums per thread (a fixed order, so the result
     // repeats bit for bit), so that four loads are in flight instead of one
     double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
@@ -1095,7 +1127,7 @@ k_reduce(const double* __restrict__ partials, int n, double* __restrict__ sums, 
     if (threadIdx.x == 0) {
         double s = 0.0;
         for (int w = 0; w < 16; ++w) s += red[w];
-        sums[slots.slot[blockIdx.x]] = s;
+        sums[R.slot[blockIdx.x]] = s;
     }
 }
 
@@ -1497,14 +1529,15 @@ void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b,
     scatter_dispatch<false>(xq, nullptr, 0.f, nullptr, L, b, mesh, 0, dense, s);
 }
 
-void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, unsigned* vmax_scratch,
+void launch_absmax(const float* v, long n, unsigned* out, hipStream_t s) {
+    const long nb = std::min<long>(grid_for(n), 1024);
+    hipLaunchKernelGGL(k_absmax, dim3((unsigned)nb), dim3(kBlock), 0, s, v, n, out);
+}
+
+void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, const unsigned* vmax,
                         const Lattice& L, const Bins& b, float* out, long outStride,
                         hipStream_t s) {
-    const long P = (long)L.np * L.np * L.np;
-    launch_zero(vmax_scratch, sizeof(unsigned), s);
-    const long nb = std::min<long>(grid_for(3 * P), 1024);
-    hipLaunchKernelGGL(k_absmax, dim3((unsigned)nb), dim3(kBlock), 0, s, v, 3 * P, vmax_scratch);
-    scatter_dispatch<true>(xq, v, coeff, vmax_scratch, L, b, out, outStride, nullptr, s);
+    scatter_dispatch<true>(xq, v, coeff, vmax, L, b, out, outStride, nullptr, s);
 }
 
 template <int MODE>
@@ -1587,8 +1620,9 @@ void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long
 
 void launch_wgrad(const float* mesh, long pitch, float g_scale, uint32_t* xq, const int32_t* pq,
                   float* xi, float* pi, const Lattice& L, const Bins& b, float drift, int mode,
-                  double* partials, hipStream_t s, bool dense, bool count_bins) {
+                  double* partials, hipStream_t s, bool dense, bool count_bins, float* pmax) {
     GatherArgs A{};
+    A.pmax = pmax;
     A.count = count_bins && mode == 1;
     A.xq = xq;
     A.pq = const_cast<int32_t*>(pq);
@@ -1613,10 +1647,11 @@ void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bi
 }
 
 void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi, const Lattice& L,
-                    const Bins& b, float drift, double* partials, int nblocks, hipStream_t s) {
+                    const Bins& b, float drift, double* partials, float* pmax, int nblocks,
+                    hipStream_t s) {
     const long P = (long)L.np * L.np * L.np;
     hipLaunchKernelGGL(k_undrift, dim3(nblocks), dim3(kBlock), 0, s, xq, pq, xi, pi, L, P, drift,
-                       b.tile, b.counts, b.keys, b.ranks, partials);
+                       b.tile, b.counts, b.keys, b.ranks, partials, pmax);
 }
 
 void launch_final_state(const uint32_t* xq, const int32_t* pq, const uint32_t* id,
@@ -1637,14 +1672,13 @@ void launch_iota(uint32_t* id, long P, hipStream_t s) {
 }
 
 void launch_reduce(const double* partials, int nblocks, double* sums, int slot, hipStream_t s) {
-    Slots one{};
-    one.slot[0] = slot;
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, s, partials, nblocks, sums, one);
+    ReduceSets one;
+    one.add(partials, nblocks, slot);
+    launch_reduce_sets(one, sums, s);
 }
 
-void launch_reduce_sets(const double* partials, int nblocks, int nsets, double* sums,
-                        const Slots& slots, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce, dim3(nsets), dim3(1024), 0, s, partials, nblocks, sums, slots);
+void launch_reduce_sets(const ReduceSets& r, double* sums, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce, dim3(r.nsets + (r.maxs ? 1 : 0)), dim3(1024), 0, s, r, sums);
 }
 
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,

@@ -108,6 +108,7 @@ struct Plan {
     size_t radial_f, radial_ic, radial_ic_dom, radial_lpt, losstab, tw, tw_stages, partials, sums, maxbits,
         pkbins;
     size_t theta, gtheta, fbar, mlp_scratch, ovf;
+    size_t step_parts, parts_a, parts_b, pmax;
     long cplx_elems, P, nkeys, ntab_f, ntab_p;
     int cs, cs_p, tile, nt, nckpt;
 
@@ -160,12 +161,15 @@ struct Plan {
         losstab = take(ntab_f * sizeof(float));
         tw = take((size_t)ng * sizeof(float2));
         tw_stages = take(kStageTableSize * sizeof(float2));
-        // FP64 block partials: three sets of at most 4096 grid-stride blocks (IC
-        // check, dot products, losses), and one per tile for the tile-based
-        // gathers, whose count nt^3 exceeds that when the mesh has many more
-        // cells than there are particles (32768 tiles at 512^3)
-        partials = take(std::max(3 * (size_t)((P + 255) / 256) + 3 * 4096,
-                                 (size_t)nt * nt * nt) * sizeof(double));
+        // FP64 block partials: sets of at most 4096 grid-stride blocks (nine of
+        // 1024 at the adjoint's end, checks, losses), and one set for each of the
+        // two gathers of a reverse step (one value per tile, or per block of the
+        // un-drift), whose sums and maximum |pi| one launch forms
+        step_parts = std::max((size_t)nt * nt * nt, (size_t)4096);
+        partials = take((3 * (size_t)((P + 255) / 256) + 3 * 4096) * sizeof(double));
+        parts_a = take(step_parts * sizeof(double));
+        parts_b = take(step_parts * sizeof(double));
+        pmax = take(step_parts * sizeof(float));
         sums = take((2 * (size_t)c.n_steps + 2 + kExtraSlots) * sizeof(double));
         maxbits = take(kExtraSlots * sizeof(unsigned));
         pkbins = take(3 * (size_t)ng * sizeof(double));
@@ -211,6 +215,8 @@ struct pm_ctx {
     float2* tw_stages;
     Twiddles twd;
     double *partials, *sums, *pkbins;
+    double *parts_a, *parts_b;      // partials of a reverse step's two gathers
+    float* pmax;                    // and max |pi| beside the first's
     unsigned* maxbits;
     unsigned* ovf;                  // set by the forward kicks on a momentum overflow
     Schedule sched, dsched;         // KDK factors in use (scaled) and their d/dOmega_m
@@ -496,15 +502,17 @@ void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr
 }
 
 // delta_bar (real, in C0) = transposed spectral operator applied to the CIC
-// scatter of coeff * v at the current bins; filter cotangent into gtheta.
+// scatter of coeff * v at the current bins; filter cotangent into gtheta.  The
+// word vmax_word(ctx) holds max |v| as float bits.
+unsigned* vmax_word(pm_ctx* ctx) { return ctx->maxbits + kExtraSlots - 1; }
 void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, double a) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
     const double r = mesh_r(ng), c = mesh_c(ng), P = (double)ctx->P;
     { KTimer t(ctx, PM_K_SCATTER_VEC, 24 * P + 3 * r);
-      launch_scatter_vec(xq, v, coeff, ctx->maxbits + kExtraSlots - 1, ctx->lat, ctx->bins,
-                         ctx->creal(1), ctx->creal_stride(), s); }
+      launch_scatter_vec(xq, v, coeff, vmax_word(ctx), ctx->lat, ctx->bins, ctx->creal(1),
+                         ctx->creal_stride(), s); }
     // G_0 into C1 and n1 G_1 + n2 G_2 into C2, the transposed axis-0 pass's inputs
     const bool planes = ng <= kMaxPlane;
     if (planes) {
@@ -840,6 +848,9 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
     ctx->tw_stages = ctx->at<float2>(p.tw_stages);
     ctx->twd = Twiddles{ctx->tw, ctx->ng, ctx->tw_stages};
     ctx->partials = ctx->at<double>(p.partials);
+    ctx->parts_a = ctx->at<double>(p.parts_a);
+    ctx->parts_b = ctx->at<double>(p.parts_b);
+    ctx->pmax = ctx->at<float>(p.pmax);
     ctx->sums = ctx->at<double>(p.sums);
     ctx->maxbits = ctx->at<unsigned>(p.maxbits);
     ctx->pkbins = ctx->at<double>(p.pkbins);
@@ -1047,7 +1058,11 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     else launch_zero(ctx->pi, vec, s);
 
     // seed at x_N: xi = dL/dx_N (lattice order), sorted with the state by the
-    // force evaluation, then + m grad w . dL/ddelta
+    // force evaluation, then + m grad w . dL/ddelta.  The vector scatters need max
+    // |pi|: of a caller's cotangent here, later from the kernels that write pi (a
+    // pass of its own read pi once more per step, 16 us at 128^3 particles, 0.3 ms
+    // at 512^3, and cleared the word before it)
+    if (g_mom) launch_absmax(ctx->pi, 3 * P, vmax_word(ctx), s);
     if (g_disp) PM_TRY(copy_d2d(ctx, ctx->xi, g_disp, vec));
     else launch_zero(ctx->xi, vec, s);
     compute_force(ctx, sc.a[N], kStateCotangents);
@@ -1060,9 +1075,9 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     {
         KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
         launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
-                          ctx->bins, (float)sc.kick_b[N - 1], ctx->pi, ctx->xi, false, ctx->partials, s);
+                          ctx->bins, (float)sc.kick_b[N - 1], ctx->pi, ctx->xi, false, ctx->parts_b, s);
     }
-    launch_reduce(ctx->partials, nbu, ctx->sums, slotS + N, s);
+    launch_reduce(ctx->parts_b, nbu, ctx->sums, slotS + N, s);
 
     int nck = 0;
     for (int n = N - 1; n >= 0; --n) {
@@ -1077,15 +1092,14 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         if (pi_zero) {
             KTimer t(ctx, PM_K_WGRAD, 80.0 * P);
             launch_undrift(ctx->xq, ctx->pq, ctx->xi, ctx->pi, ctx->lat, ctx->bins,
-                           (float)sc.drift[n], ctx->partials, nb, s);
+                           (float)sc.drift[n], ctx->parts_a, ctx->pmax, nb, s);
         } else {
             KTimer t(ctx, PM_K_WGRAD, bytes_wgrad + 8.0 * P);
             launch_wgrad(ctx->creal(0), ctx->lat.rp, mass, ctx->xq, ctx->pq, ctx->xi, ctx->pi,
-                         ctx->lat, ctx->bins, (float)sc.drift[n], 1, ctx->partials, s, false,
-                         true);
+                         ctx->lat, ctx->bins, (float)sc.drift[n], 1, ctx->parts_a, s, false,
+                         true, ctx->pmax);
         }
         ctx->counts_ready = true;
-        launch_reduce(ctx->partials, pi_zero ? nb : nbw, ctx->sums, slotD + n, s);
         // checkpoint: compare the reconstructed (x_n, p_{n+1/2}) and reset to it
         if (c.checkpoint_every > 0 && n > 0 && n % c.checkpoint_every == 0) {
             const int slot = n / c.checkpoint_every - 1;
@@ -1110,9 +1124,15 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         {
             KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
             launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
-                              ctx->bins, (float)c0, ctx->pi, ctx->xi, false, ctx->partials, s);
+                              ctx->bins, (float)c0, ctx->pi, ctx->xi, false, ctx->parts_b, s);
         }
-        launch_reduce(ctx->partials, nbu, ctx->sums, slotS + n, s);
+        ReduceSets step;
+        step.add(ctx->parts_a, pi_zero ? nb : nbw, slotD + n);
+        step.add(ctx->parts_b, nbu, slotS + n);
+        step.maxs = ctx->pmax;
+        step.nmax = step.n[0];
+        step.vmax = vmax_word(ctx);
+        launch_reduce_sets(step, ctx->sums, s);
     }
     // (ii) + (iii) at x_0
     vjp_mesh(ctx, ctx->xq, ctx->pi, (float)sc.kick_a[0], sc.a[0]);
@@ -1130,13 +1150,15 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         KTimer t(ctx, PM_K_OTHER, 0);
         // checks and scalar sums; s_bar = D0 xi + G0 pi over s in C1..C3, and s2_bar =
         // D20 xi + G20 pi in xi_alt (lattice order)
-        const int nsets = lpt2 ? 9 : 6;
-        const Slots slots{{xIc, xIcMom, xIcMomRef, xD0, xG0, xSig, xD20, xG20, xSig2}};
+        const int slots[9] = {xIc, xIcMom, xIcMomRef, xD0, xG0, xSig, xD20, xG20, xSig2};
+        ReduceSets end;
+        for (int k = 0; k < (lpt2 ? 9 : 6); ++k)
+            end.add(ctx->partials + (long)k * nb_ic, nb_ic, slots[k]);
         launch_ic_adjoint(ctx->creal(1), ctx->creal_stride(), 2L * ctx->cs_p, (float)sc.D0,
                           (float)sc.G0, ctx->lat, ctx->xq, ctx->pq, ctx->id, ctx->xi, ctx->pi,
                           ctx->partials, nb_ic, ctx->maxbits, s, lpt2 ? ctx->pi_alt : nullptr,
                           lpt2 ? ctx->xi_alt : nullptr, (float)sc.D20, (float)sc.G20);
-        launch_reduce_sets(ctx->partials, nb_ic, nsets, ctx->sums, slots, s);
+        launch_reduce_sets(end, ctx->sums, s);
         // dL/dnoise = transpose of the synthesis applied to s_bar; and, with the
         // Omega_m derivative of its table, the field whose product with the noise is
         // <s_bar, ds/dOmega_m> (the synthesis is linear in the noise)
@@ -1349,6 +1371,8 @@ int pm_force_vjp(pm_ctx* ctx, const float* disp, double a, const float* v, float
     launch_unkick_vjp(ctx->xq, nullptr, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins,
                       1.f, v, xi, true, nullptr, s);
     if (ctx->cfg.filter) launch_zero(ctx->gtheta, kNParam * sizeof(float), s);
+    launch_zero(vmax_word(ctx), sizeof(unsigned), s);
+    launch_absmax(v, 3 * ctx->P, vmax_word(ctx), s);
     vjp_mesh(ctx, ctx->xq, v, 1.f, a);
     launch_wgrad(ctx->creal(0), ctx->lat.rp, ctx->mass(), ctx->xq, nullptr, xi, nullptr, ctx->lat,
                  ctx->bins, 0.f, 2, nullptr, s);
