@@ -272,6 +272,10 @@ struct ReduceSets {
     }
 };
 void launch_reduce_sets(const ReduceSets& r, double* sums, hipStream_t s);
+// out[0..nsum) = sums, then as 32-bit words words[0..nwords) and *last; out is host
+// memory mapped to the device.
+void launch_collect(const double* sums, int nsum, const unsigned* words, int nwords,
+                    const unsigned* last, double* out, hipStream_t s);
 // Reconstruction error of fixed-point positions in cells: partials of
 // Sum_k |a[k] - b[id[k]]|^2 (minimum image), *maxbits (as float bits) = max.
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,

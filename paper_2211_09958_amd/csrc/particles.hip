@@ -1131,6 +1131,17 @@ k_reduce(ReduceSets R, double* __restrict__ sums) {
     }
 }
 
+// out (host memory mapped to the device): nsum sums, then nwords words and *last.
+__global__ void __launch_bounds__(kBlock)
+k_collect(const double* __restrict__ sums, int nsum, const unsigned* __restrict__ words, int nwords,
+          const unsigned* __restrict__ last, double* __restrict__ out) {
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    unsigned* w = reinterpret_cast<unsigned*>(out + nsum);
+    if (i < nsum) out[i] = sums[i];
+    if (i < nwords) w[i] = words[i];
+    if (i == nwords) w[i] = *last;
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_recon_err(const uint32_t* __restrict__ a, const uint32_t* __restrict__ id,
             const uint32_t* __restrict__ b, Lattice L, long P, double* partials,
@@ -1679,6 +1690,12 @@ void launch_reduce(const double* partials, int nblocks, double* sums, int slot, 
 
 void launch_reduce_sets(const ReduceSets& r, double* sums, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce, dim3(r.nsets + (r.maxs ? 1 : 0)), dim3(1024), 0, s, r, sums);
+}
+
+void launch_collect(const double* sums, int nsum, const unsigned* words, int nwords,
+                    const unsigned* last, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_collect, dim3((std::max(nsum, nwords + 1) + kBlock - 1) / kBlock),
+                       dim3(kBlock), 0, s, sums, nsum, words, nwords, last, out);
 }
 
 void launch_recon_err(const uint32_t* a, const uint32_t* id, const uint32_t* b, const Lattice& L,

@@ -211,6 +211,12 @@ struct pm_ctx {
     float *radial_f, *radial_ic, *radial_ic_dom, *radial_lpt, *theta, *gtheta, *fbar, *mlp_scratch;
     float* losstab;                    // targets, loss and shell factors of pm_loss_pk
     std::vector<double> loss_target;   // the targets, kept alive across their async upload
+    // Pinned host memory that kernels write the scalar results to (res_host as the
+    // device sees it: res_dev): after the synchronisation they are there.  Copying
+    // them to ordinary memory took 23 us from the last kernel's launch to the end of
+    // the wait, this takes 12.5.
+    double* res_host = nullptr;
+    double* res_dev = nullptr;
     float2* tw;
     float2* tw_stages;
     Twiddles twd;
@@ -220,7 +226,7 @@ struct pm_ctx {
     unsigned* maxbits;
     unsigned* ovf;                  // set by the forward kicks on a momentum overflow
     Schedule sched, dsched;         // KDK factors in use (scaled) and their d/dOmega_m
-    Schedule sched0;                // the unscaled growth-factor schedule
+    Schedule sched0, dsched0;       // the unscaled growth-factor schedule and derivative
     std::vector<double> step_scale; // [3N] multipliers of kick_a | drift | kick_b
     std::vector<double> g_step;     // [3N] dL/d(step_scale) of the last adjoint
     bool have_step_grads = false;
@@ -270,6 +276,11 @@ struct pm_ctx {
         if (e != hipSuccess) return fail(PM_EHIP, std::string(where) + ": " + hipGetErrorString(e));
         return PM_OK;
     }
+    int wait(const char* what) {
+        if (hipStreamSynchronize(stream) != hipSuccess)
+            return fail(PM_EHIP, std::string("reading ") + what + " failed");
+        return PM_OK;
+    }
     float* creal(int k) { return reinterpret_cast<float*>(C[k]); }
     bool lpt2() const { return (cfg.flags & PM_F_2LPT) != 0; }
     long creal_stride() const { return 2 * plan.cplx_elems; }
@@ -309,12 +320,14 @@ double mesh_c(int n) { return 8.0 * n * (double)n * (n / 2 + 1); }
         if (_rc != PM_OK) return _rc; \
     } while (0)
 
-// Multiply the schedule's kick/drift factors (and their Omega_m derivatives)
-// by the per-step scales; sched0 keeps the unscaled factors.
+// The schedule in use: sched0 and dsched0 (the cosmology's growth-factor schedule
+// and its Omega_m derivative, integrals that take the host about 20 us per step)
+// with the kick/drift factors multiplied by the per-step scales.
 void apply_step_scales(pm_ctx* ctx) {
     const int N = ctx->cfg.n_steps;
     if (ctx->step_scale.empty()) ctx->step_scale.assign(3 * (size_t)N, 1.0);
-    ctx->sched0 = ctx->sched;
+    ctx->sched = ctx->sched0;
+    ctx->dsched = ctx->dsched0;
     const double* f = ctx->step_scale.data();
     for (Schedule* t : {&ctx->sched, &ctx->dsched})
         for (int n = 0; n < N; ++n) {
@@ -328,8 +341,8 @@ void apply_step_scales(pm_ctx* ctx) {
 int upload_tables(pm_ctx* ctx) {
     const pm_config& c = ctx->cfg;
     Cosmo co = to_cosmo(&ctx->cosmo);
-    ctx->sched = schedule(co.omega_m, c.a_start, c.a_stop, c.n_steps);
-    ctx->dsched = schedule_domega(co.omega_m, c.a_start, c.a_stop, c.n_steps);
+    ctx->sched0 = schedule(co.omega_m, c.a_start, c.a_stop, c.n_steps);
+    ctx->dsched0 = schedule_domega(co.omega_m, c.a_start, c.a_stop, c.n_steps);
     apply_step_scales(ctx);
     const int np = ctx->np, ng = ctx->ng;
     const long ntp = ctx->plan.ntab_p, ntf = ctx->plan.ntab_f;
@@ -895,6 +908,19 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
             delete ctx;
             return PM_EHIP;
         }
+    {
+        const size_t n = std::max<size_t>(3 * (size_t)ctx->ng,
+                                          2 * (size_t)cfg->n_steps + 2 + 2 * kExtraSlots);
+        void* dev = nullptr;
+        if (hipHostMalloc(reinterpret_cast<void**>(&ctx->res_host), n * sizeof(double),
+                          hipHostMallocMapped) != hipSuccess ||
+            hipHostGetDevicePointer(&dev, ctx->res_host, 0) != hipSuccess) {
+            g_err = "hipHostMalloc failed";
+            pm_destroy(ctx);
+            return PM_EHIP;
+        }
+        ctx->res_dev = static_cast<double*>(dev);
+    }
     if (cfg->flags & PM_F_TIMING) {
         ctx->timing = true;
         ctx->pool.assign(2 * pm_ctx::kPool, nullptr);
@@ -936,10 +962,6 @@ int pm_set_step_scales(pm_ctx* ctx, const double* scales) {
     for (int i = 0; i < 3 * N; ++i)
         if (!std::isfinite(scales[i])) return ctx->fail(PM_EINVAL, "step scales must be finite");
     ctx->step_scale.assign(scales, scales + 3 * (size_t)N);
-    Cosmo co = to_cosmo(&ctx->cosmo);
-    const pm_config& c = ctx->cfg;
-    ctx->sched = schedule(co.omega_m, c.a_start, c.a_stop, N);
-    ctx->dsched = schedule_domega(co.omega_m, c.a_start, c.a_stop, N);
     apply_step_scales(ctx);
     ctx->have_forward = false;
     ctx->have_step_grads = false;
@@ -1173,14 +1195,12 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
 
     // scalar results (synchronises)
     const int nsum = 2 * N + 1 + kExtraSlots;
-    std::vector<double> h(nsum);
-    std::vector<unsigned> mb(kExtraSlots);
-    unsigned ovf = 0;
-    if (hipMemcpyAsync(h.data(), ctx->sums, nsum * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(mb.data(), ctx->maxbits, kExtraSlots * sizeof(unsigned), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&ovf, ctx->ovf, sizeof(unsigned), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return ctx->fail(PM_EHIP, "reading adjoint sums failed");
+    launch_collect(ctx->sums, nsum, ctx->maxbits, kExtraSlots, ctx->ovf, ctx->res_dev, s);
+    PM_TRY(ctx->hip_check("pm_adjoint"));
+    PM_TRY(ctx->wait("adjoint sums"));
+    const double* h = ctx->res_host;
+    const unsigned* mb = reinterpret_cast<const unsigned*>(h + nsum);
+    const unsigned ovf = mb[kExtraSlots];
     if (ovf)
         return ctx->fail(PM_ENUMERIC, "a momentum of the forward run left the fixed-point range "
                                       "(see pm_state_units)");
@@ -1192,8 +1212,8 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     // 2LPT: s2 ~ sigma_8^2, hence the factor 2 (the slots stay 0 otherwise)
     g_om += h[xD20] * d.D20 + h[xG20] * d.G20 + h[xOm2];
     const double g_s8 = (h[xSig] + 2.0 * h[xSig2]) / ctx->cosmo.sigma8;
-    for (double v : h)
-        if (!std::isfinite(v)) return ctx->fail(PM_ENUMERIC, "non-finite adjoint sum");
+    for (int i = 0; i < nsum; ++i)
+        if (!std::isfinite(h[i])) return ctx->fail(PM_ENUMERIC, "non-finite adjoint sum");
     // dL/d(scale) = unscaled factor * dL/d(factor) per step
     ctx->g_step.assign(3 * (size_t)N, 0.0);
     for (int n = 0; n < N; ++n) {
@@ -1246,12 +1266,10 @@ int pm_loss_mse(pm_ctx* ctx, const float* dens, const float* target, float* g_de
     launch_mse(dens, target, g_dens, n3, ctx->partials, nb, ctx->stream);
     PM_TRY(ctx->hip_check("pm_loss_mse"));
     if (loss) {
-        launch_reduce(ctx->partials, nb, ctx->pkbins, 0, ctx->stream);
-        double v = 0.0;
-        if (hipMemcpyAsync(&v, ctx->pkbins, sizeof(double), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-            hipStreamSynchronize(ctx->stream) != hipSuccess)
-            return ctx->fail(PM_EHIP, "reading loss failed");
-        *loss = v / n3;
+        launch_reduce(ctx->partials, nb, ctx->res_dev, 0, ctx->stream);
+        PM_TRY(ctx->hip_check("pm_loss_mse"));
+        PM_TRY(ctx->wait("the loss"));
+        *loss = ctx->res_host[0] / n3;
     }
     return PM_OK;
 }
@@ -1272,24 +1290,21 @@ int pm_loss_pk(pm_ctx* ctx, const float* dens, int32_t n_bins, const double* pk_
     const int ng = ctx->ng;
     // P_b = L^3 / Ng^6 <|delta_k|^2>_b; dL/d delta(x) = 2 Sum_k t_k delta_k e^{ik.x}
     // (unnormalised inverse DFT) with t_k = dL/dP_b L^3 / (Ng^6 N_b), one value per
-    // shell.  Targets, loss and shell factors live in losstab: [n_bins] | [2] | [n_bins]
+    // shell.  Targets and shell factors live in losstab: [n_bins] | [n_bins]
     const double L = ctx->cfg.box, norm = L * L * L / std::pow((double)ng, 6.0);
     double* target_dev = reinterpret_cast<double*>(ctx->losstab);
-    double* loss_dev = target_dev + n_bins;
-    float* table_dev = reinterpret_cast<float*>(loss_dev + 2);
+    float* table_dev = reinterpret_cast<float*>(target_dev + n_bins);
     ctx->loss_target.assign(pk_target, pk_target + n_bins);
     if (hipMemcpyAsync(target_dev, ctx->loss_target.data(), n_bins * sizeof(double),
                        hipMemcpyHostToDevice, s) != hipSuccess)
         return ctx->fail(PM_EHIP, "upload of the loss targets failed");
     launch_fft_shells(dens, ctx->C[0], ctx->C[1], ng, ctx->cs, n_bins, ctx->pkbins, ctx->twd, s);
-    launch_pk_loss(ctx->pkbins, target_dev, n_bins, norm, weight, loss_dev, table_dev, s);
+    launch_pk_loss(ctx->pkbins, target_dev, n_bins, norm, weight, ctx->res_dev, table_dev, s);
     if (g_dens)
         launch_fft_shell_scale(ctx->C[0], g_dens, ng, ctx->cs, n_bins, table_dev, ctx->twd, s);
     PM_TRY(ctx->hip_check("pm_loss_pk"));
-    double v = 0.0;
-    if (hipMemcpyAsync(&v, loss_dev, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return ctx->fail(PM_EHIP, "reading the P(k) loss failed");
+    PM_TRY(ctx->wait("the P(k) loss"));
+    const double v = ctx->res_host[0];
     if (loss) *loss = v;
     if (!std::isfinite(v)) return ctx->fail(PM_ENUMERIC, "non-finite P(k) loss");
     return PM_OK;
@@ -1308,12 +1323,10 @@ int pm_loss_disp(pm_ctx* ctx, const float* disp, const float* disp_target, doubl
                         ctx->partials, nb, ctx->stream);
     PM_TRY(ctx->hip_check("pm_loss_disp"));
     if (loss) {
-        launch_reduce(ctx->partials, nb, ctx->pkbins, 0, ctx->stream);
-        double v = 0.0;
-        if (hipMemcpyAsync(&v, ctx->pkbins, sizeof(double), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-            hipStreamSynchronize(ctx->stream) != hipSuccess)
-            return ctx->fail(PM_EHIP, "reading loss failed");
-        *loss = norm * v;
+        launch_reduce(ctx->partials, nb, ctx->res_dev, 0, ctx->stream);
+        PM_TRY(ctx->hip_check("pm_loss_disp"));
+        PM_TRY(ctx->wait("the loss"));
+        *loss = norm * ctx->res_host[0];
     }
     return PM_OK;
 }
@@ -1325,12 +1338,10 @@ int pm_power_spectrum(pm_ctx* ctx, const float* dens, int32_t n_bins, double* k_
     if (n_bins < 1 || n_bins > ctx->ng) return ctx->fail(PM_EINVAL, "n_bins must be in [1, mesh]");
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng;
-    launch_fft_shells(dens, ctx->C[0], ctx->C[0], ng, ctx->cs, n_bins, ctx->pkbins, ctx->twd, s);
+    launch_fft_shells(dens, ctx->C[0], ctx->C[0], ng, ctx->cs, n_bins, ctx->res_dev, ctx->twd, s);
     PM_TRY(ctx->hip_check("pm_power_spectrum"));
-    std::vector<double> h(3 * (size_t)n_bins);
-    if (hipMemcpyAsync(h.data(), ctx->pkbins, h.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return ctx->fail(PM_EHIP, "reading P(k) failed");
+    PM_TRY(ctx->wait("P(k)"));
+    const double* h = ctx->res_host;
     const double L = ctx->cfg.box, n6 = std::pow((double)ng, 6.0);
     for (int b = 0; b < n_bins; ++b) {
         const double cnt = h[3 * b + 2];
@@ -1431,7 +1442,8 @@ int pm_stats_get(pm_ctx* ctx, pm_stats* out) {
     ctx->flush_timing();
     (void)hipGetLastError();
     unsigned ovf = 0;
-    if (hipMemcpyAsync(&ovf, ctx->ovf, sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
+    if (hipMemcpyAsync(&ovf, ctx->ovf, sizeof(unsigned), hipMemcpyDeviceToHost, ctx->stream) !=
+            hipSuccess ||
         hipStreamSynchronize(ctx->stream) != hipSuccess)
         return ctx->fail(PM_EHIP, "reading the overflow flag failed");
     ctx->stats.momentum_overflow = ovf ? 1 : 0;
@@ -1456,6 +1468,7 @@ void pm_destroy(pm_ctx* ctx) {
         if (ctx->ev[k]) (void)hipEventDestroy(ctx->ev[k]);
     for (hipEvent_t e : ctx->pool)
         if (e) (void)hipEventDestroy(e);
+    if (ctx->res_host) (void)hipHostFree(ctx->res_host);   // waits for the device's streams
     delete ctx;
 }
 
