@@ -62,6 +62,11 @@ struct Cfg {
     // segments; XCD-aware numbering keeps both halves of a 128-byte line on
     // the same L2)
     static constexpr int W = H >= 512 ? 8 : 16;
+    // columns of the plain strided passes: at 512 points two work-groups of 16
+    // columns (full 128-byte lines, 1024 threads) fit on a CU, 252 -> 227 us per
+    // 512^3 pass; the passes with a second transform or stream keep 8 (split
+    // 380 -> 434 us, merge 376 -> 402 with 16)
+    static constexpr int WS = H == 512 ? 16 : W;
     // minimum waves per SIMD requested from the compiler (caps VGPRs so that
     // two work-groups fit on a CU for the large transforms)
     static constexpr int MINW = H >= 512 ? 4 : 1;
@@ -193,11 +198,11 @@ __device__ __forceinline__ int signed_freq(int p, int n) { return p < n / 2 ? p 
 // which the forward pass writes and the inverse pass reads in place of the
 // buffer, so that no separate pass changes the layout (512^3: 251 us each way).
 template <int H, int DIR, int AXIS, bool SPEC>
-__global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W, Cfg<H>::MINW)
+__global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::WS, Cfg<H>::MINW)
 k_fft_strided(float2* __restrict__ buf, typename std::conditional<DIR < 0, float2*, const float2*>::type
               __restrict__ spec, int cs, int ncb, long bufStride, const float2* __restrict__ st) {
     static_assert(!SPEC || AXIS == 0, "dense spectra are the first or last pass, along axis 0");
-    constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W;
+    constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::WS;
     __shared__ float2 lds[lds_slots(H) * W];
     const int c = threadIdx.x % W, j = threadIdx.x / W;
     const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
@@ -626,21 +631,55 @@ k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
     }
 }
 
+// Addresses of an axis-0 column's elements p = j + e T (mesh row (p, i1), column
+// k2) of one lane.  Where T is a multiple of the row block's side, element e sits
+// a wave-uniform e T H cs after element 0 (block and in-block indices are sums of
+// separate i0 and i1 terms), and element 0 below 2^32 bytes.
+template <int H>
+struct Column {
+    static constexpr int T = Cfg<H>::T;
+    int i1, k2, j, cs;
+    __device__ __forceinline__ Column(int i1_, int k2_, int j_, int cs_)
+        : i1(i1_), k2(k2_), j(j_), cs(cs_) {}
+    template <class F>
+    __device__ __forceinline__ F* at(F* base, int e) const {
+        if constexpr (T % 16 == 0) {
+            using Byte = typename std::conditional<std::is_const<F>::value, const char, char>::type;
+            const uint32_t lane = (uint32_t)(
+                ((mesh_row(j, 0, H) + mesh_row(0, i1, H)) * cs + k2) * sizeof(float2));
+            return reinterpret_cast<F*>(reinterpret_cast<Byte*>(base + (long)e * T * H * cs) + lane);
+        } else {
+            return base + mesh_row(j + e * T, i1, H) * cs + k2;
+        }
+    }
+};
+
 // Axis-0 pass with the fused gradient multiply (see launch_grad_z).  Writes
 // F~_0 = IFFT_0(i n0 radial delta) and G = IFFT_0(radial delta); F~_1 and F~_2
 // are i n1 G and i n2 G, and since n1 and n2 are constant along axis 0 those
 // factors are applied by the later passes (k_fft_y_split multiplies by i n1
 // before its axis-1 transform, the last-axis C2R by i k2), so this pass stores
 // two spectra instead of three.
+//
+// From 256 points on, each lane looks up the radial multiplier of |n0| <= H/2
+// only, with its column, and passes it to the lanes of n0 and -n0 through LDS (as
+// k_grad_z_pipe), and the column is addressed by a wave-uniform part and 32 bits
+// per lane: 72 VGPRs instead of 95 and 527 -> 505 us per 512^3 launch.  Occupancy
+// is not what bounds it (four work-groups per CU without the sharing: 534 us),
+// nor are streaming stores of use at this size (561 us; with streaming loads 611),
+// and 16 columns per tile cost more (653 us, one work-group per CU).
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __restrict__ dst_g,
          int cs, int ncb, const float* __restrict__ radial, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
+    constexpr bool SHARE = H >= 256;
+    constexpr int EQ = SHARE ? (H / 2) / T + 1 : 1;   // lookups: q = j + e T, and q = H/2
     // exchange buffer | the H-point part of the stage-twiddle table (read from
     // LDS rather than hoisted into registers, which hold the column)
     __shared__ float2 lds[lds_slots(H) * W + H];
+    __shared__ float rq[SHARE ? (H / 2 + 1) * W : 1];   // the multipliers by q = |n0|
     float2* tab = lds + lds_slots(H) * W;
     // read first in the second stage, after the first stage's barrier
     for (int i = threadIdx.x; i < H - 1; i += T * W) tab[i] = st[H + i];
@@ -648,22 +687,38 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __res
     const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
     const int i1 = tile / ncb, cb = tile % ncb;
     const int k2 = cb * W + c;
-    // element p of the column (mesh row (p, i1), column k2)
-    auto off = [&](int p) -> long { return mesh_row(p, i1, n) * cs + k2; };
-    float2 v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = src[off(j + e * T)];
-    fft_lds_tab<H, E, -1>(v, lds, W, c, j, tab);
-    __syncthreads();
+    const Column<H> col(i1, k2, j, cs);
     const int n1 = signed_freq(i1, n);
     const bool in_half = k2 <= n / 2;
+    [[maybe_unused]] float nr[EQ];
+    if constexpr (SHARE) {
+#pragma unroll
+        for (int e = 0; e < EQ; ++e) {
+            const int q = e < EQ - 1 ? j + e * T : n / 2;
+            nr[e] = radial[in_half ? q * q + n1 * n1 + k2 * k2 : 0];
+        }
+    }
+    float2 v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = *col.at(src, e);
+    if constexpr (SHARE) {
+#pragma unroll
+        for (int e = 0; e < EQ - 1; ++e) rq[(j + e * T) * W + c] = in_half ? nr[e] : 0.f;
+        // keeps the H/2 lookup with the others (as in k_grad_adj_z_pipe)
+        __asm__ volatile("" ::"v"(nr[EQ - 1]));
+        if (j == 0) rq[(n / 2) * W + c] = in_half ? nr[EQ - 1] : 0.f;
+    }
+    fft_lds_tab<H, E, -1>(v, lds, W, c, j, tab);
+    __syncthreads();
     // radial * delta (kept: the F~_0 multiplier is n0 times it)
     float2 d[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int p = j + e * T;
         const int n0 = signed_freq(p, n);
-        const float rad = in_half ? radial[n0 * n0 + n1 * n1 + k2 * k2] : 0.f;
+        float rad;
+        if constexpr (SHARE) rad = rq[(p <= n / 2 ? p : n - p) * W + c];
+        else rad = in_half ? radial[n0 * n0 + n1 * n1 + k2 * k2] : 0.f;
         const float2 x = lds[lpad(p) * W + c];
         d[e] = make_float2(rad * x.x, rad * x.y);
         v[e] = d[e];
@@ -672,7 +727,7 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __res
     fft_lds_tab<H, E, 1>(v, lds, W, c, j, tab);
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < E; ++e) dst_g[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
+    for (int e = 0; e < E; ++e) *col.at(dst_g, e) = lds[lpad(j + e * T) * W + c];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int n0 = signed_freq(j + e * T, n);
@@ -683,7 +738,7 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __res
     fft_lds_tab<H, E, 1>(v, lds, W, c, j, tab);
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < E; ++e) dst[off(j + e * T)] = lds[lpad(j + e * T) * W + c];
+    for (int e = 0; e < E; ++e) *col.at(dst, e) = lds[lpad(j + e * T) * W + c];
 }
 
 // k_grad_z for the largest transforms, whose register footprint allows one
@@ -1315,7 +1370,7 @@ void x_c2r(float2* buf, float* real, int cs, int nbuf, long bufStride, int kmul_
 template <int N, int DIR, int AXIS, bool SPEC, class Spec>
 void strided(float2* buf, Spec spec, int cs, int nbuf, long bufStride, const Twiddles& tw,
              hipStream_t s) {
-    constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
+    constexpr int W = Cfg<N>::WS, T = Cfg<N>::T;
     int ncb = cs / W;
     hipLaunchKernelGGL((k_fft_strided<N, DIR, AXIS, SPEC>), dim3(N * ncb, nbuf), dim3(T * W), 0, s,
                        buf, spec, cs, ncb, bufStride, tw.stages);
