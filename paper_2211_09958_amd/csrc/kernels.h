@@ -339,13 +339,20 @@ void launch_pk_loss(const double* bins, const double* target, int nbins, double 
 void launch_mse_periodic(const float* a, const float* b, float* g, long n, float box, float gscale,
                          double* partials, int nblocks, hipStream_t s);
 
-// Filter network (2-64-64-1 SiLU): radial[n2] = (1 + g(|k|/kNyq, a)) * base(n2)
-// with base(n2) = fscale / n2 (0 at n2 = 0); also table (nullable) = 1 + g.
-void launch_mlp_table(const float* theta, int n, float box, float a, float fscale,
+// Filter network (2-64-64-1 SiLU) at sf.n scale factors, table t at offset t stride:
+// radial[n2] = (1 + g(|k|/kNyq, a)) * base(n2) with base(n2) = fscale / n2 (0 at
+// n2 = 0); also table = 1 + g (both nullable).
+constexpr int kMaxTables = 32;
+struct ScaleFactors {
+    int n = 0;
+    float a[kMaxTables];
+    void add(double v) { a[n++] = (float)v; }
+};
+void launch_mlp_table(const float* theta, int n, const ScaleFactors& sf, float fscale, long stride,
                       float* radial, float* table, hipStream_t s);
-// dL/dtheta += backprop of fbar[n2] (dL/df) through the network at scale factor a.
-void launch_mlp_backward(const float* theta, int n, float box, float a, const float* fbar,
-                         float* gtheta, float* scratch, long scratch_elems, hipStream_t s);
+// dL/dtheta += backprop of the sf.n tables fbar[n2] (dL/df) through the network.
+void launch_mlp_backward(const float* theta, int n, const ScaleFactors& sf, long stride,
+                         const float* fbar, float* gtheta, float* scratch, hipStream_t s);
 long mlp_backward_scratch(int n);
 // Adam step on the mean of ngrad gradients g[ngrad][n]
 void launch_adam(float* p, const float* g, int ngrad, float* m, float* v, int n, float lr,

@@ -8,6 +8,8 @@
 // W3[1][64] | b3[1], output index first.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace pmx {
@@ -38,14 +40,16 @@ __device__ __forceinline__ float feature0(long n2, int n) {
 // Bound by the vector ALUs (4160 FMAs and 128 SiLUs per entry; an FMA costs a
 // SiLU's thirtieth).  One lane per entry with the weights read from LDS took
 // 47 us for the 12289 entries of a 128^3 mesh (192 waves on 1024 SIMDs) and
-// 100 us for the 196609 of 512^3 (LDS reads); this takes 16.5 and 54 us.  Every
+// 100 us for the 196609 of 512^3 (LDS reads); this takes 16.5 and 54 us, and 34 us
+// for the tables of nine scale factors at 128^3 (blockIdx.y: the table).  Every
 // sum runs over its inputs in index order.
 __global__ void __launch_bounds__(256)
-k_mlp_table(const float* __restrict__ theta, int n, float a, float fscale, long ntab,
-            float* __restrict__ radial, float* __restrict__ table) {
+k_mlp_table(const float* __restrict__ theta, int n, ScaleFactors sf, float fscale, long ntab,
+            long stride, float* __restrict__ radial, float* __restrict__ table) {
     __shared__ float hs[HID][64];   // first-layer units, then second-layer terms, by entry
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float a = sf.a[blockIdx.y];
     for (long e0 = (long)blockIdx.x * 64; e0 < ntab; e0 += (long)gridDim.x * 64) {
         const long e = e0 + lane;
         const float x0 = feature0(e < ntab ? e : 0, n), x1 = a;
@@ -76,8 +80,9 @@ k_mlp_table(const float* __restrict__ theta, int n, float a, float fscale, long 
             for (int o = 0; o < HID; ++o) g += theta[OW3 + o] * hs[o][lane];
             const float f = 1.f + g;
             if (e < ntab) {
-                if (table) table[e] = f;
-                if (radial) radial[e] = e == 0 ? 0.f : f * fscale / (float)e;
+                const long o = blockIdx.y * stride + e;
+                if (table) table[o] = f;
+                if (radial) radial[o] = e == 0 ? 0.f : f * fscale / (float)e;
             }
         }
         __syncthreads();   // hs is rewritten by the next entries
@@ -114,8 +119,8 @@ __device__ __forceinline__ int mfma_row(int r, int lane) {
 // 21 us.  Sums over entries stay in registers until the last chunk, in a fixed
 // order.
 __global__ void __launch_bounds__(256)
-k_mlp_bwd(const float* __restrict__ theta, int n, float a, long ntab,
-          const float* __restrict__ fbar, float* __restrict__ scratch) {
+k_mlp_bwd(const float* __restrict__ theta, int n, ScaleFactors sf, long ntab, long stride,
+          int nchunks, const float* __restrict__ fbar, float* __restrict__ scratch) {
     constexpr int PL = kChunk + 1;
     static_assert(kChunk == 64 && HID == 64, "one entry per lane, four 32 x 32 quadrants");
     __shared__ float h1s[HID * PL];    // H1, then dH1
@@ -135,7 +140,10 @@ k_mlp_bwd(const float* __restrict__ theta, int n, float a, long ntab,
     float db2[16], dw3[16], dw1[16][3], db3 = 0.f;
 #pragma unroll
     for (int k = 0; k < 16; ++k) db2[k] = dw3[k] = dw1[k][0] = dw1[k][1] = dw1[k][2] = 0.f;
-    for (long c0 = (long)blockIdx.x * kChunk; c0 < ntab; c0 += (long)gridDim.x * kChunk) {
+    for (int q = blockIdx.x; q < nchunks * sf.n; q += gridDim.x) {
+        const int t = q / nchunks;   // the table of this chunk
+        const long c0 = (long)(q - t * nchunks) * kChunk;
+        const float a = sf.a[t];
         // first layer at entry c0 + lane
         const long e = c0 + lane;
         const float x0 = feature0(e < ntab ? e : 0, n), x1 = a;
@@ -150,7 +158,7 @@ k_mlp_bwd(const float* __restrict__ theta, int n, float a, long ntab,
         }
         // dL/df at this lane's column of the second layer's quadrant
         const long ec = c0 + nh + c;
-        const float dg = ec < ntab ? fbar[ec] : 0.f;
+        const float dg = ec < ntab ? fbar[t * stride + ec] : 0.f;
         if (mh == 0 && kh == 0) db3 += dg;
         __syncthreads();
         v16f z2 = {0.f};
@@ -276,24 +284,23 @@ k_adam(float* __restrict__ p, const float* __restrict__ g, int ngrad, float* __r
 
 long mlp_backward_scratch(int) { return (long)kBwdBlocks * NPAR; }
 
-void launch_mlp_table(const float* theta, int n, float, float a, float fscale, float* radial,
-                      float* table, hipStream_t s) {
+void launch_mlp_table(const float* theta, int n, const ScaleFactors& sf, float fscale, long stride,
+                      float* radial, float* table, hipStream_t s) {
     const long ntab = 3L * (n / 2) * (n / 2) + 1;
     long nb = (ntab + 63) / 64;
     if (nb > 4096) nb = 4096;
-    hipLaunchKernelGGL(k_mlp_table, dim3((unsigned)nb), dim3(256), 0, s, theta, n, a, fscale, ntab,
-                       radial, table);
+    hipLaunchKernelGGL(k_mlp_table, dim3((unsigned)nb, sf.n), dim3(256), 0, s, theta, n, sf, fscale,
+                       ntab, stride, radial, table);
 }
 
-void launch_mlp_backward(const float* theta, int n, float, float a, const float* fbar,
-                         float* gtheta, float* scratch, long, hipStream_t s) {
+void launch_mlp_backward(const float* theta, int n, const ScaleFactors& sf, long stride,
+                         const float* fbar, float* gtheta, float* scratch, hipStream_t s) {
     const long ntab = 3L * (n / 2) * (n / 2) + 1;
-    long nb = (ntab + kChunk - 1) / kChunk;
-    if (nb > kBwdBlocks) nb = kBwdBlocks;
-    hipLaunchKernelGGL(k_mlp_bwd, dim3((unsigned)nb), dim3(256), 0, s, theta, n, a, ntab, fbar,
-                       scratch);
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + 63) / 64), dim3(1024), 0, s, scratch, (int)nb,
-                       gtheta);
+    const int nchunks = (int)((ntab + kChunk - 1) / kChunk);
+    const int nb = std::min(nchunks * sf.n, kBwdBlocks);
+    hipLaunchKernelGGL(k_mlp_bwd, dim3(nb), dim3(256), 0, s, theta, n, sf, ntab, stride, nchunks,
+                       fbar, scratch);
+    hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + 63) / 64), dim3(1024), 0, s, scratch, nb, gtheta);
 }
 
 void launch_adam(float* p, const float* g, int ngrad, float* m, float* v, int n, float lr,

@@ -109,8 +109,8 @@ struct Plan {
         pkbins;
     size_t theta, gtheta, fbar, mlp_scratch, ovf;
     size_t step_parts, parts_a, parts_b, pmax;
-    long cplx_elems, P, nkeys, ntab_f, ntab_p;
-    int cs, cs_p, tile, nt, nckpt;
+    long cplx_elems, P, nkeys, ntab_f, ntab_p, tab_stride;
+    int cs, cs_p, tile, nt, nckpt, ntables;
 
     size_t take(size_t bytes) {
         size_t off = total;
@@ -128,6 +128,16 @@ struct Plan {
         nkeys = (long)nt * nt * nt * 8;
         ntab_f = 3L * (ng / 2) * (ng / 2) + 1;
         ntab_p = 3L * (np / 2) * (np / 2) + 1;
+        // learned runs: as many force evaluations' filter tables are formed in one
+        // launch as fit in 2^17 entries, and their cotangents go through the network
+        // in one.  A table of a 128^3 mesh (12289 entries, 193 work-groups) takes
+        // 16 us alone and nine of them 34 us, the backward pass 25 us for one and
+        // 69 us for eight; from 256^3 on a table fills the GPU by itself, and the
+        // bound keeps the tables under 1 MB together with their cotangents.
+        tab_stride = (ntab_f + 63) / 64 * 64;
+        ntables = c.filter ? (int)std::min<long>({std::max<long>(1, (1L << 17) / tab_stride),
+                                                  (long)c.n_steps + 1, kMaxTables})
+                           : 1;
         nckpt = n_checkpoints(c);
         const size_t vec = (size_t)P * 3 * sizeof(float);
         // a fifth buffer where the plane kernels read G while they write the
@@ -154,7 +164,7 @@ struct Plan {
         ranks = take((size_t)P * sizeof(uint32_t));
         ord = take((size_t)P * sizeof(uint32_t));
         scan_tmp = take(scan_tmp_elems(nkeys) * sizeof(uint32_t));
-        radial_f = take(ntab_f * sizeof(float));
+        radial_f = take((size_t)ntables * tab_stride * sizeof(float));
         radial_ic = take(ntab_p * sizeof(float));
         radial_ic_dom = take(ntab_p * sizeof(float));
         radial_lpt = take(ntab_p * sizeof(float));
@@ -175,7 +185,7 @@ struct Plan {
         pkbins = take(3 * (size_t)ng * sizeof(double));
         theta = take(kNParam * sizeof(float));
         gtheta = take(kNParam * sizeof(float));
-        fbar = take(c.filter ? ntab_f * sizeof(float) : 0);
+        fbar = take(c.filter ? (size_t)ntables * tab_stride * sizeof(float) : 0);
         mlp_scratch = take(c.filter ? mlp_backward_scratch(ng) * sizeof(float) : 0);
         ovf = take(sizeof(unsigned));
     }
@@ -387,15 +397,65 @@ int upload_tables(pm_ctx* ctx) {
     return PM_OK;
 }
 
-// radial table of the force at scale factor a (plain: precomputed; learned: MLP).
+// Radial tables of the force at sf's scale factors (plain: the precomputed one;
+// learned: from the filter network, table t at t tab_stride).
+void force_radials(pm_ctx* ctx, const ScaleFactors& sf) {
+    if (!ctx->cfg.filter) return;
+    KTimer t(ctx, PM_K_MLP, 0);
+    const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ctx->ng, 3.0));
+    launch_mlp_table(ctx->theta, ctx->ng, sf, fscale, ctx->plan.tab_stride, ctx->radial_f, nullptr,
+                     ctx->stream);
+}
 const float* force_radial(pm_ctx* ctx, double a) {
-    if (ctx->cfg.filter) {
-        const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ctx->ng, 3.0));
-        launch_mlp_table(ctx->theta, ctx->ng, (float)ctx->cfg.box, (float)a, fscale,
-                         ctx->radial_f, nullptr, ctx->stream);
-    }
+    ScaleFactors sf;
+    sf.add(a);
+    force_radials(ctx, sf);
     return ctx->radial_f;
 }
+
+// A run's evaluations 0, 1, ... of the force, at scale factors a(i): the table of
+// evaluation i, formed with those of the next ones (their number is bounded by
+// the plan) when it is the first of a batch, and of the transposed pass's cotangent.
+struct RunTables {
+    pm_ctx* ctx;
+    std::vector<double> a;
+    int first_bar = -1;   // evaluations first_bar .. last_bar: cotangents not yet
+    int last_bar = -1;    // taken through the network
+
+    const float* radial(int i) {
+        const int K = ctx->plan.ntables;
+        if (ctx->cfg.filter && i % K == 0) {
+            ScaleFactors sf;
+            for (int k = i; k < std::min(i + K, (int)a.size()); ++k) sf.add(a[k]);
+            force_radials(ctx, sf);
+        }
+        return ctx->radial_f + offset(i);
+    }
+    // where evaluation i's dL/df goes (null for plain runs)
+    float* bar(int i) {
+        if (!ctx->cfg.filter) return nullptr;
+        if (first_bar < 0) first_bar = i;
+        last_bar = i;
+        return ctx->fbar + offset(i);
+    }
+    // after evaluation i's transposed pass: a full batch, or the last one, is taken on
+    void done(int i) {
+        if (!ctx->cfg.filter || first_bar < 0) return;
+        if ((i + 1) % ctx->plan.ntables != 0 && i + 1 < (int)a.size()) return;
+        ScaleFactors sf;
+        for (int k = first_bar; k <= last_bar; ++k) sf.add(a[k]);
+        KTimer t(ctx, PM_K_MLP, 0);
+        launch_mlp_backward(ctx->theta, ctx->ng, sf, ctx->plan.tab_stride,
+                            ctx->fbar + offset(first_bar), ctx->gtheta, ctx->mlp_scratch,
+                            ctx->stream);
+        first_bar = -1;
+    }
+
+  private:
+    long offset(int i) const {
+        return ctx->cfg.filter ? (i % ctx->plan.ntables) * ctx->plan.tab_stride : 0;
+    }
+};
 
 // Records are moved into bin order on every kCompactEvery-th sort, and on the
 // first sort after they were written in lattice order; in between, the sort
@@ -479,7 +539,7 @@ enum Particles { kState, kStateCotangents, kOnce };
 // PM force meshes of the working particles: sort into bins, delta -> C0
 // (x,y-transformed spectrum left in C0) and, when given, to the caller's plain
 // array `dens` in the same write-out, F~_j real meshes in C1..C3.
-void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr) {
+void compute_force(pm_ctx* ctx, const float* radial, Particles which, float* dens = nullptr) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
@@ -488,11 +548,9 @@ void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr
       t.bytes = which == kOnce ? order_once(ctx) : sort_particles(ctx, which == kStateCotangents); }
     { KTimer t(ctx, PM_K_SCATTER, 12 * P + (dens ? 2 : 1) * r);
       launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), dens, s); }
-    const float* radial;
     if (ng <= kMaxPlane) {   // planes: one launch for axes 2 and 1, timed with the last axis
         { KTimer t(ctx, PM_K_FFT_X, r + c);
           launch_fft_xy_r2c(nullptr, ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
-        { KTimer t(ctx, PM_K_MLP, 0); radial = force_radial(ctx, a); }
         { KTimer t(ctx, PM_K_GRAD_Z, 3 * c);
           launch_grad_z(ctx->C[0], ctx->C[1], ctx->C[4], ng, cs, radial, ctx->twd, s); }
         { KTimer t(ctx, PM_K_FFT_X, 3 * r + 2 * c);
@@ -502,7 +560,6 @@ void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr
     { KTimer t(ctx, PM_K_FFT_X, r + c); launch_fft_x_r2c(ctx->C[0], ng, cs, 1, cst, ctx->twd, s); }
     { KTimer t(ctx, PM_K_FFT_STRIDED, 2 * c);
       launch_fft_y(ctx->C[0], ng, cs, -1, 1, cst, ctx->twd, s); }
-    { KTimer t(ctx, PM_K_MLP, 0); radial = force_radial(ctx, a); }
     // F~_0 -> C1 and G -> C2; axis 1: F~_0 in place, G -> F~_1 (C2) and IFFT_1(G)
     // (C3); last axis: C2R of the three, C3 times i k2 first (= F~_2)
     { KTimer t(ctx, PM_K_GRAD_Z, 3 * c);
@@ -515,10 +572,11 @@ void compute_force(pm_ctx* ctx, double a, Particles which, float* dens = nullptr
 }
 
 // delta_bar (real, in C0) = transposed spectral operator applied to the CIC
-// scatter of coeff * v at the current bins; filter cotangent into gtheta.  The
-// word vmax_word(ctx) holds max |v| as float bits.
+// scatter of coeff * v at the current bins; the cotangent of the filter table to fbar
+// (learned).  The word vmax_word(ctx) holds max |v| as float bits.
 unsigned* vmax_word(pm_ctx* ctx) { return ctx->maxbits + kExtraSlots - 1; }
-void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, double a) {
+void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, const float* radial,
+              float* fbar) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
@@ -539,18 +597,11 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, doub
         { KTimer t(ctx, PM_K_FFT_STRIDED, 3 * c);
           launch_fft_y_merge(ctx->C[2], ctx->C[3], ng, cs, ctx->twd, s); }
     }
-    float* fbar = nullptr;
     const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ng, 3.0));
-    if (ctx->cfg.filter) fbar = ctx->fbar;
     // (C3 is free: its spectrum went into C2's)
     { KTimer t(ctx, PM_K_GRAD_ADJ_Z, (fbar ? 4 : 3) * c);
-      launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], ng, cs, ctx->radial_f, fbar,
+      launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], ng, cs, radial, fbar,
                         ctx->creal(3), fscale, ctx->twd, s); }
-    if (ctx->cfg.filter) {
-        KTimer t(ctx, PM_K_MLP, 0);
-        launch_mlp_backward(ctx->theta, ng, (float)ctx->cfg.box, (float)a, fbar, ctx->gtheta,
-                            ctx->mlp_scratch, mlp_backward_scratch(ng), s);
-    }
     if (planes) {
         KTimer t(ctx, PM_K_FFT_X, r + c);
         launch_fft_yx_c2r(ctx->C[0], nullptr, ng, cs, 1, cst, ctx->twd, s);
@@ -1010,10 +1061,11 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
                         ctx->lpt2() ? ctx->tmpv : nullptr, (float)sc.D20, (float)sc.G20);
     }
     records_in_lattice_order(ctx);
+    RunTables tables{ctx, sc.a};
     for (int n = 0; n <= N; ++n) {
         // the last force is taken at the final positions: its density is the run's
         // (a sort and a scatter of their own took 3.6 ms at 512^3/1024^3)
-        compute_force(ctx, sc.a[n], kState, n == N ? dens : nullptr);
+        compute_force(ctx, tables.radial(n), kState, n == N ? dens : nullptr);
         const double kick = (n > 0 ? sc.kick_b[n - 1] : 0.0) + (n < N ? sc.kick_a[n] : 0.0);
         uint32_t* ckx = nullptr;
         int32_t* ckp = nullptr;
@@ -1087,7 +1139,9 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     if (g_mom) launch_absmax(ctx->pi, 3 * P, vmax_word(ctx), s);
     if (g_disp) PM_TRY(copy_d2d(ctx, ctx->xi, g_disp, vec));
     else launch_zero(ctx->xi, vec, s);
-    compute_force(ctx, sc.a[N], kStateCotangents);
+    RunTables tables{ctx, {sc.a.rbegin(), sc.a.rend()}};   // evaluation N - n is at x_n
+    const float* radial = tables.radial(0);
+    compute_force(ctx, radial, kStateCotangents);
     const int nbu = (int)unkick_vjp_partials(ctx->bins), nbw = (int)wgrad_partials(ctx->bins);
     if (g_dens) {
         KTimer t(ctx, PM_K_WGRAD, 24.0 * P + mesh_r(ctx->ng));
@@ -1109,7 +1163,9 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         // of 312 ms on 512^3 particles, 1024^3 mesh, two steps)
         const double c1 = sc.kick_b[n] + (n + 1 < N ? sc.kick_a[n + 1] : 0.0);
         const bool pi_zero = n == N - 1 && !g_mom;
-        if (!pi_zero) vjp_mesh(ctx, ctx->xq, ctx->pi, (float)c1, sc.a[n + 1]);
+        if (!pi_zero)
+            vjp_mesh(ctx, ctx->xq, ctx->pi, (float)c1, radial, tables.bar(N - n - 1));
+        tables.done(N - n - 1);
         count_next_bins(ctx);   // the un-drifted particles are binned for F(x_n)
         if (pi_zero) {
             KTimer t(ctx, PM_K_WGRAD, 80.0 * P);
@@ -1141,7 +1197,8 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
             ++nck;
         }
         // recompute F(x_n); un-kick and (i) at x_n
-        compute_force(ctx, sc.a[n], kStateCotangents);
+        radial = tables.radial(N - n);
+        compute_force(ctx, radial, kStateCotangents);
         const double c0 = (n > 0 ? sc.kick_b[n - 1] : 0.0) + sc.kick_a[n];
         {
             KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
@@ -1157,7 +1214,8 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         launch_reduce_sets(step, ctx->sums, s);
     }
     // (ii) + (iii) at x_0
-    vjp_mesh(ctx, ctx->xq, ctx->pi, (float)sc.kick_a[0], sc.a[0]);
+    vjp_mesh(ctx, ctx->xq, ctx->pi, (float)sc.kick_a[0], radial, tables.bar(N));
+    tables.done(N);
     {
         KTimer t(ctx, PM_K_WGRAD, 36.0 * P + mesh_r(ctx->ng));
         launch_wgrad(ctx->creal(0), ctx->lat.rp, mass, ctx->xq, ctx->pq, ctx->xi, ctx->pi,
@@ -1366,7 +1424,7 @@ int pm_force(pm_ctx* ctx, const float* disp, double a, float* force) {
     if (!disp || !force) return ctx->fail(PM_EINVAL, "disp and force are required");
     if (ctx->cfg.filter && !ctx->have_filter) return ctx->fail(PM_ESTATE, "pm_set_filter not called");
     load_once(ctx, disp);
-    compute_force(ctx, a, kOnce);
+    compute_force(ctx, force_radial(ctx, a), kOnce);
     launch_gather_force(ctx->xq, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins, force,
                         ctx->stream);
     return ctx->hip_check("pm_force");
@@ -1378,13 +1436,16 @@ int pm_force_vjp(pm_ctx* ctx, const float* disp, double a, const float* v, float
     if (ctx->cfg.filter && !ctx->have_filter) return ctx->fail(PM_ESTATE, "pm_set_filter not called");
     hipStream_t s = ctx->stream;
     load_once(ctx, disp);
-    compute_force(ctx, a, kOnce);
+    RunTables tables{ctx, {a}};
+    const float* radial = tables.radial(0);
+    compute_force(ctx, radial, kOnce);
     launch_unkick_vjp(ctx->xq, nullptr, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins,
                       1.f, v, xi, true, nullptr, s);
     if (ctx->cfg.filter) launch_zero(ctx->gtheta, kNParam * sizeof(float), s);
     launch_zero(vmax_word(ctx), sizeof(unsigned), s);
     launch_absmax(v, 3 * ctx->P, vmax_word(ctx), s);
-    vjp_mesh(ctx, ctx->xq, v, 1.f, a);
+    vjp_mesh(ctx, ctx->xq, v, 1.f, radial, tables.bar(0));
+    tables.done(0);
     launch_wgrad(ctx->creal(0), ctx->lat.rp, ctx->mass(), ctx->xq, nullptr, xi, nullptr, ctx->lat,
                  ctx->bins, 0.f, 2, nullptr, s);
     return ctx->hip_check("pm_force_vjp");
@@ -1413,8 +1474,9 @@ int pm_filter_table(pm_ctx* ctx, double a, float* table) {
     PM_TRY(ctx_check(ctx));
     if (!table) return ctx->fail(PM_EINVAL, "table is required");
     if (!ctx->cfg.filter || !ctx->have_filter) return ctx->fail(PM_ESTATE, "no filter weights set");
-    launch_mlp_table(ctx->theta, ctx->ng, (float)ctx->cfg.box, (float)a, 0.f, nullptr, table,
-                     ctx->stream);
+    ScaleFactors sf;
+    sf.add(a);
+    launch_mlp_table(ctx->theta, ctx->ng, sf, 0.f, 0, nullptr, table, ctx->stream);
     return ctx->hip_check("pm_filter_table");
 }
 

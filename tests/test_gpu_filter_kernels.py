@@ -44,3 +44,23 @@ def test_weight_gradient(np_, ng):
     g_noise, _, g_filter = pm.adjoint(g_disp=dev(gd), want_filter=True)
     assert rel_l2(host(g_noise), ref.noise) < 2e-5
     assert rel_l2(host(g_filter), ref.theta) < 2e-5
+
+
+def test_run_over_several_table_batches():
+    """41 force evaluations: their tables and cotangents come in batches of 32 and 9.  Each step may
+    add the 2e-5 of one (above), so 41 x 2e-5 < 1e-3 for the run."""
+    np_, ng, steps = 8, 16, 40
+    theta = mlp_init(8, zero_last=False)
+    noise, gd = normal((np_,) * 3, 9), normal((np_ ** 3, 3), 10)
+    st = opm.Setup(np_, ng, 4.0 * ng, steps, Cosmology())
+    st.a_stop = 0.5
+    run = opm.forward(noise, st, theta)
+    ref = opm.adjoint(run, noise, g_disp=gd)
+    from paper_2211_09958_amd import api
+    pm = api.PMContext(api.make_config(np_, ng, 4.0 * ng, steps, a_stop=0.5, filter=True), Cosmology())
+    pm.set_filter(dev(theta))
+    disp, _, _ = pm.forward(dev(noise))
+    g_noise, _, g_filter = pm.adjoint(g_disp=dev(gd), want_filter=True)
+    assert rel_l2(host(disp), run.disp[-1]) < 1e-3
+    assert rel_l2(host(g_noise), ref.noise) < 1e-3
+    assert rel_l2(host(g_filter), ref.theta) < 1e-3
