@@ -183,7 +183,7 @@ bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
 // Density delta = rho - 1 (particle mass (ng/np)^3) into a real mesh with pitch
 // L.rp (nullable) and/or a caller's dense [ng]^3 array in plain order (nullable,
 // any 4-byte alignment); every cell written once (no pre-zeroing), deterministic.
-void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
+void launch_scatter_density(const uint32_t* xq, const Lattice& L, Bins& b, float* mesh,
                             float* dense, hipStream_t s);
 // out_j = Sum_p coeff v_{p,j} w(x_p, node) for j = 0..2 into meshes out + j*outStride
 // (64-bit fixed point, bitwise reproducible); *vmax holds max |v| as float bits

@@ -47,6 +47,19 @@ def test_density_into_any_alignment(np_, ng, kind):
     assert np.abs(host(got[0]).reshape(want.shape) - want).max() < 1e-6 * max(1.0, want.max())
 
 
+@pytest.mark.parametrize("np_,ng", [(8, 8), (16, 64), (64, 64), (32, 128)])
+def test_one_context_bins_set_after_set(np_, ng):
+    """The counts of one sort are cleared for the next, and order and offsets cover every particle:
+    from no full work-group to 256 of them, at and beyond the meshes sorted in one launch.  The
+    density is a sum of integers, so a used context gives the bits of a new one."""
+    box = 50.0
+    used = context(np_, ng, box, 1)
+    for d in disps(np_, box).values():
+        got = used.density(dev(d)).clone()
+        assert torch.equal(got, context(np_, ng, box, 1).density(dev(d)))
+        assert abs(got.double().sum().item()) < 1e-6 * ng ** 3 * max(1.0, got.max().item())
+
+
 def test_building_blocks_leave_the_stored_run():
     """Force, VJP and density between pm_forward and pm_adjoint change nothing in the adjoint,
     and a second call gives the same bits as the first."""
