@@ -195,12 +195,11 @@ void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, const u
 // *out = max(*out, max |v| over n floats), as float bits.
 void launch_absmax(const float* v, long n, unsigned* out, hipStream_t s);
 
-// Gathers: one work-group per tile of the current bins (the particles' state
-// is read and written in their storage slots, through b.ord); partials
-// (nullable) get one FP64 value per tile: unkick_vjp_partials(b) and
-// wgrad_partials(b) values.
-long unkick_vjp_partials(const Bins& b);
-long wgrad_partials(const Bins& b);
+// Gathers: one work-group per tile of the current bins, or for few particles per
+// cell a grid over the storage slots (the particles' state is read and written in
+// their storage slots); partials (nullable) get one FP64 value per work-group,
+// gather_partials(np, ng) values.
+long gather_partials(int np, int ng);
 // F = gather(force meshes), p += kick F, optional checkpoint copy of (x, p) in
 // lattice order (by id), then x += drift p (if do_drift).  *ovf (nullable) is
 // set to 1 when a new momentum does not fit the int32 fixed-point range.

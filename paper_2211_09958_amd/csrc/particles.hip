@@ -850,22 +850,76 @@ __device__ __forceinline__ void gather_load(const GatherArgs& A, uint32_t p, Gat
     }
 }
 
-// Interpolates the tile's LDS meshes mf at particle p and applies the mode's
-// update; returns the particle's term of the mode's FP64 sum.
-template <int T, int MODE>
-__device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattice& L,
-                                               const float* mf, const int lo[3], uint32_t p,
-                                               const GatherRec& r, float& pmax) {
+// The corners of a particle's cell in the tile at lo, whose meshes are in LDS.
+template <int T, int NM>
+struct TileMesh {
+    static constexpr int TH = T + 1, TH3 = TH * TH * TH;
+    const float* mf;
+    const int* lo;
+    int b[3];
+    __device__ __forceinline__ void locate(const Lattice& L, const int ii[3]) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) b[a] = (ii[a] - lo[a]) & (L.ng - 1);   // in [0, T)
+    }
+    __device__ __forceinline__ float at(int m, int c0, int c1, int c2) const {
+        return mf[m * TH3 + ((b[0] + c0) * TH + b[1] + c1) * TH + b[2] + c2];
+    }
+};
+
+// The corners read from the meshes themselves, before anything else: a row's two
+// nodes in one 8-byte load (in the last cell of a row, whose second node is the
+// row's first, the pair before it and one more load).
+template <int NM>
+struct GlobalMesh {
+    struct __attribute__((packed, aligned(4))) Pair {
+        float a, b;
+    };
+    const GatherArgs& A;
+    float f[NM][8];
+    __device__ __forceinline__ void locate(const Lattice& L, const int ii[3]) {
+        const int mask = L.ng - 1;
+        const bool wrap = ii[2] == mask;
+        const int i2 = wrap ? mask - 1 : ii[2];
+        const float* row[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int r0 = (ii[0] + (r >> 1)) & mask, r1 = (ii[1] + (r & 1)) & mask;
+            row[r] = A.mesh + (A.dense ? (long)r0 * L.ng + r1 : mesh_row(r0, r1, L.ng)) * A.pitch;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const Pair v = *reinterpret_cast<const Pair*>(row[r] + m * A.mStride + i2);
+                f[m][2 * r] = v.a;
+                f[m][2 * r + 1] = v.b;
+            }
+        if (wrap) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    f[m][2 * r] = f[m][2 * r + 1];
+                    f[m][2 * r + 1] = row[r][m * A.mStride];
+                }
+        }
+    }
+    __device__ __forceinline__ float at(int m, int c0, int c1, int c2) const {
+        return f[m][4 * c0 + 2 * c1 + c2];
+    }
+};
+
+// Interpolates the meshes at particle p and applies the mode's update; returns
+// the particle's term of the mode's FP64 sum.
+template <int MODE, class Mesh>
+__device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattice& L, Mesh mesh,
+                                               uint32_t p, const GatherRec& r, float& pmax) {
     constexpr int NM = MODE == kWgrad ? 1 : 3;
-    constexpr int TH = T + 1, TH3 = TH * TH * TH;
-    const int mask = L.ng - 1;
     const float ic = L.inv_cell;
     int ii[3];
     float t[3];
     locate(r.x, L, ii, t);
-    int b[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) b[a] = (ii[a] - lo[a]) & mask;   // in [0, T)
+    mesh.locate(L, ii);
     // G[a]: the gradient of the interpolated mesh along axis a; for the
     // transposed kick only its contraction with the momentum cotangent is used,
     // Sum_m pin_m dF_m/dx_a = Sum_corners dw/dx_a (Sum_m pin_m f_m), which is
@@ -874,7 +928,6 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int c0 = c >> 2, c1 = (c >> 1) & 1, c2 = c & 1;
-        const int li = ((b[0] + c0) * TH + b[1] + c1) * TH + b[2] + c2;
         const float a0 = c0 ? t[0] : 1.f - t[0];
         const float a1 = c1 ? t[1] : 1.f - t[1];
         const float a2 = c2 ? t[2] : 1.f - t[2];
@@ -883,7 +936,7 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
         float g = 0.f;   // kWgrad: f; kUnkickVjp: Sum_m pin_m f_m
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
-            const float f = mf[m * TH3 + li];
+            const float f = mesh.at(m, c0, c1, c2);
             if constexpr (MODE != kWgrad) F[m] = __fmaf_rn(w, f, F[m]);
             if constexpr (MODE == kUnkickVjp) g += r.pin[m] * f;
             if constexpr (MODE == kWgrad) g = f;
@@ -1016,12 +1069,13 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
             dst[T * TH * TH] = src[rowh * A.pitch];
         }
         __syncthreads();
-        if (k0 < pend) acc += gather_apply<T, MODE>(A, L, mf, lo, p0, r0, pmax);
+        const TileMesh<T, NM> mesh{mf, lo};
+        if (k0 < pend) acc += gather_apply<MODE>(A, L, mesh, p0, r0, pmax);
         for (uint32_t k = k0 + NTH; k < pend; k += NTH) {   // bins larger than the work-group
             const uint32_t p = A.ord[k];
             GatherRec r;
             gather_load<MODE>(A, p, r);
-            acc += gather_apply<T, MODE>(A, L, mf, lo, p, r, pmax);
+            acc += gather_apply<MODE>(A, L, mesh, p, r, pmax);
         }
     }
     if (A.partials) {
@@ -1031,6 +1085,36 @@ k_gather_tile(GatherArgs A, Lattice L, int nt, const uint32_t* __restrict__ offs
     if (MODE == kWgrad && A.pmax) {
         pmax = block_max<NTH>(pmax);
         if (threadIdx.x == 0) A.pmax[tile] = pmax;
+    }
+}
+
+// The gathers for few particles per cell (gather_direct): the particles in storage
+// order, each reading the nodes it needs from the meshes.  Where particles are
+// cells apart, the tiles of k_gather_tile stage the whole meshes, mostly nodes
+// that no particle reads, for 64 particles or fewer each; here the records stream
+// and every line of mesh fetched is used by one or two particles.  Bound by the
+// loads' latency and the lines they touch.
+template <int MODE>
+__global__ void __launch_bounds__(kBlock)
+k_gather(GatherArgs A, Lattice L, long P, int per) {
+    constexpr int NM = MODE == kWgrad ? 1 : 3;
+    const long first = (long)xcd_block(blockIdx.x, gridDim.x) * per;
+    double acc = 0.0;
+    float pmax = 0.f;
+    for (int c = 0; c < per; ++c) {
+        const long p = (first + c) * kBlock + threadIdx.x;
+        if (p >= P) break;
+        GatherRec r;
+        gather_load<MODE>(A, (uint32_t)p, r);
+        acc += gather_apply<MODE>(A, L, GlobalMesh<NM>{A}, (uint32_t)p, r, pmax);
+    }
+    if (A.partials) {
+        const double s = block_sum(acc);
+        if (threadIdx.x == 0) A.partials[blockIdx.x] = s;
+    }
+    if (MODE == kWgrad && A.pmax) {
+        pmax = block_max(pmax);
+        if (threadIdx.x == 0) A.pmax[blockIdx.x] = pmax;
     }
 }
 
@@ -1597,6 +1681,26 @@ void launch_scatter_vec(const uint32_t* xq, const float* v, float coeff, const u
     scatter_dispatch<true>(xq, v, coeff, vmax, L, b, out, outStride, nullptr, nullptr, s);
 }
 
+// Particles at least four cells apart on a mesh of 128^3 or more: the nodes of
+// their cells straight from the meshes (k_gather) instead of tiles of the meshes in
+// LDS (128^3 particles on 512^3: transposed kick 596 -> 471 us, cotangent gather
+// 217 -> 150; two steps and their adjoint 28.2 -> 25.7 ms, 256^3 on 1024^3 one step
+// 161 -> 148 ms, five steps of 16^3 on 128^3 1.64 -> 1.61 ms).  At two cells the
+// tiles are the faster ones (256^3 on 512^3: kick and drift 700 us against 930,
+// transposed kick 765 against 956), at one cell by far (512^3 on 512^3: 2.2 ms
+// against 7.3): neighbouring particles then share most of their lines.  Smaller
+// meshes have too few particles for the grid (five steps of 16^3 on 64^3: 774 us
+// against 808).
+static bool gather_direct(int np, int ng) { return 4 * np <= ng && ng >= 128; }
+struct GatherGrid {
+    unsigned blocks;
+    int per;   // chunks of kBlock particles per work-group
+};
+static GatherGrid gather_grid(long P) {
+    const long chunks = (P + kBlock - 1) / kBlock, per = (chunks + 8191) / 8192;
+    return {(unsigned)((chunks + per - 1) / per), (int)per};
+}
+
 template <int MODE>
 static void gather_dispatch(GatherArgs A, const Lattice& L, const Bins& b, hipStream_t s) {
     const unsigned ntiles = (unsigned)b.nt * b.nt * b.nt;
@@ -1606,6 +1710,12 @@ static void gather_dispatch(GatherArgs A, const Lattice& L, const Bins& b, hipSt
         A.bkeys = b.keys;
         A.branks = b.ranks;
         A.btile = b.tile;
+    }
+    if (gather_direct(L.np, L.ng)) {
+        const long P = (long)L.np * L.np * L.np;
+        const GatherGrid g = gather_grid(P);
+        hipLaunchKernelGGL((k_gather<MODE>), dim3(g.blocks), dim3(kBlock), 0, s, A, L, P, g.per);
+        return;
     }
     switch (b.tile) {
         case 4:
@@ -1623,8 +1733,10 @@ static void gather_dispatch(GatherArgs A, const Lattice& L, const Bins& b, hipSt
     }
 }
 
-long unkick_vjp_partials(const Bins& b) { return (long)b.nt * b.nt * b.nt; }
-long wgrad_partials(const Bins& b) { return (long)b.nt * b.nt * b.nt; }
+long gather_partials(int np, int ng) {
+    const long nt = ng / choose_tile(ng);
+    return gather_direct(np, ng) ? gather_grid((long)np * np * np).blocks : nt * nt * nt;
+}
 
 void launch_gather_kick_drift(uint32_t* xq, int32_t* pq, const uint32_t* id, const float* fmesh,
                               long fStride, const Lattice& L, const Bins& b, float kick,

@@ -175,7 +175,7 @@ struct Plan {
         // 1024 at the adjoint's end, checks, losses), and one set for each of the
         // two gathers of a reverse step (one value per tile, or per block of the
         // un-drift), whose sums and maximum |pi| one launch forms
-        step_parts = std::max((size_t)nt * nt * nt, (size_t)4096);
+        step_parts = std::max((size_t)gather_partials(np, ng), (size_t)4096);
         partials = take((3 * (size_t)((P + 255) / 256) + 3 * 4096) * sizeof(double));
         parts_a = take(step_parts * sizeof(double));
         parts_b = take(step_parts * sizeof(double));
@@ -1142,7 +1142,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     RunTables tables{ctx, {sc.a.rbegin(), sc.a.rend()}};   // evaluation N - n is at x_n
     const float* radial = tables.radial(0);
     compute_force(ctx, radial, kStateCotangents);
-    const int nbu = (int)unkick_vjp_partials(ctx->bins), nbw = (int)wgrad_partials(ctx->bins);
+    const int ngather = (int)gather_partials(ctx->np, ctx->ng);
     if (g_dens) {
         KTimer t(ctx, PM_K_WGRAD, 24.0 * P + mesh_r(ctx->ng));
         launch_wgrad(g_dens, ctx->ng, mass, ctx->xq, ctx->pq, ctx->xi, ctx->pi, ctx->lat,
@@ -1153,7 +1153,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
                           ctx->bins, (float)sc.kick_b[N - 1], ctx->pi, ctx->xi, false, ctx->parts_b, s);
     }
-    launch_reduce(ctx->parts_b, nbu, ctx->sums, slotS + N, s);
+    launch_reduce(ctx->parts_b, ngather, ctx->sums, slotS + N, s);
 
     int nck = 0;
     for (int n = N - 1; n >= 0; --n) {
@@ -1206,8 +1206,8 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
                               ctx->bins, (float)c0, ctx->pi, ctx->xi, false, ctx->parts_b, s);
         }
         ReduceSets step;
-        step.add(ctx->parts_a, pi_zero ? nb : nbw, slotD + n);
-        step.add(ctx->parts_b, nbu, slotS + n);
+        step.add(ctx->parts_a, pi_zero ? nb : ngather, slotD + n);
+        step.add(ctx->parts_b, ngather, slotS + n);
         step.maxs = ctx->pmax;
         step.nmax = step.n[0];
         step.vmax = vmax_word(ctx);

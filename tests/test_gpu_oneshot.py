@@ -9,7 +9,7 @@ import torch
 from gpu_util import context, dev, host
 from oracle import mesh as M
 from oracle import pm as opm
-from synthetic import normal
+from synthetic import Cosmology, normal
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,29 @@ def test_building_blocks_leave_the_stored_run():
     again = [pm.force(d, 0.5), pm.force_vjp(d, 0.5, v), pm.density(d)]
     assert all(torch.equal(a, b) for a, b in zip(first, again))
     assert torch.equal(pm.adjoint(g_dens=g)[0], want)
+
+
+@pytest.mark.parametrize("np_,ng", [(16, 32), (8, 128), (16, 128), (32, 128), (64, 128)])
+@pytest.mark.parametrize("kind", ["spread", "edge"])
+def test_force_and_vjp_from_tiles_and_from_the_meshes(np_, ng, kind):
+    """Particles everywhere, or all in the last cells of every axis, whose far nodes are the first
+    ones: on either side of the spacing and mesh size from which the gathers read the meshes
+    themselves."""
+    box, n = 50.0, np_ ** 3
+    q = opm.lattice(np_, box)
+    if kind == "spread":
+        d = disps(np_, box)["spread"]
+    else:   # x in the last 1.5 cells below the box's end
+        d = box - 1.5 * box / ng * np.random.default_rng(5).random((n, 3)) - q
+    v = normal((n, 3), 11).astype(np.float32)
+    d = d.astype(np.float32)
+    units = np.rint(d * np.float32(2.0 ** 32 / box)).astype(np.float64)
+    x = np.mod(q + units * (box / 2.0 ** 32), box)
+    st = opm.Setup(np_, ng, box, 1, Cosmology())
+    want, _, force = opm.pm_force_vjp(x, v.astype(np.float64), st)
+    pm = context(np_, ng, box, 1)
+    rel = lambda got, ref: np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    # 32-bit transforms: some 2^-24 log2(ng^3) = 1.3e-6 of the field's norm; the VJP takes
+    # differences of neighbouring nodes and adds three terms of either sign, ten times that
+    assert rel(host(pm.force(dev(d), 0.5)), force) < 1e-5
+    assert rel(host(pm.force_vjp(dev(d), 0.5, dev(v))), want) < 1e-4
