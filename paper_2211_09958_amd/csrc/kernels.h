@@ -167,10 +167,11 @@ struct Records {
 // offsets and the sorted order b.ord (bin k of the offsets holds the particles
 // in storage slots ord[offsets[k]], ..., ord[offsets[k + 1] - 1]); the records
 // stay where they are.
-// With `counted`, the counts, keys and ranks were already produced by the
-// gather that moved the particles (see count_bins below) and only the scan and
-// the order remain.
-void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, bool counted, hipStream_t s);
+// kCounted: the counts, keys and ranks were already produced by the gather that
+// moved the particles (see count_bins below) and only the scan and the order
+// remain; kCountedOnce: by launch_to_fixed_count, in the order of its waves.
+enum Counted { kNotCounted, kCounted, kCountedOnce };
+void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, hipStream_t s);
 // Zeroes the bin counts (unless the last sort left them so) ahead of a kernel that
 // counts particles.
 void launch_bin_zero(Bins& b, hipStream_t s);
@@ -204,7 +205,7 @@ long gather_partials(int np, int ng);
 // lattice order (by id), then x += drift p (if do_drift).  *ovf (nullable) is
 // set to 1 when a new momentum does not fit the int32 fixed-point range.
 // With count_bins (and do_drift), the drifted particles are also counted into
-// b's counts, keys and ranks for the next launch_bin(counted = true); the
+// b's counts, keys and ranks for the next launch_bin(kCounted); the
 // counts must have been zeroed (launch_bin_zero) after the last scan.
 void launch_gather_kick_drift(uint32_t* xq, int32_t* pq, const uint32_t* id, const float* fmesh,
                               long fStride, const Lattice& L, const Bins& b, float kick,
@@ -239,7 +240,7 @@ void launch_undrift(uint32_t* xq, const int32_t* pq, const float* xi, float* pi,
                     hipStream_t s);
 // Displacements (float, Mpc/h, lattice order) -> fixed-point positions q + s in
 // lattice order, counted into b's counts, keys and ranks for a following
-// launch_bin(counted = true).
+// launch_bin(kCountedOnce).
 void launch_to_fixed_count(const float* disp, uint32_t* xq, const Lattice& L, Bins& b,
                            hipStream_t s);
 // Fixed-point state (any order) -> lattice order: displacement (minimum image of

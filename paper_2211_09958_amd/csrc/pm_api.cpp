@@ -473,7 +473,8 @@ constexpr int kLatticeOrder = 1 << 20;   // forces a compaction
 // due.  Returns the bytes moved, for the timing statistics.
 double sort_particles(pm_ctx* ctx, bool cotangents) {
     const double P = (double)ctx->P;
-    launch_bin(ctx->xq, ctx->lat, ctx->bins, ctx->counts_ready, ctx->stream);
+    launch_bin(ctx->xq, ctx->lat, ctx->bins, ctx->counts_ready ? kCounted : kNotCounted,
+               ctx->stream);
     // positions read, keys and ranks written and read, order written (the
     // gather that counted accounts for its own key and rank writes)
     double bytes = ctx->counts_ready ? 12.0 * P : 32.0 * P;
@@ -511,7 +512,7 @@ void load_once(pm_ctx* ctx, const float* disp) {
 
 // Bins the positions of load_once; the records stay in lattice order.
 double order_once(pm_ctx* ctx) {
-    launch_bin(ctx->xq, ctx->lat, ctx->bins, true, ctx->stream);
+    launch_bin(ctx->xq, ctx->lat, ctx->bins, kCountedOnce, ctx->stream);
     return 12.0 * ctx->P;
 }
 
