@@ -38,7 +38,7 @@ FAMILY_KERNELS = {
     "scatter": ["k_scatter_tile<16, false>"], "scatter_vec": ["k_scatter_tile<16, true>"],
     "gather": ["k_gather_tile<16, 0>"], "unkick_vjp": ["k_gather_tile<16, 2>"],
     "wgrad": ["k_gather_tile<16, 3>"],
-    "bin": ["k_bin_count", "k_scan_local", "k_scan_bsum", "k_scan_add", "k_permute"],
+    "bin": ["k_bin_count", "k_scan_local", "k_scan_add", "k_index", "k_compact_sorted"],
 }
 
 

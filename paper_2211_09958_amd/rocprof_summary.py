@@ -105,8 +105,12 @@ def family(sym: str, ng: int):
         # and rank (8 bytes) for the next sort
         return {"0": ("gather", "56P+3r"), "1": ("gather", "24P+3r"),
                 "2": ("unkick_vjp", "72P+3r"), "3": ("wgrad", "92P+r")}.get(mode, (None, None))
-    if base in ("k_bin_count", "k_scan_local", "k_scan_bsum", "k_scan_add", "k_index",
-                "k_compact_sorted"):
+    if base == "k_gather":   # the same modes without tiles
+        return {"0": ("gather", "56P+3r"), "1": ("gather", "24P+3r"),
+                "2": ("unkick_vjp", "72P+3r"), "3": ("wgrad", "92P+r")}.get(
+                    targs[0] if targs else "", (None, None))
+    if base in ("k_bin_count", "k_to_fixed_count", "k_scan_local", "k_scan_add", "k_scan_index",
+                "k_index", "k_compact_sorted"):
         return "bin", None
     if base.startswith("k_mlp") or base == "k_adam":
         return "mlp", None
