@@ -155,6 +155,9 @@ struct Records {
     const uint32_t* src[6];
     uint32_t* dst[6];
     int words[6];       // 32-bit words per particle
+    // sources in lattice order: the ids (third) are the slots and are not read, and
+    // a null source of the fourth and fifth (xi, pi) stands for zeros
+    bool lattice = false;
     void add(const void* from, void* to, int w) {
         src[n] = static_cast<const uint32_t*>(from);
         dst[n] = static_cast<uint32_t*>(to);

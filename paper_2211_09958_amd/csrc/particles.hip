@@ -404,7 +404,9 @@ constexpr int kSortWords[5] = {3, 3, 1, 3, 3};
 // first wait and before any store (a load after a store to an array the
 // compiler cannot prove disjoint waits for the store; a branch on a run-time
 // layout waits for the loads in it).
-template <int N>
+// LATTICE: as Records::lattice; a source that stands for zeros loads the position
+// again instead, so that no load sits in a branch.
+template <int N, bool LATTICE>
 __global__ void __launch_bounds__(kBlock)
 k_compact_sorted(uint32_t* __restrict__ ord, long P, Records rec) {
     const long k = (long)xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -413,9 +415,17 @@ k_compact_sorted(uint32_t* __restrict__ ord, long P, Records rec) {
     uint32_t buf[N][3];
 #pragma unroll
     for (int a = 0; a < N; ++a) {
-        const uint32_t* src = rec.src[a] + i * kSortWords[a];
+        if (LATTICE && a == 2) {
+            buf[a][0] = (uint32_t)i;
+            continue;
+        }
+        const bool zero = LATTICE && a > 2 && !rec.src[a];
+        const uint32_t* src = (zero ? rec.src[0] : rec.src[a]) + i * kSortWords[a];
 #pragma unroll
-        for (int j = 0; j < kSortWords[a]; ++j) buf[a][j] = src[j];
+        for (int j = 0; j < kSortWords[a]; ++j) {
+            const uint32_t v = src[j];
+            buf[a][j] = zero ? 0u : v;
+        }
     }
 #pragma unroll
     for (int a = 0; a < N; ++a) {
@@ -1680,9 +1690,11 @@ bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
     if (!sorted_layout) return false;
     const dim3 grid((unsigned)((P + kBlock - 1) / kBlock));
     if (rec.n == 3)
-        hipLaunchKernelGGL(k_compact_sorted<3>, grid, dim3(kBlock), 0, s, b.ord, P, rec);
+        hipLaunchKernelGGL((k_compact_sorted<3, false>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
+    else if (rec.lattice)
+        hipLaunchKernelGGL((k_compact_sorted<5, true>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
     else
-        hipLaunchKernelGGL(k_compact_sorted<5>, grid, dim3(kBlock), 0, s, b.ord, P, rec);
+        hipLaunchKernelGGL((k_compact_sorted<5, false>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
     return true;
 }
 

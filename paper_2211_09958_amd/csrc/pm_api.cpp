@@ -468,13 +468,31 @@ struct RunTables {
 constexpr int kCompactEvery = 4;
 constexpr int kLatticeOrder = 1 << 20;   // forces a compaction
 
+// The working records were just written in lattice order.
+void records_in_lattice_order(pm_ctx* ctx) {
+    ctx->sorts_since_compact = kLatticeOrder;
+    ctx->counts_ready = false;
+}
+
+// Where the records of a reverse run come from at x_N, in lattice order: the stored
+// final state and the caller's cotangents (null: zero).
+struct ReverseStart {
+    const uint32_t* x;
+    const int32_t* p;
+    const float *xi, *pi;
+};
+
 // Bin the working particles (bin offsets and order in ctx->bins); compact the
 // records (positions, momenta, ids, and with `cotangents` also xi and pi) when
-// due.  Returns the bytes moved, for the timing statistics.
-double sort_particles(pm_ctx* ctx, bool cotangents) {
+// due.  With `start` (and cotangents) the compaction takes the records from there,
+// so that they are never copied in lattice order first (512^3 particles: 2.7 ms of
+// copies, clears and their reading back).  Returns the bytes moved, for the timing
+// statistics.
+double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = nullptr) {
     const double P = (double)ctx->P;
-    launch_bin(ctx->xq, ctx->lat, ctx->bins, ctx->counts_ready ? kCounted : kNotCounted,
-               ctx->stream);
+    if (start) records_in_lattice_order(ctx);
+    launch_bin(start ? start->x : ctx->xq, ctx->lat, ctx->bins,
+               ctx->counts_ready ? kCounted : kNotCounted, ctx->stream);
     // positions read, keys and ranks written and read, order written (the
     // gather that counted accounts for its own key and rank writes)
     double bytes = ctx->counts_ready ? 12.0 * P : 32.0 * P;
@@ -482,12 +500,13 @@ double sort_particles(pm_ctx* ctx, bool cotangents) {
     if (++ctx->sorts_since_compact <= kCompactEvery) return bytes;
     ctx->sorts_since_compact = 1;
     Records rec;
-    rec.add(ctx->xq, ctx->xq_alt, 3);
-    rec.add(ctx->pq, ctx->pq_alt, 3);
+    rec.lattice = start != nullptr;
+    rec.add(start ? start->x : ctx->xq, ctx->xq_alt, 3);
+    rec.add(start ? start->p : ctx->pq, ctx->pq_alt, 3);
     rec.add(ctx->id, ctx->id_alt, 1);
     if (cotangents) {
-        rec.add(ctx->xi, ctx->xi_alt, 3);
-        rec.add(ctx->pi, ctx->pi_alt, 3);
+        rec.add(start ? start->xi : ctx->xi, ctx->xi_alt, 3);
+        rec.add(start ? start->pi : ctx->pi, ctx->pi_alt, 3);
     }
     // (the set above is the one launch_compact moves; were it refused, the
     // records would stay where they are and the order would still hold)
@@ -516,12 +535,6 @@ double order_once(pm_ctx* ctx) {
     return 12.0 * ctx->P;
 }
 
-// The working records were just written in lattice order.
-void records_in_lattice_order(pm_ctx* ctx) {
-    ctx->sorts_since_compact = kLatticeOrder;
-    ctx->counts_ready = false;
-}
-
 // Zeroes the bin counts for a gather that counts the particles it moves into
 // the next sort's bins.
 void count_next_bins(pm_ctx* ctx) { launch_bin_zero(ctx->bins, ctx->stream); }
@@ -540,13 +553,15 @@ enum Particles { kState, kStateCotangents, kOnce };
 // PM force meshes of the working particles: sort into bins, delta -> C0
 // (x,y-transformed spectrum left in C0) and, when given, to the caller's plain
 // array `dens` in the same write-out, F~_j real meshes in C1..C3.
-void compute_force(pm_ctx* ctx, const float* radial, Particles which, float* dens = nullptr) {
+void compute_force(pm_ctx* ctx, const float* radial, Particles which, float* dens = nullptr,
+                   const ReverseStart* start = nullptr) {
     hipStream_t s = ctx->stream;
     const int ng = ctx->ng, cs = ctx->cs;
     const long cst = ctx->plan.cplx_elems;
     const double r = mesh_r(ng), c = mesh_c(ng), P = (double)ctx->P;
     { KTimer t(ctx, PM_K_BIN, 0);
-      t.bytes = which == kOnce ? order_once(ctx) : sort_particles(ctx, which == kStateCotangents); }
+      t.bytes = which == kOnce ? order_once(ctx)
+                               : sort_particles(ctx, which == kStateCotangents, start); }
     { KTimer t(ctx, PM_K_SCATTER, 12 * P + (dens ? 2 : 1) * r);
       launch_scatter_density(ctx->xq, ctx->lat, ctx->bins, ctx->creal(0), dens, s); }
     if (ng <= kMaxPlane) {   // planes: one launch for axes 2 and 1, timed with the last axis
@@ -1122,27 +1137,20 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     const double bytes_unkick = 72.0 * P + 3 * mesh_r(ctx->ng);
     const double bytes_wgrad = 84.0 * P + mesh_r(ctx->ng);
     (void)hipEventRecord(ctx->ev[2], s);
-    PM_TRY(copy_d2d(ctx, ctx->xq, ctx->fin_x, vec));
-    PM_TRY(copy_d2d(ctx, ctx->pq, ctx->fin_p, vec));
-    launch_iota(ctx->id, P, s);   // records start in lattice order
-    records_in_lattice_order(ctx);
     launch_zero(ctx->sums, (2 * (size_t)N + 2 + kExtraSlots) * sizeof(double), s);
     launch_zero(ctx->maxbits, kExtraSlots * sizeof(unsigned), s);
     if (c.filter) launch_zero(ctx->gtheta, kNParam * sizeof(float), s);
-    if (g_mom) PM_TRY(copy_d2d(ctx, ctx->pi, g_mom, vec));
-    else launch_zero(ctx->pi, vec, s);
 
     // seed at x_N: xi = dL/dx_N (lattice order), sorted with the state by the
     // force evaluation, then + m grad w . dL/ddelta.  The vector scatters need max
     // |pi|: of a caller's cotangent here, later from the kernels that write pi (a
     // pass of its own read pi once more per step, 16 us at 128^3 particles, 0.3 ms
     // at 512^3, and cleared the word before it)
-    if (g_mom) launch_absmax(ctx->pi, 3 * P, vmax_word(ctx), s);
-    if (g_disp) PM_TRY(copy_d2d(ctx, ctx->xi, g_disp, vec));
-    else launch_zero(ctx->xi, vec, s);
+    if (g_mom) launch_absmax(g_mom, 3 * P, vmax_word(ctx), s);
+    const ReverseStart start{ctx->fin_x, ctx->fin_p, g_disp, g_mom};
     RunTables tables{ctx, {sc.a.rbegin(), sc.a.rend()}};   // evaluation N - n is at x_n
     const float* radial = tables.radial(0);
-    compute_force(ctx, radial, kStateCotangents);
+    compute_force(ctx, radial, kStateCotangents, nullptr, &start);
     const int ngather = (int)gather_partials(ctx->np, ctx->ng);
     if (g_dens) {
         KTimer t(ctx, PM_K_WGRAD, 24.0 * P + mesh_r(ctx->ng));
