@@ -156,7 +156,8 @@ struct Records {
     uint32_t* dst[6];
     int words[6];       // 32-bit words per particle
     // sources in lattice order: the ids (third) are the slots and are not read, and
-    // a null source of the fourth and fifth (xi, pi) stands for zeros
+    // a null source of the fourth and fifth (xi, pi) stands for zeros (fifth: not
+    // written either when its destination is null)
     bool lattice = false;
     void add(const void* from, void* to, int w) {
         src[n] = static_cast<const uint32_t*>(from);
@@ -219,7 +220,7 @@ void launch_gather_force(const uint32_t* xq, const float* fmesh, long fStride, c
                          const Bins& b, float* out, hipStream_t s);
 // Reverse step at x: F = gather; p -= coeff F (exact inverse of the forward
 // kick; pq nullable); xi (taken as zero with xi_zero) += coeff Sum_j pi_j grad w .
-// F~_j; partials Sum pi . F.
+// F~_j; partials Sum pi . F.  pi null: zero, xi is then neither read nor written.
 void launch_unkick_vjp(const uint32_t* xq, int32_t* pq, const float* fmesh, long fStride,
                        const Lattice& L, const Bins& b, float coeff, const float* pi, float* xi,
                        bool xi_zero, double* partials, hipStream_t s);

@@ -429,6 +429,7 @@ k_compact_sorted(uint32_t* __restrict__ ord, long P, Records rec) {
     }
 #pragma unroll
     for (int a = 0; a < N; ++a) {
+        if (LATTICE && a == 4 && !rec.dst[a]) break;
         uint32_t* dst = rec.dst[a] + k * kSortWords[a];
 #pragma unroll
         for (int j = 0; j < kSortWords[a]; ++j) dst[j] = buf[a][j];
@@ -836,7 +837,7 @@ struct GatherArgs {
     uint32_t* ck_x;       // kKickDrift checkpoint, lattice order (nullable)
     int32_t* ck_p;
     float* out;           // kForce output, by storage slot
-    const float* pi_in;   // kUnkickVjp
+    const float* pi_in;   // kUnkickVjp (null: zero, only p changes)
     float* xi;            // kUnkickVjp, kWgrad
     float* pi;            // kWgrad
     double* partials;     // one per tile (nullable)
@@ -883,13 +884,14 @@ __device__ __forceinline__ void gather_load(const GatherArgs& A, uint32_t p, Gat
             for (int a = 0; a < 3; ++a) r.pm[a] = A.pq[3 * (size_t)p + a];
         }
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            r.pin[a] = A.pi_in[3 * (size_t)p + a];
-            r.xin[a] = 0.f;
-        }
-        if (!A.flag) {
+        for (int a = 0; a < 3; ++a) r.pin[a] = r.xin[a] = 0.f;
+        if (A.pi_in) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) r.xin[a] = A.xi[3 * (size_t)p + a];
+            for (int a = 0; a < 3; ++a) r.pin[a] = A.pi_in[3 * (size_t)p + a];
+            if (!A.flag) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) r.xin[a] = A.xi[3 * (size_t)p + a];
+            }
         }
     } else if constexpr (MODE == kWgrad) {
 #pragma unroll
@@ -1046,8 +1048,10 @@ __device__ __forceinline__ double gather_apply(const GatherArgs& A, const Lattic
 #pragma unroll
             for (int a = 0; a < 3; ++a) A.pq[3 * (size_t)p + a] = r.pm[a] - kick_units(A.coeff, F[a], L);
         }
+        if (A.pi_in) {   // pi = 0 adds nothing to xi
 #pragma unroll
-        for (int a = 0; a < 3; ++a) A.xi[3 * (size_t)p + a] = r.xin[a] + A.coeff * G[a];
+            for (int a = 0; a < 3; ++a) A.xi[3 * (size_t)p + a] = r.xin[a] + A.coeff * G[a];
+        }
         acc = (double)r.pin[0] * F[0] + (double)r.pin[1] * F[1] + (double)r.pin[2] * F[2];
     } else {   // kWgrad
         float xv[3];
