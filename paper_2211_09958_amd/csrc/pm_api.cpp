@@ -521,6 +521,7 @@ double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = 
         std::swap(ctx->xi, ctx->xi_alt);
         std::swap(ctx->pi, ctx->pi_alt);
     }
+    if (start) return bytes + (64.0 + (start->xi ? 12 : 0) + (start->pi ? 24 : 0)) * P;
     return bytes + (cotangents ? 112.0 : 64.0) * P;
 }
 
@@ -1161,7 +1162,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
                      ctx->bins, 0.f, 2, nullptr, s, true);
     }
     {
-        KTimer t(ctx, PM_K_UNKICK_VJP, bytes_unkick);
+        KTimer t(ctx, PM_K_UNKICK_VJP, g_mom ? bytes_unkick : 36.0 * P + 3 * mesh_r(ctx->ng));
         launch_unkick_vjp(ctx->xq, ctx->pq, ctx->creal(1), ctx->creal_stride(), ctx->lat,
                           ctx->bins, (float)sc.kick_b[N - 1], g_mom ? ctx->pi : nullptr, ctx->xi,
                           false, ctx->parts_b, s);
