@@ -142,7 +142,10 @@ struct Bins {
     uint32_t* ranks;    // [P]
     uint32_t* ord;      // [P] storage slot of the k-th particle in bin order
     uint32_t* scan_tmp; // scan block sums
-    bool zeroed = false; // the counts are zero once the stream's work is done
+    // The counts are zero between calls: zeroed with the tables, and every sort's
+    // counts are cleared by the same call's later kernels.  dirty: a call failed in
+    // between, so that they may not be
+    bool dirty = false;
     long nkeys() const { return (long)nt * nt * nt * 8; }
 };
 
@@ -176,8 +179,7 @@ struct Records {
 // remain; kCountedOnce: by launch_to_fixed_count, in the order of its waves.
 enum Counted { kNotCounted, kCounted, kCountedOnce };
 void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, hipStream_t s);
-// Zeroes the bin counts (unless the last sort left them so) ahead of a kernel that
-// counts particles.
+// Zeroes the bin counts ahead of a kernel that counts particles, if they are dirty.
 void launch_bin_zero(Bins& b, hipStream_t s);
 // Moves every record array from src to dst in the order b.ord and resets b.ord
 // to the identity (each bin then a contiguous range of the records).  The
@@ -188,7 +190,8 @@ bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
 // Density delta = rho - 1 (particle mass (ng/np)^3) into a real mesh with pitch
 // L.rp (nullable) and/or a caller's dense [ng]^3 array in plain order (nullable,
 // any 4-byte alignment); every cell written once (no pre-zeroing), deterministic.
-void launch_scatter_density(const uint32_t* xq, const Lattice& L, Bins& b, float* mesh,
+// Follows a launch_bin (whose counts it clears where that has not).
+void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
                             float* dense, hipStream_t s);
 // out_j = Sum_p coeff v_{p,j} w(x_p, node) for j = 0..2 into meshes out + j*outStride
 // (64-bit fixed point, bitwise reproducible); *vmax holds max |v| as float bits
@@ -209,8 +212,8 @@ long gather_partials(int np, int ng);
 // lattice order (by id), then x += drift p (if do_drift).  *ovf (nullable) is
 // set to 1 when a new momentum does not fit the int32 fixed-point range.
 // With count_bins (and do_drift), the drifted particles are also counted into
-// b's counts, keys and ranks for the next launch_bin(kCounted); the
-// counts must have been zeroed (launch_bin_zero) after the last scan.
+// b's counts, keys and ranks for the next launch_bin(kCounted), after a
+// launch_bin_zero.
 void launch_gather_kick_drift(uint32_t* xq, int32_t* pq, const uint32_t* id, const float* fmesh,
                               long fStride, const Lattice& L, const Bins& b, float kick,
                               float drift, int do_drift, uint32_t* ck_x, int32_t* ck_p,

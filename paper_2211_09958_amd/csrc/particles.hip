@@ -1652,9 +1652,16 @@ void launch_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 void launch_bin_zero(Bins& b, hipStream_t s) {
-    if (!b.zeroed) launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
-    b.zeroed = false;
+    if (!b.dirty) return;
+    launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
+    // a capture only records the clearing, and may never be replayed
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone)
+        b.dirty = false;
 }
+
+// Whether one launch takes the scan and the order (k_scan_index).
+static bool scan_with_order(const Bins& b) { return b.nkeys() <= kScanChunk; }
 
 void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, hipStream_t s) {
     const long P = (long)L.np * L.np * L.np;
@@ -1664,7 +1671,7 @@ void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, 
         hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((P + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            s, xq, L, b.tile, P, b.counts, b.keys, b.ranks);
     }
-    if (b.nkeys() <= kScanChunk) {
+    if (scan_with_order(b)) {
         hipLaunchKernelGGL(k_scan_index, dim3((unsigned)((P + kScanThreads - 1) / kScanThreads)),
                            dim3(kScanThreads), 0, s, b.counts, b.offsets, (int)b.nkeys(), b.keys,
                            b.ranks, P, np, b.ord);
@@ -1685,7 +1692,6 @@ void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, 
     }
     hipLaunchKernelGGL(k_index, dim3(grid_for(std::max((P + kIndexPer - 1) / kIndexPer, n))),
                        dim3(kBlock), 0, s, b.keys, b.ranks, b.offsets, P, np, b.ord, b.counts, n);
-    b.zeroed = true;
 }
 
 bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
@@ -1724,11 +1730,10 @@ static void scatter_dispatch(const uint32_t* xq, const float* v, float coeff, co
     }
 }
 
-void launch_scatter_density(const uint32_t* xq, const Lattice& L, Bins& b, float* mesh,
+void launch_scatter_density(const uint32_t* xq, const Lattice& L, const Bins& b, float* mesh,
                             float* dense, hipStream_t s) {
     scatter_dispatch<false>(xq, nullptr, 0.f, nullptr, L, b, mesh, 0, dense,
-                            b.zeroed ? nullptr : b.counts, s);
-    b.zeroed = true;
+                            scan_with_order(b) ? b.counts : nullptr, s);
 }
 
 void launch_absmax(const float* v, long n, unsigned* out, hipStream_t s) {

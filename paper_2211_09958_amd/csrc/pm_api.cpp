@@ -278,6 +278,7 @@ struct pm_ctx {
     template <class Tp>
     Tp* at(size_t off) { return reinterpret_cast<Tp*>(ws + off); }
     int fail(int code, const std::string& msg) {
+        if (code == PM_EHIP) bins.dirty = true;   // a sort may have been left half done
         err = msg;
         return code;
     }
@@ -539,8 +540,8 @@ double order_once(pm_ctx* ctx) {
     return 12.0 * ctx->P;
 }
 
-// Zeroes the bin counts for a gather that counts the particles it moves into
-// the next sort's bins.
+// Zero bin counts for a gather that counts the particles it moves into the next
+// sort's bins.
 void count_next_bins(pm_ctx* ctx) { launch_bin_zero(ctx->bins, ctx->stream); }
 
 // What compute_force and the building blocks bin: the running state (with or
@@ -1002,12 +1003,13 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
                 return PM_EHIP;
             }
     }
-    rc = upload_tables(ctx);
-    if (rc == PM_OK) {
-        launch_zero(ctx->theta, kNParam * sizeof(float), ctx->stream);
-        launch_zero(ctx->ovf, sizeof(unsigned), ctx->stream);
-        rc = ctx->hip_check("pm_init");
-    }
+    // what later calls take for granted, on whatever stream a captured one is
+    // replayed: done when pm_init returns (upload_tables waits for the stream)
+    launch_zero(ctx->theta, kNParam * sizeof(float), ctx->stream);
+    launch_zero(ctx->ovf, sizeof(unsigned), ctx->stream);
+    launch_zero(ctx->bins.counts, (ctx->bins.nkeys() + 1) * sizeof(uint32_t), ctx->stream);
+    rc = ctx->hip_check("pm_init");
+    if (rc == PM_OK) rc = upload_tables(ctx);
     if (rc != PM_OK) {
         g_err = ctx->err;
         pm_destroy(ctx);
