@@ -76,3 +76,21 @@ def test_calls_after_a_failed_one(np_, ng):
             torch.cuda.synchronize()
             assert torch.equal(out, want)
             out.zero_()
+
+
+@pytest.mark.parametrize("np_,ng", [(8, 8), (16, 64), (32, 128)])
+def test_runs_and_building_blocks_in_turn(np_, ng):
+    """Counts left by the gathers of a run and by the building blocks: a used context gives the
+    bits of a new one (densities and forces are sums of integers and fixed-order arithmetic)."""
+    noise = dev(normal((np_,) * 3, 3))
+    used = fresh(np_, ng, 2)
+    for seed in (4, 5):
+        d = dev(0.5 * 50.0 / np_ * normal((np_ ** 3, 3), seed))
+        disp = used.forward(noise)[0]
+        used.adjoint(g_disp=d)
+        got = used.density(d), used.force(d, 0.5), disp
+        new = fresh(np_, ng, 2)
+        assert new is not used
+        assert torch.equal(got[0], new.density(d))
+        assert torch.equal(got[1], new.force(d, 0.5))
+        assert torch.equal(got[2], new.forward(noise)[0])
