@@ -142,13 +142,14 @@ struct Bins {
     uint32_t* ranks;    // [P]
     uint32_t* ord;      // [P] storage slot of the k-th particle in bin order
     uint32_t* scan_tmp; // scan block sums
-    // The counts are zero between calls: zeroed with the tables, and every sort's
-    // counts are cleared by the same call's later kernels.  dirty: a call failed in
-    // between, so that they may not be
+    // The counts are zero between calls: zeroed in pm_init, and every sort's counts
+    // are cleared by the same call's later kernels.  dirty: they may not be, since a
+    // call failed in between or particles were counted that are not sorted
     bool dirty = false;
     long nkeys() const { return (long)nt * nt * nt * 8; }
 };
 
+void launch_zero(void* p, size_t bytes, hipStream_t s);
 int choose_tile(int ng);
 long scan_tmp_elems(long nkeys);
 
@@ -180,7 +181,14 @@ struct Records {
 enum Counted { kNotCounted, kCounted, kCountedOnce };
 void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, hipStream_t s);
 // Zeroes the bin counts ahead of a kernel that counts particles, if they are dirty.
-void launch_bin_zero(Bins& b, hipStream_t s);
+inline void launch_bin_zero(Bins& b, hipStream_t s) {
+    if (!b.dirty) return;
+    launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
+    // a capture only records the clearing, and may never be replayed
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone)
+        b.dirty = false;
+}
 // Moves every record array from src to dst in the order b.ord and resets b.ord
 // to the identity (each bin then a contiguous range of the records).  The
 // records must be the sorts' set: positions (3 words), momenta (3), ids (1),
@@ -364,7 +372,6 @@ long mlp_backward_scratch(int n);
 // Adam step on the mean of ngrad gradients g[ngrad][n]
 void launch_adam(float* p, const float* g, int ngrad, float* m, float* v, int n, float lr,
                  float b1, float b2, float eps, float bc1, float bc2, hipStream_t s);
-void launch_zero(void* p, size_t bytes, hipStream_t s);
 
 // Message returned by pm_last_error(NULL) (calls without a context).
 void set_context_free_error(const char* msg);

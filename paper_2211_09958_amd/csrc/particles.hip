@@ -1651,15 +1651,6 @@ void launch_zero(void* p, size_t bytes, hipStream_t s) {
     hipLaunchKernelGGL(k_zero, dim3(grid_for(n)), dim3(kBlock), 0, s, (uint32_t*)p, n);
 }
 
-void launch_bin_zero(Bins& b, hipStream_t s) {
-    if (!b.dirty) return;
-    launch_zero(b.counts, (b.nkeys() + 1) * sizeof(uint32_t), s);
-    // a capture only records the clearing, and may never be replayed
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone)
-        b.dirty = false;
-}
-
 // Whether one launch takes the scan and the order (k_scan_index).
 static bool scan_with_order(const Bins& b) { return b.nkeys() <= kScanChunk; }
 

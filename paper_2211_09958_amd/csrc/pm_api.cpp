@@ -469,9 +469,12 @@ struct RunTables {
 constexpr int kCompactEvery = 4;
 constexpr int kLatticeOrder = 1 << 20;   // forces a compaction
 
-// The working records were just written in lattice order.
+// The working records are (re)written in lattice order.  Particles already counted
+// for the next sort were counted where they no longer are (a checkpoint reset after
+// the un-drift): those counts are to be cleared.
 void records_in_lattice_order(pm_ctx* ctx) {
     ctx->sorts_since_compact = kLatticeOrder;
+    if (ctx->counts_ready) ctx->bins.dirty = true;
     ctx->counts_ready = false;
 }
 
@@ -529,9 +532,8 @@ double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = 
 // Fixed-point positions of a caller's displacements in the working positions,
 // in lattice order and counted into the bins; the running state is gone.
 void load_once(pm_ctx* ctx, const float* disp) {
+    records_in_lattice_order(ctx);
     launch_to_fixed_count(disp, ctx->xq, ctx->lat, ctx->bins, ctx->stream);
-    ctx->sorts_since_compact = kLatticeOrder;
-    ctx->counts_ready = false;
 }
 
 // Bins the positions of load_once; the records stay in lattice order.
