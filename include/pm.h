@@ -247,8 +247,9 @@ int pm_loss_mse(pm_ctx* ctx, const float* dens_dev, const float* target_dev,
  *   b = 1..n_bins (1 <= n_bins <= Ng) that hold modes and have a nonzero finite
  *   target, P_b measured from dens_dev [Ng]^3 exactly as pm_power_spectrum does.
  *   g_dens_dev [Ng]^3 out = dL/d(dens) (nullable).  loss_host nullable.  Always
- *   synchronises (the shell sums are read on the host).  PM_EINVAL when no shell
- *   is usable.  Uses the workspace meshes, so it may run between pm_forward and
+ *   synchronises (the loss is read on the host).  PM_EINVAL when no shell is
+ *   usable; PM_ENUMERIC when the sum over the shells is not finite, with g_dens left
+ *   as it was.  Uses the workspace meshes, so it may run between pm_forward and
  *   pm_adjoint.
  * pm_loss_disp: L = weight * mean_p |s_p - t_p|^2 / (box/Ng)^2 over the Np^3
  *   particles of displacement arrays disp_dev and disp_target_dev ([Np^3][3],

@@ -133,11 +133,12 @@ k_fft_x_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
 // kmul_buf >= 0: the spectrum of buffer kmul_buf is first multiplied by i k2
 // (zero on the Nyquist column), i.e. this pass also takes the spectral
 // derivative along the last axis.  DENSE: the real rows go to a caller's
-// [N][N][N] array in plain row order (as in k_fft_x_r2c).
+// [N][N][N] array in plain row order (as in k_fft_x_r2c), unless *open is 0
+// (nullable; one wave-uniform load).
 template <int N, bool DENSE>
 __global__ void __launch_bounds__(Cfg<N / 2>::T * Cfg<N / 2>::ROWS)
-k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, int cs, long nrows, long bufStride, int kmul_buf,
-            const float2* __restrict__ tw, int ntw,
+k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, const int* __restrict__ open, int cs,
+            long nrows, long bufStride, int kmul_buf, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     constexpr int H = N / 2, E = Cfg<H>::E, T = Cfg<H>::T, ROWS = Cfg<H>::ROWS;
     constexpr int LS = lds_slots(H);
@@ -149,6 +150,7 @@ k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, int cs, long nro
     const int twN = ntw / N;
     float2* L = lds + r * LS;
     const bool kmul = (int)blockIdx.y == kmul_buf;
+    const bool store = !DENSE || !open || *open != 0;
     // rowp points at row 0 for rows past the end, so every load is in bounds
     // and none sits in a branch (which would make each wait for its data)
     float2 x[E];
@@ -180,7 +182,7 @@ k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, int cs, long nro
     __syncthreads();
     fft_lds<H, E, 1>(v, L, 1, 0, j, st);
     __syncthreads();
-    if (!valid) return;
+    if (!valid || !store) return;
     float* dst = reinterpret_cast<float*>(rowp);
     if constexpr (DENSE) dst = real + plain_row(row, N) * N;
 #pragma unroll
@@ -589,20 +591,22 @@ k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
 }
 
 // Inverse: spectrum of plane blockIdx.x -> real rows, in place in buffer
-// blockIdx.y or to the dense array `real` when given.  FORCE: grid row 0 takes
+// blockIdx.y or to the dense array `real` when given (unless *open is 0, as in
+// k_fft_x_c2r).  FORCE: grid row 0 takes
 // buffer 0 in place; rows 1 and 2 both read `g` and leave the axis-1 derivative
 // (times i n1 before the axis-1 transform) in buffer 1 and the axis-2 derivative
 // (times i k2 before the axis-2 transform) in buffer 2.
 template <int N, bool FORCE>
 __global__ void __launch_bounds__(Plane<N>::NT)
-k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real, int cs,
-            long bufStride, const float2* __restrict__ tw, int ntw,
+k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
+            const int* __restrict__ open, int cs, long bufStride, const float2* __restrict__ tw, int ntw,
             const float2* __restrict__ st) {
     using P = Plane<N>;
     __shared__ float2 lds[P::ALL];
     const int i0 = (int)xcd_block(blockIdx.x, N), comp = blockIdx.y;
     float2* b = buf + comp * bufStride;
     const float2* src = FORCE && comp > 0 ? g : b;
+    const bool store = FORCE || !open || *open != 0;
     float2 w[P::EX];
 #pragma unroll
     for (int e = 0; e < P::EX; ++e)
@@ -618,6 +622,7 @@ k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
         plane_columns<N, 1, false>(lds, st, spectrum);
     }
     plane_rows_c2r<N>(lds, FORCE && comp == 2, w, st);
+    if (!store) return;
 #pragma unroll
     for (int u = 0; u < (N * P::H + P::NT - 1) / P::NT; ++u) {
         const int i = u * P::NT + threadIdx.x;
@@ -1355,16 +1360,16 @@ void x_r2c(const float* real, float2* buf, int cs, int nbuf, long bufStride, con
 
 template <int N>
 void x_c2r(float2* buf, float* real, int cs, int nbuf, long bufStride, int kmul_buf,
-           const Twiddles& tw, hipStream_t s) {
+           const Twiddles& tw, hipStream_t s, const int* open = nullptr) {
     constexpr int ROWS = Cfg<N / 2>::ROWS, T = Cfg<N / 2>::T;
     long nrows = (long)N * N;
     dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS), nbuf);
     if (real)
-        hipLaunchKernelGGL((k_fft_x_c2r<N, true>), grid, dim3(T * ROWS), 0, s, buf, real, cs, nrows,
-                           bufStride, kmul_buf, tw.w, tw.n, tw.stages);
-    else
-        hipLaunchKernelGGL((k_fft_x_c2r<N, false>), grid, dim3(T * ROWS), 0, s, buf, nullptr, cs,
+        hipLaunchKernelGGL((k_fft_x_c2r<N, true>), grid, dim3(T * ROWS), 0, s, buf, real, open, cs,
                            nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
+    else
+        hipLaunchKernelGGL((k_fft_x_c2r<N, false>), grid, dim3(T * ROWS), 0, s, buf, nullptr, nullptr,
+                           cs, nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
 }
 
 template <int N, int DIR, int AXIS, bool SPEC, class Spec>
@@ -1396,8 +1401,10 @@ void launch_fft_x_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, cons
 }
 
 void launch_fft_x_c2r_to(float2* buf, float* real, int n, int cs, const Twiddles& tw,
-                         hipStream_t s) {
-    pass_switch(n, [&](auto nn) { x_c2r<decltype(nn)::value>(buf, real, cs, 1, 0, -1, tw, s); });
+                         hipStream_t s, const int* open) {
+    pass_switch(n, [&](auto nn) {
+        x_c2r<decltype(nn)::value>(buf, real, cs, 1, 0, -1, tw, s, open);
+    });
 }
 
 void launch_fft_x_c2r_dk2(float2* buf, int n, int cs, int nbuf, long bufStride, int kmul_buf,
@@ -1531,17 +1538,17 @@ void launch_fft_xy_r2c(const float* real, float2* buf, int n, int cs, int nbuf, 
 }
 
 void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long bufStride,
-                       const Twiddles& tw, hipStream_t s) {
+                       const Twiddles& tw, hipStream_t s, const int* open) {
     if (n <= kMaxPlane) {
         plane_switch(n, [&](auto nn) {
             constexpr int N = decltype(nn)::value;
             hipLaunchKernelGGL((k_plane_c2r<N, false>), dim3(N, nbuf), dim3(Plane<N>::NT), 0, s,
-                               buf, nullptr, real, cs, bufStride, tw.w, tw.n, tw.stages);
+                               buf, nullptr, real, open, cs, bufStride, tw.w, tw.n, tw.stages);
         });
         return;
     }
     launch_fft_y(buf, n, cs, 1, nbuf, bufStride, tw, s);
-    if (real) launch_fft_x_c2r_to(buf, real, n, cs, tw, s);
+    if (real) launch_fft_x_c2r_to(buf, real, n, cs, tw, s, open);
     else launch_fft_x_c2r(buf, n, cs, nbuf, bufStride, tw, s);
 }
 
@@ -1559,7 +1566,7 @@ void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bu
     plane_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         hipLaunchKernelGGL((k_plane_c2r<N, true>), dim3(N, 3), dim3(Plane<N>::NT), 0, s, buf, g,
-                           nullptr, cs, bufStride, tw.w, tw.n, tw.stages);
+                           nullptr, nullptr, cs, bufStride, tw.w, tw.n, tw.stages);
     });
 }
 
@@ -1598,7 +1605,7 @@ void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int 
 }
 
 void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, const float* table,
-                            const Twiddles& tw, hipStream_t s) {
+                            const int* open, const Twiddles& tw, hipStream_t s) {
     size_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
         constexpr int W = Cfg<N>::W, T = Cfg<N>::T;
@@ -1606,7 +1613,7 @@ void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, 
         hipLaunchKernelGGL(k_fft_shell_scale<N>, dim3(N * ncb), dim3(T * W), 0, s, buf, cs, ncb,
                            nbins, table, tw.stages);
     });
-    launch_fft_yx_c2r(buf, real, n, cs, 1, 0, tw, s);
+    launch_fft_yx_c2r(buf, real, n, cs, 1, 0, tw, s, open);
 }
 
 void launch_fft3_r2c_dense(const float* real, float2* buf, float2* spec, int n, int cs,

@@ -33,11 +33,12 @@ constexpr int kMaxPlane = 64;
 // Axes 2 and 1 of `nbuf` buffers `bufStride` float2 apart, in place: real rows ->
 // half spectra transformed along both (r2c), and back (c2r).  With `real` (one
 // buffer) the real rows are read from, or written to, a dense [n]^3 array in
-// plain row order.
+// plain row order.  c2r with `real` and `open`: nothing is written to `real` when
+// *open, on the device, is 0.
 void launch_fft_xy_r2c(const float* real, float2* buf, int n, int cs, int nbuf, long bufStride,
                        const Twiddles& tw, hipStream_t s);
 void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long bufStride,
-                       const Twiddles& tw, hipStream_t s);
+                       const Twiddles& tw, hipStream_t s, const int* open = nullptr);
 // n <= kMaxPlane: three real buffers -> S_0 in the first and n1 S_1 + k2 S_2 in
 // the second (the inputs of launch_grad_adj_z)
 void launch_plane_r2c_merge(float2* buf, int n, int cs, long bufStride, const Twiddles& tw,
@@ -56,9 +57,10 @@ void launch_fft_x_r2c_from(const float* real, float2* buf, int n, int cs, const 
                            hipStream_t s);
 // Inverse of the above without the 1/n factor (Hermitian rows assumed).
 void launch_fft_x_c2r(float2* buf, int n, int cs, int nbuf, long bufStride, const Twiddles& tw, hipStream_t s);
-// The same with the real rows written to a dense [n]^3 array in plain row order.
+// The same with the real rows written to a dense [n]^3 array in plain row order
+// (unless `open` is given and *open is 0).
 void launch_fft_x_c2r_to(float2* buf, float* real, int n, int cs, const Twiddles& tw,
-                         hipStream_t s);
+                         hipStream_t s, const int* open = nullptr);
 // as launch_fft_x_c2r, with buffer kmul_buf multiplied by i k2 first
 void launch_fft_x_c2r_dk2(float2* buf, int n, int cs, int nbuf, long bufStride, int kmul_buf,
                           const Twiddles& tw, hipStream_t s);
@@ -107,9 +109,10 @@ void launch_fft3_c2r_dense(const float2* spec, float2* buf, float* real, int n, 
 void launch_fft_shells(const float* real, float2* buf, float2* part, int n, int cs, int nbins,
                        double* bins, const Twiddles& tw, hipStream_t s);
 // real = unnormalised inverse DFT of table[b - 1] d_k (0 off the shells) for the
-// spectrum that launch_fft_shells left in `buf`; table has nbins values.
+// spectrum that launch_fft_shells left in `buf`; table has nbins values.  Nothing is
+// written to `real` when *open is 0.
 void launch_fft_shell_scale(float2* buf, float* real, int n, int cs, int nbins, const float* table,
-                            const Twiddles& tw, hipStream_t s);
+                            const int* open, const Twiddles& tw, hipStream_t s);
 
 // ---------------------------------------------------------------- particles
 // Particle state is fixed point so that kick and drift are exactly invertible:
@@ -346,10 +349,11 @@ void launch_mse(const float* d, const float* t, float* g, long n3, double* parti
                 int nblocks, hipStream_t s);
 // P(k) loss from launch_fft_shells' bins: with P_b = norm bins[3b]/bins[3b+2] and
 // the shells that hold modes and a nonzero finite target,
-// out[0] = weight mean_b (P_b / target_b - 1)^2, and table[b] = 2 norm /
-// bins[3b+2] dL/dP_b (0 on the other shells).
+// out[0] = weight mean_b (P_b / target_b - 1)^2, out[1] = the sum of the squares,
+// *finite = whether that is finite, and table[b] = 2 norm / bins[3b+2] dL/dP_b (0 on
+// the other shells).
 void launch_pk_loss(const double* bins, const double* target, int nbins, double norm, double weight,
-                    double* out, float* table, hipStream_t s);
+                    double* out, float* table, int* finite, hipStream_t s);
 // block partials of Sum (minimum-image a - b)^2; g = gscale * (a - b) wrapped (nullable)
 void launch_mse_periodic(const float* a, const float* b, float* g, long n, float box, float gscale,
                          double* partials, int nblocks, hipStream_t s);

@@ -1570,7 +1570,8 @@ k_mse(const float* __restrict__ d, const float* __restrict__ t, float* __restric
 // One work-group (see launch_pk_loss).
 __global__ void __launch_bounds__(kBlock)
 k_pk_loss(const double* __restrict__ bins, const double* __restrict__ target, int nbins,
-          double norm, double weight, double* __restrict__ out, float* __restrict__ table) {
+          double norm, double weight, double* __restrict__ out, float* __restrict__ table,
+          int* __restrict__ finite) {
     __shared__ double tot[2];
     double acc = 0.0, used = 0.0;
     auto usable = [&](int b) {
@@ -1588,6 +1589,8 @@ k_pk_loss(const double* __restrict__ bins, const double* __restrict__ target, in
         tot[0] = acc;
         tot[1] = used;
         out[0] = weight * acc / used;
+        out[1] = acc;
+        *finite = isfinite(acc) ? 1 : 0;
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nbins; b += kBlock) {
@@ -1987,9 +1990,9 @@ void launch_mse(const float* d, const float* t, float* g, long n3, double* parti
 }
 
 void launch_pk_loss(const double* bins, const double* target, int nbins, double norm, double weight,
-                    double* out, float* table, hipStream_t s) {
+                    double* out, float* table, int* finite, hipStream_t s) {
     hipLaunchKernelGGL(k_pk_loss, dim3(1), dim3(kBlock), 0, s, bins, target, nbins, norm, weight,
-                       out, table);
+                       out, table, finite);
 }
 
 void launch_mse_periodic(const float* a, const float* b, float* g, long n, float box, float gscale,

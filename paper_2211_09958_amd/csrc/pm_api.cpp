@@ -168,7 +168,8 @@ struct Plan {
         radial_ic = take(ntab_p * sizeof(float));
         radial_ic_dom = take(ntab_p * sizeof(float));
         radial_lpt = take(ntab_p * sizeof(float));
-        losstab = take(ntab_f * sizeof(float));
+        losstab = take(std::max(ntab_f * sizeof(float),
+                                ng * (sizeof(double) + sizeof(float)) + sizeof(int)));
         tw = take((size_t)ng * sizeof(float2));
         tw_stages = take(kStageTableSize * sizeof(float2));
         // FP64 block partials: sets of at most 4096 grid-stride blocks (nine of
@@ -1366,23 +1367,26 @@ int pm_loss_pk(pm_ctx* ctx, const float* dens, int32_t n_bins, const double* pk_
     const int ng = ctx->ng;
     // P_b = L^3 / Ng^6 <|delta_k|^2>_b; dL/d delta(x) = 2 Sum_k t_k delta_k e^{ik.x}
     // (unnormalised inverse DFT) with t_k = dL/dP_b L^3 / (Ng^6 N_b), one value per
-    // shell.  Targets and shell factors live in losstab: [n_bins] | [n_bins]
+    // shell.  Targets, shell factors and whether the loss is finite (only then is
+    // g_dens written) live in losstab: [n_bins] | [n_bins] | 1
     const double L = ctx->cfg.box, norm = L * L * L / std::pow((double)ng, 6.0);
     double* target_dev = reinterpret_cast<double*>(ctx->losstab);
     float* table_dev = reinterpret_cast<float*>(target_dev + n_bins);
+    int* finite_dev = reinterpret_cast<int*>(table_dev + n_bins);
     ctx->loss_target.assign(pk_target, pk_target + n_bins);
     if (hipMemcpyAsync(target_dev, ctx->loss_target.data(), n_bins * sizeof(double),
                        hipMemcpyHostToDevice, s) != hipSuccess)
         return ctx->fail(PM_EHIP, "upload of the loss targets failed");
     launch_fft_shells(dens, ctx->C[0], ctx->C[1], ng, ctx->cs, n_bins, ctx->pkbins, ctx->twd, s);
-    launch_pk_loss(ctx->pkbins, target_dev, n_bins, norm, weight, ctx->res_dev, table_dev, s);
+    launch_pk_loss(ctx->pkbins, target_dev, n_bins, norm, weight, ctx->res_dev, table_dev,
+                   finite_dev, s);
     if (g_dens)
-        launch_fft_shell_scale(ctx->C[0], g_dens, ng, ctx->cs, n_bins, table_dev, ctx->twd, s);
+        launch_fft_shell_scale(ctx->C[0], g_dens, ng, ctx->cs, n_bins, table_dev, finite_dev,
+                               ctx->twd, s);
     PM_TRY(ctx->hip_check("pm_loss_pk"));
     PM_TRY(ctx->wait("the P(k) loss"));
-    const double v = ctx->res_host[0];
-    if (loss) *loss = v;
-    if (!std::isfinite(v)) return ctx->fail(PM_ENUMERIC, "non-finite P(k) loss");
+    if (loss) *loss = ctx->res_host[0];
+    if (!std::isfinite(ctx->res_host[1])) return ctx->fail(PM_ENUMERIC, "non-finite P(k) loss");
     return PM_OK;
 }
 
