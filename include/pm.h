@@ -169,7 +169,9 @@ int pm_lpt2_growth(const pm_config* cfg, const pm_cosmology* cosmo, double* out_
 
 /* Create a context.  `workspace_dev` must hold pm_workspace_bytes(cfg) bytes,
  * 256-byte aligned, and stay valid until pm_destroy.  `hip_stream` is a
- * hipStream_t (NULL = the default stream).  Uploads the host tables. */
+ * hipStream_t (NULL = the default stream).  Uploads the host tables and waits for
+ * the stream.  Takes pinned host memory for scalar results: 24 Ng or 16 n_steps +
+ * 2320 bytes, whichever is more, rounded up to a power of two of 4096 or more. */
 int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace_dev,
             size_t workspace_bytes, void* hip_stream, pm_ctx** out);
 
@@ -333,7 +335,10 @@ int pm_adam(pm_ctx* ctx, float* param_dev, const float* grad_dev, int32_t n_grad
 int pm_stats_get(pm_ctx* ctx, pm_stats* out);
 int pm_stats_reset(pm_ctx* ctx);
 
-/* Free host-side state (never the caller's device memory). */
+/* Free host-side state (never the caller's device memory).  Does not wait for the
+ * device: of the contexts' pinned host memory, up to 32 blocks and 1 MB in all are
+ * kept for later contexts of the process.  Only beyond that, and after PM_EHIP, is it
+ * freed here, which waits for the device's streams. */
 void pm_destroy(pm_ctx* ctx);
 
 /* Message for the last error on ctx (or of context-less calls when ctx is

@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <utility>
 #include <string>
 #include <vector>
@@ -39,6 +40,60 @@ constexpr int kNParam = 4417;
 constexpr int kExtraSlots = 16 + 2 * PM_MAX_CHECKPOINTS;
 
 thread_local std::string g_err;
+
+// Pinned host memory for the scalar results of the process's contexts.  Freeing it
+// waits for the whole device and invalidates captures on other streams, so a block
+// that pm_destroy gives back is kept for a later pm_init, up to kKept blocks and
+// kKeptBytes; only what is beyond that is freed.  No kernel writes to a block that is
+// given back: every call that has one do so waits for it.
+class ResultBlocks {
+  public:
+    static constexpr int kKept = 32;
+    static constexpr size_t kKeptBytes = 1u << 20;
+
+    // a block of at least `need` bytes (sizes are powers of two, so that contexts of
+    // one configuration find each other's), on any device; null when that fails
+    void* take(size_t need, size_t* bytes) {
+        *bytes = 4096;
+        while (*bytes < need) *bytes *= 2;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            for (int i = 0; i < n_; ++i)
+                if (kept_[i].bytes == *bytes) {
+                    void* p = kept_[i].p;
+                    kept_[i] = kept_[--n_];
+                    total_ -= *bytes;
+                    return p;
+                }
+        }
+        void* p = nullptr;
+        return hipHostMalloc(&p, *bytes, hipHostMallocMapped | hipHostMallocPortable) == hipSuccess
+                   ? p
+                   : nullptr;
+    }
+    void give(void* p, size_t bytes) {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            if (n_ < kKept && total_ + bytes <= kKeptBytes) {
+                kept_[n_++] = {p, bytes};
+                total_ += bytes;
+                return;
+            }
+        }
+        (void)hipHostFree(p);
+    }
+
+  private:
+    struct Block {
+        void* p;
+        size_t bytes;
+    };
+    std::mutex mu_;
+    Block kept_[kKept];
+    int n_ = 0;
+    size_t total_ = 0;
+};
+ResultBlocks g_results;
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
@@ -228,6 +283,8 @@ struct pm_ctx {
     // the wait, this takes 12.5.
     double* res_host = nullptr;
     double* res_dev = nullptr;
+    size_t res_bytes = 0;
+    bool hip_failed = false;   // a call ended without its wait: writes may be under way
     float2* tw;
     float2* tw_stages;
     Twiddles twd;
@@ -279,7 +336,10 @@ struct pm_ctx {
     template <class Tp>
     Tp* at(size_t off) { return reinterpret_cast<Tp*>(ws + off); }
     int fail(int code, const std::string& msg) {
-        if (code == PM_EHIP) bins.dirty = true;   // a sort may have been left half done
+        if (code == PM_EHIP) {
+            bins.dirty = true;   // a sort may have been left half done
+            hip_failed = true;
+        }
         err = msg;
         return code;
     }
@@ -987,8 +1047,8 @@ int pm_init(const pm_config* cfg, const pm_cosmology* cosmo, void* workspace, si
         const size_t n = std::max<size_t>(3 * (size_t)ctx->ng,
                                           2 * (size_t)cfg->n_steps + 2 + 2 * kExtraSlots);
         void* dev = nullptr;
-        if (hipHostMalloc(reinterpret_cast<void**>(&ctx->res_host), n * sizeof(double),
-                          hipHostMallocMapped) != hipSuccess ||
+        ctx->res_host = static_cast<double*>(g_results.take(n * sizeof(double), &ctx->res_bytes));
+        if (!ctx->res_host ||
             hipHostGetDevicePointer(&dev, ctx->res_host, 0) != hipSuccess) {
             g_err = "hipHostMalloc failed";
             pm_destroy(ctx);
@@ -1552,7 +1612,8 @@ void pm_destroy(pm_ctx* ctx) {
         if (ctx->ev[k]) (void)hipEventDestroy(ctx->ev[k]);
     for (hipEvent_t e : ctx->pool)
         if (e) (void)hipEventDestroy(e);
-    if (ctx->res_host) (void)hipHostFree(ctx->res_host);   // waits for the device's streams
+    if (ctx->res_host && ctx->hip_failed) (void)hipHostFree(ctx->res_host);   // waits
+    else if (ctx->res_host) g_results.give(ctx->res_host, ctx->res_bytes);
     delete ctx;
 }
 

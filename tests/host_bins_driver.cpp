@@ -26,6 +26,7 @@ hipError_t last_error = hipSuccess;
 const char* where = "";
 
 long checks = 0;
+std::map<void*, size_t> pinned;
 
 void need(const void* p, State want, const char* what) {
     ++checks;
@@ -73,9 +74,11 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
     *p = std::calloc(n, 1);
+    pinned[*p] = n;
     return hipSuccess;
 }
 hipError_t hipHostFree(void* p) {
+    pinned.erase(p);
     std::free(p);
     return hipSuccess;
 }
@@ -223,6 +226,29 @@ int main() {
                         r.everything();
                     }
                 }
+    // pinned memory kept from many contexts at a time: bounded, and used again
+    pm_config c{8, 8, 32.0, 1.0 / 64, 0.5, 1, 0, 0, 0};
+    for (int turn = 0; turn < 2; ++turn) {
+        std::vector<Run*> runs;
+        for (int k = 0; k < 40; ++k) {
+            c.mesh = k % 2 ? 8 : 256;
+            runs.push_back(new Run(c));
+        }
+        if (pinned.size() != 40) return 6;
+        for (Run* r : runs) delete r;
+        size_t bytes = 0;
+        for (auto& b : pinned) bytes += b.second;
+        if (pinned.size() > 32 || bytes > (1u << 20)) return 7;
+    }
+    // a block that a failed call may still write to is not kept
+    const size_t before = pinned.size();
+    {
+        Run r(c);
+        if (pinned.size() != before) return 8;
+        last_error = hipErrorUnknown;
+        if (pm_density(r.ctx, r.x, r.x) != PM_EHIP) return 8;
+    }
+    if (pinned.size() != before - 1) return 9;
     std::printf("ok %ld\n", checks);
     return 0;
 }
