@@ -156,21 +156,33 @@ void launch_zero(void* p, size_t bytes, hipStream_t s);
 int choose_tile(int ng);
 long scan_tmp_elems(long nkeys);
 
-// Per-particle arrays that move together when the particles are re-sorted.
+// The per-particle arrays that move together when the particles are re-sorted, from
+// src to dst: positions, momenta and ids (3, 3 and 1 words per particle), and with
+// `cotangents` also xi and pi (3 words each).
 struct Records {
-    int n = 0;
-    const uint32_t* src[6];
-    uint32_t* dst[6];
-    int words[6];       // 32-bit words per particle
-    // sources in lattice order: the ids (third) are the slots and are not read, and
-    // a null source of the fourth and fifth (xi, pi) stands for zeros (fifth: not
-    // written either when its destination is null)
+    const uint32_t* src[5] = {};
+    uint32_t* dst[5] = {};
+    bool cotangents = false;
+    // with cotangents, sources in lattice order: the ids are the slots and are not
+    // read, and a null xi or pi stands for zeros (pi: not written either when its
+    // destination is null)
     bool lattice = false;
-    void add(const void* from, void* to, int w) {
-        src[n] = static_cast<const uint32_t*>(from);
-        dst[n] = static_cast<uint32_t*>(to);
-        words[n] = w;
-        ++n;
+    void set(int k, const void* from, void* to) {
+        src[k] = static_cast<const uint32_t*>(from);
+        dst[k] = static_cast<uint32_t*>(to);
+    }
+    void state(const uint32_t* x, uint32_t* x_to, const int32_t* p, int32_t* p_to,
+               const uint32_t* id, uint32_t* id_to) {
+        set(0, x, x_to);
+        set(1, p, p_to);
+        set(2, id, id_to);
+    }
+    void add_cotangents(const float* xi, float* xi_to, const float* pi, float* pi_to,
+                        bool from_lattice) {
+        set(3, xi, xi_to);
+        set(4, pi, pi_to);
+        cotangents = true;
+        lattice = from_lattice;
     }
 };
 
@@ -193,11 +205,8 @@ inline void launch_bin_zero(Bins& b, hipStream_t s) {
         b.dirty = false;
 }
 // Moves every record array from src to dst in the order b.ord and resets b.ord
-// to the identity (each bin then a contiguous range of the records).  The
-// records must be the sorts' set: positions (3 words), momenta (3), ids (1),
-// optionally followed by xi (3) and pi (3); returns false, launching nothing,
-// for any other layout.
-bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
+// to the identity (each bin then a contiguous range of the records).
+void launch_compact(Bins& b, const Records& rec, long P, hipStream_t s);
 // Density delta = rho - 1 (particle mass (ng/np)^3) into a real mesh with pitch
 // L.rp (nullable) and/or a caller's dense [ng]^3 array in plain order (nullable,
 // any 4-byte alignment); every cell written once (no pre-zeroing), deterministic.

@@ -394,11 +394,10 @@ k_scan_index(const uint32_t* __restrict__ counts, uint32_t* __restrict__ offsets
     if (i < P) ord[off[key] + rank] = (uint32_t)(np ? patch_index(i, np, jj) : i);
 }
 
-// Words per particle of the record sets the sorts move: positions, momenta,
-// ids, then (with the cotangents) xi and pi.
+// Words per particle of the arrays of Records.
 constexpr int kSortWords[5] = {3, 3, 1, 3, 3};
 
-// Compaction of the first N arrays of that layout: record k of every dst array
+// Compaction of the first N of them: record k of every dst array
 // <- record ord[k] of its src array, then ord[k] = k.  With the word counts
 // fixed at compile time every gather load of a particle is issued before the
 // first wait and before any store (a load after a store to an array the
@@ -1688,18 +1687,14 @@ void launch_bin(const uint32_t* xq, const Lattice& L, Bins& b, Counted counted, 
                        dim3(kBlock), 0, s, b.keys, b.ranks, b.offsets, P, np, b.ord, b.counts, n);
 }
 
-bool launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
-    bool sorted_layout = rec.n == 3 || rec.n == 5;
-    for (int a = 0; a < rec.n && sorted_layout; ++a) sorted_layout = rec.words[a] == kSortWords[a];
-    if (!sorted_layout) return false;
+void launch_compact(Bins& b, const Records& rec, long P, hipStream_t s) {
     const dim3 grid((unsigned)((P + kBlock - 1) / kBlock));
-    if (rec.n == 3)
+    if (!rec.cotangents)
         hipLaunchKernelGGL((k_compact_sorted<3, false>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
     else if (rec.lattice)
         hipLaunchKernelGGL((k_compact_sorted<5, true>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
     else
         hipLaunchKernelGGL((k_compact_sorted<5, false>), grid, dim3(kBlock), 0, s, b.ord, P, rec);
-    return true;
 }
 
 template <bool VEC>

@@ -549,12 +549,13 @@ struct ReverseStart {
 
 // Bin the working particles (bin offsets and order in ctx->bins); compact the
 // records (positions, momenta, ids, and with `cotangents` also xi and pi) when
-// due.  With `start` (and cotangents) the compaction takes the records from there,
+// due.  With `start` (with cotangents) the compaction takes the records from there,
 // so that they are never copied in lattice order first (512^3 particles: 2.7 ms of
 // copies, clears and their reading back).  Returns the bytes moved, for the timing
 // statistics.
 double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = nullptr) {
     const double P = (double)ctx->P;
+    cotangents = cotangents || start;
     if (start) records_in_lattice_order(ctx);
     launch_bin(start ? start->x : ctx->xq, ctx->lat, ctx->bins,
                ctx->counts_ready ? kCounted : kNotCounted, ctx->stream);
@@ -565,20 +566,16 @@ double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = 
     if (++ctx->sorts_since_compact <= kCompactEvery) return bytes;
     ctx->sorts_since_compact = 1;
     Records rec;
-    rec.lattice = start != nullptr;
-    rec.add(start ? start->x : ctx->xq, ctx->xq_alt, 3);
-    rec.add(start ? start->p : ctx->pq, ctx->pq_alt, 3);
-    rec.add(ctx->id, ctx->id_alt, 1);
-    if (cotangents) {
-        rec.add(start ? start->xi : ctx->xi, ctx->xi_alt, 3);
-        // without a momentum cotangent nothing reads pi before the un-drift writes it
-        // (512^3 particles on 1024^3: compaction 3.93 -> 2.64 ms, un-kick at x_N,
-        // which then leaves xi alone, 6.18 -> 5.15)
-        rec.add(start ? start->pi : ctx->pi, start && !start->pi ? nullptr : ctx->pi_alt, 3);
-    }
-    // (the set above is the one launch_compact moves; were it refused, the
-    // records would stay where they are and the order would still hold)
-    if (!launch_compact(ctx->bins, rec, ctx->P, ctx->stream)) return bytes;
+    rec.state(start ? start->x : ctx->xq, ctx->xq_alt, start ? start->p : ctx->pq, ctx->pq_alt,
+              ctx->id, ctx->id_alt);
+    // without a momentum cotangent nothing reads pi before the un-drift writes it
+    // (512^3 particles on 1024^3: compaction 3.93 -> 2.64 ms, un-kick at x_N,
+    // which then leaves xi alone, 6.18 -> 5.15)
+    if (start)
+        rec.add_cotangents(start->xi, ctx->xi_alt, start->pi, start->pi ? ctx->pi_alt : nullptr, true);
+    else if (cotangents)
+        rec.add_cotangents(ctx->xi, ctx->xi_alt, ctx->pi, ctx->pi_alt, false);
+    launch_compact(ctx->bins, rec, ctx->P, ctx->stream);
     std::swap(ctx->xq, ctx->xq_alt);
     std::swap(ctx->pq, ctx->pq_alt);
     std::swap(ctx->id, ctx->id_alt);

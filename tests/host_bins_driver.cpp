@@ -134,7 +134,6 @@ void launch_undrift(uint32_t*, const int32_t*, const float*, float*, const Latti
                     float, double*, float*, int, hipStream_t) {
     count(b, "first un-drift");
 }
-bool launch_compact(Bins&, const Records&, long, hipStream_t) { return true; }
 
 }  // namespace pmx
 
