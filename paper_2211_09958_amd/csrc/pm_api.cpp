@@ -583,7 +583,7 @@ double sort_particles(pm_ctx* ctx, bool cotangents, const ReverseStart* start = 
         std::swap(ctx->xi, ctx->xi_alt);
         std::swap(ctx->pi, ctx->pi_alt);
     }
-    if (start) return bytes + (64.0 + (start->xi ? 12 : 0) + (start->pi ? 24 : 0)) * P;
+    if (start) return bytes + (72.0 + (start->xi ? 12 : 0) + (start->pi ? 24 : 0)) * P;
     return bytes + (cotangents ? 112.0 : 64.0) * P;
 }
 
@@ -680,7 +680,9 @@ void vjp_mesh(pm_ctx* ctx, const uint32_t* xq, const float* v, float coeff, cons
     }
     const float fscale = (float)(ctx->cfg.box / (2.0 * kPi) / std::pow((double)ng, 3.0));
     // (C3 is free: its spectrum went into C2's)
-    { KTimer t(ctx, PM_K_GRAD_ADJ_Z, (fbar ? 4 : 3) * c);
+    // filter: delta_k read again, and the terms of +-n0 written and read (4 bytes each)
+    const double terms = 4.0 * ng * (ng / 2 + 1.0) * (ng / 2 + 1.0);
+    { KTimer t(ctx, PM_K_GRAD_ADJ_Z, fbar ? 4 * c + 2 * terms : 3 * c);
       launch_grad_adj_z(ctx->C[1], cst, ctx->C[0], ctx->C[0], ng, cs, radial, fbar,
                         ctx->creal(3), fscale, ctx->twd, s); }
     if (planes) {
@@ -1219,7 +1221,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     compute_force(ctx, radial, kStateCotangents, nullptr, &start);
     const int ngather = (int)gather_partials(ctx->np, ctx->ng);
     if (g_dens) {
-        KTimer t(ctx, PM_K_WGRAD, 24.0 * P + mesh_r(ctx->ng));
+        KTimer t(ctx, PM_K_WGRAD, 36.0 * P + mesh_r(ctx->ng));
         launch_wgrad(g_dens, ctx->ng, mass, ctx->xq, ctx->pq, ctx->xi, ctx->pi, ctx->lat,
                      ctx->bins, 0.f, 2, nullptr, s, true);
     }
@@ -1244,7 +1246,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
         tables.done(N - n - 1);
         count_next_bins(ctx);   // the un-drifted particles are binned for F(x_n)
         if (pi_zero) {
-            KTimer t(ctx, PM_K_WGRAD, 80.0 * P);
+            KTimer t(ctx, PM_K_WGRAD, 68.0 * P);
             launch_undrift(ctx->xq, ctx->pq, ctx->xi, ctx->pi, ctx->lat, ctx->bins,
                            (float)sc.drift[n], ctx->parts_a, ctx->pmax, nb, s);
         } else {

@@ -1,5 +1,5 @@
 // Host-only model of what the library's calls do to the bin counts, built with g++
-// by tests/test_host_bin_counts.py: pm_api.cpp as it is, over launchers that only
+// by tests/host_model.py: pm_api.cpp as it is, over launchers that only
 // track whether a context's counts are zero, counted or unknown on the device.  A
 // kernel that counts must find them zero and a sort must find them counted exactly
 // once; anything else would write the order out of range on a GPU.
@@ -177,7 +177,25 @@ struct Run {
 
 }  // namespace
 
-int main() {
+// kernel_bytes of one step and its adjoint: family, bytes
+int print_bytes(int mesh, int filter, bool density, bool displacement, bool momentum) {
+    const pm_config c{8, mesh, 32.0, 1.0 / 64, 0.5, 1, 0, filter, PM_F_TIMING};
+    Run r(c);
+    if (r.forward() != PM_OK || pm_stats_reset(r.ctx) != PM_OK) return 1;
+    float* x = r.x;
+    if (pm_adjoint(r.ctx, density ? x : nullptr, displacement ? x : nullptr,
+                   momentum ? x : nullptr, x, nullptr, nullptr) != PM_OK)
+        return 1;
+    pm_stats s;
+    if (pm_stats_get(r.ctx, &s) != PM_OK) return 1;
+    for (int k = 0; k < PM_NKERNELS; ++k) std::printf("%.0f\n", s.kernel_bytes[k]);
+    return 0;
+}
+
+int main(int argc, char** argv) {
+    if (argc == 6)
+        return print_bytes(std::atoi(argv[1]), std::atoi(argv[2]), std::atoi(argv[3]),
+                           std::atoi(argv[4]), std::atoi(argv[5]));
     for (int ng : {8, 128})
         for (int steps : {1, 5})
             for (int ckpt : {0, 1, 2})
