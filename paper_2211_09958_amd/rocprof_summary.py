@@ -13,7 +13,7 @@ Only the dispatches between the two marker kernels that bench.py launches around
 timed region (a one-element uint8 fill before and after) are counted, so the launch mix
 is that of the timed steps.  The family byte models are the ones the library uses for
 its live accounting (mesh r = 4 Ng^3 bytes, half spectrum c = 8 Ng^2 (Ng/2+1), P
-particles).
+particles, filter terms t = 4 Ng (Ng/2+1)^2).
 
     python -m paper_2211_09958_amd.rocprof_summary --kt DIR/kt_results.db \
         [--fetch DB --write DB] --ptcl 512 --mesh 1024 --workload NAME --out DIR \
@@ -96,7 +96,11 @@ def family(sym: str, ng: int):
     if base in ("k_grad_z", "k_grad_z_pipe") and targs[:1] == [str(ng)]:
         return "grad_z", "3c"
     if base in ("k_grad_adj_z", "k_grad_adj_z_pipe") and targs[:1] == [str(ng)]:
-        return "grad_adj_z", "4c" if targs[1:] == ["true"] else "3c"
+        return "grad_adj_z", "4c+t" if targs[1:] == ["true"] else "3c"
+    # the sums of the filter's mode terms (t), in the same family as the pass that
+    # writes them; the second kernel's partial sums are not algorithmic bytes
+    if base in ("k_filter_shells", "k_filter_sum"):
+        return "grad_adj_z", "t" if base == "k_filter_shells" else None
     if base == "k_scatter_tile":
         return ("scatter_vec", "24P+3r") if targs[1:] == ["true"] else ("scatter", "12P+r")
     if base == "k_gather_tile":
@@ -109,6 +113,8 @@ def family(sym: str, ng: int):
         return {"0": ("gather", "56P+3r"), "1": ("gather", "24P+3r"),
                 "2": ("unkick_vjp", "72P+3r"), "3": ("wgrad", "92P+r")}.get(
                     targs[0] if targs else "", (None, None))
+    if base == "k_undrift":   # a reverse step without a momentum cotangent
+        return "wgrad", "68P"
     if base in ("k_bin_count", "k_to_fixed_count", "k_scan_local", "k_scan_add", "k_scan_index",
                 "k_index", "k_compact_sorted"):
         return "bin", None
@@ -120,8 +126,9 @@ def family(sym: str, ng: int):
 def alg_bytes(rule, grid_y, P, ng):
     r = 4.0 * ng ** 3
     c = 8.0 * ng * ng * (ng // 2 + 1)
-    return {"rc_per_buf": grid_y * (r + c), "2c_per_buf": grid_y * 2 * c, "3c": 3 * c, "4c": 4 * c,
-            "5c": 5 * c, "24P+3r": 24 * P + 3 * r, "12P+r": 12 * P + r,
+    t = 4.0 * ng * (ng // 2 + 1) ** 2   # one FP32 term per |n0|, n1, k2
+    return {"rc_per_buf": grid_y * (r + c), "2c_per_buf": grid_y * 2 * c, "3c": 3 * c,
+            "4c+t": 4 * c + t, "t": t, "68P": 68 * P, "24P+3r": 24 * P + 3 * r, "12P+r": 12 * P + r,
             "56P+3r": 56 * P + 3 * r,
             "72P+3r": 72 * P + 3 * r, "92P+r": 92 * P + r}.get(rule)
 
