@@ -252,7 +252,7 @@ k_fft_strided(float2* __restrict__ buf, typename std::conditional<DIR < 0, float
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::WY, Cfg<H>::MINW)
 k_fft_y_split(float2* __restrict__ g, float2* __restrict__ out_g, int cs, int ncb,
-              const float2* __restrict__ tw, int ntw, const float2* __restrict__ st) {
+              const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::WY;
     // exchange buffer | the H-point part of the stage-twiddle table (H - 1 entries)
     __shared__ float2 lds[lds_slots(H) * W + H];
@@ -676,8 +676,7 @@ struct Column {
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __restrict__ dst_g,
-         int cs, int ncb, const float* __restrict__ radial, const float2* __restrict__ tw, int ntw,
-            const float2* __restrict__ st) {
+         int cs, int ncb, const float* __restrict__ radial, const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     constexpr bool SHARE = H >= 256;
     constexpr int EQ = SHARE ? (H / 2) / T + 1 : 1;   // lookups: q = j + e T, and q = H/2
@@ -772,8 +771,8 @@ k_grad_z(const float2* __restrict__ src, float2* __restrict__ dst, float2* __res
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_z_pipe(const float2* __restrict__ src, float2* __restrict__ dst,
-              float2* __restrict__ dst_g, int cs, int ncb, int ntiles, const float* __restrict__ radial, const float2* __restrict__ tw,
-              int ntw, const float2* __restrict__ st) {
+              float2* __restrict__ dst_g, int cs, int ncb, int ntiles,
+              const float* __restrict__ radial, const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     constexpr int LS = lds_slots(H) * W;
     // radial lookups per lane: q = j + e T for e < EQ - 1, and q = H/2
@@ -893,8 +892,7 @@ template <int H, bool FILT>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_adj_z(const float2* __restrict__ src, long srcStride, float2* dst,
              const float2* dens, int cs, int ncb, const float* __restrict__ radial,
-             float* __restrict__ modes, float fscale, const float2* __restrict__ tw, int ntw,
-            const float2* __restrict__ st) {
+             float* __restrict__ modes, float fscale, const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     // exchange buffer | the H-point part of the stage-twiddle table (read from
     // LDS rather than hoisted into registers, which hold the column)
@@ -1055,8 +1053,7 @@ k_filter_sum(const float* __restrict__ part, int ntab, float* __restrict__ fbar)
 template <int H>
 __global__ void __launch_bounds__(Cfg<H>::T * Cfg<H>::W)
 k_grad_adj_z_pipe(const float2* __restrict__ src, long srcStride, float2* dst, int cs, int ncb,
-                  int ntiles, const float* __restrict__ radial, const float2* __restrict__ tw,
-                  int ntw, const float2* __restrict__ st) {
+                  int ntiles, const float* __restrict__ radial, const float2* __restrict__ st) {
     constexpr int E = Cfg<H>::E, T = Cfg<H>::T, W = Cfg<H>::W, n = H;
     constexpr int LS = lds_slots(H) * W;
     constexpr int EQ = (H / 2) / T + 1;   // radial lookups per lane (k_grad_z_pipe)
@@ -1421,7 +1418,7 @@ void launch_fft_y_split(float2* g, float2* out_g, int n, int cs, const Twiddles&
         constexpr int W = Cfg<N>::WY, T = Cfg<N>::T;
         const int ncb = cs / W;
         hipLaunchKernelGGL(k_fft_y_split<N>, dim3(N * ncb), dim3(T * W), 0, s, g, out_g, cs, ncb,
-                           tw.w, tw.n, tw.stages);
+                           tw.stages);
     });
 }
 
@@ -1455,10 +1452,10 @@ void launch_grad_z(const float2* src, float2* dst, float2* dst_g, int n, int cs,
             const int ntiles = NN * ncb;
             const int nwg = std::min(ntiles, device_cus());
             hipLaunchKernelGGL(k_grad_z_pipe<NN>, dim3(nwg), dim3(T * W), 0, s, src, dst,
-                               dst_g, cs, ncb, ntiles, radial, tw.w, tw.n, tw.stages);
+                               dst_g, cs, ncb, ntiles, radial, tw.stages);
         } else {
             hipLaunchKernelGGL(k_grad_z<NN>, dim3(NN * ncb), dim3(T * W), 0, s, src, dst,
-                               dst_g, cs, ncb, radial, tw.w, tw.n, tw.stages);
+                               dst_g, cs, ncb, radial, tw.stages);
         }
     });
 }
@@ -1472,8 +1469,7 @@ void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const flo
         int ncb = cs / W;
         if (fbar) {
             hipLaunchKernelGGL((k_grad_adj_z<NN, true>), dim3(NN * ncb), dim3(T * W), 0, s, src,
-                               srcStride, dst, dens, cs, ncb, radial, modes, fscale, tw.w, tw.n,
-                               tw.stages);
+                               srcStride, dst, dens, cs, ncb, radial, modes, fscale, tw.stages);
             constexpr int ntab = 3 * (NN / 2) * (NN / 2) + 1, width = 8 * NN;
             float* part = modes + (long)(NN / 2 + 1) * NN * cs;
             hipLaunchKernelGGL(k_filter_shells, dim3((ntab + width - 1) / width, kFilterSplits),
@@ -1485,11 +1481,10 @@ void launch_grad_adj_z(const float2* src, long srcStride, float2* dst, const flo
             const int ntiles = NN * ncb;
             const int nwg = std::min(ntiles, device_cus());
             hipLaunchKernelGGL(k_grad_adj_z_pipe<NN>, dim3(nwg), dim3(T * W), 0, s, src,
-                               srcStride, dst, cs, ncb, ntiles, radial, tw.w, tw.n, tw.stages);
+                               srcStride, dst, cs, ncb, ntiles, radial, tw.stages);
         } else {
             hipLaunchKernelGGL((k_grad_adj_z<NN, false>), dim3(NN * ncb), dim3(T * W), 0, s, src,
-                               srcStride, dst, dens, cs, ncb, radial, nullptr, 0.f, tw.w, tw.n,
-                               tw.stages);
+                               srcStride, dst, dens, cs, ncb, radial, nullptr, 0.f, tw.stages);
         }
     });
 }
