@@ -282,9 +282,10 @@ int pm_power_spectrum(pm_ctx* ctx, const float* dens_dev, int32_t n_bins,
  * Allocates no device memory: its scratch (the half spectrum and twiddle tables)
  * is a static device array of PM_NOALLOC_SCRATCH_BYTES that every GPU the library
  * runs on holds until the process ends; the first call on a device sets it up,
- * with 3 KB of pinned host memory for the results.  All calls on one GPU share that array, so calls that overlap on one
- * GPU (two streams or two host threads) race.  Errors: PM_EINVAL (arguments,
- * checked before any GPU work), PM_EHIP; message via pm_last_error(NULL). */
+ * with 3 KB of pinned host memory for the results.  All calls on one GPU share
+ * that array, so calls that overlap on one GPU (two streams or two host threads)
+ * race.  Errors: PM_EINVAL (arguments, checked before any GPU work), PM_EHIP;
+ * message via pm_last_error(NULL). */
 #define PM_NOALLOC_MAX_MESH 128
 #define PM_NOALLOC_SCRATCH_BYTES 10506240u
 int pm_power_spectrum_noalloc(const float* dens_dev, int32_t mesh, double box, int32_t n_bins,

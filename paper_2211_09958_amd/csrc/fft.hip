@@ -1243,7 +1243,9 @@ k_fft_shells(const float2* buf, float2* part, int cs, int ncb, int ntiles, int n
 
 // bins[i] = the sum of the nparts work-groups' values i, 64 values per
 // work-group: each of its 16 waves adds every 16th part, then wave 0 adds the
-// waves' sums (a fixed order: the sums repeat bit for bit).
+// waves' sums, in a fixed order.  (The parts themselves come from FP64 LDS atomics,
+// whose order varies: shell sums, and the P(k) and loss formed from them, repeat to
+// rounding, not bit for bit.)
 template <int H>
 __global__ void __launch_bounds__(1024)
 k_shell_reduce(const float2* __restrict__ part, int cs, int ncb, int nparts, int nvals,

@@ -3,9 +3,10 @@
 // tight serving or training loops, harnesses that forbid hipMalloc).  It needs
 // no context and no workspace: its scratch is `scratch`, a static device array
 // of kScratchBytes that every GPU the library runs on holds until the process
-// ends, and 3 KB of pinned host memory per GPU for the results.  The array's name is only a host-side stand-in for the device symbol, so
-// host code never passes it to a kernel: the per-device address comes from
-// hipGetSymbolAddress, taken once per device on the first call there.
+// ends, and 3 KB of pinned host memory per GPU for the results.  The array's name is
+// only a host-side stand-in for the device symbol, so host code never passes it to a
+// kernel: the per-device address comes from hipGetSymbolAddress, taken once per
+// device on the first call there.
 //
 // Calls on one GPU share that GPU's array and its contents; two calls that
 // overlap on one GPU (two streams or two host threads) race.  Everything a call

@@ -187,8 +187,9 @@ struct Plan {
         // launch as fit in 2^17 entries, and their cotangents go through the network
         // in one.  A table of a 128^3 mesh (12289 entries, 193 work-groups) takes
         // 16 us alone and nine of them 34 us, the backward pass 25 us for one and
-        // 69 us for eight; from 256^3 on a table fills the GPU by itself, and the
-        // bound keeps the tables under 1 MB together with their cotangents.
+        // 69 us for eight; from 256^3 on a table fills the GPU by itself.  A batch and
+        // its cotangents stay within 1 MB; a single table may be larger (with its
+        // cotangent 1.6 MB at 512^3, 6.3 MB at 1024^3).
         tab_stride = (ntab_f + 63) / 64 * 64;
         ntables = c.filter ? (int)std::min<long>({std::max<long>(1, (1L << 17) / tab_stride),
                                                   (long)c.n_steps + 1, kMaxTables})
