@@ -133,9 +133,9 @@ k_fft_x_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
 // kmul_buf >= 0: the spectrum of buffer kmul_buf is first multiplied by i k2
 // (zero on the Nyquist column), i.e. this pass also takes the spectral
 // derivative along the last axis.  DENSE: the real rows go to a caller's
-// [N][N][N] array in plain row order (as in k_fft_x_r2c), unless *open is 0
-// (nullable; one wave-uniform load).
-template <int N, bool DENSE>
+// [N][N][N] array in plain row order (as in k_fft_x_r2c).  OPEN: unless *open is 0
+// (an instance of its own: a test of the pointer cost the smallest meshes 0.2 us).
+template <int N, bool DENSE, bool OPEN>
 __global__ void __launch_bounds__(Cfg<N / 2>::T * Cfg<N / 2>::ROWS)
 k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, const int* __restrict__ open, int cs,
             long nrows, long bufStride, int kmul_buf, const float2* __restrict__ tw, int ntw,
@@ -150,7 +150,7 @@ k_fft_x_c2r(float2* __restrict__ buf, float* __restrict__ real, const int* __res
     const int twN = ntw / N;
     float2* L = lds + r * LS;
     const bool kmul = (int)blockIdx.y == kmul_buf;
-    const bool store = !DENSE || !open || *open != 0;
+    const bool store = !OPEN || *open != 0;
     // rowp points at row 0 for rows past the end, so every load is in bounds
     // and none sits in a branch (which would make each wait for its data)
     float2 x[E];
@@ -591,12 +591,11 @@ k_plane_r2c(const float* __restrict__ real, float2* __restrict__ buf, int cs, lo
 }
 
 // Inverse: spectrum of plane blockIdx.x -> real rows, in place in buffer
-// blockIdx.y or to the dense array `real` when given (unless *open is 0, as in
-// k_fft_x_c2r).  FORCE: grid row 0 takes
+// blockIdx.y or to the dense array `real` when given (OPEN: unless *open is 0).  FORCE: grid row 0 takes
 // buffer 0 in place; rows 1 and 2 both read `g` and leave the axis-1 derivative
 // (times i n1 before the axis-1 transform) in buffer 1 and the axis-2 derivative
 // (times i k2 before the axis-2 transform) in buffer 2.
-template <int N, bool FORCE>
+template <int N, bool FORCE, bool OPEN>
 __global__ void __launch_bounds__(Plane<N>::NT)
 k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
             const int* __restrict__ open, int cs, long bufStride, const float2* __restrict__ tw, int ntw,
@@ -606,7 +605,7 @@ k_plane_c2r(float2* buf, const float2* __restrict__ g, float* __restrict__ real,
     const int i0 = (int)xcd_block(blockIdx.x, N), comp = blockIdx.y;
     float2* b = buf + comp * bufStride;
     const float2* src = FORCE && comp > 0 ? g : b;
-    const bool store = FORCE || !open || *open != 0;
+    const bool store = !OPEN || *open != 0;
     float2 w[P::EX];
 #pragma unroll
     for (int e = 0; e < P::EX; ++e)
@@ -1363,12 +1362,15 @@ void x_c2r(float2* buf, float* real, int cs, int nbuf, long bufStride, int kmul_
     constexpr int ROWS = Cfg<N / 2>::ROWS, T = Cfg<N / 2>::T;
     long nrows = (long)N * N;
     dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS), nbuf);
-    if (real)
-        hipLaunchKernelGGL((k_fft_x_c2r<N, true>), grid, dim3(T * ROWS), 0, s, buf, real, open, cs,
-                           nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
+    if (real && open)
+        hipLaunchKernelGGL((k_fft_x_c2r<N, true, true>), grid, dim3(T * ROWS), 0, s, buf, real,
+                           open, cs, nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
+    else if (real)
+        hipLaunchKernelGGL((k_fft_x_c2r<N, true, false>), grid, dim3(T * ROWS), 0, s, buf, real,
+                           nullptr, cs, nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
     else
-        hipLaunchKernelGGL((k_fft_x_c2r<N, false>), grid, dim3(T * ROWS), 0, s, buf, nullptr, nullptr,
-                           cs, nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
+        hipLaunchKernelGGL((k_fft_x_c2r<N, false, false>), grid, dim3(T * ROWS), 0, s, buf, nullptr,
+                           nullptr, cs, nrows, bufStride, kmul_buf, tw.w, tw.n, tw.stages);
 }
 
 template <int N, int DIR, int AXIS, bool SPEC, class Spec>
@@ -1539,8 +1541,14 @@ void launch_fft_yx_c2r(float2* buf, float* real, int n, int cs, int nbuf, long b
     if (n <= kMaxPlane) {
         plane_switch(n, [&](auto nn) {
             constexpr int N = decltype(nn)::value;
-            hipLaunchKernelGGL((k_plane_c2r<N, false>), dim3(N, nbuf), dim3(Plane<N>::NT), 0, s,
-                               buf, nullptr, real, open, cs, bufStride, tw.w, tw.n, tw.stages);
+            if (real && open)
+                hipLaunchKernelGGL((k_plane_c2r<N, false, true>), dim3(N, nbuf),
+                                   dim3(Plane<N>::NT), 0, s, buf, nullptr, real, open, cs,
+                                   bufStride, tw.w, tw.n, tw.stages);
+            else
+                hipLaunchKernelGGL((k_plane_c2r<N, false, false>), dim3(N, nbuf),
+                                   dim3(Plane<N>::NT), 0, s, buf, nullptr, real, nullptr, cs,
+                                   bufStride, tw.w, tw.n, tw.stages);
         });
         return;
     }
@@ -1562,7 +1570,7 @@ void launch_plane_c2r_force(float2* buf, const float2* g, int n, int cs, long bu
                             const Twiddles& tw, hipStream_t s) {
     plane_switch(n, [&](auto nn) {
         constexpr int N = decltype(nn)::value;
-        hipLaunchKernelGGL((k_plane_c2r<N, true>), dim3(N, 3), dim3(Plane<N>::NT), 0, s, buf, g,
+        hipLaunchKernelGGL((k_plane_c2r<N, true, false>), dim3(N, 3), dim3(Plane<N>::NT), 0, s, buf, g,
                            nullptr, nullptr, cs, bufStride, tw.w, tw.n, tw.stages);
     });
 }
