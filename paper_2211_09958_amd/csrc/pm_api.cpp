@@ -476,12 +476,13 @@ const float* force_radial(pm_ctx* ctx, double a) {
     return ctx->radial_f;
 }
 
-// A run's evaluations 0, 1, ... of the force, at scale factors a(i): the table of
+// A run's n evaluations 0, 1, ... of the force, at scale factors a[i stride]: the table of
 // evaluation i, formed with those of the next ones (their number is bounded by
 // the plan) when it is the first of a batch, and of the transposed pass's cotangent.
 struct RunTables {
     pm_ctx* ctx;
-    std::vector<double> a;
+    const double* a;   // outlives this
+    int n, stride;
     int first_bar = -1;   // evaluations first_bar .. last_bar: cotangents not yet
     int last_bar = -1;    // taken through the network
 
@@ -489,7 +490,7 @@ struct RunTables {
         const int K = ctx->plan.ntables;
         if (ctx->cfg.filter && i % K == 0) {
             ScaleFactors sf;
-            for (int k = i; k < std::min(i + K, (int)a.size()); ++k) sf.add(a[k]);
+            for (int k = i; k < std::min(i + K, n); ++k) sf.add(a[k * stride]);
             force_radials(ctx, sf);
         }
         return ctx->radial_f + offset(i);
@@ -504,9 +505,9 @@ struct RunTables {
     // after evaluation i's transposed pass: a full batch, or the last one, is taken on
     void done(int i) {
         if (!ctx->cfg.filter || first_bar < 0) return;
-        if ((i + 1) % ctx->plan.ntables != 0 && i + 1 < (int)a.size()) return;
+        if ((i + 1) % ctx->plan.ntables != 0 && i + 1 < n) return;
         ScaleFactors sf;
-        for (int k = first_bar; k <= last_bar; ++k) sf.add(a[k]);
+        for (int k = first_bar; k <= last_bar; ++k) sf.add(a[k * stride]);
         KTimer t(ctx, PM_K_MLP, 0);
         launch_mlp_backward(ctx->theta, ctx->ng, sf, ctx->plan.tab_stride,
                             ctx->fbar + offset(first_bar), ctx->gtheta, ctx->mlp_scratch,
@@ -1146,7 +1147,7 @@ int pm_forward(pm_ctx* ctx, const float* noise, float* disp_out, float* mom_out,
                         ctx->lpt2() ? ctx->tmpv : nullptr, (float)sc.D20, (float)sc.G20);
     }
     records_in_lattice_order(ctx);
-    RunTables tables{ctx, sc.a};
+    RunTables tables{ctx, sc.a.data(), N + 1, 1};
     for (int n = 0; n <= N; ++n) {
         // the last force is taken at the final positions: its density is the run's
         // (a sort and a scatter of their own took 3.6 ms at 512^3/1024^3)
@@ -1217,7 +1218,7 @@ int pm_adjoint(pm_ctx* ctx, const float* g_dens, const float* g_disp, const floa
     // at 512^3, and cleared the word before it)
     if (g_mom) launch_absmax(g_mom, 3 * P, vmax_word(ctx), s);
     const ReverseStart start{ctx->fin_x, ctx->fin_p, g_disp, g_mom};
-    RunTables tables{ctx, {sc.a.rbegin(), sc.a.rend()}};   // evaluation N - n is at x_n
+    RunTables tables{ctx, sc.a.data() + N, N + 1, -1};   // evaluation N - n is at x_n
     const float* radial = tables.radial(0);
     compute_force(ctx, radial, kStateCotangents, nullptr, &start);
     const int ngather = (int)gather_partials(ctx->np, ctx->ng);
@@ -1518,7 +1519,7 @@ int pm_force_vjp(pm_ctx* ctx, const float* disp, double a, const float* v, float
     if (ctx->cfg.filter && !ctx->have_filter) return ctx->fail(PM_ESTATE, "pm_set_filter not called");
     hipStream_t s = ctx->stream;
     load_once(ctx, disp);
-    RunTables tables{ctx, {a}};
+    RunTables tables{ctx, &a, 1, 1};
     const float* radial = tables.radial(0);
     compute_force(ctx, radial, kOnce);
     launch_unkick_vjp(ctx->xq, nullptr, ctx->creal(1), ctx->creal_stride(), ctx->lat, ctx->bins,
